@@ -41,13 +41,12 @@ struct ff_plan {
     uint32_t verify_group = 1;
     uint32_t affine = 0;  // preset/complement term of a chunk_bytes-long CRC
     // fused optimizer step (only when every parameter group is complete)
-    const WorkTile* work = nullptr;
-    uint32_t n_work = 0;        // all work tiles: parameter tiles first, then RAW tiles
-    uint32_t n_work_param = 0;
-    uint32_t fused_xcd_group = 4;  // XCD-aware order of the fused step's tiles (kernels.hpp)
+    FusedWork work;
+    // XCD-aware order of the fused step's workgroups (kernels.hpp): runs of 1, 4, 16 and 64 are within
+    // the 3 % that runs differ by on aligned shards; on 7 GB of odd-sized parameters 64 is ahead
+    // (3.67 against 3.82-4.0 ms)
+    uint32_t fused_xcd_group = 64;
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
-    // entry k: first parameter tile of parameter group k * kGradsPerLaunch; last entry: n_work_param
-    std::vector<uint32_t> group_tile_begin;
     const uint32_t* fused_tabs = nullptr;
 };
 
@@ -104,10 +103,15 @@ int upload_tables(ff_plan* p)
     const uint64_t o_first = align_up(o_ptr + n * 8, 256);
     const uint64_t o_tab = align_up(o_first + L.n_tiles * 4, 256);
     std::vector<WorkTile> work;
-    if (L.adam_ok && !L.params.empty()) build_work_tiles(L, work);
-    if (work.size() > 0xFFFFFFF0ull) return FF_ERR_INVALID;
+    std::vector<WorkWave> waves;
+    if (L.adam_ok && !L.params.empty()) {
+        build_work_tiles(L, work);
+        if (work.size() > 0x1FFFFFF0ull) return FF_ERR_INVALID;  // at most 8 wavefronts each
+        build_work_waves(work, L.params.size(), kGradsPerLaunch, waves, p->work.launch_wave);
+    }
     const uint64_t o_work = align_up(o_tab + kTabWords * 4, 256);
-    const uint64_t o_ftabs = align_up(o_work + work.size() * sizeof(WorkTile), 256);
+    const uint64_t o_waves = align_up(o_work + work.size() * sizeof(WorkTile), 256);
+    const uint64_t o_ftabs = align_up(o_waves + waves.size() * sizeof(WorkWave), 256);
     const uint64_t o_tbase = align_up(o_ftabs + kFusedTabWords * 4, 256);
     const uint64_t o_shift = align_up(o_tbase + L.n_tiles * 8, 256);
     const uint64_t total = align_up(o_shift + uint64_t(L.tiles_per_chunk) * 4, 256);
@@ -135,6 +139,8 @@ int upload_tables(ff_plan* p)
     }
     build_tab_u(reinterpret_cast<uint32_t*>(host.data() + o_tab));
     if (!work.empty()) std::memcpy(host.data() + o_work, work.data(), work.size() * sizeof(WorkTile));
+    if (!waves.empty())
+        std::memcpy(host.data() + o_waves, waves.data(), waves.size() * sizeof(WorkWave));
     build_fused_tabs(reinterpret_cast<uint32_t*>(host.data() + o_ftabs));
 
     FF_HIP_TRY(hipGetDevice(&p->device));
@@ -151,17 +157,17 @@ int upload_tables(ff_plan* p)
     t.tile_base = reinterpret_cast<const uint64_t*>(d + o_tbase);
     t.tile_shift = reinterpret_cast<const uint32_t*>(d + o_shift);
     t.tab_u = reinterpret_cast<const uint32_t*>(d + o_tab);
-    p->work = reinterpret_cast<const WorkTile*>(d + o_work);
-    p->n_work = static_cast<uint32_t>(work.size());
-    p->n_work_param = 0;
-    for (const WorkTile& w : work) p->n_work_param += (w.kind == kWorkParam) ? 1u : 0u;
-    // the parameter tiles are sorted by parameter group: where each launch of the fused step begins
-    p->group_tile_begin.clear();
-    for (uint32_t i = 0; i < p->n_work_param; i++)
-        while (p->group_tile_begin.size() <= work[i].grad_index / kGradsPerLaunch)
-            p->group_tile_begin.push_back(i);
-    while (p->group_tile_begin.size() <= (L.params.size() + kGradsPerLaunch - 1) / kGradsPerLaunch)
-        p->group_tile_begin.push_back(p->n_work_param);
+    p->work.tiles = reinterpret_cast<const WorkTile*>(d + o_work);
+    p->work.waves = reinterpret_cast<const WorkWave*>(d + o_waves);
+    // the parameter tiles are sorted by parameter group: where each launch of the step begins
+    uint32_t n_param_tiles = 0;
+    for (const WorkTile& w : work) n_param_tiles += (w.kind == kWorkParam) ? 1u : 0u;
+    std::vector<uint32_t>& lt = p->work.launch_tile;
+    lt.clear();
+    for (uint32_t i = 0; i < n_param_tiles; i++)
+        while (lt.size() <= work[i].grad_index / kGradsPerLaunch) lt.push_back(i);
+    while (lt.size() <= (L.params.size() + kGradsPerLaunch - 1) / kGradsPerLaunch)
+        lt.push_back(n_param_tiles);
     p->fused_tabs = reinterpret_cast<const uint32_t*>(d + o_ftabs);
     return FF_OK;
 }
@@ -421,11 +427,9 @@ int adam_impl(const ff_plan* p, const void* const* grads, const ff_adam_hparams*
     c.xcd_group = bare ? p->mix_xcd_group : p->fused_xcd_group;
     c.n_nonfinite = n_nonfinite;
     c.prev = static_cast<const uint8_t*>(prev);
-    FF_HIP_TRY(launch_fused(half_dtype == FF_F16, p->work, p->n_work_param,
-                            p->n_work - p->n_work_param, grads,
-                            static_cast<uint32_t>(L.params.size()), p->group_tile_begin.data(),
-                            p->fused_tabs, chunks, crcs, L.n_chunks, L.payload, L.buffer_bytes,
-                            p->affine, c, bare, s));
+    FF_HIP_TRY(launch_fused(half_dtype == FF_F16, p->work, grads,
+                            static_cast<uint32_t>(L.params.size()), p->fused_tabs, chunks, crcs,
+                            L.n_chunks, L.payload, L.buffer_bytes, p->affine, c, bare, s));
     return FF_OK;
 }
 

@@ -16,6 +16,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
 
 // Every pointer the kernels dereference is device global memory.  Addresses that come out of
 // tables are plain integers, so the compiler would fall back to flat (generic) accesses, whose
@@ -110,24 +111,29 @@ __device__ __forceinline__ void fold_row(uint32_t (&S)[F::NE][F::NF], const uint
     });
 }
 
-// After K rows folded with J = 0..K-1 the physical register rows lag the logical ones by K;
-// moving them back makes J = 0 valid again (physical row q takes what physical row q - K held).
-template <class F, int K>
-__device__ __forceinline__ void rotate_state(uint32_t (&S)[F::NE][F::NF])
+// a ^ b ^ c in one instruction (the compiler keeps chains of two-operand XORs otherwise).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
-    constexpr int NE = F::NE, NF = F::NF;
-    uint32_t old[NE][NF];
-    static_for<NE>([&](auto e) { static_for<NF>([&](auto f) { old[e][f] = S[e][f]; }); });
-    static_for<NE>([&](auto q) {
-        static_for<NF>([&](auto f) { S[q][f] = old[(q - K % NE + NE) % NE][f]; });
-    });
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// Multiply by a fixed power of x with four byte tables (LDS).
-__device__ __forceinline__ uint32_t mul_tab(const uint32_t* tab, uint32_t a)
+// a * (a fixed power of x) ^ b with four byte tables (LDS): 4 extractions, 4 lookups, 2 XORs.
+__device__ __forceinline__ uint32_t mul_tab_add(const uint32_t* tab, uint32_t a, uint32_t b)
 {
-    return tab[a & 0xFFu] ^ tab[256 + ((a >> 8) & 0xFFu)] ^ tab[512 + ((a >> 16) & 0xFFu)] ^
-           tab[768 + (a >> 24)];
+    return xor3(xor3(tab[a & 0xFFu], tab[256 + ((a >> 8) & 0xFFu)], tab[512 + ((a >> 16) & 0xFFu)]),
+                tab[768 + (a >> 24)], b);
+}
+
+// XOR over the 64 lanes, the same value in every lane: inside each row of 16 lanes with DPP moves
+// (no LDS round trip as in a shuffle), across the four rows through scalar registers.
+__device__ __forceinline__ uint32_t wave_xor(uint32_t v)
+{
+    v ^= __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]: lane ^ 1
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]: lane ^ 2
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);  // row_half_mirror: the other quad
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);  // row_mirror: the other eight
+    return __builtin_amdgcn_readlane(v, 0) ^ __builtin_amdgcn_readlane(v, 16) ^
+           __builtin_amdgcn_readlane(v, 32) ^ __builtin_amdgcn_readlane(v, 48);
 }
 
 // State of all lanes -> R / x^32, where R is the CRC register (run from 0) of the rows folded so
@@ -144,14 +150,11 @@ __device__ __forceinline__ uint32_t reduce_state(const uint32_t (&S)[F::NE][F::N
     static_for<NF>([&](auto f) { acc[f] = 0; });
     static_for<NE>([&](auto i) {
         constexpr int e = NE - 1 - i;
-        static_for<NF>([&](auto f) { acc[f] = mul_tab(tab, acc[f]) ^ S[e][f]; });
+        static_for<NF>([&](auto f) { acc[f] = mul_tab_add(tab, acc[f], S[e][f]); });
     });
     uint32_t v = acc[NF - 1];
     static_for<NF - 1>([&](auto i) { v = gf2_mul_const<kX32>(v) ^ acc[NF - 2 - i]; });
-    v = gf2_mul(v, lane_c);
-#pragma unroll
-    for (int l = 0; l < 6; l++) v ^= __shfl_xor(v, 1 << l, kWaveSize);
-    return v;
+    return wave_xor(gf2_mul(v, lane_c));
 }
 
 }  // namespace ffsnap

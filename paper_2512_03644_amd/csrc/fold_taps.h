@@ -15,24 +15,4 @@ struct Fold16x16 {
     static constexpr unsigned char TAP_F[NF][NTAP] = {{0, 1, 2, 1, 0, 3, 3, 2, 3}, {0, 1, 3, 0, 3, 0, 1, 0, 2}, {0, 1, 2, 1, 2, 1, 3, 0, 1}, {1, 3, 0, 0, 3, 3, 0, 1, 3}};
 };
 
-struct Fold16x10 {
-    static constexpr int ROW_BYTES = 1024;  // bytes one wavefront reads per step
-    static constexpr int STRIDE = 256;     // dword distance between a lane's rows
-    static constexpr int NF = 4;         // dwords per lane per row
-    static constexpr int NE = 10;         // rows of state
-    static constexpr int NTAP = 11;       // slots per column (255 = unused)
-    static constexpr unsigned char TAP_E[NF][NTAP] = {{0, 1, 1, 1, 2, 2, 3, 5, 7, 8, 9}, {0, 1, 2, 3, 4, 6, 6, 7, 8, 8, 9}, {0, 0, 0, 2, 4, 5, 5, 6, 6, 7, 9}, {0, 1, 2, 2, 3, 4, 5, 7, 8, 9, 9}};
-    static constexpr unsigned char TAP_F[NF][NTAP] = {{0, 0, 2, 3, 2, 3, 1, 0, 0, 0, 1}, {1, 2, 0, 1, 2, 1, 2, 1, 1, 2, 3}, {0, 2, 3, 0, 0, 2, 3, 1, 2, 3, 0}, {3, 2, 1, 3, 1, 1, 2, 1, 3, 0, 3}};
-};
-
-struct Fold8x20 {
-    static constexpr int ROW_BYTES = 512;  // bytes one wavefront reads per step
-    static constexpr int STRIDE = 128;     // dword distance between a lane's rows
-    static constexpr int NF = 2;         // dwords per lane per row
-    static constexpr int NE = 20;         // rows of state
-    static constexpr int NTAP = 13;       // slots per column (255 = unused)
-    static constexpr unsigned char TAP_E[NF][NTAP] = {{1, 1, 2, 3, 4, 4, 7, 8, 8, 11, 12, 15, 19}, {0, 2, 3, 7, 8, 9, 11, 15, 17, 18, 19, 255, 255}};
-    static constexpr unsigned char TAP_F[NF][NTAP] = {{0, 1, 1, 1, 0, 1, 1, 0, 1, 0, 0, 1, 0}, {0, 0, 0, 0, 0, 0, 1, 0, 0, 0, 0, 255, 255}};
-};
-
 }  // namespace ffsnap

@@ -1,19 +1,21 @@
 // Fused optimizer step + snapshot for gfx950.
 //
-// Work tiles (layout.hpp) are runs of up to kParamTileElems elements of one parameter group, one
-// workgroup each, and runs of up to kRawTileBytes of a RAW segment, one wavefront each in a
-// kernel of their own that only copies and folds.  A parameter tile is walked in rows of 256
-// elements, lane l taking 4 consecutive elements: 8 bytes of 16-bit gradient and 3 x 16 bytes of
-// fp32 master/m/v come in, the AdamW update runs in registers, and the four results go out
-// twice -- in place, and at their stream offsets in the chunk buffer -- plus once into LDS,
-// from where four folding wavefronts (one per output stream) take them into their CRC states,
-// so the snapshot is never read back from memory.  Rows are aligned to the END of the tile: a
-// tile whose length is not a multiple of 256 has a partial FIRST row, whose missing leading
-// elements are zeros that do not change a CRC register started from 0.  At the end of the tile
-// each stream's state is reduced to a register, multiplied by x^(8 * distance to the end of its
-// chunk) and XORed into crcs[chunk] with an atomic; XOR is commutative, so the result does not
-// depend on the order in which tiles finish.  A prepare kernel sets crcs[] to the preset/complement
-// term and writes the zero tail of the last chunk.
+// Work tiles (layout.hpp) are blocks of up to kParamTileElems elements of one parameter group, or of
+// up to kRawTileBytes bytes of a RAW segment.  One wavefront takes one sub-block: 4 rows of 256
+// elements, lane l of a row taking 4 consecutive elements: 8 bytes of 16-bit gradient and 3 x 16
+// bytes of fp32 master/m/v come in, the AdamW update runs in registers, and the four results go out
+// twice -- in place, and at their stream offsets in the chunk buffer -- and, from the same registers,
+// into the CRC of their stream, so the snapshot is never read back from memory.  Rows are aligned
+// to the tensors' elements; elements of a row that are not the tile's count as zeros.
+//
+// A sub-block is straight-line code: 16 loads up front, then row by row update, 8 stores and one
+// Horner step of each stream's register through byte tables in LDS (x^8192 or x^4096 per row).  No
+// loop, no barrier behind the loads and no hand-off between wavefronts; what overlaps one wavefront's
+// arithmetic with another's memory is 4 of them on every SIMD.  The sub-blocks of a tile that share a
+// workgroup sum their registers in LDS; the last one to arrive multiplies the sums by x^(8 * distance
+// to the end of the chunk) and XORs them into crcs[chunk] with an atomic; XOR is commutative, so the
+// result does not depend on the order in which tiles finish.  A prepare kernel sets crcs[] to the
+// preset/complement term and writes the zero tail of the last chunk.
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
@@ -24,55 +26,48 @@ namespace ffsnap {
 
 namespace {
 
-constexpr int kUpdateWaves = 4;  // one row of a batch each
-constexpr int kFoldWaves = 4;    // one output stream each
-constexpr int kWavesPerBlock = kUpdateWaves + kFoldWaves;
-constexpr int kBatchRows = kUpdateWaves;
-using F32Fold = Fold16x16;  // 16 bytes per lane per row (parameter tiles)
-using B16Fold = Fold8x20;   // 8 bytes per lane per row
-using RawFold = Fold16x10;  // RAW copy tiles
-constexpr int kPhases = 5;  // rows folded between two physical rotations of the state
-static_assert(kPhases <= RawFold::NE, "rotation step");
+constexpr int kWavesPerBlock = kWavesPerGroup;
+constexpr int kThreads = kWavesPerBlock * kWaveSize;
 constexpr int kRowElems = 256;
-constexpr int kRawRows = kRawTileBytes / 1024;  // rows of a whole RAW tile
-constexpr int kRawDepth = 16;                   // rows in flight on its straight-line path
-static_assert(kRawRows % F32Fold::NE == 0 && kRawDepth <= kRawRows, "whole RAW tile");
+constexpr int kRows = kSubElems / kRowElems;   // rows of a parameter sub-block
+constexpr int kRawRows = kSubRawBytes / 1024;  // rows of a RAW sub-block
+static_assert(kRows == 4 && kRawRows == 8, "sub-blocks");
 
 __device__ __forceinline__ float bits_to_f32(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f32_to_bits(float f) { return __float_as_uint(f); }
 
-// fp32 -> bf16 bits, round to nearest even; NaN keeps sign and top payload bits, forced quiet.
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
+// Two fp32 -> two bf16, the first in the low half: round to nearest even in one instruction.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f32_to_bf16_pair(float lo, float hi)
 {
-    const uint32_t u = f32_to_bits(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x0040u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// fp32 -> fp16 bits: the hardware conversion rounds to nearest even, overflows to infinity and
-// produces subnormals; NaN is given a fixed form (sign, top 9 payload bits, quiet).
-__device__ __forceinline__ uint32_t f32_to_f16_bits(float f)
+// Two fp32 -> two fp16: the hardware conversion rounds to nearest even, overflows to infinity and
+// produces subnormals.
+__device__ __forceinline__ uint32_t f32_to_f16_pair(float lo, float hi)
 {
-    const uint32_t u = f32_to_bits(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return ((u >> 16) & 0x8000u) | 0x7E00u | ((u >> 13) & 0x1FFu);
-    return __half_as_ushort(__float2half_rn(f));
+    return __half_as_ushort(__float2half_rn(lo)) | (uint32_t(__half_as_ushort(__float2half_rn(hi))) << 16);
 }
 
 // IEEE 754 leaves sign and payload of a NaN that an operation produces open, and processors differ
 // in them.  A snapshot is compared byte for byte and CRC'd across machines, so a NaN result of the
-// update is stored in one form: quiet, positive, empty payload.
+// update is stored in one form: quiet, positive, empty payload; the 16-bit weight is rounded from
+// that form, which both conversions turn into the 16-bit format's own.
 constexpr uint32_t kCanonicalNaN = 0x7FC00000u;
 __device__ __forceinline__ float canonical_nan(float x) { return (x != x) ? bits_to_f32(kCanonicalNaN) : x; }
 
 // One element of the update; every operation is a separately rounded fp32 operation (the file
-// is compiled with -ffp-contract=off, division and square root are correctly rounded).  New
-// master, m and v that are NaN are stored as the canonical NaN, and the 16-bit weight is rounded
-// from that.
-// F16: the gradient is fp16 of a loss scaled by S and is multiplied by inv_scale = 1/S first;
-// the working weight is rounded to fp16.  Otherwise both are bf16 and nothing is scaled.
-template <bool F16>
+// is compiled with -ffp-contract=off, division and square root are correctly rounded).
+// F16: the gradient is fp16 of a loss scaled by S and is multiplied by inv_scale = 1/S first.
+// Otherwise it is bf16 and nothing is scaled.  BC2: the second bias correction has not yet rounded
+// to one (x / 1.0f is x exactly, so the division is left out then; beta2 = 0.95 gets there at step
+// 333).  A NaN in the new m or v makes the new master NaN too, so that one comparison per element
+// finds the rare row whose NaNs have to be put into their stored form.
+template <bool F16, bool BC2>
 __device__ __forceinline__ void adam_element(const FusedConsts& C, uint32_t g_bits, float& p,
-                                             float& m, float& v, uint32_t& w_bits)
+                                             float& m, float& v)
 {
     const AdamConsts& k = C.adam;
     float g;
@@ -81,38 +76,32 @@ __device__ __forceinline__ void adam_element(const FusedConsts& C, uint32_t g_bi
     else
         g = bits_to_f32(g_bits << 16);
     const float pd = p * k.decay;
-    const float m1 = (k.b1 * m) + (k.omb1 * g);
-    const float v1 = (k.b2 * v) + ((k.omb2 * g) * g);
-    // x / 1.0f is x exactly, so the division is skipped once the second bias correction has
-    // rounded to one (wave-uniform test; beta2 = 0.95 gets there at step 333)
-    const float r = sqrtf(v1);
-    const float d = ((k.bc2s == 1.0f) ? r : (r / k.bc2s)) + k.eps;
-    const float p1 = canonical_nan(pd - (k.step_size * (m1 / d)));
-    p = p1;
-    m = canonical_nan(m1);
-    v = canonical_nan(v1);
-    w_bits = F16 ? f32_to_f16_bits(p1) : f32_to_bf16_bits(p1);
+    m = (k.b1 * m) + (k.omb1 * g);
+    v = (k.b2 * v) + ((k.omb2 * g) * g);
+    const float r = sqrtf(v);
+    const float d = (BC2 ? r / k.bc2s : r) + k.eps;
+    p = pd - (k.step_size * (m / d));
 }
 
 // fp16 infinity or NaN
 __device__ __forceinline__ bool f16_nonfinite(uint32_t bits) { return (bits & 0x7C00u) == 0x7C00u; }
 
+// the same bytes of LDS seen as halfwords and as 16-byte slots
+typedef uint16_t u16_alias __attribute__((may_alias));
+typedef u32x4 u32x4_alias __attribute__((may_alias));
+
 struct Lds {
     uint32_t tab16[1024];  // multiply by x^8192  (1 KiB rows)
     uint32_t tab8[1024];   // multiply by x^4096  (512 B rows)
-    uint32_t lane16[64];   // x^(128 * (63 - lane))
-    uint32_t lane8[64];    // x^(64 * (63 - lane))
+    uint32_t tab4[1024];   // multiply by x^32    (neighbouring dwords)
+    uint32_t sum[kWavesPerBlock][4];  // per run (at its first wavefront's place): XOR of its registers
+    uint32_t arrived[kWavesPerBlock]; // wavefronts of the run that have added theirs
+    // the up to 8 elements (16 halfwords, RAW) at a sub-block's ends that do not fill a lane's slot
+    __attribute__((aligned(16))) uint32_t edge[kWavesPerBlock][4][8];
 };
 
-// Tile registers come out of reduce_state without the factor x^32 that a CRC register carries.
+// Tile registers come out of the folds without the factor x^32 that a CRC register carries.
 constexpr uint32_t kX16 = gf2_xpow(16);
-
-__device__ __forceinline__ void add_piece(uint32_t* __restrict__ crcs, const WorkTile& t, int piece,
-                                          uint32_t reg)
-{
-    if (t.shift[piece])
-        atomicXor(&crcs[t.chunk[piece]], gf2_mul_const<kX32>(gf2_mul(reg, t.shift[piece])));
-}
 
 // Head piece: the first two bytes of a split element, which are the last two bytes of their
 // chunk.  In the low half of a dword they read M(x) * x^16, and their register is M(x) * x^32.
@@ -122,440 +111,403 @@ __device__ __forceinline__ void add_head_piece(uint32_t* __restrict__ crcs, cons
     atomicXor(&crcs[t.chunk[piece]], gf2_mul_const<kX16>(low_half));
 }
 
-// ---- parameter tile ----------------------------------------------------------------------------
-//
-// A workgroup of 8 wavefronts owns one parameter tile.  Wavefronts 0..3 update: in every batch of
-// 4 rows each takes one row, runs the AdamW update in registers, stores the results twice (in
-// place, snapshot) and leaves a copy in LDS.  Wavefronts 4..7 fold: each owns ONE output stream
-// (w16, master, m, v) and one CRC state, and folds the 4 rows of the previous batch out of LDS.
-// One barrier per batch separates writers and readers of the two LDS batch buffers.  Splitting
-// the roles keeps every wavefront's register set small (one fold state instead of four), which
-// lets several wavefronts share a SIMD and overlap arithmetic with memory waits.
-
-struct Batch {          // results of 4 rows, as they lie in the streams
-    uint32_t w[kBatchRows][128];
-    uint32_t p[kBatchRows][256];
-    uint32_t m[kBatchRows][256];
-    uint32_t v[kBatchRows][256];
+// The byte tables on their way to LDS: fetched first thing, stored (put) behind the loads of the
+// wavefront's own data, so that the two latencies overlap.  put() is the workgroup's only barrier.
+struct TableFetch {
+    u32x4 a;
+    u32x2 b;
+    __device__ __forceinline__ explicit TableFetch(const uint32_t* __restrict__ tabs)
+    {
+        a = *as_global(reinterpret_cast<const u32x4*>(tabs) + threadIdx.x);
+        b = *as_global(reinterpret_cast<const u32x2*>(tabs + 2048) + threadIdx.x);
+    }
+    __device__ __forceinline__ void put(Lds& lds) const
+    {
+        static_assert(kThreads * 4 == 2048 && kThreads * 2 == 1024, "three tables");
+        *(reinterpret_cast<u32x4*>(lds.tab16) + threadIdx.x) = a;  // tab16, tab8
+        *(reinterpret_cast<u32x2*>(lds.tab4) + threadIdx.x) = b;
+        if (threadIdx.x < kWavesPerBlock * 4) (&lds.sum[0][0])[threadIdx.x] = 0;
+        if (threadIdx.x < kWavesPerBlock) lds.arrived[threadIdx.x] = 0;
+        __syncthreads();
+    }
 };
+
+// One more row of a stream: reg[f] holds column f (dword f of every lane's slot) of the rows so far.
+template <int DW, bool FIRST>
+__device__ __forceinline__ void add_row(uint32_t (&reg)[DW], const uint32_t* tab, const uint32_t (&d)[DW])
+{
+    static_for<DW>([&](auto f) { reg[f] = FIRST ? d[f] : mul_tab_add(tab, reg[f], d[f]); });
+}
+
+// Columns -> one register per lane -> times the lane's constant -> XOR over the lanes.
+template <int DW>
+__device__ __forceinline__ uint32_t finish_rows(const uint32_t (&reg)[DW], const uint32_t* tab4,
+                                                uint32_t lane_c)
+{
+    uint32_t v = reg[0];
+    static_for<DW - 1>([&](auto f) { v = mul_tab_add(tab4, v, reg[f + 1]); });
+    return wave_xor(gf2_mul(v, lane_c));
+}
+
+// Sum of the run's registers; in the run's last wavefront, on to memory.
+template <int N>
+__device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info,
+                                        const uint32_t (&reg)[N], uint32_t* __restrict__ crcs, int lane)
+{
+    const uint32_t run = (info >> 3) & 7u, len = (info >> 8) & 15u;
+    uint32_t v = reg[0];
+    static_for<N>([&](auto x) { v = (lane == x) ? reg[x] : v; });  // lane x: stream x
+    if (len > 1) {
+        // LDS operations of a wavefront complete in order: the sum is complete when the count is
+        uint32_t before = 0;
+        if (lane < N) atomicXor(&lds.sum[run][lane], v);
+        asm volatile("" ::: "memory");
+        if (lane == 0) before = atomicAdd(&lds.arrived[run], 1u);
+        if (__builtin_amdgcn_readfirstlane(before) + 1 != len) return;
+        if (lane < N) v = *const_cast<volatile uint32_t*>(&lds.sum[run][lane]);
+    }
+    uint32_t s = t.shift[0], c = t.chunk[0];
+    static_for<N>([&](auto x) {
+        s = (lane == x) ? t.shift[x] : s;
+        c = (lane == x) ? t.chunk[x] : c;
+    });
+    v = gf2_mul(v, s);
+    bool one = true;  // all streams in one chunk (any parameter much smaller than a chunk)
+    static_for<N>([&](auto x) { one = one && t.chunk[x] == t.chunk[0]; });
+    if (N == 4 && one) {
+        v ^= __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+        v ^= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
+        if (lane == 0) atomicXor(&crcs[c], v);
+    } else if (lane < N) {
+        atomicXor(&crcs[c], v);
+    }
+}
+
+// ---- parameter sub-block -------------------------------------------------------------------------
 
 struct RowIn {
     u32x2 g;
     u32x4 p, m, v;
 };
 
-struct TileGeom {
-    int n, pad_el, rows, n_batches, pad_rows;
-};
-
-__device__ __forceinline__ TileGeom tile_geom(const WorkTile& t)
-{
-    TileGeom g;
-    g.n = static_cast<int>(t.n);
-    g.pad_el = (kRowElems - g.n % kRowElems) % kRowElems;  // elements missing in front of row 0
-    g.rows = (g.n + g.pad_el) / kRowElems;
-    g.n_batches = (g.rows + kBatchRows - 1) / kBatchRows;
-    g.pad_rows = g.n_batches * kBatchRows - g.rows;  // virtual zero rows in front of row 0
-    return g;
-}
-
-// Update wavefront `u` (0..3): rows u - pad_rows, u - pad_rows + 4, ...
+// The elements [lo, hi) of the sub-block (element 0 = its first place, `at` elements behind the
+// tile's first element, perhaps before it) are the tile's.  WHOLE: all kSubElems of them, and no
+// split element among them.
 //
-// Only the first of these rows can be virtual or partial; it is handled before the loop.  From
-// then on every row is full, so the loop has no branch around a memory access: its loads are
-// unconditional and refill, in place, the register set whose values were just taken out (two sets,
-// for even and odd batches).  Registers that are never copied while a load into them is in flight,
-// and no branch between issue and use, let the compiler wait for exactly the loads a row needs,
-// while the loads of the next batch and the stores of the last one stay in flight.
-template <bool F16, bool CHAINED>
-__device__ __forceinline__ void update_role(const WorkTile& t, const TileGeom& G,
-                                            const uint8_t* __restrict__ grad,
-                                            uint8_t* __restrict__ chunks,
-                                            uint32_t* __restrict__ crcs, const FusedConsts& C,
-                                            Batch (&buf)[2], int u, int lane)
+// Not WHOLE: lanes whose four elements are all the tile's work as in a whole sub-block; the up to
+// three elements at either end that do not fill a lane's slot are updated one per lane, by lanes 0-3
+// (the slot that holds lo) and 4-7 (the slot that holds hi), and go through LDS into the slots of the
+// lanes that own them, for the CRC only.  Everything else in a slot is zero.
+template <bool F16, bool CHAINED, bool BC2, bool WHOLE>
+__device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_t info, const int at,
+                                                const int lo, const int hi,
+                                                const uint8_t* __restrict__ grad,
+                                                uint8_t* __restrict__ chunks,
+                                                uint32_t* __restrict__ crcs, const FusedConsts& C,
+                                                const TableFetch& tf, Lds& lds,
+                                                const uint32_t* __restrict__ lane_tab, int wave, int lane)
 {
-    uint8_t* const tw = reinterpret_cast<uint8_t*>(t.ptr[0]);
-    uint8_t* const tp = reinterpret_cast<uint8_t*>(t.ptr[1]);
-    uint8_t* const tm = reinterpret_cast<uint8_t*>(t.ptr[2]);
-    uint8_t* const tv = reinterpret_cast<uint8_t*>(t.ptr[3]);
-    const uint8_t* const tg = grad + 2 * t.e0;
-    uint8_t* const sw = chunks + t.soff[0];
-    uint8_t* const sp = chunks + t.soff[1];
-    uint8_t* const sm = chunks + t.soff[2];
-    uint8_t* const sv = chunks + t.soff[3];
+    const int sub = info & 7u;
+    // lane constants x^(8 * bytes between the lane's slot and the end of the block)
+    const uint32_t lane_c4 = lane_tab[(7 - sub) * 64 + lane];
+    const uint32_t lane_c2 = lane_tab[512 + (7 - sub) * 64 + lane];
+    // wave-uniform addresses of the sub-block's element 0 in every stream; a lane adds 32 bits
+    const int64_t at64 = at;
+    uint8_t* const tw = reinterpret_cast<uint8_t*>(t.ptr[0]) + 2 * at64;
+    uint8_t* const tp = reinterpret_cast<uint8_t*>(t.ptr[1]) + 4 * at64;
+    uint8_t* const tm = reinterpret_cast<uint8_t*>(t.ptr[2]) + 4 * at64;
+    uint8_t* const tv = reinterpret_cast<uint8_t*>(t.ptr[3]) + 4 * at64;
+    const uint8_t* const tg = grad + 2 * (static_cast<int64_t>(t.e0) + at64);
+    uint8_t* const sw = chunks + (static_cast<int64_t>(t.soff[0]) + 2 * at64);
+    uint8_t* const sp = chunks + (static_cast<int64_t>(t.soff[1]) + 4 * at64);
+    uint8_t* const sm = chunks + (static_cast<int64_t>(t.soff[2]) + 4 * at64);
+    uint8_t* const sv = chunks + (static_cast<int64_t>(t.soff[3]) + 4 * at64);
     // where the old master, m, v come from: their tensors, or the previous snapshot
-    const uint8_t* const lp = CHAINED ? C.prev + t.soff[1] : tp;
-    const uint8_t* const lm = CHAINED ? C.prev + t.soff[2] : tm;
-    const uint8_t* const lv = CHAINED ? C.prev + t.soff[3] : tv;
+    const uint8_t* const lp = CHAINED ? C.prev + (static_cast<int64_t>(t.soff[1]) + 4 * at64) : tp;
+    const uint8_t* const lm = CHAINED ? C.prev + (static_cast<int64_t>(t.soff[2]) + 4 * at64) : tm;
+    const uint8_t* const lv = CHAINED ? C.prev + (static_cast<int64_t>(t.soff[3]) + 4 * at64) : tv;
+    const uint32_t lane8 = 8u * lane, lane16 = 16u * lane;
+
+    auto mine = [&](int r) {  // all four elements of the lane's slot in row r
+        const int x = r * kRowElems + 4 * lane;
+        return WHOLE || (x >= lo && x + 4 <= hi);
+    };
+    RowIn q[kRows];
+    static_for<kRows>([&](auto r) {
+        if (!WHOLE) q[r] = RowIn{u32x2{0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}};
+        if (mine(r)) {
+            q[r].g = load8_unaligned<true>(tg + (lane8 + 2 * kRowElems * r));
+            q[r].p = load16_unaligned<true>(lp + (lane16 + 4 * kRowElems * r));
+            q[r].m = load16_unaligned<true>(lm + (lane16 + 4 * kRowElems * r));
+            q[r].v = load16_unaligned<true>(lv + (lane16 + 4 * kRowElems * r));
+        }
+    });
+    // edge elements: lane 0..3 element lane of the slot that holds lo, 4..7 of the slot that holds hi
+    const int edge_lo = lo & ~3, edge_hi = hi & ~3;  // first elements of those slots
+    const bool lo_cut = (lo & 3) || edge_lo + 4 > hi, hi_cut = (hi & 3) && edge_hi > edge_lo;
+    bool has_edge = false;
+    uint32_t ej = 0;  // the lane's edge element, if it has one
+    uint32_t eg = 0;
+    float ep = 0.f, em = 0.f, ev = 0.f;
+    if (!WHOLE) {
+        const int x = (lane < 4 ? edge_lo : edge_hi) + (lane & 3);
+        has_edge = lane < 8 && (lane < 4 ? lo_cut : hi_cut) && x >= lo && x < hi;
+        auto f32_at = [](const uint8_t* p) {  // stream offsets of fp32 segments may be 2 mod 4
+            return bits_to_f32(*as_global(reinterpret_cast<const u32_a2*>(p)));
+        };
+        if (has_edge) {
+            ej = static_cast<uint32_t>(x);
+            eg = *as_global(reinterpret_cast<const uint16_t*>(tg + 2 * ej));
+            ep = f32_at(lp + 4 * ej);
+            em = f32_at(lm + 4 * ej);
+            ev = f32_at(lv + 4 * ej);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    tf.put(lds);
+
     uint32_t nonfinite = 0;  // this lane's count of infinite or NaN gradient elements (fp16 only)
+    if (!WHOLE) {
+        uint32_t wb = 0;
+        if (has_edge) {
+            if constexpr (F16) nonfinite += f16_nonfinite(eg) ? 1u : 0u;
+            adam_element<F16, BC2>(C, eg, ep, em, ev);
+            ep = canonical_nan(ep);
+            em = canonical_nan(em);
+            ev = canonical_nan(ev);
+            wb = (F16 ? f32_to_f16_pair(ep, 0.f) : f32_to_bf16_pair(ep, 0.f)) & 0xFFFFu;
+            auto put32 = [](uint8_t* p, float f) { *as_global(reinterpret_cast<u32_a2*>(p)) = f32_to_bits(f); };
+            auto put16 = [](uint8_t* p, uint32_t h) {
+                *as_global(reinterpret_cast<uint16_t*>(p)) = static_cast<uint16_t>(h);
+            };
+            put16(tw + 2 * ej, wb);
+            if constexpr (!CHAINED) {
+                put32(tp + 4 * ej, ep);
+                put32(tm + 4 * ej, em);
+                put32(tv + 4 * ej, ev);
+            }
+            put16(sw + 2 * ej, wb);
+            put32(sp + 4 * ej, ep);
+            put32(sm + 4 * ej, em);
+            put32(sv + 4 * ej, ev);
+        }
+        if (lane < 8) {  // zeros where there is no edge element; LDS keeps a wavefront's order
+            reinterpret_cast<u16_alias*>(lds.edge[wave][0])[lane] = static_cast<uint16_t>(wb);
+            lds.edge[wave][1][lane] = f32_to_bits(ep);
+            lds.edge[wave][2][lane] = f32_to_bits(em);
+            lds.edge[wave][3][lane] = f32_to_bits(ev);
+        }
+    }
 
-    // A row can use vector accesses if every lane holds 4 real elements.
-    auto full_row = [&](int r) { return r > 0 || (r == 0 && G.pad_el == 0); };
-    auto load_row = [&](int r, RowIn& in) {  // r must be a full row of the tile
-        const int j0 = r * kRowElems + 4 * lane - G.pad_el;
-        in.g = load8_unaligned<true>(tg + 2 * j0);
-        in.p = load16_unaligned<true>(lp + 4 * j0);
-        in.m = load16_unaligned<true>(lm + 4 * j0);
-        in.v = load16_unaligned<true>(lv + 4 * j0);
-    };
-
-    // copy of a row's results for the folding wavefronts, which fold them and store the full rows
-    auto publish = [&](Batch& out, uint32_t (&fw)[2], uint32_t (&fp)[4], uint32_t (&fm)[4],
-                       uint32_t (&fv)[4]) {
-        *reinterpret_cast<u32x2*>(&out.w[u][2 * lane]) = u32x2{fw[0], fw[1]};
-        *reinterpret_cast<u32x4*>(&out.p[u][4 * lane]) = u32x4{fp[0], fp[1], fp[2], fp[3]};
-        *reinterpret_cast<u32x4*>(&out.m[u][4 * lane]) = u32x4{fm[0], fm[1], fm[2], fm[3]};
-        *reinterpret_cast<u32x4*>(&out.v[u][4 * lane]) = u32x4{fv[0], fv[1], fv[2], fv[3]};
-    };
-
-    // a full row from registers
-    auto full_row_step = [&](Batch& out, const RowIn& cur) {
-        uint32_t gb[4], wb[4];
-        float p[4], m[4], v[4];
-        gb[0] = cur.g.x & 0xFFFFu; gb[1] = cur.g.x >> 16;
-        gb[2] = cur.g.y & 0xFFFFu; gb[3] = cur.g.y >> 16;
-        p[0] = bits_to_f32(cur.p.x); p[1] = bits_to_f32(cur.p.y);
-        p[2] = bits_to_f32(cur.p.z); p[3] = bits_to_f32(cur.p.w);
-        m[0] = bits_to_f32(cur.m.x); m[1] = bits_to_f32(cur.m.y);
-        m[2] = bits_to_f32(cur.m.z); m[3] = bits_to_f32(cur.m.w);
-        v[0] = bits_to_f32(cur.v.x); v[1] = bits_to_f32(cur.v.y);
-        v[2] = bits_to_f32(cur.v.z); v[3] = bits_to_f32(cur.v.w);
+    static_for<kRows>([&](auto r) {
+        const RowIn& cur = q[r];
+        const uint32_t gb[4] = {cur.g.x & 0xFFFFu, cur.g.x >> 16, cur.g.y & 0xFFFFu, cur.g.y >> 16};
+        float p[4] = {bits_to_f32(cur.p.x), bits_to_f32(cur.p.y), bits_to_f32(cur.p.z), bits_to_f32(cur.p.w)};
+        float m[4] = {bits_to_f32(cur.m.x), bits_to_f32(cur.m.y), bits_to_f32(cur.m.z), bits_to_f32(cur.m.w)};
+        float v[4] = {bits_to_f32(cur.v.x), bits_to_f32(cur.v.y), bits_to_f32(cur.v.z), bits_to_f32(cur.v.w)};
 #pragma unroll
         for (int s = 0; s < 4; s++) {
             if constexpr (F16) nonfinite += f16_nonfinite(gb[s]) ? 1u : 0u;
-            adam_element<F16>(C, gb[s], p[s], m[s], v[s], wb[s]);
+            adam_element<F16, BC2>(C, gb[s], p[s], m[s], v[s]);
         }
-        uint32_t fw[2] = {wb[0] | (wb[1] << 16), wb[2] | (wb[3] << 16)};
-        uint32_t fp[4], fm[4], fv[4];
+        if (__any(__builtin_isunordered(p[0], p[1]) | __builtin_isunordered(p[2], p[3]))) {
+            asm volatile("");  // a branch, not 24 selections in every row
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            fp[s] = f32_to_bits(p[s]);
-            fm[s] = f32_to_bits(m[s]);
-            fv[s] = f32_to_bits(v[s]);
-        }
-        publish(out, fw, fp, fm, fv);
-    };
-
-    // the partial first row of a tile: element by element; absent elements stay zero
-    auto partial_row_step = [&](Batch& out, int r) {
-        const int j0 = r * kRowElems + 4 * lane - G.pad_el;
-        uint32_t gb[4], wb[4];
-        float p[4], m[4], v[4];
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const int j = j0 + s;
-            gb[s] = 0; wb[s] = 0; p[s] = 0.f; m[s] = 0.f; v[s] = 0.f;
-            if (j >= 0) {
-                gb[s] = *as_global(reinterpret_cast<const uint16_t*>(tg + 2 * j));
-                if constexpr (CHAINED) {
-                    // stream offsets of fp32 segments may be 2 mod 4: halfword loads
-                    auto f32_at = [](const uint8_t* q) {
-                        const uint16_t* h = reinterpret_cast<const uint16_t*>(q);
-                        return bits_to_f32(uint32_t(*as_global(h)) | (uint32_t(*as_global(h + 1)) << 16));
-                    };
-                    p[s] = f32_at(lp + 4 * j);
-                    m[s] = f32_at(lm + 4 * j);
-                    v[s] = f32_at(lv + 4 * j);
-                } else {
-                    p[s] = *as_global(reinterpret_cast<const float*>(tp + 4 * j));
-                    m[s] = *as_global(reinterpret_cast<const float*>(tm + 4 * j));
-                    v[s] = *as_global(reinterpret_cast<const float*>(tv + 4 * j));
-                }
-                if constexpr (F16) nonfinite += f16_nonfinite(gb[s]) ? 1u : 0u;
-                adam_element<F16>(C, gb[s], p[s], m[s], v[s], wb[s]);
-                *as_global(reinterpret_cast<uint16_t*>(tw + 2 * j)) = static_cast<uint16_t>(wb[s]);
-                if constexpr (!CHAINED) {
-                    *as_global(reinterpret_cast<float*>(tp + 4 * j)) = p[s];
-                    *as_global(reinterpret_cast<float*>(tm + 4 * j)) = m[s];
-                    *as_global(reinterpret_cast<float*>(tv + 4 * j)) = v[s];
-                }
-                *as_global(reinterpret_cast<uint16_t*>(sw + 2 * j)) = static_cast<uint16_t>(wb[s]);
-                // stream offsets of fp32 segments may be 2 mod 4: halfword stores
-                const uint32_t pb = f32_to_bits(p[s]), mb = f32_to_bits(m[s]), vb = f32_to_bits(v[s]);
-                uint16_t* qp = reinterpret_cast<uint16_t*>(sp + 4 * j);
-                uint16_t* qm = reinterpret_cast<uint16_t*>(sm + 4 * j);
-                uint16_t* qv = reinterpret_cast<uint16_t*>(sv + 4 * j);
-                *as_global(qp) = static_cast<uint16_t>(pb);
-                *as_global(qp + 1) = static_cast<uint16_t>(pb >> 16);
-                *as_global(qm) = static_cast<uint16_t>(mb);
-                *as_global(qm + 1) = static_cast<uint16_t>(mb >> 16);
-                *as_global(qv) = static_cast<uint16_t>(vb);
-                *as_global(qv + 1) = static_cast<uint16_t>(vb >> 16);
+            for (int s = 0; s < 4; s++) {
+                p[s] = canonical_nan(p[s]);
+                m[s] = canonical_nan(m[s]);
+                v[s] = canonical_nan(v[s]);
             }
         }
-        uint32_t fw[2] = {wb[0] | (wb[1] << 16), wb[2] | (wb[3] << 16)};
-        uint32_t fp[4], fm[4], fv[4];
+        uint32_t fw[2], fp[4], fm[4], fv[4];
+        fw[0] = F16 ? f32_to_f16_pair(p[0], p[1]) : f32_to_bf16_pair(p[0], p[1]);
+        fw[1] = F16 ? f32_to_f16_pair(p[2], p[3]) : f32_to_bf16_pair(p[2], p[3]);
 #pragma unroll
         for (int s = 0; s < 4; s++) {
             fp[s] = f32_to_bits(p[s]);
             fm[s] = f32_to_bits(m[s]);
             fv[s] = f32_to_bits(v[s]);
         }
-        publish(out, fw, fp, fm, fv);
+        // the results take the place of the inputs
+        q[r].g = u32x2{fw[0], fw[1]};
+        q[r].p = u32x4{fp[0], fp[1], fp[2], fp[3]};
+        q[r].m = u32x4{fm[0], fm[1], fm[2], fm[3]};
+        q[r].v = u32x4{fv[0], fv[1], fv[2], fv[3]};
+    });
+    // stores stream by stream: 4 KiB of one stream after the other
+    auto store_w = [&](uint8_t* base) {
+        static_for<kRows>([&](auto r) {
+            if (mine(r)) store8_unaligned<true>(base + (lane8 + 2 * kRowElems * r), q[r].g);
+        });
     };
+    auto store_f = [&](uint8_t* base, u32x4 RowIn::*x) {
+        static_for<kRows>([&](auto r) {
+            if (mine(r)) store16_unaligned<true>(base + (lane16 + 4 * kRowElems * r), q[r].*x);
+        });
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    store_w(tw);
+    if constexpr (!CHAINED) {
+        store_f(tp, &RowIn::p);
+        store_f(tm, &RowIn::m);
+        store_f(tv, &RowIn::v);
+    }
+    store_w(sw);
+    store_f(sp, &RowIn::p);
+    store_f(sm, &RowIn::m);
+    store_f(sv, &RowIn::v);
+    __builtin_amdgcn_sched_barrier(0);
 
-    const int first = u - G.pad_rows;  // this wavefront's row of batch 0
-    const int nb = G.n_batches;
-    int b = 0;
-    if (!full_row(first)) {
-        // a virtual row (zeros) or the partial first row of the tile
-        if (first < 0) {
-            uint32_t zw[2] = {0, 0}, z4[4] = {0, 0, 0, 0};
-            publish(buf[0], zw, z4, z4, z4);
-        } else {
-            partial_row_step(buf[0], first);
+    uint32_t rw[2], rp[4], rm[4], rv[4];
+    static_for<kRows>([&](auto r) {
+        uint32_t fw[2] = {q[r].g.x, q[r].g.y};
+        uint32_t fp[4] = {q[r].p.x, q[r].p.y, q[r].p.z, q[r].p.w};
+        uint32_t fm[4] = {q[r].m.x, q[r].m.y, q[r].m.z, q[r].m.w};
+        uint32_t fv[4] = {q[r].v.x, q[r].v.y, q[r].v.z, q[r].v.w};
+        if (!WHOLE) {
+            const int x = r * kRowElems + 4 * lane;
+            // an edge slot takes its elements from LDS, a slot outside the tile is zero
+            const int e = (lo_cut && x == edge_lo) ? 0 : (hi_cut && x == edge_hi) ? 4 : -1;
+            const bool take = e >= 0;
+            if (!mine(r)) {
+                const uint32_t k = take ? e : 0;
+                const u16_alias* w16 = reinterpret_cast<const u16_alias*>(lds.edge[wave][0]) + k;
+                fw[0] = take ? w16[0] | (uint32_t(w16[1]) << 16) : 0u;
+                fw[1] = take ? w16[2] | (uint32_t(w16[3]) << 16) : 0u;
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    fp[s] = take ? lds.edge[wave][1][k + s] : 0u;
+                    fm[s] = take ? lds.edge[wave][2][k + s] : 0u;
+                    fv[s] = take ? lds.edge[wave][3][k + s] : 0u;
+                }
+            }
+            // split first element: its first two bytes close the previous chunk and must not
+            // enter this tile's CRC of that stream
+            if (t.head_split && at <= 0 && x == edge_lo) {
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    if (s != (lo & 3)) continue;
+                    if (t.head_split & 2u) { add_head_piece(crcs, t, 4, fp[s] & 0xFFFFu); fp[s] &= 0xFFFF0000u; }
+                    if (t.head_split & 4u) { add_head_piece(crcs, t, 5, fm[s] & 0xFFFFu); fm[s] &= 0xFFFF0000u; }
+                    if (t.head_split & 8u) { add_head_piece(crcs, t, 6, fv[s] & 0xFFFFu); fv[s] &= 0xFFFF0000u; }
+                }
+            }
         }
-        __syncthreads();  // the barrier of batch 0
-        b = 1;
-    }
-    // rows first + 4b', b' >= b, are full rows
-    RowIn qa, qb;  // inputs of batch b, b + 2, ... and of batch b + 1, b + 3, ...
-    qa = qb = RowIn{u32x2{0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}};
-    if (b < nb) load_row(first + kBatchRows * b, qa);
-    if (b + 1 < nb) load_row(first + kBatchRows * (b + 1), qb);
-    // one batch: take the inputs out of `q`, refill `q` for two batches later, update the row
-    auto batch_step = [&](int bb, RowIn& q, auto prefetch_c) {
-        const int r = first + kBatchRows * bb;
-        const RowIn cur = q;
-        if constexpr (decltype(prefetch_c)::value) load_row(r + 2 * kBatchRows, q);
-        full_row_step(buf[bb & 1], cur);
-        __syncthreads();
-    };
-    // steady part: the batches two ahead exist.  Its first round stands in front of the loop, so
-    // that the loop is entered with the same loads and stores in flight as on its back edge.
-    if (b + 3 < nb) {
-        batch_step(b, qa, std::true_type{});
-        batch_step(b + 1, qb, std::true_type{});
-        b += 2;
-    }
-    while (b + 3 < nb) {
-        batch_step(b, qa, std::true_type{});
-        batch_step(b + 1, qb, std::true_type{});
-        b += 2;
-    }
-    // up to three batches are left; only the first of three still has something to prefetch
-    const int left = nb - b;
-    if (left == 3) {
-        batch_step(b, qa, std::true_type{});
-        batch_step(b + 1, qb, std::false_type{});
-        batch_step(b + 2, qa, std::false_type{});
-    } else if (left == 2) {
-        batch_step(b, qa, std::false_type{});
-        batch_step(b + 1, qb, std::false_type{});
-    } else if (left == 1) {
-        batch_step(b, qa, std::false_type{});
-    }
-    __syncthreads();  // the folding wavefronts take the last batch after this one
+        add_row<2, r == 0>(rw, lds.tab8, fw);
+        add_row<4, r == 0>(rp, lds.tab16, fp);
+        add_row<4, r == 0>(rm, lds.tab16, fm);
+        add_row<4, r == 0>(rv, lds.tab16, fv);
+    });
+    const uint32_t reg[4] = {finish_rows(rw, lds.tab4, lane_c2), finish_rows(rp, lds.tab4, lane_c4),
+                             finish_rows(rm, lds.tab4, lane_c4), finish_rows(rv, lds.tab4, lane_c4)};
+    deliver(lds, t, info, reg, crcs, lane);
 
     if constexpr (F16) {
-        if (C.n_nonfinite) {
+        if (C.n_nonfinite && __any(nonfinite != 0)) {
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) nonfinite += __shfl_xor(nonfinite, d);
-            if (lane == 0 && nonfinite)
+            if (lane == 0)
                 atomicAdd(reinterpret_cast<unsigned long long*>(C.n_nonfinite),
                           static_cast<unsigned long long>(nonfinite));
         }
     }
 }
 
-// Folding wavefront of stream x (0 = w16, 1..3 = master, m, v): takes the rows of the previous
-// batch out of LDS, stores every full row to the snapshot and (if `tensor` is set) in place, and
-// folds it.  A wavefront thus sweeps two store streams that carry the same bytes, instead of every
-// updating wavefront scattering its row over eight; the partial first row of a tile is stored
-// element by element by the updating wavefront that produced it.
-template <class F, int DW>
-__device__ __forceinline__ uint32_t fold_stream(const WorkTile& t, const TileGeom& G,
-                                                Batch (&buf)[2], int x, int lane,
-                                                uint8_t* __restrict__ tensor,
-                                                uint8_t* __restrict__ snap,
-                                                uint32_t* __restrict__ crcs, const uint32_t* tab,
-                                                const uint32_t* lane_tab)
+// ---- RAW sub-block: plain copy into the snapshot -------------------------------------------------
+//
+// Rows are aligned to the stream, so the stores go to whole lines; bytes [lo, hi) of the sub-block
+// are the tile's, and its first byte is `at` bytes behind the tile's first (perhaps before it).  A
+// slot of 16 bytes that is the tile's only in part is moved halfword by halfword, by lanes 0-7 (the
+// slot that holds lo) and 8-15 (the one that holds hi), and reaches its owner through LDS.
+__device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t info, const int at,
+                                              const int lo, const int hi, uint8_t* __restrict__ chunks,
+                                              uint32_t* __restrict__ crcs, const TableFetch& tf,
+                                              Lds& lds, const uint32_t* __restrict__ lane_tab, int wave,
+                                              int lane)
 {
-    constexpr int NE = F::NE;
-    static_assert(NE % kBatchRows == 0 && F::NF == DW, "a batch never straddles the rotation");
-    uint32_t S[NE][DW];
-    static_for<NE>([&](auto e) { static_for<DW>([&](auto f) { S[e][f] = 0; }); });
-    const int head_lane = G.pad_el / 4, head_sub = G.pad_el % 4;  // where element 0 sits in row 0
-    auto store_row = [&](int r, const uint32_t (&d)[DW]) {
-        const int j0 = r * kRowElems + 4 * lane - G.pad_el;  // first element of the lane
-        if constexpr (DW == 2) {
-            const u32x2 w = {d[0], d[1]};
-            if (tensor) store8_unaligned<true>(tensor + 2 * j0, w);
-            store8_unaligned<true>(snap + 2 * j0, w);
-        } else {
-            const u32x4 w = {d[0], d[1], d[2], d[3]};
-            if (tensor) store16_unaligned<true>(tensor + 4 * j0, w);
-            store16_unaligned<true>(snap + 4 * j0, w);
-        }
+    const int sub = info & 7u;
+    // a RAW sub-block is as long as two fp32 sub-blocks
+    const uint32_t lane_c = lane_tab[2 * (3 - sub) * 64 + lane];
+    const uint8_t* const src = reinterpret_cast<const uint8_t*>(t.ptr[0]) + at;
+    uint8_t* const dst = chunks + (static_cast<int64_t>(t.soff[0]) + at);
+    auto mine = [&](int r) {
+        const int x = r * 1024 + 16 * lane;
+        return x >= lo && x + 16 <= hi;
     };
-    // start the rotation so that it is back at zero after the last batch
-    int phase = (NE - (G.n_batches * kBatchRows) % NE) % NE;
-    for (int b = 0; b <= G.n_batches; b++) {
-        if (b >= 1) {
-            const Batch& in = buf[(b - 1) & 1];
-            uint32_t d[kBatchRows][DW];
-            static_for<kBatchRows>([&](auto k) {
-                const uint32_t* row = (DW == 2) ? &in.w[k][2 * lane]
-                                                : (x == 1 ? &in.p[k][4 * lane]
-                                                          : (x == 2 ? &in.m[k][4 * lane] : &in.v[k][4 * lane]));
-                static_for<DW>([&](auto f) { d[k][f] = row[f]; });
-            });
-            const int r0 = (b - 1) * kBatchRows - G.pad_rows;  // tile row of the batch's first row
-            if (b == 1) {
-                // the first batch may hold virtual rows (r < 0) and the partial row (r == 0)
-                static_for<kBatchRows>([&](auto k) {
-                    const int r = r0 + k;
-                    if (r > 0 || (r == 0 && G.pad_el == 0)) store_row(r, d[k]);
-                    // split first element: its first two bytes close the previous chunk and
-                    // must not enter this tile's CRC of that stream
-                    if (DW == 4 && r == 0 && (t.head_split & (1u << x)) && lane == head_lane) {
-                        static_for<DW>([&](auto sc) {
-                            if (sc == head_sub) {
-                                // two message bytes in the low half are M(x) * x^16; their
-                                // register is M(x) * x^32
-                                add_head_piece(crcs, t, 3 + x, d[k][sc] & 0xFFFFu);
-                                d[k][sc] &= 0xFFFF0000u;
-                            }
-                        });
-                    }
-                });
-            } else {
-                static_for<kBatchRows>([&](auto k) { store_row(r0 + k, d[k]); });
-            }
-            static_for<NE / kBatchRows>([&](auto Qc) {
-                constexpr int Q = Qc;
-                if (phase == Q * kBatchRows) {
-                    static_for<kBatchRows>([&](auto k) { fold_row<F, Q * kBatchRows + k>(S, d[k]); });
-                }
-            });
-            phase = (phase + kBatchRows) % NE;
+    u32x4 w[kRawRows];
+    static_for<kRawRows>([&](auto r) {
+        w[r] = u32x4{0, 0, 0, 0};
+        if (mine(r)) w[r] = load16_unaligned<true>(src + r * 1024 + 16 * lane);
+    });
+    const int edge_lo = lo & ~15, edge_hi = hi & ~15;
+    const bool lo_cut = (lo & 15) || edge_lo + 16 > hi, hi_cut = (hi & 15) && edge_hi > edge_lo;
+    uint32_t eh = 0;
+    if (lane < 16) {
+        const int x = (lane < 8 ? edge_lo : edge_hi) + 2 * (lane & 7);
+        if ((lane < 8 ? lo_cut : hi_cut) && x >= lo && x < hi) {
+            eh = *as_global(reinterpret_cast<const uint16_t*>(src + x));
+            *as_global(reinterpret_cast<uint16_t*>(dst + x)) = static_cast<uint16_t>(eh);
         }
-        __syncthreads();
     }
-    return reduce_state<F>(S, tab, lane_tab[lane]);  // tables are complete after any barrier
-}
-
-// ---- RAW tile: plain copy into the snapshot -----------------------------------------------------
-
-__device__ __forceinline__ void run_raw_tile(const WorkTile& t, uint8_t* __restrict__ chunks,
-                                             uint32_t* __restrict__ crcs, const Lds& lds, int lane)
-{
-    const int n = static_cast<int>(t.n);  // bytes, even
-    const uint8_t* const src = reinterpret_cast<const uint8_t*>(t.ptr[0]);
-    uint8_t* const dst = chunks + t.soff[0];
-    if (n == kRawRows * 1024) {
-        // a whole tile: straight-line code, kRawDepth rows in flight
-        uint32_t S[F32Fold::NE][4];
-        static_for<F32Fold::NE>([&](auto e) { static_for<4>([&](auto f) { S[e][f] = 0; }); });
-        u32x4 w[kRawDepth];
-        static_for<kRawDepth>(
-            [&](auto k) { w[k] = load16_unaligned<true>(src + k * 1024 + 16 * lane); });
-        static_for<kRawRows>([&](auto Jc) {
-            constexpr int J = Jc;
-            const u32x4 x = w[J % kRawDepth];
-            store16_unaligned<true>(dst + J * 1024 + 16 * lane, x);
-            const uint32_t d[4] = {x.x, x.y, x.z, x.w};
-            fold_row<F32Fold, J % F32Fold::NE>(S, d);
-            if constexpr (J + kRawDepth < kRawRows) {
-                __builtin_amdgcn_sched_barrier(0);
-                w[J % kRawDepth] = load16_unaligned<true>(src + (J + kRawDepth) * 1024 + 16 * lane);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        });
-        const uint32_t reg = reduce_state<F32Fold>(S, lds.tab16, lds.lane16[lane]);
-        if (lane == 0) add_piece(crcs, t, 0, reg);
-        return;
-    }
-    constexpr int NE = RawFold::NE;
-    const int pad_b = (1024 - n % 1024) % 1024;
-    const int rows = (n + pad_b) / 1024;
-    const int pad_rows = (kPhases - rows % kPhases) % kPhases;
-
-    uint32_t S[NE][4];
-    static_for<NE>([&](auto e) { static_for<4>([&](auto f) { S[e][f] = 0; }); });
-    for (int r = 0; r < rows; r++) {
-        const int b0 = r * 1024 + 16 * lane - pad_b;
-        uint32_t d[4] = {0, 0, 0, 0};
-        if (b0 >= 0) {
-            const u32x4 w = load16_unaligned<true>(src + b0);
-            store16_unaligned<true>(dst + b0, w);
-            d[0] = w.x; d[1] = w.y; d[2] = w.z; d[3] = w.w;
-        } else {
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int b = b0 + 2 * u;
-                if (b >= 0) {
-                    const uint32_t h = *as_global(reinterpret_cast<const uint16_t*>(src + b));
-                    *as_global(reinterpret_cast<uint16_t*>(dst + b)) = static_cast<uint16_t>(h);
-                    d[u >> 1] |= h << ((u & 1) * 16);
-                }
-            }
-        }
-        const int phase = (r + pad_rows) % kPhases;
-        static_for<kPhases>([&](auto Jc) {
-            constexpr int J = Jc;
-            if (phase == J) {
-                fold_row<RawFold, J>(S, d);
-                if constexpr (J == kPhases - 1) rotate_state<RawFold, kPhases>(S);
-            }
-        });
-    }
-    const uint32_t reg = reduce_state<RawFold>(S, lds.tab16, lds.lane16[lane]);
-    if (lane == 0) add_piece(crcs, t, 0, reg);
+    tf.put(lds);
+    u16_alias* const edge = reinterpret_cast<u16_alias*>(lds.edge[wave][0]);
+    if (lane < 16) edge[lane] = static_cast<uint16_t>(eh);
+    uint32_t reg[4];
+    static_for<kRawRows>([&](auto r) {
+        const int x = r * 1024 + 16 * lane;
+        if (mine(r)) store16_stream<true>(dst + x, w[r]);
+        if (lo_cut && x == edge_lo) w[r] = *reinterpret_cast<const u32x4_alias*>(edge);
+        if (hi_cut && x == edge_hi) w[r] = *reinterpret_cast<const u32x4_alias*>(edge + 8);
+        const uint32_t d[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
+        add_row<4, r == 0>(reg, lds.tab16, d);
+    });
+    const uint32_t out[1] = {finish_rows(reg, lds.tab4, lane_c)};
+    deliver(lds, t, info, out, crcs, lane);
 }
 
 // The gradient pointers of the parameter groups [grad_base, grad_base + kGradsPerLaunch) travel by
 // value in the kernel arguments: the step keeps no per-call table in device memory, so calls on
 // one plan may overlap and a captured launch carries its own pointers.
-template <bool F16, bool CHAINED>
-__global__ __launch_bounds__(kWaveSize* kWavesPerBlock) void fused_kernel(
-    const WorkTile* __restrict__ tiles, uint32_t n_tiles, uint32_t grad_base,
+template <bool F16, bool CHAINED, bool BC2>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void fused_kernel(
+    const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
     const uint32_t* __restrict__ tabs, uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs,
     FusedConsts C, GradPtrs grads)
 {
     __shared__ Lds lds;
-    __shared__ Batch buf[2];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const uint32_t ti = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);  // one tile per workgroup
-    if (ti >= n_tiles) return;
-    // The reduction tables are used after the last barrier of a tile only (every tile passes at
-    // least two), so the folding wavefronts fetch them while the updating wavefronts are already
-    // loading their first rows.
-    if (wave >= kUpdateWaves) {
-        for (int i = threadIdx.x - kUpdateWaves * kWaveSize; i < 1024; i += kFoldWaves * kWaveSize) {
-            lds.tab16[i] = tabs[i];
-            lds.tab8[i] = tabs[1024 + i];
-        }
-        if (wave == kUpdateWaves) {
-            lds.lane16[lane] = tabs[2048 + lane];
-            lds.lane8[lane] = tabs[2048 + 64 + lane];
-        }
+    const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
+    const TableFetch tf(tabs);
+    const WorkWave e = waves[group * kWavesPerBlock + wave];
+    if (e.tile == kNoTile) {
+        tf.put(lds);
+        return;
     }
     // the tile descriptor is uniform and read-only: the loads below go through scalar registers
     // (a private copy indexed by the stream number would live in scratch memory instead)
-    const WorkTile& t = tiles[ti];
-    if (t.kind != kWorkParam) return;  // RAW tiles belong to raw_kernel
-    // every wavefront of the workgroup passes the same n_batches + 1 barriers
-    const TileGeom G = tile_geom(t);
-    if (wave < kUpdateWaves) {
-        const uint8_t* grad = reinterpret_cast<const uint8_t*>(grads.p[t.grad_index - grad_base]);
-        update_role<F16, CHAINED>(t, G, grad, chunks, crcs, C, buf, wave, lane);
-    } else {
-        const int x = wave - kUpdateWaves;
-        uint8_t* const snap = chunks + t.soff[x];
-        uint32_t reg;
-        if (x == 0) {
-            reg = fold_stream<B16Fold, 2>(t, G, buf, x, lane, reinterpret_cast<uint8_t*>(t.ptr[0]),
-                                          snap, crcs, lds.tab8, lds.lane8);
-        } else {
-            // chained step: master, m and v live in the snapshots only
-            uint8_t* const tensor = CHAINED ? nullptr : reinterpret_cast<uint8_t*>(t.ptr[x]);
-            reg = fold_stream<F32Fold, 4>(t, G, buf, x, lane, tensor, snap, crcs, lds.tab16,
-                                          lds.lane16);
-        }
-        if (lane == 0) add_piece(crcs, t, x, reg);
+    const WorkTile& t = tiles[e.tile];
+    const int sub = e.info & 7u;
+    const uint32_t* const lane_tab = tabs + 3072;
+    if (t.kind == kWorkRaw) {
+        const int at = sub * int(kSubRawBytes) - static_cast<int>(t.soff[0] % kRawTileBytes);
+        const int lo = at < 0 ? -at : 0;
+        const int left = static_cast<int>(t.n) - at;
+        raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
+                      crcs, tf, lds, lane_tab, wave, lane);
+        return;
     }
+    const int at = sub * int(kSubElems) - static_cast<int>(t.e0 % kParamTileElems);
+    const int lo = at < 0 ? -at : 0;
+    const int left = static_cast<int>(t.n) - at;
+    const int hi = left < int(kSubElems) ? left : int(kSubElems);
+    const uint8_t* const grad = reinterpret_cast<const uint8_t*>(grads.p[t.grad_index - grad_base]);
+    if (lo == 0 && hi == int(kSubElems) && !(t.head_split && at == 0))
+        param_sub_block<F16, CHAINED, BC2, true>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds,
+                                            lane_tab, wave, lane);
+    else
+        param_sub_block<F16, CHAINED, BC2, false>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds,
+                                             lane_tab, wave, lane);
 }
 
 // ---- the step's traffic alone (bench helper) -------------------------------------------------------
@@ -736,26 +688,6 @@ __global__ __launch_bounds__(kStageThreads) void mix_ceiling_kernel(
     }
 }
 
-// RAW tiles: one wavefront per tile copies its bytes into the snapshot and folds them.
-constexpr int kRawWaves = 4;
-__global__ __launch_bounds__(kWaveSize* kRawWaves) void raw_kernel(
-    const WorkTile* __restrict__ tiles, uint32_t n_tiles, const uint32_t* __restrict__ tabs,
-    uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs)
-{
-    __shared__ Lds lds;
-    for (int i = threadIdx.x; i < 1024; i += blockDim.x) lds.tab16[i] = tabs[i];
-    if (threadIdx.x < kWaveSize) lds.lane16[threadIdx.x] = tabs[2048 + threadIdx.x];
-    __syncthreads();
-    const int lane = threadIdx.x & (kWaveSize - 1);
-    // consecutive tiles per XCD, as in the tile kernel (a RAW tile is a 32 KiB copy as well)
-    const uint32_t ti = xcd_order(blockIdx.x, gridDim.x, kDefaultXcdGroup) * kRawWaves +
-                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    if (ti >= n_tiles) return;
-    const WorkTile& t = tiles[ti];
-    if (t.kind != kWorkRaw) return;
-    run_raw_tile(t, chunks, crcs, lds, lane);
-}
-
 // crcs[] = the preset/complement term (the tiles XOR their pieces into it), the tail of the last
 // chunk = 0, and the non-finite gradient counter = 0
 __global__ void fused_prepare_kernel(uint32_t* __restrict__ crcs, uint64_t n_chunks, uint32_t affine,
@@ -775,21 +707,25 @@ __global__ void fused_prepare_kernel(uint32_t* __restrict__ crcs, uint64_t n_chu
 
 void build_fused_tabs(uint32_t* tab)
 {
-    const uint64_t row_bytes[2] = {1024, 512};
-    for (int t = 0; t < 2; t++) {
-        const uint32_t u = gf2_xpow(8 * row_bytes[t]);
+    const uint64_t step[3] = {8192, 4096, 32};
+    for (int t = 0; t < 3; t++) {
+        const uint32_t u = gf2_xpow(step[t]);
         for (int k = 0; k < 4; k++)
             for (uint32_t b = 0; b < 256; b++) tab[t * 1024 + k * 256 + b] = gf2_mul(b << (8 * k), u);
-        for (int lane = 0; lane < 64; lane++)
-            tab[2048 + t * 64 + lane] = gf2_xpow(8 * (row_bytes[t] / 64) * (63 - lane));
+    }
+    for (int w = 0; w < 2; w++) {
+        const uint64_t lane_bytes = w ? 8 : 16;
+        for (int k = 0; k < 8; k++)
+            for (int lane = 0; lane < 64; lane++)
+                tab[3072 + w * 512 + k * 64 + lane] =
+                    gf2_xpow(8 * (lane_bytes * (63 - lane) + lane_bytes * kWaveSize * kRows * k));
     }
 }
 
-hipError_t launch_fused(bool f16, const WorkTile* tiles, uint32_t n_param_tiles,
-                        uint32_t n_raw_tiles, const void* const* grads, uint32_t n_params,
-                        const uint32_t* group_tile_begin, const uint32_t* tabs, void* chunks,
-                        uint32_t* crcs, uint64_t n_chunks, uint64_t payload, uint64_t buffer_bytes,
-                        uint32_t affine, const FusedConsts& consts, bool bare, hipStream_t stream)
+hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grads, uint32_t n_params,
+                        const uint32_t* tabs, void* chunks, uint32_t* crcs, uint64_t n_chunks,
+                        uint64_t payload, uint64_t buffer_bytes, uint32_t affine,
+                        const FusedConsts& consts, bool bare, hipStream_t stream)
 {
     uint8_t* c = static_cast<uint8_t*>(chunks);
     hipError_t e = hipSuccess;
@@ -807,36 +743,38 @@ hipError_t launch_fused(bool f16, const WorkTile* tiles, uint32_t n_param_tiles,
         if (e != hipSuccess) return e;
     }
     const bool chained = consts.prev != nullptr;
-    auto kernel = chained ? (f16 ? fused_kernel<true, true> : fused_kernel<false, true>)
-                          : (f16 ? fused_kernel<true, false> : fused_kernel<false, false>);
-    // one launch per kGradsPerLaunch parameter groups; the parameter tiles are sorted by group
-    for (uint32_t k = 0, p0 = 0; p0 < n_params && n_param_tiles; k++, p0 += kGradsPerLaunch) {
-        const uint32_t t0 = group_tile_begin[k], t1 = group_tile_begin[k + 1];
-        if (t1 == t0) continue;
+    using Kernel = decltype(&fused_kernel<false, false, false>);
+    static const Kernel kernels[8] = {
+        fused_kernel<false, false, false>, fused_kernel<false, false, true>,
+        fused_kernel<false, true, false>,  fused_kernel<false, true, true>,
+        fused_kernel<true, false, false>,  fused_kernel<true, false, true>,
+        fused_kernel<true, true, false>,   fused_kernel<true, true, true>};
+    const bool bc2 = consts.adam.bc2s != 1.0f;
+    const Kernel kernel = kernels[(f16 ? 4 : 0) + (chained ? 2 : 0) + (bc2 ? 1 : 0)];
+    // one launch per kGradsPerLaunch parameter groups; tiles and wavefronts are sorted by group
+    for (uint32_t k = 0, p0 = 0; p0 < n_params; k++, p0 += kGradsPerLaunch) {
         GradPtrs g;
         for (uint32_t i = 0; i < kGradsPerLaunch; i++)
             g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
         if (bare) {
+            const uint32_t t0 = work.launch_tile[k], t1 = work.launch_tile[k + 1];
+            if (t1 == t0) continue;
             // two workgroups per tile, one per half
             if (chained)
                 hipLaunchKernelGGL(mix_ceiling_kernel<true>, dim3(2 * (t1 - t0)), dim3(kStageThreads),
-                                   0, stream, tiles + t0, t1 - t0, p0, c, consts, g);
+                                   0, stream, work.tiles + t0, t1 - t0, p0, c, consts, g);
             else
                 hipLaunchKernelGGL(mix_ceiling_kernel<false>, dim3(2 * (t1 - t0)),
-                                   dim3(kStageThreads), 0, stream, tiles + t0, t1 - t0, p0, c, consts,
+                                   dim3(kStageThreads), 0, stream, work.tiles + t0, t1 - t0, p0, c, consts,
                                    g);
         } else {
-            hipLaunchKernelGGL(kernel, dim3(t1 - t0), dim3(kWaveSize * kWavesPerBlock), 0, stream,
-                               tiles + t0, t1 - t0, p0, tabs, c, crcs, consts, g);
+            const uint32_t w0 = work.launch_wave[k], w1 = work.launch_wave[k + 1];
+            if (w1 == w0) continue;
+            hipLaunchKernelGGL(kernel, dim3((w1 - w0) / kWavesPerGroup), dim3(kThreads), 0, stream,
+                               work.waves + w0, work.tiles, p0, tabs, c, crcs, consts, g);
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-    }
-    if (n_raw_tiles && !bare) {
-        const unsigned grid = (n_raw_tiles + kRawWaves - 1) / kRawWaves;
-        hipLaunchKernelGGL(raw_kernel, dim3(grid), dim3(kWaveSize * kRawWaves), 0, stream,
-                           tiles + n_param_tiles, n_raw_tiles, tabs, c, crcs);
-        e = hipGetLastError();
     }
     return e;
 }

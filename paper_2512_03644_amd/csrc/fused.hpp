@@ -24,9 +24,10 @@ struct FusedConsts {
 };
 
 // Device table of the fused kernels (kFusedTabWords entries): byte tables of multiplication by
-// x^8192 (1 KiB rows) and by x^4096 (512 B rows), then the lane constants x^(128 * (63 - lane))
-// and x^(64 * (63 - lane)).
-constexpr int kFusedTabWords = 2048 + 128;
+// x^8192 (1 KiB rows), x^4096 (512 B rows) and x^32, then the lane constants of 16-byte and of
+// 8-byte slots: for k = 0..7 and every lane, x^(8 * bytes between the end of the lane's slot in a
+// row and the end of that row, plus k sub-blocks).
+constexpr int kFusedTabWords = 3072 + 1024;
 void build_fused_tabs(uint32_t* tab);
 
 // Gradient pointers of up to kGradsPerLaunch consecutive parameter groups, handed to the kernel by
@@ -36,19 +37,24 @@ struct GradPtrs {
     uint64_t p[kGradsPerLaunch];
 };
 
+// A plan's work lists on the device, and on the host where the part of every launch begins (one
+// entry more than there are launches).
+struct FusedWork {
+    const WorkTile* tiles = nullptr;       // parameter tiles first, sorted by group, then RAW tiles
+    const WorkWave* waves = nullptr;
+    std::vector<uint32_t> launch_tile;     // parameter tiles only
+    std::vector<uint32_t> launch_wave;
+};
+
 // Enqueues prepare (crcs = affine, zero tail, counter = 0) and the tile kernels.
-// tiles/tabs: device tables (tabs = tables for 1024-byte rows, then for 512-byte rows); tiles holds
-// the parameter tiles first, sorted by parameter group, then the RAW tiles (a kernel of their own).
-// grads: HOST array of n_params device pointers, read during the call only.  group_tile_begin:
-// HOST array, entry k = index of the first parameter tile of group k * kGradsPerLaunch, one more
-// entry = n_param_tiles.  f16: gradients and working weights are fp16 (else bf16).  bare: the
+// tabs: device table (build_fused_tabs).  grads: HOST array of n_params device pointers, read
+// during the call only.  f16: gradients and working weights are fp16 (else bf16).  bare: the
 // step's traffic alone -- every parameter tile's loads and stores with no arithmetic and no CRC
 // (16-bit weights := gradient bits, master, m, v unchanged); crcs, the RAW segments and the zero
 // tail are not touched.
-hipError_t launch_fused(bool f16, const WorkTile* tiles, uint32_t n_param_tiles,
-                        uint32_t n_raw_tiles, const void* const* grads, uint32_t n_params,
-                        const uint32_t* group_tile_begin, const uint32_t* tabs, void* chunks,
-                        uint32_t* crcs, uint64_t n_chunks, uint64_t payload, uint64_t buffer_bytes,
-                        uint32_t affine, const FusedConsts& consts, bool bare, hipStream_t stream);
+hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grads, uint32_t n_params,
+                        const uint32_t* tabs, void* chunks, uint32_t* crcs, uint64_t n_chunks,
+                        uint64_t payload, uint64_t buffer_bytes, uint32_t affine,
+                        const FusedConsts& consts, bool bare, hipStream_t stream);
 
 }  // namespace ffsnap

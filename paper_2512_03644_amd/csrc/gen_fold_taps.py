@@ -53,58 +53,7 @@ def xpow(e):
     return r
 
 
-def solve_min_weight(S, F, NE):
-    """For a small surplus of candidates over the 32 dimensions of the residue space: solve the
-    linear system by Gaussian elimination, then walk the whole solution set (one particular
-    solution plus the null space) and keep the representation with the fewest terms."""
-    cand = [S * e + f for e in range(NE) for f in range(F)]
-    n = len(cand)
-    vecs = [xpow(32 * E) for E in cand]
-    basis = {}     # highest bit -> (value, mask of candidates)
-    null = []      # masks of candidate subsets that XOR to zero
-    for i, v in enumerate(vecs):
-        m = 1 << i
-        while v:
-            hb = v.bit_length() - 1
-            if hb in basis:
-                v ^= basis[hb][0]
-                m ^= basis[hb][1]
-            else:
-                basis[hb] = (v, m)
-                break
-        if not v:
-            null.append(m)
-    assert len(null) <= 20, "too many candidates for exhaustive enumeration"
-    out = []
-    for f in range(F):
-        v, m = xpow(32 * (S * NE + f)), 0
-        while v:
-            hb = v.bit_length() - 1
-            if hb not in basis:
-                raise SystemExit("target outside the span for S=%d F=%d NE=%d f=%d" % (S, F, NE, f))
-            v ^= basis[hb][0]
-            m ^= basis[hb][1]
-        best = None
-        for k in range(1 << len(null)):
-            mm = m
-            for j, nm in enumerate(null):
-                if (k >> j) & 1:
-                    mm ^= nm
-            key = (bin(mm).count("1"), mm)
-            if best is None or key < best:
-                best = key
-        taps = [i for i in range(n) if (best[1] >> i) & 1]
-        acc = xpow(32 * (S * NE + f))
-        for i in taps:
-            acc ^= vecs[i]
-        assert acc == 0
-        out.append([(cand[i] // S, cand[i] % S) for i in taps])
-    return out
-
-
 def search(S, F, NE, ntaps):
-    if ntaps == 0:
-        return solve_min_weight(S, F, NE)
     cand = [S * e + f for e in range(NE) for f in range(F)]
     r = np.array([xpow(32 * E) for E in cand], dtype=np.uint64)
     n = len(cand)
@@ -151,9 +100,6 @@ def search(S, F, NE, ntaps):
 SETS = [
     # name, row bytes, dwords per lane, NE, taps
     ("Fold16x16", 1024, 4, 16, 9),
-    # 0 = fewest terms found by exhaustive walk of the solution set (few candidates, small state)
-    ("Fold16x10", 1024, 4, 10, 0),
-    ("Fold8x20", 512, 2, 20, 0),
 ]
 
 

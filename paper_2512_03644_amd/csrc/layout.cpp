@@ -109,10 +109,37 @@ int build_layout(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_bytes, 
 
 namespace {
 
-uint32_t shift_to_chunk_end(uint64_t piece_end, uint64_t chunk_bytes)
+// x has order 2^31 - 1 modulo the generator (a primitive polynomial of degree 31 times x + 1), so
+// exponents can be taken modulo that, negative ones too.
+constexpr int64_t kOrder = 0x7FFFFFFF;
+static_assert(gf2_xpow(kOrder) == kOne, "order of x");
+
+// x^n from one table per byte of the exponent: three multiplications.
+struct PowTable {
+    uint32_t t[4][256];
+    PowTable()
+    {
+        for (int i = 0; i < 4; i++) {
+            const uint32_t base = gf2_xpow(1ull << (8 * i));
+            t[i][0] = kOne;
+            for (int b = 1; b < 256; b++) t[i][b] = gf2_mul(t[i][b - 1], base);
+        }
+    }
+    uint32_t operator()(int64_t n) const
+    {
+        const uint32_t e = static_cast<uint32_t>((n % kOrder + kOrder) % kOrder);
+        return gf2_mul(gf2_mul(t[0][e & 255], t[1][(e >> 8) & 255]),
+                       gf2_mul(t[2][(e >> 16) & 255], t[3][e >> 24]));
+    }
+};
+
+// The factor that takes the register of a block (without its x^32) whose last byte ends at stream
+// offset block_end to the end of chunk `chunk`.
+uint32_t shift_to_chunk_end(const PowTable& xp, uint64_t chunk, uint64_t block_end,
+                            uint64_t chunk_bytes)
 {
-    const uint64_t chunk_end = (piece_end + chunk_bytes - 1) / chunk_bytes * chunk_bytes;
-    return gf2_xpow(8 * (chunk_end - piece_end));
+    const int64_t d = static_cast<int64_t>((chunk + 1) * chunk_bytes) - static_cast<int64_t>(block_end);
+    return xp(32 + 8 * d);
 }
 
 }  // namespace
@@ -120,6 +147,7 @@ uint32_t shift_to_chunk_end(uint64_t piece_end, uint64_t chunk_bytes)
 void build_work_tiles(const Layout& L, std::vector<WorkTile>& out)
 {
     out.clear();
+    const PowTable xp;
     const uint64_t C = L.chunk_bytes;
     std::vector<bool> in_group(L.segs.size(), false);
     for (size_t pi = 0; pi < L.params.size(); pi++) {
@@ -145,27 +173,28 @@ void build_work_tiles(const Layout& L, std::vector<WorkTile>& out)
         for (auto it = cuts.begin(); it != cuts.end(); ++it) {
             auto nx = std::next(it);
             const uint64_t end = (nx == cuts.end()) ? p.numel : nx->first;
-            for (uint64_t e0 = it->first; e0 < end; e0 += kParamTileElems) {
+            for (uint64_t e0 = it->first; e0 < end;) {
+                const uint64_t block_end = (e0 / kParamTileElems + 1) * kParamTileElems;
                 WorkTile t{};
                 t.kind = kWorkParam;
                 t.grad_index = static_cast<uint32_t>(pi);
                 t.e0 = e0;
-                t.n = static_cast<uint32_t>(std::min<uint64_t>(kParamTileElems, end - e0));
+                t.n = static_cast<uint32_t>(std::min(block_end, end) - e0);
                 t.head_split = (e0 == it->first) ? it->second : 0;
                 for (int x = 0; x < 4; x++) {
                     t.ptr[x] = ptr[x] + size[x] * e0;
                     t.soff[x] = off[x] + size[x] * e0;
                     uint64_t begin = t.soff[x];
-                    const uint64_t stop = t.soff[x] + size[x] * t.n;
                     if (t.head_split & (1u << x)) {
                         t.chunk[3 + x] = static_cast<uint32_t>(begin / C);
                         t.shift[3 + x] = kOne;  // the two head bytes end their chunk
                         begin += 2;
                     }
                     t.chunk[x] = static_cast<uint32_t>(begin / C);
-                    t.shift[x] = shift_to_chunk_end(stop, C);
+                    t.shift[x] = shift_to_chunk_end(xp, t.chunk[x], off[x] + size[x] * block_end, C);
                 }
                 out.push_back(t);
+                e0 += t.n;
             }
         }
     }
@@ -175,7 +204,8 @@ void build_work_tiles(const Layout& L, std::vector<WorkTile>& out)
         uint64_t pos = 0;
         while (pos < s.nbytes) {
             const uint64_t abs = s.off + pos;
-            uint64_t len = std::min<uint64_t>(kRawTileBytes, s.nbytes - pos);
+            const uint64_t block_end = (abs / kRawTileBytes + 1) * kRawTileBytes;
+            uint64_t len = std::min<uint64_t>(block_end - abs, s.nbytes - pos);
             len = std::min<uint64_t>(len, (abs / C + 1) * C - abs);
             WorkTile t{};
             t.kind = kWorkRaw;
@@ -183,11 +213,51 @@ void build_work_tiles(const Layout& L, std::vector<WorkTile>& out)
             t.ptr[0] = s.ptr + pos;
             t.soff[0] = abs;
             t.chunk[0] = static_cast<uint32_t>(abs / C);
-            t.shift[0] = shift_to_chunk_end(abs + len, C);
+            t.shift[0] = shift_to_chunk_end(xp, t.chunk[0], block_end, C);
             out.push_back(t);
             pos += len;
         }
     }
+}
+
+void build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
+                      uint32_t groups_per_launch, std::vector<WorkWave>& out,
+                      std::vector<uint32_t>& begin)
+{
+    out.clear();
+    begin.assign(1, 0);
+    auto fill_group = [&] {
+        while (out.size() % kWavesPerGroup) out.push_back(WorkWave{kNoTile, 0});
+    };
+    const uint64_t launches = (n_params + groups_per_launch - 1) / groups_per_launch;
+    for (size_t i = 0; i < tiles.size(); i++) {
+        const WorkTile& t = tiles[i];
+        uint64_t first, last;  // sub-blocks the tile touches
+        if (t.kind == kWorkParam) {
+            const uint64_t in_block = t.e0 % kParamTileElems;
+            first = in_block / kSubElems;
+            last = (in_block + t.n - 1) / kSubElems;
+            while (begin.size() <= t.grad_index / groups_per_launch) {
+                fill_group();
+                begin.push_back(static_cast<uint32_t>(out.size()));
+            }
+        } else {
+            const uint64_t in_block = t.soff[0] % kRawTileBytes;
+            first = in_block / kSubRawBytes;
+            last = (in_block + t.n - 1) / kSubRawBytes;
+        }
+        // a tile that fills a workgroup gets one to itself
+        if (last - first + 1 == kWavesPerGroup) fill_group();
+        for (uint64_t s = first; s <= last;) {
+            const uint64_t slot = out.size() % kWavesPerGroup;
+            const uint64_t run = std::min<uint64_t>(last - s + 1, kWavesPerGroup - slot);
+            for (uint64_t k = 0; k < run; k++, s++)
+                out.push_back(WorkWave{static_cast<uint32_t>(i),
+                                       static_cast<uint32_t>(s | (slot << 3) | (run << 8))});
+        }
+    }
+    fill_group();
+    while (begin.size() < launches + 1) begin.push_back(static_cast<uint32_t>(out.size()));
 }
 
 }  // namespace ffsnap

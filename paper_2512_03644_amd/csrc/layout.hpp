@@ -40,18 +40,23 @@ struct Layout {
     std::vector<uint64_t> tile_base;
 };
 
-// Unit of work of the fused optimizer step: a run of elements of one parameter group (its four
-// streams w16/master/m/v), or a run of bytes of a RAW segment.  Runs are cut wherever one of
-// their streams crosses a chunk boundary, so each stream of a tile lies inside one chunk and
-// adds one term ("piece") to that chunk's CRC: register(piece) * x^(8 * bytes from the end of
-// the piece to the end of the chunk).  An fp32 element that straddles a chunk boundary (its
-// stream offset is 2 mod 4) starts a tile; its first two bytes form a separate "head" piece
-// that ends the previous chunk.
+// Unit of work of the fused optimizer step: the elements of one parameter group (its four streams
+// w16/master/m/v) that lie in one aligned block of kParamTileElems elements, or the bytes of a RAW
+// segment that lie in one aligned block of kRawTileBytes bytes of the stream.  A block is cut wherever
+// one of its streams crosses a chunk boundary, so each stream of a tile lies inside one chunk and
+// adds one term ("piece") to that chunk's CRC.  Tiles are aligned to the tensors' elements rather
+// than to the cuts, so that behind a cut the rows go on where the tensors' memory lines lie.
+// A tile's register is taken over the whole block, with zeros where the block is not the tile's;
+// zeros in front do not change a register started from 0 and zeros behind multiply it by a power of
+// x, so shift = x^(32 + 8 * bytes from the END OF THE BLOCK to the end of the chunk), an exponent
+// that may be negative.  (The register lacks the factor x^32 that a CRC register carries.)
+// An fp32 element that straddles a chunk boundary (its stream offset is 2 mod 4) starts a tile; its
+// first two bytes form a separate "head" piece that ends the previous chunk.
 struct WorkTile {
     uint64_t ptr[4];    // addresses of the tile's first element: w16, master, m, v (RAW: ptr[0])
     uint64_t soff[4];   // stream offsets of the tile's first byte in each stream
     uint32_t chunk[7];  // pieces 0..3: the four streams; 4..6: head pieces of master, m, v
-    uint32_t shift[7];  // x^(8 * distance to the chunk end) mod P; 0 = piece absent
+    uint32_t shift[7];  // see above; head pieces: 1; 0 = piece absent
     uint64_t e0;        // first element within the parameter (indexes the gradient)
     uint32_t n;         // elements (parameter tile) or bytes (RAW tile)
     uint32_t kind;      // 0 = parameter group, 1 = RAW
@@ -63,9 +68,30 @@ constexpr uint32_t kWorkParam = 0, kWorkRaw = 1;
 constexpr uint32_t kParamTileElems = 1u << 13;
 constexpr uint32_t kRawTileBytes = 1u << 15;
 
+// What one wavefront of the fused step works on: one sub-block of a tile.  kWavesPerGroup
+// consecutive entries make a workgroup; the entries of one tile that share a workgroup (a run) sum
+// their registers in LDS before they go to memory.
+struct WorkWave {
+    uint32_t tile;  // index into the tile list, or kNoTile: nothing to do
+    uint32_t info;  // bits 0..2 sub-block of the tile's block, 3..5 place of the run's first
+                    // wavefront in the workgroup, 8..11 wavefronts in the run
+};
+constexpr uint32_t kNoTile = 0xFFFFFFFFu;
+constexpr uint32_t kWavesPerGroup = 8;
+constexpr uint32_t kSubElems = kParamTileElems / 8;  // 4 rows of 256 elements
+constexpr uint32_t kSubRawBytes = kRawTileBytes / 4; // 8 rows of 1 KiB
+
 // Work list of the fused step over the whole layout (needs L.adam_ok): the parameter tiles first,
 // then the RAW tiles.
 void build_work_tiles(const Layout& L, std::vector<WorkTile>& out);
+
+// The wavefronts of the tiles, launch by launch: launch k takes the parameter groups
+// [k * groups_per_launch, (k + 1) * groups_per_launch), the last launch the RAW tiles as well.
+// begin[k] is the first entry of launch k, one more entry the end; each a multiple of
+// kWavesPerGroup.
+void build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
+                      uint32_t groups_per_launch, std::vector<WorkWave>& out,
+                      std::vector<uint32_t>& begin);
 
 // Returns FF_OK or a negative ff_status; `out` is valid only on FF_OK.
 // tile_log2: 0 = default tile size, else log2 of the tile size in bytes (clamped to

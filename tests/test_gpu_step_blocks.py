@@ -1,0 +1,62 @@
+"""The optimizer step's sub-blocks of 1024 elements (8 KiB of a RAW segment) at the sizes where they
+can go wrong: around a lane's slot, a row, a sub-block and a block, with chunk boundaries that cut
+blocks anywhere, and on tensors that start off every alignment."""
+import pytest
+import torch
+
+from paper_2512_03644_amd import binding as ff
+from paper_2512_03644_amd import workloads as wl
+from test_gpu_parity import DEV, HP, _adam_and_compare, _chained_and_compare
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 2, 3, 4, 5, 7, 8, 9, 255, 256, 257, 259, 1023, 1024, 1025, 1027, 8188, 8191, 8192, 8193,
+         8197, 16384 + 1022]
+
+
+def _raw(numels, dtype, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return [torch.randn(n, device=DEV, generator=g).to(dtype) for n in numels]
+
+
+@pytest.mark.parametrize("chunk", [1024, 2048, 1 << 15, 1 << 22])
+def test_block_edges_in_place_and_chained(oracle, chunk):
+    raw = _raw([1, 3, 7, 8, 9, 511, 4095, 4096, 4097, 16383, 16384, 16385 + 4096], torch.bfloat16, chunk)
+    extra = [(5 * i, t) for i, t in enumerate(raw)]
+    _adam_and_compare(oracle, EDGES, chunk, seed=chunk, hp=dict(HP, step=3), extra_raw=extra)
+    _chained_and_compare(oracle, EDGES, chunk, seed=chunk + 1, steps=2, half=torch.float16,
+                         loss_scale=1024.0, extra_raw=extra)
+
+
+@pytest.mark.parametrize("shift", [1, 3, 7])
+def test_step_on_tensors_off_every_alignment(shift):
+    """Tensors and gradients that start `shift` elements into an allocation give the same snapshot,
+    CRCs and state as aligned ones."""
+    numels, chunk = [5, 1030, 8192, 20001], 1 << 14
+    a = wl.param_shard("a", numels, chunk, 5 + shift, DEV, with_grads=True)
+
+    def moved(t):
+        room = torch.zeros(t.numel() + shift + 8, dtype=t.dtype, device=DEV)
+        room[shift:shift + t.numel()] = t
+        return room[shift:shift + t.numel()], room
+
+    b, rooms = [], []
+    for t in a.segments + [p.grad for p in a.params]:
+        view, room = moved(t)
+        b.append(view)
+        rooms.append((room, t.numel()))
+    segs_b, grads_b = b[:len(a.segments)], b[len(a.segments):]
+    kinds = [ff.FF_KIND_W16, ff.FF_KIND_MASTER, ff.FF_KIND_M, ff.FF_KIND_V] * len(numels)
+    pids = [k for k in range(len(numels)) for _ in range(4)]
+    got = []
+    for segs, grads in ((a.segments, [p.grad for p in a.params]), (segs_b, grads_b)):
+        plan = ff.ff_snapshot_plan(segs, chunk, 0, kinds, pids)
+        chunks, crcs, _, _ = ff.alloc_outputs(plan, DEV)
+        ff.ff_adam_step_snapshot(plan, grads, HP, chunks, crcs)
+        torch.cuda.synchronize()
+        got.append((chunks, crcs))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    for x, y, (room, n) in zip(a.segments, segs_b, rooms):
+        assert torch.equal(x, y)
+        assert not room[:shift].any() and not room[shift + n:].any()  # nothing around it is touched
