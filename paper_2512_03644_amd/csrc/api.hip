@@ -42,10 +42,10 @@ struct ff_plan {
     uint32_t affine = 0;  // preset/complement term of a chunk_bytes-long CRC
     // fused optimizer step (only when every parameter group is complete)
     FusedWork work;
-    // XCD-aware order of the fused step's workgroups (kernels.hpp): runs of 1, 4, 16 and 64 are within
-    // the 3 % that runs differ by on aligned shards; on 7 GB of odd-sized parameters 64 is ahead
-    // (3.67 against 3.82-4.0 ms)
-    uint32_t fused_xcd_group = 64;
+    // XCD-aware order (kernels.hpp) of the step's workgroups of 4096 elements, in place and chained;
+    // runs of 4 / 16 / 64 on the 7B shard 6.69 / 6.62 / 6.60 and 4.66 / 4.52 / 4.57 ms, on 360 million
+    // odd-sized elements 2.81 / 2.80 / 2.78 and 2.05 / 2.02 / 2.06 ms
+    uint32_t fused_xcd_group = 64, chained_xcd_group = 16;
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
 };
@@ -231,8 +231,9 @@ int ff_snapshot_plan(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_byt
             delete p;
             return FF_ERR_INVALID;
         }
-        if (xg == 31u) t.xcd_group = p->fused_xcd_group = p->mix_xcd_group = 0;
-        else if (xg) t.xcd_group = p->fused_xcd_group = p->mix_xcd_group = 1u << (xg - 1);
+        if (xg == 31u) t.xcd_group = p->fused_xcd_group = p->chained_xcd_group = p->mix_xcd_group = 0;
+        else if (xg)
+            t.xcd_group = p->fused_xcd_group = p->chained_xcd_group = p->mix_xcd_group = 1u << (xg - 1);
     }
     if (L.n_tiles > 0xFFFFFFF0ull) {
         delete p;
@@ -424,7 +425,7 @@ int adam_impl(const ff_plan* p, const void* const* grads, const ff_adam_hparams*
         c.adam.eps = hp->eps;
     }
     c.inv_scale = inv_scale;
-    c.xcd_group = bare ? p->mix_xcd_group : p->fused_xcd_group;
+    c.xcd_group = bare ? p->mix_xcd_group : prev ? p->chained_xcd_group : p->fused_xcd_group;
     c.n_nonfinite = n_nonfinite;
     c.prev = static_cast<const uint8_t*>(prev);
     FF_HIP_TRY(launch_fused(half_dtype == FF_F16, p->work, grads,

@@ -136,6 +136,18 @@ __device__ __forceinline__ uint32_t wave_xor(uint32_t v)
            __builtin_amdgcn_readlane(v, 32) ^ __builtin_amdgcn_readlane(v, 48);
 }
 
+// XOR over the lanes with the same lane mod 4, the same value in all of them.
+__device__ __forceinline__ uint32_t quad_place_xor(uint32_t v)
+{
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, true);  // row_ror:4
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror:8
+    // both halves of a swapped pair of copies: the neighbouring row of 16 lanes, the other 32 lanes
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = a[0] ^ a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return b[0] ^ b[1];
+}
+
 // State of all lanes -> R / x^32, where R is the CRC register (run from 0) of the rows folded so
 // far; the factor x^32 that every register carries is applied once per chunk by the combine
 // step.  The result is valid in every lane.  tab: byte tables of x^(8*ROW_BYTES);

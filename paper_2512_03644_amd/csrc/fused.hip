@@ -1,21 +1,32 @@
 // Fused optimizer step + snapshot for gfx950.
 //
 // Work tiles (layout.hpp) are blocks of up to kParamTileElems elements of one parameter group, or of
-// up to kRawTileBytes bytes of a RAW segment.  One wavefront takes one sub-block: 4 rows of 256
+// up to kRawTileBytes bytes of a RAW segment.  One wavefront takes one sub-block: 2 rows of 256
 // elements, lane l of a row taking 4 consecutive elements: 8 bytes of 16-bit gradient and 3 x 16
 // bytes of fp32 master/m/v come in, the AdamW update runs in registers, and the four results go out
 // twice -- in place, and at their stream offsets in the chunk buffer -- and, from the same registers,
 // into the CRC of their stream, so the snapshot is never read back from memory.  Rows are aligned
 // to the tensors' elements; elements of a row that are not the tile's count as zeros.
 //
-// A sub-block is straight-line code: 16 loads up front, then row by row update, 8 stores and one
-// Horner step of each stream's register through byte tables in LDS (x^8192 or x^4096 per row).  No
-// loop, no barrier behind the loads and no hand-off between wavefronts; what overlaps one wavefront's
-// arithmetic with another's memory is 4 of them on every SIMD.  The sub-blocks of a tile that share a
-// workgroup sum their registers in LDS; the last one to arrive multiplies the sums by x^(8 * distance
-// to the end of the chunk) and XORs them into crcs[chunk] with an atomic; XOR is commutative, so the
-// result does not depend on the order in which tiles finish.  A prepare kernel sets crcs[] to the
-// preset/complement term and writes the zero tail of the last chunk.
+// A sub-block is straight-line code with all its loads up front; each further row is one Horner step
+// of a stream's register through byte tables in LDS (x^8192 or x^4096 per row), and the lanes of a
+// quad share the four streams among themselves before the multiplication by the lane's constant.
+// The sub-blocks of a tile that share a workgroup sum their registers in LDS; the last one to arrive
+// multiplies the sums by x^(8 * distance to the end of the chunk) and XORs them into crcs[chunk] with
+// an atomic; XOR is commutative, so the result does not depend on the order in which tiles finish.  A
+// prepare kernel sets crcs[] to the preset/complement term and writes the zero tail of the last chunk.
+//
+// What bounds it: the memory system's handling of 4 load and 8 (chained: 5) store streams at once, not
+// arithmetic or latency (one or two workgroups per compute unit, any order of the stores and any cache
+// policy of the accesses measured the same).  What helps is fewer, longer runs: the in-place step
+// lays the new master, m and v of a workgroup out in LDS and every wavefront then stores 12 KiB
+// of consecutive rows, on the destination's own 128-byte lines.  The chained step writes 16 bytes per
+// element instead of 28 and loses more by the two workgroups per compute unit that the image leaves
+// room for than it gains: it stores from registers, stream by stream.  One process, same tensors,
+// rows handed through LDS by workgroups of 8 / rows stored from registers / as now, ms:
+//   7B shard, 842 million elements      in place 6.70 / 6.86 / 6.60   chained 4.57 / 4.59 / 4.52
+//   30 odd-sized parameters, 354 million         3.34 / 3.05 / 2.78           2.15 / 2.07 / 2.02
+//   64 parameters, 2.1 million                  0.032 / 0.028 / 0.029        0.031 / 0.030 / 0.023
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
@@ -31,7 +42,7 @@ constexpr int kThreads = kWavesPerBlock * kWaveSize;
 constexpr int kRowElems = 256;
 constexpr int kRows = kSubElems / kRowElems;   // rows of a parameter sub-block
 constexpr int kRawRows = kSubRawBytes / 1024;  // rows of a RAW sub-block
-static_assert(kRows == 4 && kRawRows == 8, "sub-blocks");
+static_assert(kRows == 2 && kRawRows == 8, "sub-blocks");
 
 __device__ __forceinline__ float bits_to_f32(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f32_to_bits(float f) { return __float_as_uint(f); }
@@ -86,18 +97,33 @@ __device__ __forceinline__ void adam_element(const FusedConsts& C, uint32_t g_bi
 // fp16 infinity or NaN
 __device__ __forceinline__ bool f16_nonfinite(uint32_t bits) { return (bits & 0x7C00u) == 0x7C00u; }
 
-// the same bytes of LDS seen as halfwords and as 16-byte slots
+// the image's bytes seen as halfwords, dwords and 16-byte slots
 typedef uint16_t u16_alias __attribute__((may_alias));
+typedef uint32_t u32_alias __attribute__((may_alias));
 typedef u32x4 u32x4_alias __attribute__((may_alias));
+
+// Lanes of one wavefront exchange data through LDS: its LDS operations complete in order, so all
+// that is needed is that the compiler neither moves accesses across nor takes a lane's own store for
+// what a later load of the lane returns.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// The in-place step's image: the new master, m and v of the workgroup's sub-blocks as they lie in
+// their streams; behind them room for the last dword that a shifted read touches.
+constexpr int kImgF = kWavesPerBlock * kSubElems * 4;  // bytes of one fp32 stream of a workgroup
+constexpr int kImgBytes = 3 * kImgF + 16;
 
 struct Lds {
     uint32_t tab16[1024];  // multiply by x^8192  (1 KiB rows)
     uint32_t tab8[1024];   // multiply by x^4096  (512 B rows)
-    uint32_t tab4[1024];   // multiply by x^32    (neighbouring dwords)
+    uint32_t tab_d[1024];  // multiply by x^32    (neighbouring dwords)
+    uint32_t tab_s[3][1024];  // multiply by x^64, x^128, x^256 (neighbouring slots and pairs of them)
     uint32_t sum[kWavesPerBlock][4];  // per run (at its first wavefront's place): XOR of its registers
     uint32_t arrived[kWavesPerBlock]; // wavefronts of the run that have added theirs
-    // the up to 8 elements (16 halfwords, RAW) at a sub-block's ends that do not fill a lane's slot
-    __attribute__((aligned(16))) uint32_t edge[kWavesPerBlock][4][8];
 };
 
 // Tile registers come out of the folds without the factor x^32 that a CRC register carries.
@@ -111,21 +137,25 @@ __device__ __forceinline__ void add_head_piece(uint32_t* __restrict__ crcs, cons
     atomicXor(&crcs[t.chunk[piece]], gf2_mul_const<kX16>(low_half));
 }
 
+static_assert(2 * (sizeof(Lds) + kImgBytes) <= 160 * 1024, "two workgroups on a compute unit");
+
 // The byte tables on their way to LDS: fetched first thing, stored (put) behind the loads of the
 // wavefront's own data, so that the two latencies overlap.  put() is the workgroup's only barrier.
 struct TableFetch {
-    u32x4 a;
-    u32x2 b;
+    static constexpr int kEach = 6 * 1024 / (4 * kThreads);
+    u32x4 a[kEach];
     __device__ __forceinline__ explicit TableFetch(const uint32_t* __restrict__ tabs)
     {
-        a = *as_global(reinterpret_cast<const u32x4*>(tabs) + threadIdx.x);
-        b = *as_global(reinterpret_cast<const u32x2*>(tabs + 2048) + threadIdx.x);
+        static_for<kEach>([&](auto i) {
+            a[i] = *as_global(reinterpret_cast<const u32x4*>(tabs) + i * kThreads + threadIdx.x);
+        });
     }
     __device__ __forceinline__ void put(Lds& lds) const
     {
-        static_assert(kThreads * 4 == 2048 && kThreads * 2 == 1024, "three tables");
-        *(reinterpret_cast<u32x4*>(lds.tab16) + threadIdx.x) = a;  // tab16, tab8
-        *(reinterpret_cast<u32x2*>(lds.tab4) + threadIdx.x) = b;
+        static_assert(kEach * kThreads * 4 == 6 * 1024, "six tables");
+        static_for<kEach>([&](auto i) {  // tab16, tab8, tab_d, tab_s
+            *(reinterpret_cast<u32x4*>(lds.tab16) + i * kThreads + threadIdx.x) = a[i];
+        });
         if (threadIdx.x < kWavesPerBlock * 4) (&lds.sum[0][0])[threadIdx.x] = 0;
         if (threadIdx.x < kWavesPerBlock) lds.arrived[threadIdx.x] = 0;
         __syncthreads();
@@ -139,48 +169,70 @@ __device__ __forceinline__ void add_row(uint32_t (&reg)[DW], const uint32_t* tab
     static_for<DW>([&](auto f) { reg[f] = FIRST ? d[f] : mul_tab_add(tab, reg[f], d[f]); });
 }
 
-// Columns -> one register per lane -> times the lane's constant -> XOR over the lanes.
+// Columns -> one value per lane and stream.
 template <int DW>
-__device__ __forceinline__ uint32_t finish_rows(const uint32_t (&reg)[DW], const uint32_t* tab4,
-                                                uint32_t lane_c)
+__device__ __forceinline__ uint32_t join_columns(const uint32_t (&reg)[DW], const uint32_t* tab_d)
 {
     uint32_t v = reg[0];
-    static_for<DW - 1>([&](auto f) { v = mul_tab_add(tab4, v, reg[f + 1]); });
-    return wave_xor(gf2_mul(v, lane_c));
+    static_for<DW - 1>([&](auto f) { v = mul_tab_add(tab_d, v, reg[f + 1]); });
+    return v;
 }
 
-// Sum of the run's registers; in the run's last wavefront, on to memory.
-template <int N>
-__device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info,
-                                        const uint32_t (&reg)[N], uint32_t* __restrict__ crcs, int lane)
+// Four streams at once (v[0]: 8-byte slots, v[1..3]: 16-byte slots): the lanes of a quad first share
+// the streams out among themselves -- two exchanges, in each of which a lane keeps half of its values
+// and gets the neighbour's share of them -- so that the multiplication by the lane's constant, 130
+// instructions, is done once and not once per stream.  Lane l ends with stream kStreamOf(l mod 4),
+// summed over all lanes.
+__device__ __forceinline__ int stream_of_lane(int lane) { return (lane & 1) * 2 + ((lane >> 1) & 1); }
+__device__ __forceinline__ uint32_t finish_streams(const uint32_t (&v)[4], const Lds& lds,
+                                                   uint32_t lane_c, int lane)
 {
-    const uint32_t run = (info >> 3) & 7u, len = (info >> 8) & 15u;
-    uint32_t v = reg[0];
-    static_for<N>([&](auto x) { v = (lane == x) ? reg[x] : v; });  // lane x: stream x
+    const bool odd = lane & 1, high = lane & 2;
+    // lane ^ 1: even lanes keep streams 0 and 1, odd lanes 2 and 3; the even lane's slot comes first
+    uint32_t u[2];
+    static_for<2>([&](auto k) {
+        const uint32_t keep = odd ? v[2 + k] : v[k], send = odd ? v[k] : v[2 + k];
+        const uint32_t got = __builtin_amdgcn_mov_dpp(send, 0xB1, 0xF, 0xF, true);
+        const uint32_t* tab = (k == 0) ? lds.tab_s[odd ? 1 : 0] : lds.tab_s[1];
+        u[k] = mul_tab_add(tab, odd ? got : keep, odd ? keep : got);
+    });
+    // lane ^ 2: the lower pair keeps u[0], the higher u[1]
+    const uint32_t keep = high ? u[1] : u[0], send = high ? u[0] : u[1];
+    const uint32_t got = __builtin_amdgcn_mov_dpp(send, 0x4E, 0xF, 0xF, true);
+    const uint32_t* tab = lds.tab_s[(odd || high) ? 2 : 1];
+    const uint32_t w = mul_tab_add(tab, high ? got : keep, high ? keep : got);
+    return quad_place_xor(gf2_mul(w, lane_c));
+}
+
+// Sum of the run's registers; in the run's last wavefront, on to memory.  v: lane l (l < n) holds
+// the register of stream x.
+__device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info, uint32_t v, int x,
+                                        int n, uint32_t* __restrict__ crcs, int lane)
+{
+    const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
     if (len > 1) {
         // LDS operations of a wavefront complete in order: the sum is complete when the count is
         uint32_t before = 0;
-        if (lane < N) atomicXor(&lds.sum[run][lane], v);
+        if (lane < n) atomicXor(&lds.sum[run][lane], v);
         asm volatile("" ::: "memory");
         if (lane == 0) before = atomicAdd(&lds.arrived[run], 1u);
         if (__builtin_amdgcn_readfirstlane(before) + 1 != len) return;
-        if (lane < N) v = *const_cast<volatile uint32_t*>(&lds.sum[run][lane]);
+        if (lane < n) v = *const_cast<volatile uint32_t*>(&lds.sum[run][lane]);
     }
     uint32_t s = t.shift[0], c = t.chunk[0];
-    static_for<N>([&](auto x) {
-        s = (lane == x) ? t.shift[x] : s;
-        c = (lane == x) ? t.chunk[x] : c;
+    static_for<3>([&](auto k) {
+        s = (x == k + 1) ? t.shift[k + 1] : s;
+        c = (x == k + 1) ? t.chunk[k + 1] : c;
     });
     v = gf2_mul(v, s);
-    bool one = true;  // all streams in one chunk (any parameter much smaller than a chunk)
-    static_for<N>([&](auto x) { one = one && t.chunk[x] == t.chunk[0]; });
-    if (N == 4 && one) {
+    // all streams in one chunk (any parameter much smaller than a chunk)?
+    const bool one = t.chunk[0] == t.chunk[1] && t.chunk[0] == t.chunk[2] && t.chunk[0] == t.chunk[3];
+    if (n == 4 && one) {
         v ^= __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
         v ^= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
-        if (lane == 0) atomicXor(&crcs[c], v);
-    } else if (lane < N) {
-        atomicXor(&crcs[c], v);
+        n = 1;
     }
+    if (lane < n) atomicXor(&crcs[c], v);
 }
 
 // ---- parameter sub-block -------------------------------------------------------------------------
@@ -190,38 +242,119 @@ struct RowIn {
     u32x4 p, m, v;
 };
 
+// Stores the elements [lo, hi) of the image (its element 0 lies `at` elements behind the tile's
+// first, perhaps before it) to every fp32 output stream: in place, and to the snapshot.  The 1 KiB
+// rows of all streams form one list that is cut into `parts` equal runs, so a wavefront sweeps
+// contiguous memory.  Rows lie on the destination's 128-byte lines, whatever its alignment: the image
+// is read at the offset that takes.  A stream's first and last row may be partial; a lane on such an
+// edge moves its bytes halfword by halfword.
+__device__ __forceinline__ void store_image(const WorkTile& t, const uint8_t* img, const int at,
+                                            const int lo, const int hi, uint8_t* __restrict__ chunks,
+                                            const int part, const int parts, const int lane)
+{
+    constexpr int kOut = 6;  // output o: master, m, v in place, then in the snapshot
+    auto stream_of = [](int o) { return o < 3 ? o + 1 : o - 2; };
+    auto dest = [&](int o) {
+        const int x = stream_of(o);
+        uint8_t* const base = o < 3 ? reinterpret_cast<uint8_t*>(t.ptr[x]) : chunks + t.soff[x];
+        return base + 4 * static_cast<int64_t>(at);
+    };
+    const int vb = 4 * lo, ve = 4 * hi;
+    auto rows_of = [&](int o, int& first, int& last) {  // rows [first, last) of output o
+        const int m = static_cast<int>(reinterpret_cast<uint64_t>(dest(o)) & 127u);
+        first = (vb + m) >> 10;
+        last = (ve + m + 1023) >> 10;
+    };
+    int total = 0;
+    static_for<kOut>([&](auto o) {
+        int a, b;
+        rows_of(o, a, b);
+        total += b - a;
+    });
+    const int per = (total + parts - 1) / parts;
+    int skip = part * per, left = per;  // rows of the list in front of this wavefront's run, rows of the run
+#pragma unroll 1
+    for (int o = 0; o < kOut; o++) {
+        int first, last;
+        rows_of(o, first, last);
+        if (skip >= last - first) {
+            skip -= last - first;
+            continue;
+        }
+        const int begin = first + skip, end = last < begin + left ? last : begin + left;
+        skip = 0;
+        left -= end - begin;
+        uint8_t* const d0 = dest(o);
+        const int m = static_cast<int>(reinterpret_cast<uint64_t>(d0) & 127u);
+        const uint8_t* const im = img + (stream_of(o) - 1) * kImgF;
+        const uint32_t sh = (m & 2) * 8;
+        auto read = [&](int off) -> u32x4 {  // 16 bytes at byte `off` of the stream's image
+            if ((m & 15) == 0) return *reinterpret_cast<const u32x4_alias*>(im + off);
+            const u32_alias* r = reinterpret_cast<const u32_alias*>(im + (off & ~3));
+            uint32_t d[5];
+            static_for<5>([&](auto k) { d[k] = r[k]; });
+            return u32x4{__builtin_amdgcn_alignbit(d[1], d[0], sh), __builtin_amdgcn_alignbit(d[2], d[1], sh),
+                         __builtin_amdgcn_alignbit(d[3], d[2], sh), __builtin_amdgcn_alignbit(d[4], d[3], sh)};
+        };
+        auto edge_row = [&](int R) {
+            const int off = 1024 * R - m + 16 * lane;
+            if (off >= vb && off + 16 <= ve) {
+                store16_stream<true>(d0 + off, read(off));
+            } else if (off + 16 > vb && off < ve) {
+#pragma unroll
+                for (int u = 0; u < 8; u++) {
+                    const int b = off + 2 * u;
+                    if (b >= vb && b < ve)
+                        *as_global(reinterpret_cast<uint16_t*>(d0 + b)) =
+                            *reinterpret_cast<const u16_alias*>(im + b);
+                }
+            }
+        };
+        int R = begin;
+        if (R == first) edge_row(R++);
+        const int inner = end == last ? last - 1 : end;  // rows [R, inner) are whole
+        for (; R + 4 <= inner; R += 4) {
+            u32x4 w[4];
+            static_for<4>([&](auto k) { w[k] = read(1024 * (R + k) - m + 16 * lane); });
+            static_for<4>([&](auto k) { store16_stream<true>(d0 + (1024 * (R + k) - m + 16 * lane), w[k]); });
+        }
+        for (; R < inner; R++) {
+            const int off = 1024 * R - m + 16 * lane;
+            store16_stream<true>(d0 + off, read(off));
+        }
+        if (R < end) edge_row(R);
+        if (left == 0) break;
+    }
+}
+
 // The elements [lo, hi) of the sub-block (element 0 = its first place, `at` elements behind the
 // tile's first element, perhaps before it) are the tile's.  WHOLE: all kSubElems of them, and no
 // split element among them.
 //
 // Not WHOLE: lanes whose four elements are all the tile's work as in a whole sub-block; the up to
 // three elements at either end that do not fill a lane's slot are updated one per lane, by lanes 0-3
-// (the slot that holds lo) and 4-7 (the slot that holds hi), and go through LDS into the slots of the
-// lanes that own them, for the CRC only.  Everything else in a slot is zero.
+// (the slot that holds lo) and 4-7 (the slot that holds hi), and handed to the lanes that own those
+// slots.  What is not the tile's counts as zero.
 template <bool F16, bool CHAINED, bool BC2, bool WHOLE>
 __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_t info, const int at,
                                                 const int lo, const int hi,
                                                 const uint8_t* __restrict__ grad,
                                                 uint8_t* __restrict__ chunks,
                                                 uint32_t* __restrict__ crcs, const FusedConsts& C,
-                                                const TableFetch& tf, Lds& lds,
+                                                const TableFetch& tf, Lds& lds, uint8_t* img,
                                                 const uint32_t* __restrict__ lane_tab, int wave, int lane)
 {
-    const int sub = info & 7u;
-    // lane constants x^(8 * bytes between the lane's slot and the end of the block)
-    const uint32_t lane_c4 = lane_tab[(7 - sub) * 64 + lane];
-    const uint32_t lane_c2 = lane_tab[512 + (7 - sub) * 64 + lane];
+    const int sub = info & 15u;
+    // x^(8 * bytes between the end of the lane's quad and the end of the block), in the lane's stream
+    const uint32_t lane_c = lane_tab[(15 - sub) * 64 + lane];
     // wave-uniform addresses of the sub-block's element 0 in every stream; a lane adds 32 bits
     const int64_t at64 = at;
     uint8_t* const tw = reinterpret_cast<uint8_t*>(t.ptr[0]) + 2 * at64;
+    uint8_t* const sw = chunks + (static_cast<int64_t>(t.soff[0]) + 2 * at64);
     uint8_t* const tp = reinterpret_cast<uint8_t*>(t.ptr[1]) + 4 * at64;
     uint8_t* const tm = reinterpret_cast<uint8_t*>(t.ptr[2]) + 4 * at64;
     uint8_t* const tv = reinterpret_cast<uint8_t*>(t.ptr[3]) + 4 * at64;
     const uint8_t* const tg = grad + 2 * (static_cast<int64_t>(t.e0) + at64);
-    uint8_t* const sw = chunks + (static_cast<int64_t>(t.soff[0]) + 2 * at64);
-    uint8_t* const sp = chunks + (static_cast<int64_t>(t.soff[1]) + 4 * at64);
-    uint8_t* const sm = chunks + (static_cast<int64_t>(t.soff[2]) + 4 * at64);
-    uint8_t* const sv = chunks + (static_cast<int64_t>(t.soff[3]) + 4 * at64);
     // where the old master, m, v come from: their tensors, or the previous snapshot
     const uint8_t* const lp = CHAINED ? C.prev + (static_cast<int64_t>(t.soff[1]) + 4 * at64) : tp;
     const uint8_t* const lm = CHAINED ? C.prev + (static_cast<int64_t>(t.soff[2]) + 4 * at64) : tm;
@@ -267,6 +400,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     tf.put(lds);
 
     uint32_t nonfinite = 0;  // this lane's count of infinite or NaN gradient elements (fp16 only)
+    uint32_t edge_w = 0;
     if (!WHOLE) {
         uint32_t wb = 0;
         if (has_edge) {
@@ -276,27 +410,8 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
             em = canonical_nan(em);
             ev = canonical_nan(ev);
             wb = (F16 ? f32_to_f16_pair(ep, 0.f) : f32_to_bf16_pair(ep, 0.f)) & 0xFFFFu;
-            auto put32 = [](uint8_t* p, float f) { *as_global(reinterpret_cast<u32_a2*>(p)) = f32_to_bits(f); };
-            auto put16 = [](uint8_t* p, uint32_t h) {
-                *as_global(reinterpret_cast<uint16_t*>(p)) = static_cast<uint16_t>(h);
-            };
-            put16(tw + 2 * ej, wb);
-            if constexpr (!CHAINED) {
-                put32(tp + 4 * ej, ep);
-                put32(tm + 4 * ej, em);
-                put32(tv + 4 * ej, ev);
-            }
-            put16(sw + 2 * ej, wb);
-            put32(sp + 4 * ej, ep);
-            put32(sm + 4 * ej, em);
-            put32(sv + 4 * ej, ev);
         }
-        if (lane < 8) {  // zeros where there is no edge element; LDS keeps a wavefront's order
-            reinterpret_cast<u16_alias*>(lds.edge[wave][0])[lane] = static_cast<uint16_t>(wb);
-            lds.edge[wave][1][lane] = f32_to_bits(ep);
-            lds.edge[wave][2][lane] = f32_to_bits(em);
-            lds.edge[wave][3][lane] = f32_to_bits(ev);
-        }
+        edge_w = wb;
     }
 
     static_for<kRows>([&](auto r) {
@@ -334,28 +449,70 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         q[r].m = u32x4{fm[0], fm[1], fm[2], fm[3]};
         q[r].v = u32x4{fv[0], fv[1], fv[2], fv[3]};
     });
-    // stores stream by stream: 4 KiB of one stream after the other
+    if (!WHOLE) {
+        // slots that are not the tile's are zero, but for the edge elements, which sit in lanes 0..7
+        const uint32_t ex[4] = {edge_w, f32_to_bits(ep), f32_to_bits(em), f32_to_bits(ev)};
+        static_for<kRows>([&](auto r) {
+            const int x = r * kRowElems + 4 * lane;
+            if (!mine(r)) q[r] = RowIn{u32x2{0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}};
+            static_for<2>([&](auto e) {
+                uint32_t h[4][4];
+                static_for<4>([&](auto i) {
+                    static_for<4>([&](auto k) { h[i][k] = __builtin_amdgcn_readlane(ex[i], 4 * e + k); });
+                });
+                if ((e == 0 ? lo_cut : hi_cut) && x == (e == 0 ? edge_lo : edge_hi)) {
+                    q[r].g = u32x2{h[0][0] | (h[0][1] << 16), h[0][2] | (h[0][3] << 16)};
+                    q[r].p = u32x4{h[1][0], h[1][1], h[1][2], h[1][3]};
+                    q[r].m = u32x4{h[2][0], h[2][1], h[2][2], h[2][3]};
+                    q[r].v = u32x4{h[3][0], h[3][1], h[3][2], h[3][3]};
+                }
+            });
+        });
+    }
+    // The 16-bit weights go out from here, stream by stream, and so do the chained step's fp32
+    // streams.  The in-place step stores those by way of the workgroup's image in LDS.
     auto store_w = [&](uint8_t* base) {
         static_for<kRows>([&](auto r) {
             if (mine(r)) store8_unaligned<true>(base + (lane8 + 2 * kRowElems * r), q[r].g);
         });
-    };
-    auto store_f = [&](uint8_t* base, u32x4 RowIn::*x) {
-        static_for<kRows>([&](auto r) {
-            if (mine(r)) store16_unaligned<true>(base + (lane16 + 4 * kRowElems * r), q[r].*x);
-        });
+        if (!WHOLE && has_edge)
+            *as_global(reinterpret_cast<uint16_t*>(base + 2 * ej)) = static_cast<uint16_t>(edge_w);
     };
     __builtin_amdgcn_sched_barrier(0);
     store_w(tw);
-    if constexpr (!CHAINED) {
-        store_f(tp, &RowIn::p);
-        store_f(tm, &RowIn::m);
-        store_f(tv, &RowIn::v);
-    }
     store_w(sw);
-    store_f(sp, &RowIn::p);
-    store_f(sm, &RowIn::m);
-    store_f(sv, &RowIn::v);
+    if constexpr (CHAINED) {
+        auto store_f = [&](uint8_t* base, u32x4 RowIn::*x, float e) {
+            static_for<kRows>([&](auto r) {
+                if (mine(r)) store16_unaligned<true>(base + (lane16 + 4 * kRowElems * r), q[r].*x);
+            });
+            if (!WHOLE && has_edge)
+                *as_global(reinterpret_cast<u32_a2*>(base + 4 * ej)) = f32_to_bits(e);
+        };
+        store_f(chunks + (static_cast<int64_t>(t.soff[1]) + 4 * at64), &RowIn::p, ep);
+        store_f(chunks + (static_cast<int64_t>(t.soff[2]) + 4 * at64), &RowIn::m, em);
+        store_f(chunks + (static_cast<int64_t>(t.soff[3]) + 4 * at64), &RowIn::v, ev);
+    } else {
+        uint8_t* const im = img + wave * (kSubElems * 4);  // this wavefront's share of every stream
+        static_for<kRows>([&](auto r) {
+            *reinterpret_cast<u32x4_alias*>(im + (lane16 + 4 * kRowElems * r)) = q[r].p;
+            *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
+            *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
+        });
+        constexpr int kAll = kWavesPerBlock * int(kSubElems);
+        if (((info >> 8) & 15u) == kWavesPerBlock) {
+            // the whole workgroup is at this tile: its image is one run of elements
+            __syncthreads();
+            const int from = at - wave * int(kSubElems);
+            const int end = static_cast<int>(t.n) - from;
+            store_image(t, img, from, from < 0 ? -from : 0, end < kAll ? end : kAll, chunks, wave,
+                        kWavesPerBlock, lane);
+        } else {
+            wave_sync();
+            const int base = wave * int(kSubElems);
+            store_image(t, img, at - base, base + lo, base + hi, chunks, 0, 1, lane);
+        }
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     uint32_t rw[2], rp[4], rm[4], rv[4];
@@ -366,21 +523,6 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         uint32_t fv[4] = {q[r].v.x, q[r].v.y, q[r].v.z, q[r].v.w};
         if (!WHOLE) {
             const int x = r * kRowElems + 4 * lane;
-            // an edge slot takes its elements from LDS, a slot outside the tile is zero
-            const int e = (lo_cut && x == edge_lo) ? 0 : (hi_cut && x == edge_hi) ? 4 : -1;
-            const bool take = e >= 0;
-            if (!mine(r)) {
-                const uint32_t k = take ? e : 0;
-                const u16_alias* w16 = reinterpret_cast<const u16_alias*>(lds.edge[wave][0]) + k;
-                fw[0] = take ? w16[0] | (uint32_t(w16[1]) << 16) : 0u;
-                fw[1] = take ? w16[2] | (uint32_t(w16[3]) << 16) : 0u;
-#pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    fp[s] = take ? lds.edge[wave][1][k + s] : 0u;
-                    fm[s] = take ? lds.edge[wave][2][k + s] : 0u;
-                    fv[s] = take ? lds.edge[wave][3][k + s] : 0u;
-                }
-            }
             // split first element: its first two bytes close the previous chunk and must not
             // enter this tile's CRC of that stream
             if (t.head_split && at <= 0 && x == edge_lo) {
@@ -398,9 +540,9 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         add_row<4, r == 0>(rm, lds.tab16, fm);
         add_row<4, r == 0>(rv, lds.tab16, fv);
     });
-    const uint32_t reg[4] = {finish_rows(rw, lds.tab4, lane_c2), finish_rows(rp, lds.tab4, lane_c4),
-                             finish_rows(rm, lds.tab4, lane_c4), finish_rows(rv, lds.tab4, lane_c4)};
-    deliver(lds, t, info, reg, crcs, lane);
+    const uint32_t v[4] = {join_columns(rw, lds.tab_d), join_columns(rp, lds.tab_d),
+                           join_columns(rm, lds.tab_d), join_columns(rv, lds.tab_d)};
+    deliver(lds, t, info, finish_streams(v, lds, lane_c, lane), stream_of_lane(lane), 4, crcs, lane);
 
     if constexpr (F16) {
         if (C.n_nonfinite && __any(nonfinite != 0)) {
@@ -418,16 +560,15 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
 // Rows are aligned to the stream, so the stores go to whole lines; bytes [lo, hi) of the sub-block
 // are the tile's, and its first byte is `at` bytes behind the tile's first (perhaps before it).  A
 // slot of 16 bytes that is the tile's only in part is moved halfword by halfword, by lanes 0-7 (the
-// slot that holds lo) and 8-15 (the one that holds hi), and reaches its owner through LDS.
+// slot that holds lo) and 8-15 (the one that holds hi), and handed to its owner for the CRC.
 __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t info, const int at,
                                               const int lo, const int hi, uint8_t* __restrict__ chunks,
                                               uint32_t* __restrict__ crcs, const TableFetch& tf,
-                                              Lds& lds, const uint32_t* __restrict__ lane_tab, int wave,
-                                              int lane)
+                                              Lds& lds, const uint32_t* __restrict__ lane_tab, int lane)
 {
-    const int sub = info & 7u;
-    // a RAW sub-block is as long as two fp32 sub-blocks
-    const uint32_t lane_c = lane_tab[2 * (3 - sub) * 64 + lane];
+    const int sub = info & 15u;
+    // x^(8 * bytes between the end of the lane's slot and the end of the block)
+    const uint32_t lane_c = lane_tab[(3 - sub) * 64 + lane];
     const uint8_t* const src = reinterpret_cast<const uint8_t*>(t.ptr[0]) + at;
     uint8_t* const dst = chunks + (static_cast<int64_t>(t.soff[0]) + at);
     auto mine = [&](int r) {
@@ -450,19 +591,23 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
         }
     }
     tf.put(lds);
-    u16_alias* const edge = reinterpret_cast<u16_alias*>(lds.edge[wave][0]);
-    if (lane < 16) edge[lane] = static_cast<uint16_t>(eh);
+    u32x4 edge[2];  // the two slots, put together from the halfwords of lanes 0..15
+    static_for<2>([&](auto e) {
+        uint32_t h[8];
+        static_for<8>([&](auto k) { h[k] = __builtin_amdgcn_readlane(eh, 8 * e + k); });
+        edge[e] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+    });
     uint32_t reg[4];
     static_for<kRawRows>([&](auto r) {
         const int x = r * 1024 + 16 * lane;
         if (mine(r)) store16_stream<true>(dst + x, w[r]);
-        if (lo_cut && x == edge_lo) w[r] = *reinterpret_cast<const u32x4_alias*>(edge);
-        if (hi_cut && x == edge_hi) w[r] = *reinterpret_cast<const u32x4_alias*>(edge + 8);
+        if (lo_cut && x == edge_lo) w[r] = edge[0];
+        if (hi_cut && x == edge_hi) w[r] = edge[1];
         const uint32_t d[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
         add_row<4, r == 0>(reg, lds.tab16, d);
     });
-    const uint32_t out[1] = {finish_rows(reg, lds.tab4, lane_c)};
-    deliver(lds, t, info, out, crcs, lane);
+    const uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
+    deliver(lds, t, info, v, 0, 1, crcs, lane);
 }
 
 // The gradient pointers of the parameter groups [grad_base, grad_base + kGradsPerLaunch) travel by
@@ -475,6 +620,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     FusedConsts C, GradPtrs grads)
 {
     __shared__ Lds lds;
+    __shared__ __attribute__((aligned(16))) uint8_t img[CHAINED ? 16 : kImgBytes];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
@@ -487,14 +633,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     // the tile descriptor is uniform and read-only: the loads below go through scalar registers
     // (a private copy indexed by the stream number would live in scratch memory instead)
     const WorkTile& t = tiles[e.tile];
-    const int sub = e.info & 7u;
-    const uint32_t* const lane_tab = tabs + 3072;
+    const int sub = e.info & 15u;
+    const uint32_t* const lane_tab = tabs + 6 * 1024;
     if (t.kind == kWorkRaw) {
         const int at = sub * int(kSubRawBytes) - static_cast<int>(t.soff[0] % kRawTileBytes);
         const int lo = at < 0 ? -at : 0;
         const int left = static_cast<int>(t.n) - at;
         raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
-                      crcs, tf, lds, lane_tab, wave, lane);
+                      crcs, tf, lds, lane_tab + 16 * 64, lane);
         return;
     }
     const int at = sub * int(kSubElems) - static_cast<int>(t.e0 % kParamTileElems);
@@ -503,10 +649,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const int hi = left < int(kSubElems) ? left : int(kSubElems);
     const uint8_t* const grad = reinterpret_cast<const uint8_t*>(grads.p[t.grad_index - grad_base]);
     if (lo == 0 && hi == int(kSubElems) && !(t.head_split && at == 0))
-        param_sub_block<F16, CHAINED, BC2, true>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds,
+        param_sub_block<F16, CHAINED, BC2, true>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds, img,
                                             lane_tab, wave, lane);
     else
-        param_sub_block<F16, CHAINED, BC2, false>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds,
+        param_sub_block<F16, CHAINED, BC2, false>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds, img,
                                              lane_tab, wave, lane);
 }
 
@@ -707,19 +853,21 @@ __global__ void fused_prepare_kernel(uint32_t* __restrict__ crcs, uint64_t n_chu
 
 void build_fused_tabs(uint32_t* tab)
 {
-    const uint64_t step[3] = {8192, 4096, 32};
-    for (int t = 0; t < 3; t++) {
+    const uint64_t step[6] = {8192, 4096, 32, 64, 128, 256};
+    for (int t = 0; t < 6; t++) {
         const uint32_t u = gf2_xpow(step[t]);
         for (int k = 0; k < 4; k++)
             for (uint32_t b = 0; b < 256; b++) tab[t * 1024 + k * 256 + b] = gf2_mul(b << (8 * k), u);
     }
-    for (int w = 0; w < 2; w++) {
-        const uint64_t lane_bytes = w ? 8 : 16;
-        for (int k = 0; k < 8; k++)
-            for (int lane = 0; lane < 64; lane++)
-                tab[3072 + w * 512 + k * 64 + lane] =
-                    gf2_xpow(8 * (lane_bytes * (63 - lane) + lane_bytes * kWaveSize * kRows * k));
-    }
+    uint32_t* const lane_tab = tab + 6 * 1024;
+    for (int k = 0; k < 16; k++)
+        for (int lane = 0; lane < 64; lane++) {
+            const uint64_t slot = ((lane & 1) * 2 + ((lane >> 1) & 1)) == 0 ? 8 : 16;  // w16 : fp32
+            lane_tab[k * 64 + lane] = gf2_xpow(8 * slot * (4 * (15 - lane / 4) + 64 * kRows * k));
+        }
+    for (int k = 0; k < 4; k++)
+        for (int lane = 0; lane < 64; lane++)
+            lane_tab[(16 + k) * 64 + lane] = gf2_xpow(8 * (16 * (63 - lane) + uint64_t(kSubRawBytes) * k));
 }
 
 hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grads, uint32_t n_params,

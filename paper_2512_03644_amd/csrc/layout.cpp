@@ -246,14 +246,14 @@ void build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
             first = in_block / kSubRawBytes;
             last = (in_block + t.n - 1) / kSubRawBytes;
         }
-        // a tile that fills a workgroup gets one to itself
-        if (last - first + 1 == kWavesPerGroup) fill_group();
+        // a tile that fills workgroups gets them to itself
+        if (last - first + 1 >= kWavesPerGroup) fill_group();
         for (uint64_t s = first; s <= last;) {
             const uint64_t slot = out.size() % kWavesPerGroup;
             const uint64_t run = std::min<uint64_t>(last - s + 1, kWavesPerGroup - slot);
             for (uint64_t k = 0; k < run; k++, s++)
                 out.push_back(WorkWave{static_cast<uint32_t>(i),
-                                       static_cast<uint32_t>(s | (slot << 3) | (run << 8))});
+                                       static_cast<uint32_t>(s | (slot << 4) | (run << 8))});
         }
     }
     fill_group();

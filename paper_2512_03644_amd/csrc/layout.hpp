@@ -73,12 +73,12 @@ constexpr uint32_t kRawTileBytes = 1u << 15;
 // their registers in LDS before they go to memory.
 struct WorkWave {
     uint32_t tile;  // index into the tile list, or kNoTile: nothing to do
-    uint32_t info;  // bits 0..2 sub-block of the tile's block, 3..5 place of the run's first
+    uint32_t info;  // bits 0..3 sub-block of the tile's block, 4..6 place of the run's first
                     // wavefront in the workgroup, 8..11 wavefronts in the run
 };
 constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 constexpr uint32_t kWavesPerGroup = 8;
-constexpr uint32_t kSubElems = kParamTileElems / 8;  // 4 rows of 256 elements
+constexpr uint32_t kSubElems = kParamTileElems / 16; // 2 rows of 256 elements
 constexpr uint32_t kSubRawBytes = kRawTileBytes / 4; // 8 rows of 1 KiB
 
 // Work list of the fused step over the whole layout (needs L.adam_ok): the parameter tiles first,
