@@ -1,0 +1,501 @@
+// Pack, restore and verify in blocks of 8 KiB: the path of small buffers and of lists of small
+// tensors (launch_tiles in kernels.hip has the rule).
+//
+// One wavefront takes one block: 8 rows of 1 KiB, lane l of a row its 16 bytes ("slot") at 16 l.  All
+// 8 loads are up front, a further row is one Horner step of the block's CRC register through byte
+// tables in LDS, and the wavefronts of a workgroup that are at the same chunk sum their registers in
+// LDS before one of them delivers the sum with an atomic.  A block is a quarter of a default tile and
+// its chain of dependent steps is short: nothing is folded, the tables are fetched beside the data,
+// and the lane's constant covers the place in the run.  That is what a launch of a few
+// thousand wavefronts or less is made of.
+//
+// A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the
+// plan's tally, which starts at zero, and whoever completes the word writes the chunk's result and
+// sets the word back to zero.  Otherwise -- a call on another stream than the tally's, or under
+// capture -- the sums are XORed into the caller's own array between a preset and a finishing kernel.
+//
+// A block that lies inside one tensor needs one address.  In any other the wavefront first puts the
+// block's tensors into a table in LDS (base address and end of each); every tensor marks the first
+// slot that starts in it, and a running maximum over the slots gives every lane its tensor: no
+// search.  Slots that straddle a boundary are listed and moved by groups of eight lanes, a halfword
+// each, all of the block's at once.  The cost is the same for 2 or 100 tensors in a block; with the
+// tile kernel's row-by-row path a block of small tensors was 32 dependent chains in a row.
+#include "kernels.hpp"
+
+#include "fold.h"
+
+namespace ffsnap {
+
+namespace {
+
+constexpr int kRows = kBlockBytes / 1024;
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWaveSize;
+constexpr int kSlots = kBlockBytes / 16;
+constexpr uint32_t kMaxSegs = 128;  // tensors of a block that the table holds
+
+typedef uint16_t u16_alias __attribute__((may_alias));
+typedef u32x4 u32x4_alias __attribute__((may_alias));
+
+struct BlockLds {
+    uint32_t tab16[1024];  // multiply by x^8192 (1 KiB rows)
+    uint32_t tab_d[1024];  // multiply by x^32   (neighbouring dwords)
+    uint32_t sum[kWaves];      // per run (at its first wavefront's place): XOR of its registers
+    uint32_t arrived[kWaves];  // wavefronts of the run that have added theirs
+};
+
+// A wavefront's own scratch for a block of several tensors.
+struct GatherLds {
+    u32x4 seg[kMaxSegs];  // x, y: address of the block's byte 0 if it were in that tensor; z: end of
+                          // the tensor relative to the block, at most kBlockBytes
+    union {
+        uint32_t mark[kSlots];          // highest tensor that has started at or before the slot
+        u32x4_alias fix[kMaxSegs + 1];  // later: contents of the straddling slots
+    };
+    uint32_t list[kMaxSegs + 1];        // straddling slots: tensor of their first byte << 16 | slot
+};
+
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// inclusive running maximum over the lanes
+__device__ __forceinline__ uint32_t scan_max(uint32_t v)
+{
+    auto step = [&](uint32_t o) { v = o > v ? o : v; };
+    step(__builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    step(__builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    step(__builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    step(__builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    step(__builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15 into rows 1, 3
+    step(__builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
+}
+
+// Where a lane's slots of the block's rows lie on the tensor side.
+struct Place {
+    uint64_t addr[kRows];
+    uint64_t straddle[kRows];  // (wave-uniform) lanes whose slot lies in several tensors or holds the end
+    uint64_t plain[kRows];     // (wave-uniform) lanes whose slot lies in one tensor
+    uint32_t n_list;           // straddling slots
+};
+
+// The block that starts at stream offset s is touched by no tensors but the n from `first` on, which
+// holds s; `end` of the block's bytes are payload.
+__device__ __forceinline__ void locate(const TileTables& T, GatherLds& G, const uint32_t first,
+                                       const uint32_t n, const uint64_t s, const uint32_t end,
+                                       const int lane, Place& P)
+{
+    u32x4_alias* const m4 = reinterpret_cast<u32x4_alias*>(G.mark);
+    static_assert(kSlots == 8 * kWaveSize, "two 16-byte stores per lane clear the marks");
+    m4[lane] = u32x4{0, 0, 0, 0};
+    m4[lane + kWaveSize] = u32x4{0, 0, 0, 0};
+    wave_sync();
+    for (uint32_t k = lane; k < n; k += kWaveSize) {
+        const uint64_t a = T.seg_off[first + k], b = T.seg_off[first + k + 1];
+        const uint64_t base = T.seg_ptr[first + k] + (s - a);
+        const uint32_t stop = b - s < uint64_t(kBlockBytes) ? static_cast<uint32_t>(b - s) : kBlockBytes;
+        G.seg[k] = u32x4{static_cast<uint32_t>(base), static_cast<uint32_t>(base >> 32), stop, 0};
+        if (k) {
+            const uint64_t slot = (a - s + 15) / 16;  // first slot that starts in this tensor
+            if (slot < kSlots) atomicMax(&G.mark[slot], k);
+        }
+    }
+    wave_sync();
+    uint32_t mark[kRows];
+    static_for<kRows>([&](auto r) { mark[r] = G.mark[r * kWaveSize + lane]; });
+    uint32_t seen = 0, n_list = 0;
+    static_for<kRows>([&](auto r) {
+        const uint32_t up = scan_max(mark[r]);
+        const uint32_t j = up > seen ? up : seen;
+        seen = __builtin_amdgcn_readlane(j, 63);
+        const u32x4 e = G.seg[j];
+        const uint32_t rel = r * 1024 + 16 * lane;
+        P.addr[r] = (uint64_t(e.y) << 32 | e.x) + rel;
+        const bool in = rel < end;
+        const bool one = in && rel + 16 <= e.z;
+        P.plain[r] = __ballot(one);
+        P.straddle[r] = __ballot(in && !one);
+        if (in && !one) G.list[n_list + lanes_below(P.straddle[r])] = j << 16 | (r * kWaveSize + lane);
+        n_list += __builtin_popcountll(P.straddle[r]);
+    });
+    P.n_list = n_list;
+    wave_sync();
+}
+
+// The straddling slots, eight lanes each: move(address of the halfword, its place in G.fix).
+template <class Fn>
+__device__ __forceinline__ void each_straddling_half(GatherLds& G, const Place& P, const uint32_t n,
+                                                     const uint32_t end, const int lane, Fn&& move)
+{
+    for (uint32_t i = lane; i < 8 * P.n_list; i += kWaveSize) {
+        const uint32_t entry = G.list[i >> 3];
+        uint32_t j = entry >> 16;
+        const uint32_t pos = (entry & 0xFFFFu) * 16 + 2 * (i & 7);
+        if (pos >= end) {
+            move(uint64_t(0), i);
+            continue;
+        }
+        u32x4 e = G.seg[j];
+        while (pos >= e.z && j + 1 < n) e = G.seg[++j];
+        move((uint64_t(e.y) << 32 | e.x) + pos, i);
+    }
+}
+
+// More tensors than the table holds (less than 64 bytes each): every lane walks through its slots
+// halfword by halfword from a bisection of its own.
+template <bool PACK>
+__device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_off,
+                                               const uint64_t* __restrict__ seg_ptr, uint32_t first,
+                                               uint32_t n, uint64_t pos, uint64_t payload, u32x4 w)
+{
+    uint32_t lo = first, hi = first + n - 1;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo + 1) / 2;
+        if (seg_off[mid] <= pos) lo = mid; else hi = mid - 1;
+    }
+    uint64_t a = seg_off[lo], b = seg_off[lo + 1], base = seg_ptr[lo];
+    uint32_t d[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const uint64_t p = pos + 2u * u;
+        uint32_t h = 0;
+        if (p < payload) {
+            while (p >= b) {
+                lo++;
+                a = b;
+                b = seg_off[lo + 1];
+                base = seg_ptr[lo];
+            }
+            uint16_t* const q = reinterpret_cast<uint16_t*>(base + (p - a));
+            if (PACK)
+                h = *as_global(q);
+            else
+                *as_global(q) = static_cast<uint16_t>(d[u >> 1] >> ((u & 1) * 16));
+        }
+        if (PACK) d[u >> 1] = (u & 1) ? d[u >> 1] | (h << 16) : h;
+    }
+    return u32x4{d[0], d[1], d[2], d[3]};
+}
+
+// One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once.
+template <int MODE, int HINT, class Ready>
+__device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, GatherLds* gather,
+                                           uint8_t* __restrict__ chunks, const uint32_t tile,
+                                           const bool folding, const int lane, Ready&& tables_ready,
+                                           uint32_t (&reg)[4])
+{
+    constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
+    const uint64_t s = static_cast<uint64_t>(tile) * kBlockBytes;
+    uint8_t* const bp = chunks + s;
+    const uint32_t lane16 = 16u * lane;
+    u32x4 w[kRows];
+    if (MODE != kPack)
+        static_for<kRows>([&](auto r) { w[r] = load16_stream<kBufNT>(bp + (lane16 + 1024 * r)); });
+    const uint32_t entry = tile >> T.block_log2;  // of the plan's tables
+    const uint32_t sub = tile - (entry << T.block_log2);
+    const uint64_t tb = MODE == kVerify ? 0 : T.tile_base[entry];
+    if (MODE == kVerify) {
+        tables_ready();
+    } else if (tb) {
+        uint8_t* const tp = reinterpret_cast<uint8_t*>(tb) + sub * kBlockBytes;
+        if (MODE == kPack)
+            static_for<kRows>([&](auto r) { w[r] = load16_unaligned<kSegNT>(tp + (lane16 + 1024 * r)); });
+        tables_ready();
+        static_for<kRows>([&](auto r) {
+            if (MODE == kPack)
+                store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]);
+            else
+                store16_unaligned<kSegNT>(tp + (lane16 + 1024 * r), w[r]);
+        });
+    } else {
+        const uint32_t end = s >= T.payload ? 0u
+                             : T.payload - s < uint64_t(kBlockBytes) ? static_cast<uint32_t>(T.payload - s)
+                                                                     : uint32_t(kBlockBytes);
+        uint32_t first = T.tile_first_seg[entry];
+        if (sub)
+            while (first + 1 < T.n_seg && T.seg_off[first + 1] <= s) first++;
+        // the tensor of the next entry's first byte is the last that can touch this block
+        const uint32_t last = entry + 1 < T.n_tiles >> T.block_log2 ? T.tile_first_seg[entry + 1] : T.n_seg - 1;
+        const uint32_t n = last - first + 1;
+        if (end == 0) {
+            if (MODE == kPack) static_for<kRows>([&](auto r) { w[r] = u32x4{0, 0, 0, 0}; });
+            tables_ready();
+        } else if (n > kMaxSegs) {
+#pragma unroll 1
+            for (int r = 0; r < kRows; r++) {
+                u32x4 x = {0, 0, 0, 0};
+                if (MODE != kPack) static_for<kRows>([&](auto k) { if (k == r) x = w[k]; });
+                x = move_crowded_row<MODE == kPack>(T.seg_off, T.seg_ptr, first, n,
+                                                    s + 1024 * r + lane16, T.payload, x);
+                if (MODE == kPack) static_for<kRows>([&](auto k) { if (k == r) w[k] = x; });
+            }
+            tables_ready();
+        } else {
+            GatherLds& G = *gather;
+            Place P;
+            locate(T, G, first, n, s, end, lane, P);
+            auto slot_in_list = [&](int r) {  // place of this lane's straddling slot of row r
+                uint32_t before = 0;
+                static_for<kRows>([&](auto k) { before += k < r ? __builtin_popcountll(P.straddle[k]) : 0; });
+                return before + lanes_below(P.straddle[r]);
+            };
+            auto bit = [&](uint64_t mask) { return ((mask >> lane) & 1) != 0; };
+            if (MODE == kPack) {
+                static_for<kRows>([&](auto r) {
+                    w[r] = u32x4{0, 0, 0, 0};
+                    if (bit(P.plain[r]))
+                        w[r] = load16_unaligned<kSegNT>(reinterpret_cast<const uint8_t*>(P.addr[r]));
+                });
+                each_straddling_half(G, P, n, end, lane, [&](uint64_t addr, uint32_t i) {
+                    const uint16_t h = addr ? *as_global(reinterpret_cast<const uint16_t*>(addr)) : uint16_t(0);
+                    reinterpret_cast<u16_alias*>(G.fix)[i] = h;
+                });
+                wave_sync();
+                static_for<kRows>([&](auto r) {
+                    if (bit(P.straddle[r])) w[r] = G.fix[slot_in_list(r)];
+                });
+            } else {
+                static_for<kRows>([&](auto r) {
+                    if (bit(P.straddle[r])) G.fix[slot_in_list(r)] = w[r];
+                });
+                wave_sync();
+                static_for<kRows>([&](auto r) {
+                    if (bit(P.plain[r])) store16_unaligned<kSegNT>(reinterpret_cast<uint8_t*>(P.addr[r]), w[r]);
+                });
+                each_straddling_half(G, P, n, end, lane, [&](uint64_t addr, uint32_t i) {
+                    if (addr) *as_global(reinterpret_cast<uint16_t*>(addr)) = reinterpret_cast<const u16_alias*>(G.fix)[i];
+                });
+            }
+            tables_ready();
+        }
+        if (MODE == kPack)
+            static_for<kRows>([&](auto r) { store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]); });
+    }
+    if (!folding) return;
+    static_for<kRows>([&](auto r) {
+        const uint32_t d[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
+        add_row<4, r == 0>(reg, lds.tab16, d);
+    });
+}
+
+// The tally of a call (see kernels.hpp for its layout).  Words are 64 bits: what has been summed
+// up, and who has contributed.  Every contribution is one returning atomic, so the one that completes
+// a word knows it and holds the whole sum; it goes on to the next level alone.
+__device__ __forceinline__ uint64_t tally_xor(uint64_t* word, uint32_t bit, uint32_t v)
+{
+    const uint64_t mine = uint64_t(bit) << 32 | v;
+    return atomicXor(reinterpret_cast<unsigned long long*>(word), mine) ^ mine;
+}
+__device__ __forceinline__ void tally_reset(uint64_t* word)
+{
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.
+template <int MODE>
+__device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const uint32_t chunk,
+                                          const uint32_t run_index, const uint32_t runs,
+                                          const uint32_t place, const uint32_t n)
+{
+    constexpr uint32_t kFan = kTallyFan;
+    auto all = [](uint32_t bits) { return bits == 32 ? 0xFFFFFFFFu : (1u << bits) - 1; };
+    uint64_t* const groups = T.tally + 1;
+    uint64_t* const by_chunk = groups + (T.n_chunks + kFan - 1) / kFan;
+    uint32_t bit = run_index, bits = runs;
+    if (runs > kFan) {
+        uint64_t* const w = by_chunk + T.n_chunks + uint64_t(chunk) * (runs / kFan) + run_index / kFan;
+        const uint64_t now = tally_xor(w, 1u << (run_index % kFan), v);
+        if ((now >> 32) != all(kFan)) return;  // runs per chunk is a power of two
+        tally_reset(w);
+        v = static_cast<uint32_t>(now);
+        bit = run_index / kFan;
+        bits = runs / kFan;
+    }
+    if (bits > 1) {
+        const uint64_t now = tally_xor(by_chunk + chunk, 1u << bit, v);
+        if ((now >> 32) != all(bits)) return;
+        tally_reset(by_chunk + chunk);
+        v = static_cast<uint32_t>(now);
+    }
+    v ^= T.affine;
+    if (MODE == kPack) {
+        T.acc[chunk] = v;
+        return;
+    }
+    const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
+    T.acc[chunk] = is_bad;
+    // how many chunks are done (low half) and how many of them are bad (high half)
+    auto count = [](uint64_t* w, uint32_t bad) {
+        const uint64_t mine = uint64_t(bad) << 32 | 1u;
+        return atomicAdd(reinterpret_cast<unsigned long long*>(w), mine) + mine;
+    };
+    const uint32_t n_groups = (n + kFan - 1) / kFan, g = place / kFan;
+    uint32_t n_bad = is_bad;
+    if (n_groups > 1) {
+        const uint64_t now = count(groups + g, n_bad);
+        if (static_cast<uint32_t>(now) != (g + 1 < n_groups ? kFan : n - g * kFan)) return;
+        tally_reset(groups + g);
+        n_bad = static_cast<uint32_t>(now >> 32);
+    }
+    const uint64_t now = count(T.tally, n_bad);
+    if (static_cast<uint32_t>(now) != (n_groups > 1 ? n_groups : n)) return;
+    tally_reset(T.tally);
+    *T.n_bad = (T.n_bad_add ? *T.n_bad : 0) + (now >> 32);
+}
+
+template <int MODE, int HINT, bool LISTED>
+__device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restrict__ chunks,
+                                           const ChunkList* list)
+{
+    __shared__ BlockLds lds;
+    __shared__ GatherLds gather[MODE == kVerify ? 1 : kWaves];
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const u32x4 tab = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + threadIdx.x);
+    auto tables_ready = [&] {
+        static_assert(kThreads * 4 == 2048, "two tables");
+        *(reinterpret_cast<u32x4*>(lds.tab16) + threadIdx.x) = tab;  // tab16, tab_d
+        if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = 0;
+        __syncthreads();
+    };
+    const uint32_t slot = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWaves + wave;
+    const uint32_t count = LISTED ? list->n << T.tpc_log2 : T.n_list ? T.n_list : T.n_tiles;
+    bool active = slot < count;
+    uint32_t chunk = 0, tile = 0;
+    if (active) {
+        if (LISTED) {
+            chunk = list->id[slot >> T.tpc_log2];
+            tile = (chunk << T.tpc_log2) + (slot & (T.tiles_per_chunk - 1));
+        } else {
+            tile = T.tile_begin + slot;
+            chunk = tile >> T.tpc_log2;
+        }
+        if (T.skip_bad) active = !__builtin_amdgcn_readfirstlane(T.skip_bad[chunk]);
+    }
+    // the wavefronts of this workgroup that are at the same chunk
+    const uint32_t run = T.tiles_per_chunk < uint32_t(kWaves) ? T.tiles_per_chunk : uint32_t(kWaves);
+    const uint32_t in_run = wave & (run - 1), lead = wave - in_run;
+    const bool folding = T.acc != nullptr;
+    uint32_t lane_c = 0, shift = 0;
+    if (folding) {
+        // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and the
+        // run's own distance to the end of its chunk (times the x^32 that the register lacks)
+        lane_c = T.block_tab[2048 + (run - 1 - in_run) * kWaveSize + lane];
+        shift = T.tile_shift[((tile & (T.tiles_per_chunk - 1)) | (run - 1)) >> T.block_log2];
+    }
+    uint32_t reg[4];
+    if (active)
+        block_rows<MODE, HINT>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
+                               tables_ready, reg);
+    else
+        tables_ready();
+    if (!active || !folding) return;
+    uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
+    if (lane != 0) return;
+    if (run > 1) {
+        // LDS operations of a wavefront complete in order: the sum is complete when the count is
+        atomicXor(&lds.sum[lead], v);
+        asm volatile("" ::: "memory");
+        if (atomicAdd(&lds.arrived[lead], 1u) + 1 != run) return;
+        v = *const_cast<volatile uint32_t*>(&lds.sum[lead]);
+    }
+    v = gf2_mul(v, shift);
+    if (T.tally)
+        tally_run<MODE>(T, v, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run,
+                        (slot >> T.tpc_log2), count >> T.tpc_log2);
+    else
+        atomicXor(T.acc + chunk, v);
+}
+
+template <int MODE, int HINT>
+__global__ __launch_bounds__(kThreads) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
+{
+    block_body<MODE, HINT, false>(T, chunks, nullptr);
+}
+
+// The blocks of the chunks in `list`, which travels in the kernel arguments, instead of a range.
+template <int MODE>
+__global__ __launch_bounds__(kThreads) void block_kernel_listed(TileTables T, uint8_t* __restrict__ chunks,
+                                                                ChunkList list)
+{
+    block_body<MODE, 3, true>(T, chunks, &list);
+}
+
+template <int MODE>
+void launch(const TileTables& t, uint8_t* chunks, unsigned grid, hipStream_t stream)
+{
+#define FF_BLOCKS(H) \
+    hipLaunchKernelGGL((block_kernel<MODE, H>), dim3(grid), dim3(kThreads), 0, stream, t, chunks)
+    switch (t.hint & 3) {
+    case 0: FF_BLOCKS(0); break;
+    case 1: FF_BLOCKS(1); break;
+    case 2: FF_BLOCKS(2); break;
+    default: FF_BLOCKS(3); break;
+    }
+#undef FF_BLOCKS
+}
+
+}  // namespace
+
+uint64_t block_tally_words(uint64_t n_chunks, uint32_t tiles_per_chunk)
+{
+    const uint64_t runs = tiles_per_chunk > kWaves ? tiles_per_chunk / kWaves : 1;
+    if (runs > kTallyFan * kTallyFan) return 0;  // chunks beyond 64 MiB: a level more than there is
+    return 1 + (n_chunks + kTallyFan - 1) / kTallyFan + n_chunks +
+           (runs > kTallyFan ? n_chunks * (runs / kTallyFan) : 0);
+}
+
+void build_block_tab(uint32_t* tab)
+{
+    const uint64_t step[2] = {8192, 32};
+    for (int t = 0; t < 2; t++) {
+        const uint32_t u = gf2_xpow(step[t]);
+        for (int k = 0; k < 4; k++)
+            for (uint32_t b = 0; b < 256; b++) tab[t * 1024 + k * 256 + b] = gf2_mul(b << (8 * k), u);
+    }
+    // lane 63 of block 0 is the last slot; a slot earlier is 16 bytes further from the end
+    const uint32_t x_slot = gf2_xpow(8 * 16);
+    const uint32_t x_block = gf2_xpow(8ull * kBlockBytes);
+    uint32_t first = kOne;
+    for (int k = 0; k < kWaves; k++, first = gf2_mul(first, x_block)) {
+        uint32_t v = first;
+        for (int lane = kWaveSize; lane-- > 0; v = gf2_mul(v, x_slot)) tab[2048 + k * kWaveSize + lane] = v;
+    }
+}
+
+hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,
+                         const ChunkList* list)
+{
+    uint8_t* c = static_cast<uint8_t*>(chunks);
+    const uint64_t count = list ? uint64_t(list->n) << t.tpc_log2 : t.n_list ? t.n_list : t.n_tiles;
+    if (count == 0) return hipSuccess;
+    if (t.tile_rows != kRows || (list && (list->n > kMaxListedChunks || mode == kPack)) || count > 0x7FFFFFF0ull)
+        return hipErrorInvalidValue;
+    const unsigned grid = static_cast<unsigned>((count + kWaves - 1) / kWaves);
+    if (t.tally && block_tally_words(1, t.tiles_per_chunk) == 0) return hipErrorInvalidValue;
+    if (list) {
+        if (mode == kRestore)
+            hipLaunchKernelGGL(block_kernel_listed<kRestore>, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);
+        else
+            hipLaunchKernelGGL(block_kernel_listed<kVerify>, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);
+    } else {
+        switch (mode) {
+        case kPack: launch<kPack>(t, c, grid, stream); break;
+        case kRestore: launch<kRestore>(t, c, grid, stream); break;
+        case kVerify: launch<kVerify>(t, c, grid, stream); break;
+        }
+    }
+    return hipGetLastError();
+}
+
+}  // namespace ffsnap

@@ -124,6 +124,22 @@ __device__ __forceinline__ uint32_t mul_tab_add(const uint32_t* tab, uint32_t a,
                 tab[768 + (a >> 24)], b);
 }
 
+// One more row of a stream: reg[f] holds column f (dword f of every lane's slot) of the rows so far.
+template <int DW, bool FIRST>
+__device__ __forceinline__ void add_row(uint32_t (&reg)[DW], const uint32_t* tab, const uint32_t (&d)[DW])
+{
+    static_for<DW>([&](auto f) { reg[f] = FIRST ? d[f] : mul_tab_add(tab, reg[f], d[f]); });
+}
+
+// Columns -> one value per lane and stream.
+template <int DW>
+__device__ __forceinline__ uint32_t join_columns(const uint32_t (&reg)[DW], const uint32_t* tab_d)
+{
+    uint32_t v = reg[0];
+    static_for<DW - 1>([&](auto f) { v = mul_tab_add(tab_d, v, reg[f + 1]); });
+    return v;
+}
+
 // XOR over the 64 lanes, the same value in every lane: inside each row of 16 lanes with DPP moves
 // (no LDS round trip as in a shuffle), across the four rows through scalar registers.
 __device__ __forceinline__ uint32_t wave_xor(uint32_t v)

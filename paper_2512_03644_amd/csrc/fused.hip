@@ -162,22 +162,6 @@ struct TableFetch {
     }
 };
 
-// One more row of a stream: reg[f] holds column f (dword f of every lane's slot) of the rows so far.
-template <int DW, bool FIRST>
-__device__ __forceinline__ void add_row(uint32_t (&reg)[DW], const uint32_t* tab, const uint32_t (&d)[DW])
-{
-    static_for<DW>([&](auto f) { reg[f] = FIRST ? d[f] : mul_tab_add(tab, reg[f], d[f]); });
-}
-
-// Columns -> one value per lane and stream.
-template <int DW>
-__device__ __forceinline__ uint32_t join_columns(const uint32_t (&reg)[DW], const uint32_t* tab_d)
-{
-    uint32_t v = reg[0];
-    static_for<DW - 1>([&](auto f) { v = mul_tab_add(tab_d, v, reg[f + 1]); });
-    return v;
-}
-
 // Four streams at once (v[0]: 8-byte slots, v[1..3]: 16-byte slots): the lanes of a quad first share
 // the streams out among themselves -- two exchanges, in each of which a lane keeps half of its values
 // and gets the neighbour's share of them -- so that the multiplication by the lane's constant, 130
@@ -860,14 +844,15 @@ void build_fused_tabs(uint32_t* tab)
             for (uint32_t b = 0; b < 256; b++) tab[t * 1024 + k * 256 + b] = gf2_mul(b << (8 * k), u);
     }
     uint32_t* const lane_tab = tab + 6 * 1024;
-    for (int k = 0; k < 16; k++)
-        for (int lane = 0; lane < 64; lane++) {
-            const uint64_t slot = ((lane & 1) * 2 + ((lane >> 1) & 1)) == 0 ? 8 : 16;  // w16 : fp32
-            lane_tab[k * 64 + lane] = gf2_xpow(8 * slot * (4 * (15 - lane / 4) + 64 * kRows * k));
-        }
-    for (int k = 0; k < 4; k++)
-        for (int lane = 0; lane < 64; lane++)
-            lane_tab[(16 + k) * 64 + lane] = gf2_xpow(8 * (16 * (63 - lane) + uint64_t(kSubRawBytes) * k));
+    for (int lane = 0; lane < kWaveSize; lane++) {
+        const uint64_t slot = ((lane & 1) * 2 + ((lane >> 1) & 1)) == 0 ? 8 : 16;  // w16 : fp32
+        uint32_t v = gf2_xpow(8 * slot * 4 * (15 - lane / 4));
+        const uint32_t x_sub = gf2_xpow(8 * slot * kWaveSize * kRows);
+        for (int k = 0; k < 16; k++, v = gf2_mul(v, x_sub)) lane_tab[k * 64 + lane] = v;
+        v = gf2_xpow(8 * 16 * (63 - lane));
+        const uint32_t x_raw = gf2_xpow(8ull * kSubRawBytes);
+        for (int k = 0; k < 4; k++, v = gf2_mul(v, x_raw)) lane_tab[(16 + k) * 64 + lane] = v;
+    }
 }
 
 hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grads, uint32_t n_params,

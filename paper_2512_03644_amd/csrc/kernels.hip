@@ -883,6 +883,7 @@ static void launch_tiles_hint(int hint, dim3 grid, dim3 block, hipStream_t strea
 hipError_t launch_tiles(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,
                         const ChunkList* list)
 {
+    if (tiles_are_blocks(t)) return launch_blocks(mode, t, chunks, stream, list);
     const dim3 block(kWaveSize * kWavesPerBlock);
     uint8_t* c = static_cast<uint8_t*>(chunks);
     if (list) {

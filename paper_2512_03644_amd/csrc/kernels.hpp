@@ -19,6 +19,7 @@ struct TileTables {
     const uint32_t* tile_first_seg = nullptr; // [n_tiles]
     const uint64_t* tile_base = nullptr;      // [n_tiles] tensor-side address of a tile that lies
                                               // inside one segment, else 0 (may be absent)
+    const uint32_t* block_tab = nullptr;      // tables of the 8 KiB blocks (build_block_tab)
     const uint32_t* tab_u = nullptr;          // [4][256] multiply-by-x^8192 byte tables, then
                                               // [64] lane constants x^(128 * (63 - lane))
     // Where a tile's register goes.  acc set: XORed (atomically) into acc[chunk of the tile], an
@@ -27,6 +28,18 @@ struct TileTables {
     // buffer CRC over caller-provided scratch).  Neither: the pass only moves bytes.
     uint32_t* acc = nullptr;
     uint32_t* partial = nullptr;
+    // Blocks only.  If tally is set (all zero before and after every call; one call at a time), acc[]
+    // gets the results themselves -- the CRC32C (pack), or 0 / 1 by comparison with want[] and *n_bad
+    // the number of ones (plus what it held, with n_bad_add) -- and no kernel before or after is
+    // needed.  Its words: [1] all chunks, [ceil(n_chunks / kTallyFan)] groups of chunks, [n_chunks]
+    // chunks, and if a chunk has more than kTallyFan runs of 8 blocks [n_chunks][runs / kTallyFan].
+    uint32_t block_log2 = 0;  // blocks: the tables' tiles hold 2^block_log2 of them
+    uint64_t* tally = nullptr;
+    const uint32_t* want = nullptr;
+    uint64_t* n_bad = nullptr;
+    uint32_t n_bad_add = 0;
+    uint32_t affine = 0;      // preset/complement term of a chunk
+    uint32_t n_chunks = 0;
     // If set: [plan tiles per chunk] x^(32 + 8 * bytes from the end of tile k of a chunk to the
     // end of the chunk).  A tile's register, which lacks the factor x^32 of a CRC register, is
     // multiplied by its entry, so that the registers of a chunk combine by XOR alone.  A pass
@@ -67,6 +80,37 @@ struct ChunkList {
 // only the tiles of the listed chunks are processed.
 hipError_t launch_tiles(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,
                         const ChunkList* list = nullptr);
+
+// The same in blocks of kBlockBytes, one wavefront each (blocks.hip): what launch_tiles does for
+// tables whose tiles have that size.  as_blocks() makes such tables of a plan's with larger tiles, up
+// to the 8 blocks of a run: tile_shift has to know the distance of every run's end.
+constexpr uint32_t kBlockBytes = 8192;
+constexpr uint32_t kMaxBlockTileBytes = 8 * kBlockBytes;
+constexpr uint32_t kTallyFan = 32;
+// 0: chunks too long for a tally
+uint64_t block_tally_words(uint64_t n_chunks, uint32_t tiles_per_chunk);
+hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,
+                         const ChunkList* list);
+inline TileTables as_blocks(TileTables t)
+{
+    for (; t.tile_rows > kBlockBytes / 1024; t.tile_rows /= 2) {
+        t.block_log2++;
+        t.n_tiles *= 2;
+        t.tiles_per_chunk *= 2;
+        t.tpc_log2++;
+    }
+    return t;
+}
+inline bool tiles_are_blocks(const TileTables& t)
+{
+    return t.tile_rows == kBlockBytes / 1024 && t.block_tab && !t.partial;
+}
+
+// Fills tab (host, kBlockTabWords entries): byte tables of multiplication by x^8192 and by x^32, then
+// for k = 0..7 and every lane x^(8 * bytes between the end of the lane's 16 bytes in a block's last
+// row and the end of that row, plus k blocks).
+constexpr int kBlockTabWords = 2048 + 8 * 64;
+void build_block_tab(uint32_t* tab);
 
 // out[j] = affine (crcs null: pack) or affine ^ crcs[j] (verify) for chunks [first, first + n), or
 // for the listed chunks; *n_bad = 0 if n_bad is not null.  The tiles then XOR their registers in.

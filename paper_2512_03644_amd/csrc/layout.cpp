@@ -85,19 +85,29 @@ int build_layout(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_bytes, 
     }
 
     // tiling
+    auto cut_tiles = [&](uint64_t tile) {
+        L.tile_bytes = tile;
+        L.tiles_per_chunk = static_cast<uint32_t>(chunk_bytes / tile);
+        L.n_tiles = L.buffer_bytes / tile;
+        L.tile_first_seg.resize(L.n_tiles);
+        size_t si = 0;
+        for (uint64_t k = 0; k < L.n_tiles; k++) {
+            const uint64_t s = k * tile;
+            while (si + 1 < L.segs.size() && L.segs[si].off + L.segs[si].nbytes <= s) si++;
+            L.tile_first_seg[k] = static_cast<uint32_t>(si);
+        }
+    };
     uint64_t tile = kDefaultTileBytes;
     if (tile_log2) tile = 1ull << std::min<unsigned>(std::max<unsigned>(tile_log2, 10), 30);
-    tile = std::min(tile, chunk_bytes);
-    L.tile_bytes = tile;
-    L.tiles_per_chunk = static_cast<uint32_t>(chunk_bytes / tile);
-    L.n_tiles = L.buffer_bytes / tile;
-    L.tile_first_seg.resize(L.n_tiles);
-    size_t si = 0;
-    for (uint64_t k = 0; k < L.n_tiles; k++) {
-        const uint64_t s = k * tile;
-        while (si + 1 < L.segs.size() && L.segs[si].off + L.segs[si].nbytes <= s) si++;
-        L.tile_first_seg[k] = static_cast<uint32_t>(si);
+    const bool small = !tile_log2 && L.buffer_bytes <= kSmallBufferBytes;
+    cut_tiles(std::min(small ? kSmallTileBytes : tile, chunk_bytes));
+    if (!tile_log2 && !small) {
+        uint64_t crowded = 0;
+        for (uint64_t k = 0; k + 1 < L.n_tiles; k++)
+            crowded += L.tile_first_seg[k + 1] - L.tile_first_seg[k] >= 4 ? 1 : 0;
+        if (crowded > L.n_tiles / kCrowdedShare) cut_tiles(std::min(kSmallTileBytes, chunk_bytes));
     }
+    tile = L.tile_bytes;
     L.tile_base.assign(L.n_tiles, 0);
     for (uint64_t k = 0; k < L.n_tiles; k++) {
         const uint64_t s = k * tile;

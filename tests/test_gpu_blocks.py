@@ -1,0 +1,130 @@
+"""Pack, restore and verify in 8 KiB blocks against the oracle: at the sizes where a block can go
+wrong (crowded blocks, slots that straddle boundaries, the payload's end, runs shorter than a
+workgroup, every level of the tally), and on every route a call can take -- the tally, a second
+stream without it, a replayed capture, listed chunks of a plan with larger tiles."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_03644_amd import binding as ff
+from paper_2512_03644_amd import workloads as wl
+from test_gpu_parity import DEV, _host_segments, _pack_and_compare, _poison_segments, \
+    _restore_and_compare, _u32
+
+pytestmark = pytest.mark.gpu
+
+
+def _ragged(n, mu, sigma, seed, chunk, max_numel=1 << 16):
+    lay = wl.fragmented_layout(seed=seed, n_tensors=n, mu=mu, sigma=sigma, max_numel=max_numel)
+    return wl.fragmented_shard(lay, chunk, seed=seed, device=DEV)
+
+
+@pytest.mark.parametrize("chunk", [1 << 13, 1 << 14, 1 << 16, 1 << 19, 1 << 20, 1 << 22])
+@pytest.mark.parametrize("mu,n", [(0.0, 40000), (2.5, 9000), (5.0, 3000), (8.0, 300)])
+def test_blocks_of_small_tensors(oracle, chunk, mu, n):
+    # on average 5, 45, 600 and 11000 bytes a tensor: from thousands in a block (beyond the table) to
+    # less than one
+    shard = _ragged(n, mu, 1.0, int(10 * mu) + chunk % 97, chunk)
+    state = _pack_and_compare(shard, oracle)
+    _restore_and_compare(shard, *state[:6])
+
+
+@pytest.mark.parametrize("n_seg", [1, 2, 127, 128, 129, 130])
+@pytest.mark.parametrize("end", [2, 14, 16, 18, 8190, 8192])
+def test_one_block_of_so_many_tensors(oracle, n_seg, end):
+    # a block whose payload ends at `end` bytes, cut into n_seg tensors of odd halfword counts
+    cuts = np.linspace(0, 8192 * 2 + end, n_seg + 1).astype(np.int64) // 2
+    lay = [(int(b - a), 2, (2 * i) % 16) for i, (a, b) in enumerate(zip(cuts[:-1], cuts[1:])) if b > a]
+    shard = wl.fragmented_shard(lay, 1 << 13, seed=n_seg, device=DEV)
+    state = _pack_and_compare(shard, oracle, tile_log2=13)
+    _restore_and_compare(shard, *state[:6])
+
+
+def _verify(plan, chunks, crcs, stream=None, flags=ff.FF_RESTORE_VERIFY_ONLY):
+    bad = torch.full((plan.num_chunks,), 7, dtype=torch.int32, device=DEV)
+    n_bad = torch.full((1,), 99, dtype=torch.int64, device=DEV)
+    torch.cuda.synchronize()
+    ff.ff_restore(plan, chunks, crcs, bad, n_bad, flags, stream=stream)
+    torch.cuda.synchronize()
+    return _u32(bad), int(n_bad.item())
+
+
+# one run per chunk, several, more than one word of 32 of them; one group of 32 chunks and more
+@pytest.mark.parametrize("chunk,n_chunks", [(1 << 13, 7), (1 << 13, 1100), (1 << 16, 33), (1 << 18, 40),
+                                            (1 << 22, 9), (1 << 23, 3)])
+def test_every_level_of_the_tally_and_the_routes_without_it(oracle, chunk, n_chunks):
+    nbytes = chunk * n_chunks - 1026
+    shard = wl.fragmented_shard([(nbytes // 2, 2, 2)], chunk, seed=n_chunks, device=DEV)
+    plan, chunks, crcs, _, _, want_buf, want_crcs = _pack_and_compare(shard, oracle, tile_log2=13)
+    assert plan.num_chunks == n_chunks
+    damaged = sorted({0, n_chunks - 1, n_chunks // 2, (5 * n_chunks) // 7})
+    for j in damaged:
+        chunks[j * chunk + 77 + j % 900] ^= 4
+    want = np.zeros(n_chunks, np.uint32)
+    want[damaged] = 1
+    side = torch.cuda.Stream()
+    for _ in range(2):                                       # the tally comes back to zero
+        for stream in (None, side):                          # the first stream's, and not its own
+            bad, n_bad = _verify(plan, chunks, crcs, stream)
+            assert np.array_equal(bad, want) and n_bad == len(damaged)
+    _poison_segments(shard)
+    bad, n_bad = _verify(plan, chunks, crcs, None, ff.FF_RESTORE_SKIP_BAD)
+    assert np.array_equal(bad, want) and n_bad == len(damaged)
+    got = _host_segments(shard)[0][0]
+    for j in range(n_chunks):
+        a, b = j * chunk, min((j + 1) * chunk, nbytes)
+        assert np.array_equal(got[a:b], np.full(b - a, 0xA5, np.uint8) if want[j] else want_buf[a:b])
+
+
+def test_replayed_capture_beside_eager_calls(oracle):
+    shard = _ragged(800, 7.0, 1.5, 3, 1 << 16)
+    plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle)
+    chunks2, crcs2 = torch.empty_like(chunks), torch.empty_like(crcs)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        ff.ff_pack(plan, chunks2, crcs2, stream=side)
+        ff.ff_restore(plan, chunks2, crcs2, bad, n_bad, ff.FF_RESTORE_VERIFY_ONLY, stream=side)
+    for _ in range(4):
+        chunks.fill_(0), crcs.fill_(0), chunks2.fill_(0), crcs2.fill_(0), bad.fill_(3), n_bad.fill_(3)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
+        for _ in range(3):
+            ff.ff_pack(plan, chunks, crcs)
+        torch.cuda.synchronize()
+        for c, r in ((chunks, crcs), (chunks2, crcs2)):
+            assert np.array_equal(c.cpu().numpy(), want_buf) and np.array_equal(_u32(r), want_crcs)
+        assert int(n_bad.item()) == 0 and not _u32(bad).any()
+
+
+@pytest.mark.parametrize("tile_log2", [13, 14, 15, 17])
+@pytest.mark.parametrize("flags", [0, ff.FF_RESTORE_VERIFY_ONLY, ff.FF_RESTORE_SKIP_BAD])
+def test_listed_chunks_of_any_plan(oracle, tile_log2, flags):
+    # listed chunks go in blocks whatever the plan's tiles are, in launches of 254 chunks
+    chunk = 1 << 17
+    shard = _ragged(7000, 9.0, 1.5, tile_log2, chunk)
+    plan, chunks, crcs, bad, n_bad, want_buf, _ = _pack_and_compare(shard, oracle, tile_log2=tile_log2)
+    n = plan.num_chunks
+    assert n > 600
+    ids = [j for j in range(n) if j % 2 == 0 or j == n - 1]
+    damaged = [ids[1], ids[300], ids[-1]]
+    for j in damaged:
+        chunks[j * chunk + 5] ^= 1
+    sent = chunks.cpu().numpy()
+    _poison_segments(shard)
+    bad.fill_(7)
+    n_bad.fill_(99)
+    ff.ff_restore_chunks(plan, chunks, crcs, ids, bad, n_bad, flags)
+    torch.cuda.synchronize()
+    assert int(n_bad.item()) == len(damaged)
+    got_bad = _u32(bad)
+    assert all(got_bad[j] == (1 if j in damaged else 0 if j in set(ids) else 7) for j in range(n))
+    want = np.full(plan.payload_bytes, 0xA5, np.uint8)
+    for j in ids:
+        if flags == ff.FF_RESTORE_VERIFY_ONLY or (flags == ff.FF_RESTORE_SKIP_BAD and j in damaged):
+            continue
+        a, b = j * chunk, min((j + 1) * chunk, plan.payload_bytes)
+        want[a:b] = sent[a:b]
+    assert np.array_equal(np.concatenate(_host_segments(shard)[0]), want)
