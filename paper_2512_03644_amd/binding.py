@@ -4,6 +4,7 @@ Tensors are torch tensors (PyTorch supplies device memory and streams, nothing e
 of the path runs inside the library's kernels.  If the library has not been built the first call
 raises: there is no fallback path.
 """
+import array
 import ctypes
 import os
 
@@ -110,21 +111,21 @@ def lib():
         L.ff_restore_checked.restype = i32
         L.ff_restore_checked.argtypes = [vp, u32, vp, vp, vp, vp, u32, vp]
         L.ff_adam_step_snapshot.restype = i32
-        L.ff_adam_step_snapshot.argtypes = [vp, ctypes.POINTER(vp),
+        L.ff_adam_step_snapshot.argtypes = [vp, vp,
                                             ctypes.POINTER(ff_adam_hparams), vp, vp, vp]
         L.ff_adam_step_snapshot_f16.restype = i32
-        L.ff_adam_step_snapshot_f16.argtypes = [vp, ctypes.POINTER(vp),
+        L.ff_adam_step_snapshot_f16.argtypes = [vp, vp,
                                                 ctypes.POINTER(ff_adam_hparams), ctypes.c_float,
                                                 vp, vp, vp, vp]
         L.ff_adam_step_chained.restype = i32
-        L.ff_adam_step_chained.argtypes = [vp, ctypes.POINTER(vp),
+        L.ff_adam_step_chained.argtypes = [vp, vp,
                                            ctypes.POINTER(ff_adam_hparams), ctypes.c_float, vp,
                                            vp, vp, vp, vp]
         L.ff_crc32c.restype, L.ff_crc32c.argtypes = i32, [vp, u64, vp, vp]
         L.ff_crc32c_noalloc.restype, L.ff_crc32c_noalloc.argtypes = i32, [vp, u64, vp, vp]
         L.ff_copy_ceiling.restype, L.ff_copy_ceiling.argtypes = i32, [vp, vp, u64, vp]
         L.ff_mix_ceiling.restype = i32
-        L.ff_mix_ceiling.argtypes = [vp, ctypes.POINTER(vp), vp, vp, vp]
+        L.ff_mix_ceiling.argtypes = [vp, vp, vp, vp, vp]
         L.ff_strerror.restype, L.ff_strerror.argtypes = ctypes.c_char_p, [i32]
         _lib = L
     return _lib
@@ -140,9 +141,22 @@ def _check(status):
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
+# The current stream's handle without a Stream object around it (1.5 us less per call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _grad_pointers(grads):
+    """The HOST array of gradient addresses: an array('Q') is filled a third faster than a ctypes array
+    (64 tensors 7.5 against 11 us, 500 tensors 53 against 80), and for lists of small parameters
+    this is what a step costs.  The caller keeps it alive across the call."""
+    return array.array("Q", [g.data_ptr() for g in grads] or [0])
 
 
 _DTYPES = {torch.bfloat16: FF_BF16, torch.float32: FF_F32, torch.float16: FF_F16}
@@ -268,10 +282,10 @@ def ff_restore_chunks(plan, chunks, crcs, chunk_ids, bad, n_bad, flags=0, stream
 def ff_adam_step_snapshot(plan, grads, hparams, chunks, crcs, stream=None):
     """grads: list of bf16 device tensors, one per parameter group in ascending param_id;
     hparams: dict(lr, beta1, beta2, eps, weight_decay, step)."""
-    ptrs = (ctypes.c_void_p * max(len(grads), 1))(*[g.data_ptr() for g in grads])
+    ptrs = _grad_pointers(grads)
     hp = ff_adam_hparams(hparams["lr"], hparams["beta1"], hparams["beta2"], hparams["eps"],
                          hparams["weight_decay"], hparams["step"])
-    _check(lib().ff_adam_step_snapshot(plan.handle, ptrs, ctypes.byref(hp), chunks.data_ptr(),
+    _check(lib().ff_adam_step_snapshot(plan.handle, ptrs.buffer_info()[0], ctypes.byref(hp), chunks.data_ptr(),
                                        crcs.data_ptr(), _stream_ptr(stream)))
 
 
@@ -279,11 +293,11 @@ def ff_adam_step_snapshot_f16(plan, grads, hparams, inv_loss_scale, n_nonfinite,
                               stream=None):
     """grads: list of fp16 device tensors (gradients of the scaled loss); n_nonfinite: one-element
     int64 device tensor, or None."""
-    ptrs = (ctypes.c_void_p * max(len(grads), 1))(*[g.data_ptr() for g in grads])
+    ptrs = _grad_pointers(grads)
     hp = ff_adam_hparams(hparams["lr"], hparams["beta1"], hparams["beta2"], hparams["eps"],
                          hparams["weight_decay"], hparams["step"])
     _check(lib().ff_adam_step_snapshot_f16(
-        plan.handle, ptrs, ctypes.byref(hp), ctypes.c_float(inv_loss_scale),
+        plan.handle, ptrs.buffer_info()[0], ctypes.byref(hp), ctypes.c_float(inv_loss_scale),
         ctypes.c_void_p(n_nonfinite.data_ptr()) if n_nonfinite is not None else None,
         chunks.data_ptr(), crcs.data_ptr(), _stream_ptr(stream)))
 
@@ -292,11 +306,11 @@ def ff_adam_step_chained(plan, grads, hparams, prev_chunks, chunks, crcs, inv_lo
                          n_nonfinite=None, stream=None):
     """The step that reads master, m, v from the snapshot `prev_chunks` and writes the new
     snapshot into `chunks`; grads in the plan's 16-bit format."""
-    ptrs = (ctypes.c_void_p * max(len(grads), 1))(*[g.data_ptr() for g in grads])
+    ptrs = _grad_pointers(grads)
     hp = ff_adam_hparams(hparams["lr"], hparams["beta1"], hparams["beta2"], hparams["eps"],
                          hparams["weight_decay"], hparams["step"])
     _check(lib().ff_adam_step_chained(
-        plan.handle, ptrs, ctypes.byref(hp), ctypes.c_float(inv_loss_scale),
+        plan.handle, ptrs.buffer_info()[0], ctypes.byref(hp), ctypes.c_float(inv_loss_scale),
         ctypes.c_void_p(n_nonfinite.data_ptr()) if n_nonfinite is not None else None,
         prev_chunks.data_ptr(), chunks.data_ptr(), crcs.data_ptr(), _stream_ptr(stream)))
 
@@ -315,8 +329,8 @@ def ff_copy_ceiling(dst, src, nbytes, stream=None):
 
 def ff_mix_ceiling(plan, grads, prev_chunks, chunks, stream=None):
     """The optimizer steps' loads and stores alone (prev_chunks None: in-place mix; else chained)."""
-    ptrs = (ctypes.c_void_p * max(len(grads), 1))(*[g.data_ptr() for g in grads])
-    _check(lib().ff_mix_ceiling(plan.handle, ptrs,
+    ptrs = _grad_pointers(grads)
+    _check(lib().ff_mix_ceiling(plan.handle, ptrs.buffer_info()[0],
                                 prev_chunks.data_ptr() if prev_chunks is not None else None,
                                 chunks.data_ptr(), _stream_ptr(stream)))
 
