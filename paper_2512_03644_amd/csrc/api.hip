@@ -50,7 +50,7 @@ struct ff_plan {
     uint32_t fused_xcd_group = 64, chained_xcd_group = 16;
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
-    uint64_t* tally = nullptr;  // plans whose tiles are blocks or can be cut into them
+    uint64_t* tally = nullptr;  // null: chunks too long for one
     mutable std::atomic<uint64_t> tally_owner{0};  // 0: nobody yet, else the stream's handle + 1
 };
 
@@ -120,9 +120,7 @@ int upload_tables(ff_plan* p)
     const uint64_t o_shift = align_up(o_tbase + L.n_tiles * 8, 256);
     const uint64_t o_btab = align_up(o_shift + uint64_t(L.tiles_per_chunk) * 4, 256);
     const uint64_t o_tally = align_up(o_btab + kBlockTabWords * 4, 256);
-    const uint64_t tally_words = L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes
-                                     ? block_tally_words(L.n_chunks, static_cast<uint32_t>(L.chunk_bytes / kBlockBytes))
-                                     : 0;
+    const uint64_t tally_words = tally_size(L.n_chunks, L.chunk_bytes, L.tile_bytes);
     const uint64_t total = align_up(o_tally + tally_words * 8, 256);
 
     std::vector<unsigned char> host(total, 0);
@@ -201,6 +199,12 @@ uint64_t* tally_for(const ff_plan* p, hipStream_t s)
     if (p->tally_owner.compare_exchange_strong(owner, me)) owner = me;
     return owner == me ? p->tally : nullptr;
 }
+
+// A pack on the tile kernel keeps the preset kernel and fire-and-forget atomics: waiting for a returning
+// one at the end of every workgroup costs more than the launch (7B shard 3.677 against 3.684 ms, 3.2 GB
+// of ragged tensors 1.097 against 1.107, 256 MB 98.8 both).  Restore and verify, which save two
+// launches, gain up to 3 % (verify of 3.2 GB 483 -> 468 us).
+bool pack_takes_tally(const TileTables& t) { return tiles_are_blocks(t); }
 
 int check_device_call(const ff_plan* p)
 {
@@ -346,7 +350,7 @@ int ff_pack(const ff_plan* p, void* chunks, uint32_t* crcs, void* hip_stream)
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     TileTables t = p->tables;
     t.acc = crcs;
-    if (tiles_are_blocks(t)) t.tally = tally_for(p, s);
+    if (pack_takes_tally(t)) t.tally = tally_for(p, s);
     if (!t.tally)
         FF_HIP_TRY(launch_preset(crcs, nullptr, 0, p->layout.n_chunks, p->affine, nullptr, nullptr, s));
     FF_HIP_TRY(launch_tiles(kPack, t, chunks, s));
@@ -383,48 +387,36 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         return FF_OK;
     }
     // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan; but a
-    // read-only pass over more than a small buffer is faster on 64 KiB tiles (350 MB: 76 against 70
+    // read-only pass over more than a small buffer is faster on 64 KiB tiles (400 MB: 70 against 76
     // us), and a longer list on the plan's own tiles.
     const uint64_t bytes = list ? list->n * L.chunk_bytes : L.buffer_bytes;
     const bool small = bytes <= kSmallBufferBytes;
     const bool pass1 = verify_only || skip_bad;
     if (small && list && L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes) t = as_blocks(t);
-    if (tiles_are_blocks(t) && (small || !pass1)) t.tally = tally_for(p, s);
-    if (t.tally) {
-        t.want = crcs;
-        t.n_bad = n_bad;
-        t.n_bad_add = clear_n_bad ? 0 : 1;
-        FF_HIP_TRY(launch_tiles(pass1 ? kVerify : kRestore, t, buf, s, list));
-        if (!skip_bad || verify_only) return FF_OK;
-        t.acc = nullptr;
-        t.tally = nullptr;
-        t.skip_bad = bad;
-        FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, list));
-        return FF_OK;
+    // The verifying pass.  With the tally it delivers bad[] and *n_bad itself; else the registers are
+    // summed in bad[] between two small kernels.
+    TileTables v = t;
+    if (pass1 && !list && !(tiles_are_blocks(t) && small)) {  // a long read-only pass: grouped tiles
+        v.tile_rows *= p->verify_group;
+        v.n_tiles /= p->verify_group;
+        v.tiles_per_chunk /= p->verify_group;
+        v.tpc_log2 = 0;
+        while ((1u << v.tpc_log2) < v.tiles_per_chunk) v.tpc_log2++;
+        v.shift_stride = p->verify_group;
     }
-    FF_HIP_TRY(launch_preset(bad, crcs, 0, L.n_chunks, p->affine, clear_n_bad ? n_bad : nullptr, list, s));
-    if (verify_only || skip_bad) {
-        // pass 1: read and fold only; over a whole buffer it runs on grouped tiles
-        TileTables v = t;
-        if (!list && !(tiles_are_blocks(t) && small)) {
-            v.tile_rows *= p->verify_group;
-            v.n_tiles /= p->verify_group;
-            v.tiles_per_chunk /= p->verify_group;
-            v.tpc_log2 = 0;
-            while ((1u << v.tpc_log2) < v.tiles_per_chunk) v.tpc_log2++;
-            v.shift_stride = p->verify_group;
-        }
-        FF_HIP_TRY(launch_tiles(kVerify, v, buf, s, list));
-        FF_HIP_TRY(launch_finish_verify(bad, L.n_chunks, n_bad, list, s));
-        if (verify_only) return FF_OK;
-        // pass 2: scatter the tiles of the chunks that verified; nothing is folded
-        t.acc = nullptr;
-        t.skip_bad = bad;
-        FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, list));
-        return FF_OK;
-    }
+    v.tally = tally_for(p, s);
+    v.want = crcs;
+    v.n_bad = n_bad;
+    v.n_bad_add = clear_n_bad ? 0 : 1;
+    if (!v.tally)
+        FF_HIP_TRY(launch_preset(bad, crcs, 0, L.n_chunks, p->affine, clear_n_bad ? n_bad : nullptr, list, s));
+    FF_HIP_TRY(launch_tiles(pass1 ? kVerify : kRestore, v, buf, s, list));
+    if (!v.tally) FF_HIP_TRY(launch_finish_verify(bad, L.n_chunks, n_bad, list, s));
+    if (!skip_bad || verify_only) return FF_OK;
+    // pass 2: scatter the tiles of the chunks that verified; nothing is folded
+    t.acc = nullptr;
+    t.skip_bad = bad;
     FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, list));
-    FF_HIP_TRY(launch_finish_verify(bad, L.n_chunks, n_bad, list, s));
     return FF_OK;
 }
 
@@ -514,7 +506,7 @@ int ff_pack_to_host(const ff_plan* p, void* chunks, uint32_t* crcs, void* host_c
         const uint64_t nj = std::min(slice_chunks, L.n_chunks - j0);
         TileTables t = p->tables;
         t.acc = crcs;
-        if (tiles_are_blocks(t)) t.tally = tally_for(p, ps);
+        if (pack_takes_tally(t)) t.tally = tally_for(p, ps);
         t.tile_begin = static_cast<uint32_t>(j0 * L.tiles_per_chunk);
         t.n_list = static_cast<uint32_t>(nj * L.tiles_per_chunk);
         if (!t.tally) FF_HIP_TRY(launch_preset(crcs, nullptr, j0, nj, p->affine, nullptr, nullptr, ps));

@@ -23,6 +23,7 @@
 #include "kernels.hpp"
 
 #include "fold.h"
+#include "tally.h"
 
 namespace ffsnap {
 
@@ -288,71 +289,6 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
     });
 }
 
-// The tally of a call (see kernels.hpp for its layout).  Words are 64 bits: what has been summed
-// up, and who has contributed.  Every contribution is one returning atomic, so the one that completes
-// a word knows it and holds the whole sum; it goes on to the next level alone.
-__device__ __forceinline__ uint64_t tally_xor(uint64_t* word, uint32_t bit, uint32_t v)
-{
-    const uint64_t mine = uint64_t(bit) << 32 | v;
-    return atomicXor(reinterpret_cast<unsigned long long*>(word), mine) ^ mine;
-}
-__device__ __forceinline__ void tally_reset(uint64_t* word)
-{
-    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.
-template <int MODE>
-__device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const uint32_t chunk,
-                                          const uint32_t run_index, const uint32_t runs,
-                                          const uint32_t place, const uint32_t n)
-{
-    constexpr uint32_t kFan = kTallyFan;
-    auto all = [](uint32_t bits) { return bits == 32 ? 0xFFFFFFFFu : (1u << bits) - 1; };
-    uint64_t* const groups = T.tally + 1;
-    uint64_t* const by_chunk = groups + (T.n_chunks + kFan - 1) / kFan;
-    uint32_t bit = run_index, bits = runs;
-    if (runs > kFan) {
-        uint64_t* const w = by_chunk + T.n_chunks + uint64_t(chunk) * (runs / kFan) + run_index / kFan;
-        const uint64_t now = tally_xor(w, 1u << (run_index % kFan), v);
-        if ((now >> 32) != all(kFan)) return;  // runs per chunk is a power of two
-        tally_reset(w);
-        v = static_cast<uint32_t>(now);
-        bit = run_index / kFan;
-        bits = runs / kFan;
-    }
-    if (bits > 1) {
-        const uint64_t now = tally_xor(by_chunk + chunk, 1u << bit, v);
-        if ((now >> 32) != all(bits)) return;
-        tally_reset(by_chunk + chunk);
-        v = static_cast<uint32_t>(now);
-    }
-    v ^= T.affine;
-    if (MODE == kPack) {
-        T.acc[chunk] = v;
-        return;
-    }
-    const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
-    T.acc[chunk] = is_bad;
-    // how many chunks are done (low half) and how many of them are bad (high half)
-    auto count = [](uint64_t* w, uint32_t bad) {
-        const uint64_t mine = uint64_t(bad) << 32 | 1u;
-        return atomicAdd(reinterpret_cast<unsigned long long*>(w), mine) + mine;
-    };
-    const uint32_t n_groups = (n + kFan - 1) / kFan, g = place / kFan;
-    uint32_t n_bad = is_bad;
-    if (n_groups > 1) {
-        const uint64_t now = count(groups + g, n_bad);
-        if (static_cast<uint32_t>(now) != (g + 1 < n_groups ? kFan : n - g * kFan)) return;
-        tally_reset(groups + g);
-        n_bad = static_cast<uint32_t>(now >> 32);
-    }
-    const uint64_t now = count(T.tally, n_bad);
-    if (static_cast<uint32_t>(now) != (n_groups > 1 ? n_groups : n)) return;
-    tally_reset(T.tally);
-    *T.n_bad = (T.n_bad_add ? *T.n_bad : 0) + (now >> 32);
-}
-
 template <int MODE, int HINT, bool LISTED>
 __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restrict__ chunks,
                                            const ChunkList* list)
@@ -402,13 +338,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     if (!active || !folding) return;
     uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
     if (lane != 0) return;
-    if (run > 1) {
-        // LDS operations of a wavefront complete in order: the sum is complete when the count is
-        atomicXor(&lds.sum[lead], v);
-        asm volatile("" ::: "memory");
-        if (atomicAdd(&lds.arrived[lead], 1u) + 1 != run) return;
-        v = *const_cast<volatile uint32_t*>(&lds.sum[lead]);
-    }
+    if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, v)) return;
     v = gf2_mul(v, shift);
     if (T.tally)
         tally_run<MODE>(T, v, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run,
@@ -447,14 +377,6 @@ void launch(const TileTables& t, uint8_t* chunks, unsigned grid, hipStream_t str
 
 }  // namespace
 
-uint64_t block_tally_words(uint64_t n_chunks, uint32_t tiles_per_chunk)
-{
-    const uint64_t runs = tiles_per_chunk > kWaves ? tiles_per_chunk / kWaves : 1;
-    if (runs > kTallyFan * kTallyFan) return 0;  // chunks beyond 64 MiB: a level more than there is
-    return 1 + (n_chunks + kTallyFan - 1) / kTallyFan + n_chunks +
-           (runs > kTallyFan ? n_chunks * (runs / kTallyFan) : 0);
-}
-
 void build_block_tab(uint32_t* tab)
 {
     const uint64_t step[2] = {8192, 32};
@@ -482,7 +404,6 @@ hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipSt
     if (t.tile_rows != kRows || (list && (list->n > kMaxListedChunks || mode == kPack)) || count > 0x7FFFFFF0ull)
         return hipErrorInvalidValue;
     const unsigned grid = static_cast<unsigned>((count + kWaves - 1) / kWaves);
-    if (t.tally && block_tally_words(1, t.tiles_per_chunk) == 0) return hipErrorInvalidValue;
     if (list) {
         if (mode == kRestore)
             hipLaunchKernelGGL(block_kernel_listed<kRestore>, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);

@@ -24,6 +24,7 @@
 #include "kernels.hpp"
 
 #include "fold.h"
+#include "tally.h"
 
 namespace ffsnap {
 
@@ -198,25 +199,10 @@ template <int MODE, int HINT>
 __device__ __forceinline__ void tile_body(
     const uint64_t* __restrict__ seg_off, const uint64_t* __restrict__ seg_ptr,
     const uint32_t* __restrict__ tile_first_seg, const uint32_t* __restrict__ tab_u_global,
-    uint32_t* __restrict__ partial, uint32_t* __restrict__ acc, uint8_t* __restrict__ chunks,
-    const TileTables& T, const uint32_t* tab, uint32_t* ring, const uint32_t tile, const int lane)
+    uint8_t* __restrict__ chunks, const TileTables& T, const uint32_t* tab, uint32_t* ring,
+    const uint32_t tile, const int lane, const bool folding, uint32_t& reg_out)
 {
-    // constant that moves this tile's register to the end of its chunk (tiles per chunk is a
-    // power of two) and supplies the factor x^32 the register lacks; fetched now, used after the
-    // last row
-    const uint32_t shift =
-        T.tile_shift ? T.tile_shift[((tile & (T.tiles_per_chunk - 1)) + 1) * T.shift_stride - 1] : 0u;
-    auto store_register = [&](uint32_t reg) {
-        if (T.tile_shift) reg = gf2_mul(reg, shift);
-        if (lane == 0) {
-            if (acc)
-                atomicXor(acc + (tile >> T.tpc_log2), reg);
-            else
-                partial[tile] = reg;
-        }
-    };
-    // a pass that only moves bytes (the scatter pass behind a verify pass) folds nothing
-    const bool folding = (acc != nullptr) || (partial != nullptr);
+    auto store_register = [&](uint32_t reg) { reg_out = reg; };
 
     // rows of this tile, as indices into the buffer's rows
     const int64_t g0 = static_cast<int64_t>(tile) * T.tile_rows - T.lead_rows;
@@ -258,7 +244,7 @@ __device__ __forceinline__ void tile_body(
     };
     auto whole_tile = [&](auto rows_c, auto depth_c, const uint8_t* bp, const uint8_t* tp) {
         whole_rows(rows_c, depth_c, bp, tp);
-        if (folding) store_register(reduce_state<Fold>(S, tab, tab_u_global[1024 + lane]));
+        if (folding) store_register(reduce_state<Fold, MODE != kPack>(S, tab, tab_u_global[1024 + lane]));
     };
     // Restore of a whole tile whose place in its tensor does not start on a 128-byte line.  Stored
     // as loaded, every row would be a 1 KiB store that straddles line boundaries at both ends and
@@ -322,7 +308,7 @@ __device__ __forceinline__ void tile_body(
                 store16_stream<kSegNT>(ap + J * kRowBytes, y);
         });
         store_part(ap + kRows * kRowBytes, take(r0), 0u, m);
-        if (folding) store_register(reduce_state<Fold>(S, tab, tab_u_global[1024 + lane]));
+        if (folding) store_register(reduce_state<Fold, MODE != kPack>(S, tab, tab_u_global[1024 + lane]));
     };
     // Pack: a default-size tile that the plan found inside one segment starts after a single
     // table read; the segment tables are walked only for the other tiles.  (Restore, whose loads
@@ -409,7 +395,7 @@ __device__ __forceinline__ void tile_body(
                            std::integral_constant<int, kWholeDepth<kVerify>>{}, bp, tp);
                 bp += kVerifyRows * kRowBytes;
             }
-            if (folding) store_register(reduce_state<Fold>(S, tab, tab_u_global[1024 + lane]));
+            if (folding) store_register(reduce_state<Fold, MODE != kPack>(S, tab, tab_u_global[1024 + lane]));
             return;
         }
         // Piecewise path: a default-size tile that starts inside the payload and touches at most
@@ -540,7 +526,7 @@ __device__ __forceinline__ void tile_body(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 });
-                if (folding) store_register(reduce_state<Fold>(S, tab, tab_u_global[1024 + lane]));
+                if (folding) store_register(reduce_state<Fold, MODE != kPack>(S, tab, tab_u_global[1024 + lane]));
                 return;
             }
         }
@@ -635,7 +621,33 @@ __device__ __forceinline__ void tile_body(
         g++;
     }
 
-    if (folding) store_register(reduce_state<Fold>(S, tab, tab_u_global[1024 + lane]));
+    if (folding) store_register(reduce_state<Fold, MODE != kPack>(S, tab, tab_u_global[1024 + lane]));
+}
+
+// A tile's register on its way: to the end of its chunk (tiles per chunk is a power of two; the
+// factor x^32 that the register lacks comes along), then by the tally with the workgroup's other
+// tiles of the chunk, or by an atomic into the caller's array; or, of a buffer CRC, to its own word.
+struct RunLds {
+    uint32_t sum[kWavesPerBlock], arrived[kWavesPerBlock];
+};
+template <int MODE>
+__device__ __forceinline__ void deliver(const TileTables& T, RunLds& lds, uint32_t reg, const uint32_t shift,
+                                        const uint32_t tile, const uint32_t wave, const uint32_t place,
+                                        const uint32_t n, const int lane)
+{
+    if (T.tile_shift) reg = gf2_mul(reg, shift);
+    if (lane != 0) return;
+    const uint32_t chunk = tile >> T.tpc_log2;
+    if (T.tally) {
+        const uint32_t run = T.tiles_per_chunk < uint32_t(kWavesPerBlock) ? T.tiles_per_chunk : uint32_t(kWavesPerBlock);
+        const uint32_t lead = wave - (wave & (run - 1));
+        if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, reg)) return;
+        tally_run<MODE>(T, reg, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run, place, n);
+    } else if (T.acc) {
+        atomicXor(T.acc + chunk, reg);
+    } else {
+        T.partial[tile] = reg;
+    }
 }
 
 // Which tile a wavefront takes: position `slot` of the launch is tile tile_begin + slot of the
@@ -647,31 +659,42 @@ __global__ __launch_bounds__(kWaveSize* kWavesPerBlock) __attribute__((amdgpu_wa
 tile_kernel(
     const uint64_t* __restrict__ seg_off, const uint64_t* __restrict__ seg_ptr,
     const uint32_t* __restrict__ tile_first_seg, const uint32_t* __restrict__ tab_u_global,
-    uint32_t* __restrict__ partial, uint32_t* __restrict__ acc, uint8_t* __restrict__ chunks,
-    TileTables T)
+    uint8_t* __restrict__ chunks, TileTables T)
 {
     __shared__ uint32_t tab[1024];
+    __shared__ RunLds run_lds;
     __shared__ __align__(16) uint32_t ring[MODE == kRestore ? kWavesPerBlock : 1][kRingWords];
     for (int i = threadIdx.x; i < 1024; i += blockDim.x) tab[i] = tab_u_global[i];
+    if (threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = run_lds.arrived[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t slot = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWavesPerBlock + wave;
-    if (slot >= (T.n_list ? T.n_list : T.n_tiles)) return;
+    const uint32_t count = T.n_list ? T.n_list : T.n_tiles;
+    if (slot >= count) return;
     const uint32_t tile = T.tile_begin + slot;
     if (T.skip_bad && __builtin_amdgcn_readfirstlane(T.skip_bad[tile >> T.tpc_log2])) return;
-    tile_body<MODE, HINT>(seg_off, seg_ptr, tile_first_seg, tab_u_global, partial, acc, chunks, T, tab,
-                          MODE == kRestore ? ring[wave] : nullptr, tile, lane);
+    // a pass that only moves bytes (the scatter pass behind a verify pass) folds nothing
+    const bool folding = T.acc || T.partial;
+    const uint32_t shift =  // fetched now, used after the last row
+        T.tile_shift ? T.tile_shift[((tile & (T.tiles_per_chunk - 1)) + 1) * T.shift_stride - 1] : 0u;
+    uint32_t reg = 0;
+    tile_body<MODE, HINT>(seg_off, seg_ptr, tile_first_seg, tab_u_global, chunks, T, tab,
+                          MODE == kRestore ? ring[wave] : nullptr, tile, lane, folding, reg);
+    if (folding)
+        deliver<MODE>(T, run_lds, reg, shift, tile, wave, slot >> T.tpc_log2, count >> T.tpc_log2, lane);
 }
 
 template <int MODE>
 __global__ __launch_bounds__(kWaveSize* kWavesPerBlock) void tile_kernel_listed(
     const uint64_t* __restrict__ seg_off, const uint64_t* __restrict__ seg_ptr,
     const uint32_t* __restrict__ tile_first_seg, const uint32_t* __restrict__ tab_u_global,
-    uint32_t* __restrict__ acc, uint8_t* __restrict__ chunks, TileTables T, ChunkList list)
+    uint8_t* __restrict__ chunks, TileTables T, ChunkList list)
 {
     __shared__ uint32_t tab[1024];
+    __shared__ RunLds run_lds;
     for (int i = threadIdx.x; i < 1024; i += blockDim.x) tab[i] = tab_u_global[i];
+    if (threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = run_lds.arrived[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
@@ -680,8 +703,12 @@ __global__ __launch_bounds__(kWaveSize* kWavesPerBlock) void tile_kernel_listed(
     const uint32_t chunk = list.id[slot >> T.tpc_log2];
     const uint32_t tile = (chunk << T.tpc_log2) + (slot & (T.tiles_per_chunk - 1));
     if (T.skip_bad && __builtin_amdgcn_readfirstlane(T.skip_bad[chunk])) return;
-    tile_body<MODE, 3>(seg_off, seg_ptr, tile_first_seg, tab_u_global, nullptr, acc, chunks, T, tab,
-                       nullptr, tile, lane);
+    const bool folding = T.acc != nullptr;
+    const uint32_t shift = T.tile_shift[(tile & (T.tiles_per_chunk - 1)) * T.shift_stride + T.shift_stride - 1];
+    uint32_t reg = 0;
+    tile_body<MODE, 3>(seg_off, seg_ptr, tile_first_seg, tab_u_global, chunks, T, tab, nullptr, tile,
+                       lane, folding, reg);
+    if (folding) deliver<MODE>(T, run_lds, reg, shift, tile, wave, slot >> T.tpc_log2, list.n, lane);
 }
 
 // ---- per-chunk kernels around the tiles ---------------------------------------------------------
@@ -807,7 +834,7 @@ __global__ __launch_bounds__(kWaveSize * WAVES) void verify_chunk_kernel(
         });
         bp += kVerifyRows * kRowBytes;
     }
-    const uint32_t reg = gf2_mul(reduce_state<Fold>(S, tab, tab_u_global[1024 + lane]), shift);
+    const uint32_t reg = gf2_mul(reduce_state<Fold, true>(S, tab, tab_u_global[1024 + lane]), shift);
     if (lane == 0) regs[wave] = reg;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -870,7 +897,7 @@ static void launch_tiles_hint(int hint, dim3 grid, dim3 block, hipStream_t strea
 {
 #define FF_LAUNCH(H)                                                                             \
     hipLaunchKernelGGL((tile_kernel<MODE, H>), grid, block, 0, stream, t.seg_off, t.seg_ptr,      \
-                       t.tile_first_seg, t.tab_u, t.partial, t.acc, c, t)
+                       t.tile_first_seg, t.tab_u, c, t)
     switch (hint & 3) {
     case 0: FF_LAUNCH(0); break;
     case 1: FF_LAUNCH(1); break;
@@ -895,10 +922,10 @@ hipError_t launch_tiles(TileMode mode, const TileTables& t, void* chunks, hipStr
         const dim3 grid(static_cast<unsigned>((count + kWavesPerBlock - 1) / kWavesPerBlock));
         if (mode == kRestore)
             hipLaunchKernelGGL((tile_kernel_listed<kRestore>), grid, block, 0, stream, t.seg_off,
-                               t.seg_ptr, t.tile_first_seg, t.tab_u, t.acc, c, t, *list);
+                               t.seg_ptr, t.tile_first_seg, t.tab_u, c, t, *list);
         else
             hipLaunchKernelGGL((tile_kernel_listed<kVerify>), grid, block, 0, stream, t.seg_off,
-                               t.seg_ptr, t.tile_first_seg, t.tab_u, t.acc, c, t, *list);
+                               t.seg_ptr, t.tile_first_seg, t.tab_u, c, t, *list);
         return hipGetLastError();
     }
     const uint32_t count = t.n_list ? t.n_list : t.n_tiles;

@@ -12,6 +12,17 @@ namespace ffsnap {
 // wavefront, 128 KiB per workgroup.
 constexpr uint32_t kDefaultXcdGroup = 2048;
 
+constexpr uint32_t kTallyFan = 32;
+// Words of a plan's tally (0: its chunks have more runs than there are levels for), enough for runs
+// of 8 blocks of 8 KiB and of 4 tiles of the plan's size or more.
+inline uint64_t tally_size(uint64_t n_chunks, uint64_t chunk_bytes, uint64_t tile_bytes)
+{
+    const uint64_t run = 4 * tile_bytes < (8ull << 13) ? 4 * tile_bytes : (8ull << 13);
+    const uint64_t runs = chunk_bytes > run ? chunk_bytes / run : 1;
+    if (runs > kTallyFan * kTallyFan) return 0;
+    return 1 + (n_chunks + kTallyFan - 1) / kTallyFan + n_chunks + (runs > kTallyFan ? n_chunks * (runs / kTallyFan) : 0);
+}
+
 // Device-side view of a plan's tables, plus the constants the tile kernels need.
 struct TileTables {
     const uint64_t* seg_off = nullptr;        // [n_seg + 1] stream offsets, seg_off[n_seg] = payload
@@ -28,11 +39,12 @@ struct TileTables {
     // buffer CRC over caller-provided scratch).  Neither: the pass only moves bytes.
     uint32_t* acc = nullptr;
     uint32_t* partial = nullptr;
-    // Blocks only.  If tally is set (all zero before and after every call; one call at a time), acc[]
+    // If tally is set (all zero before and after every call; one call at a time), acc[]
     // gets the results themselves -- the CRC32C (pack), or 0 / 1 by comparison with want[] and *n_bad
     // the number of ones (plus what it held, with n_bad_add) -- and no kernel before or after is
     // needed.  Its words: [1] all chunks, [ceil(n_chunks / kTallyFan)] groups of chunks, [n_chunks]
-    // chunks, and if a chunk has more than kTallyFan runs of 8 blocks [n_chunks][runs / kTallyFan].
+    // chunks, and if a chunk has more than kTallyFan runs -- the tiles or blocks of a chunk that one
+    // workgroup takes -- [n_chunks][runs / kTallyFan].
     uint32_t block_log2 = 0;  // blocks: the tables' tiles hold 2^block_log2 of them
     uint64_t* tally = nullptr;
     const uint32_t* want = nullptr;
@@ -86,9 +98,6 @@ hipError_t launch_tiles(TileMode mode, const TileTables& t, void* chunks, hipStr
 // to the 8 blocks of a run: tile_shift has to know the distance of every run's end.
 constexpr uint32_t kBlockBytes = 8192;
 constexpr uint32_t kMaxBlockTileBytes = 8 * kBlockBytes;
-constexpr uint32_t kTallyFan = 32;
-// 0: chunks too long for a tally
-uint64_t block_tally_words(uint64_t n_chunks, uint32_t tiles_per_chunk);
 hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,
                          const ChunkList* list);
 inline TileTables as_blocks(TileTables t)

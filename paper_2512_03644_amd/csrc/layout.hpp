@@ -106,12 +106,12 @@ int build_layout(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_bytes, 
 // 64 / 128 / 192 / 256 / 512 MB 17.6 / 21.3 / 33.8 / 56.4 / 75.5 / 97.3 / 181 us with 32 KiB tiles, 11.2 /
 // 17.1 / 29.8 / 53.2 / 75.5 / 98.0 / 188 with blocks.  And lists of small tensors, whose tiles of more
 // than four tensors take the tile kernel's row-by-row path: 5 KiB tensors (1 GB) 890 and 373 us; tensors
-// of 40 KB on average (0.8 GB) 302 and 291 us, of 110 KB 318 and 312, of 300 KB 414.6 and 415.2.  In
-// those layouts 12 %, 4 % and 1 % of the tiles hold more than four.
+// of 40 KB on average (0.8 GB) 302 and 291 us.  With 110 KB it is 318 and 312 for a pack but 459 and 483
+// for a restore that leaves bad chunks out: too few of those tiles are crowded.
 constexpr uint64_t kDefaultTileBytes = 1ull << 15;
 constexpr uint64_t kSmallTileBytes = 1ull << 13;
 constexpr uint64_t kSmallBufferBytes = 192ull << 20;
-constexpr uint64_t kCrowdedShare = 32;  // blocks if a tile in so many holds more than four tensors
+constexpr uint64_t kCrowdedShare = 16;  // blocks if a tile in so many holds more than four tensors
 constexpr uint64_t kVerifyTileBytes = 1ull << 16;
 
 }  // namespace ffsnap

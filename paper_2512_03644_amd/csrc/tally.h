@@ -1,0 +1,85 @@
+// How the registers of a chunk's tiles or blocks meet in one launch: the tally (kernels.hpp).
+#pragma once
+#include "fold.h"
+#include "kernels.hpp"
+
+namespace ffsnap {
+
+// The tally of a call (see kernels.hpp for its layout).  Words are 64 bits: what has been summed
+// up, and who has contributed.  Every contribution is one returning atomic, so the one that completes
+// a word knows it and holds the whole sum; it goes on to the next level alone.
+__device__ __forceinline__ uint64_t tally_xor(uint64_t* word, uint32_t bit, uint32_t v)
+{
+    const uint64_t mine = uint64_t(bit) << 32 | v;
+    return atomicXor(reinterpret_cast<unsigned long long*>(word), mine) ^ mine;
+}
+__device__ __forceinline__ void tally_reset(uint64_t* word)
+{
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One lane per wavefront: adds v to the run's sum in LDS.  True in the wavefront that completes the
+// run; v is then the run's whole sum.  (LDS operations of a wavefront complete in order, so the
+// sum is complete when the count is.)
+__device__ __forceinline__ bool run_complete(uint32_t& sum, uint32_t& arrived, const uint32_t run, uint32_t& v)
+{
+    atomicXor(&sum, v);
+    asm volatile("" ::: "memory");
+    if (atomicAdd(&arrived, 1u) + 1 != run) return false;
+    v = *const_cast<volatile uint32_t*>(&sum);
+    return true;
+}
+
+// v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.
+template <int MODE>
+__device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const uint32_t chunk,
+                                          const uint32_t run_index, const uint32_t runs,
+                                          const uint32_t place, const uint32_t n)
+{
+    constexpr uint32_t kFan = kTallyFan;
+    auto all = [](uint32_t bits) { return bits == 32 ? 0xFFFFFFFFu : (1u << bits) - 1; };
+    uint64_t* const groups = T.tally + 1;
+    uint64_t* const by_chunk = groups + (T.n_chunks + kFan - 1) / kFan;
+    uint32_t bit = run_index, bits = runs;
+    if (runs > kFan) {
+        uint64_t* const w = by_chunk + T.n_chunks + uint64_t(chunk) * (runs / kFan) + run_index / kFan;
+        const uint64_t now = tally_xor(w, 1u << (run_index % kFan), v);
+        if ((now >> 32) != all(kFan)) return;  // runs per chunk is a power of two
+        tally_reset(w);
+        v = static_cast<uint32_t>(now);
+        bit = run_index / kFan;
+        bits = runs / kFan;
+    }
+    if (bits > 1) {
+        const uint64_t now = tally_xor(by_chunk + chunk, 1u << bit, v);
+        if ((now >> 32) != all(bits)) return;
+        tally_reset(by_chunk + chunk);
+        v = static_cast<uint32_t>(now);
+    }
+    v ^= T.affine;
+    if (MODE == kPack) {
+        T.acc[chunk] = v;
+        return;
+    }
+    const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
+    T.acc[chunk] = is_bad;
+    // how many chunks are done (low half) and how many of them are bad (high half)
+    auto count = [](uint64_t* w, uint32_t bad) {
+        const uint64_t mine = uint64_t(bad) << 32 | 1u;
+        return atomicAdd(reinterpret_cast<unsigned long long*>(w), mine) + mine;
+    };
+    const uint32_t n_groups = (n + kFan - 1) / kFan, g = place / kFan;
+    uint32_t n_bad = is_bad;
+    if (n_groups > 1) {
+        const uint64_t now = count(groups + g, n_bad);
+        if (static_cast<uint32_t>(now) != (g + 1 < n_groups ? kFan : n - g * kFan)) return;
+        tally_reset(groups + g);
+        n_bad = static_cast<uint32_t>(now >> 32);
+    }
+    const uint64_t now = count(T.tally, n_bad);
+    if (static_cast<uint32_t>(now) != (n_groups > 1 ? n_groups : n)) return;
+    tally_reset(T.tally);
+    *T.n_bad = (T.n_bad_add ? *T.n_bad : 0) + (now >> 32);
+}
+
+}  // namespace ffsnap
