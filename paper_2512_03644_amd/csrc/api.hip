@@ -38,6 +38,7 @@ struct ff_plan {
     int device = -1;
     void* dev_block = nullptr;  // one allocation holding every device table
     TileTables tables;
+    bool hint_given = false;    // by the plan's flags
     // A pass that only reads (verify) runs fastest on larger tiles than one that also writes:
     // it folds verify_group consecutive tiles as one.
     uint32_t verify_group = 1;
@@ -200,6 +201,12 @@ uint64_t* tally_for(const ff_plan* p, hipStream_t s)
     return owner == me ? p->tally : nullptr;
 }
 
+// Cache hint of a pass of `mode` over `bytes` of the buffer.
+void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
+{
+    if (tiles_are_blocks(t) && !p->hint_given && bytes <= kWarmBytes) t.hint = kHintWarm(mode);
+}
+
 // A pack on the tile kernel keeps the preset kernel and fire-and-forget atomics: waiting for a returning
 // one at the end of every workgroup costs more than the launch (7B shard 3.677 against 3.684 ms, 3.2 GB
 // of ragged tensors 1.097 against 1.107, 256 MB 98.8 both).  Restore and verify, which save two
@@ -259,7 +266,10 @@ int ff_snapshot_plan(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_byt
     t.n_chunks = static_cast<uint32_t>(L.n_chunks);
     while ((1u << t.tpc_log2) < L.tiles_per_chunk) t.tpc_log2++;
     // bits 16..18: bit 18 set = take bits 16..17 as the cache-hint selector (tuning knob)
-    if (flags & 0x40000u) t.hint = (flags >> 16) & 3u;
+    if (flags & 0x40000u) {
+        t.hint = (flags >> 16) & 3u;
+        p->hint_given = true;
+    }
     // bits 19..23: 0 = default, else log2(xcd_group) + 1, 31 = no regrouping (tuning knob)
     {
         const unsigned xg = (flags >> 19) & 31u;
@@ -350,6 +360,7 @@ int ff_pack(const ff_plan* p, void* chunks, uint32_t* crcs, void* hip_stream)
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     TileTables t = p->tables;
     t.acc = crcs;
+    choose_hint(p, t, kPack, p->layout.buffer_bytes);
     if (pack_takes_tally(t)) t.tally = tally_for(p, s);
     if (!t.tally)
         FF_HIP_TRY(launch_preset(crcs, nullptr, 0, p->layout.n_chunks, p->affine, nullptr, nullptr, s));
@@ -386,13 +397,14 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, nullptr));
         return FF_OK;
     }
-    // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan; but a
-    // read-only pass over more than a small buffer is faster on 64 KiB tiles (400 MB: 70 against 76
-    // us), and a longer list on the plan's own tiles.
+    // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan (28 chunks
+    // of 4 MiB: 48.5-49.6 us in blocks, 47.3 on the plan's tiles; one chunk of 512 KiB 11 against 19);
+    // but a read-only pass over more than a small buffer is faster on 64 KiB tiles (400 MB: 70 against
+    // 76 us).
     const uint64_t bytes = list ? list->n * L.chunk_bytes : L.buffer_bytes;
     const bool small = bytes <= kSmallBufferBytes;
     const bool pass1 = verify_only || skip_bad;
-    if (small && list && L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes) t = as_blocks(t);
+    if (list && bytes <= kWarmBytes && L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes) t = as_blocks(t);
     // The verifying pass.  With the tally it delivers bad[] and *n_bad itself; else the registers are
     // summed in bad[] between two small kernels.
     TileTables v = t;
@@ -404,6 +416,8 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         while ((1u << v.tpc_log2) < v.tiles_per_chunk) v.tpc_log2++;
         v.shift_stride = p->verify_group;
     }
+    choose_hint(p, v, pass1 ? kVerify : kRestore, bytes);
+    choose_hint(p, t, kRestore, bytes);
     v.tally = tally_for(p, s);
     v.want = crcs;
     v.n_bad = n_bad;

@@ -34,6 +34,7 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kWaveSize;
 constexpr int kSlots = kBlockBytes / 16;
 constexpr uint32_t kMaxSegs = 128;  // tensors of a block that the table holds
+static_assert(kMaxSegs <= 256, "a place in the table is 8 bits");
 
 typedef uint16_t u16_alias __attribute__((may_alias));
 typedef u32x4 u32x4_alias __attribute__((may_alias));
@@ -84,7 +85,7 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 
 // Where a lane's slots of the block's rows lie on the tensor side.
 struct Place {
-    uint64_t addr[kRows];
+    uint32_t seg[kRows / 4];   // place in GatherLds::seg of the tensor of the slot's first byte, 8 bits a row
     uint64_t straddle[kRows];  // (wave-uniform) lanes whose slot lies in several tensors or holds the end
     uint64_t plain[kRows];     // (wave-uniform) lanes whose slot lies in one tensor
     uint32_t n_list;           // straddling slots
@@ -121,7 +122,7 @@ __device__ __forceinline__ void locate(const TileTables& T, GatherLds& G, const 
         seen = __builtin_amdgcn_readlane(j, 63);
         const u32x4 e = G.seg[j];
         const uint32_t rel = r * 1024 + 16 * lane;
-        P.addr[r] = (uint64_t(e.y) << 32 | e.x) + rel;
+        P.seg[r / 4] = r % 4 ? P.seg[r / 4] | j << (8 * (r % 4)) : j;
         const bool in = rel < end;
         const bool one = in && rel + 16 <= e.z;
         P.plain[r] = __ballot(one);
@@ -251,11 +252,16 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
                 return before + lanes_below(P.straddle[r]);
             };
             auto bit = [&](uint64_t mask) { return ((mask >> lane) & 1) != 0; };
+            // (an address per row would be 16 registers; the table is still there)
+            auto addr = [&](auto r) {
+                const u32x4 e = G.seg[(P.seg[r / 4] >> (8 * (r % 4))) & 255u];
+                return reinterpret_cast<uint8_t*>((uint64_t(e.y) << 32 | e.x) + (r * 1024 + lane16));
+            };
             if (MODE == kPack) {
                 static_for<kRows>([&](auto r) {
                     w[r] = u32x4{0, 0, 0, 0};
                     if (bit(P.plain[r]))
-                        w[r] = load16_unaligned<kSegNT>(reinterpret_cast<const uint8_t*>(P.addr[r]));
+                        w[r] = load16_unaligned<kSegNT>(addr(r));
                 });
                 each_straddling_half(G, P, n, end, lane, [&](uint64_t addr, uint32_t i) {
                     const uint16_t h = addr ? *as_global(reinterpret_cast<const uint16_t*>(addr)) : uint16_t(0);
@@ -271,7 +277,7 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
                 });
                 wave_sync();
                 static_for<kRows>([&](auto r) {
-                    if (bit(P.plain[r])) store16_unaligned<kSegNT>(reinterpret_cast<uint8_t*>(P.addr[r]), w[r]);
+                    if (bit(P.plain[r])) store16_unaligned<kSegNT>(addr(r), w[r]);
                 });
                 each_straddling_half(G, P, n, end, lane, [&](uint64_t addr, uint32_t i) {
                     if (addr) *as_global(reinterpret_cast<uint16_t*>(addr)) = reinterpret_cast<const u16_alias*>(G.fix)[i];
@@ -347,18 +353,20 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         atomicXor(T.acc + chunk, v);
 }
 
+// (six wavefronts per SIMD are three workgroups per compute unit instead of two: restore of 5 KiB
+// tensors, 1 GB, 400 -> 381 us, ragged 425 -> 408)
 template <int MODE, int HINT>
-__global__ __launch_bounds__(kThreads) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
 {
     block_body<MODE, HINT, false>(T, chunks, nullptr);
 }
 
 // The blocks of the chunks in `list`, which travels in the kernel arguments, instead of a range.
-template <int MODE>
-__global__ __launch_bounds__(kThreads) void block_kernel_listed(TileTables T, uint8_t* __restrict__ chunks,
-                                                                ChunkList list)
+template <int MODE, int HINT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void block_kernel_listed(
+    TileTables T, uint8_t* __restrict__ chunks, ChunkList list)
 {
-    block_body<MODE, 3, true>(T, chunks, &list);
+    block_body<MODE, HINT, true>(T, chunks, &list);
 }
 
 template <int MODE>
@@ -405,10 +413,11 @@ hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipSt
         return hipErrorInvalidValue;
     const unsigned grid = static_cast<unsigned>((count + kWaves - 1) / kWaves);
     if (list) {
-        if (mode == kRestore)
-            hipLaunchKernelGGL(block_kernel_listed<kRestore>, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);
-        else
-            hipLaunchKernelGGL(block_kernel_listed<kVerify>, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);
+        const auto restore = t.hint == kHintWarm(kRestore) ? block_kernel_listed<kRestore, kHintWarm(kRestore)>
+                                                           : block_kernel_listed<kRestore, 3>;
+        const auto verify = t.hint == kHintWarm(kVerify) ? block_kernel_listed<kVerify, kHintWarm(kVerify)>
+                                                         : block_kernel_listed<kVerify, 3>;
+        hipLaunchKernelGGL(mode == kRestore ? restore : verify, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);
     } else {
         switch (mode) {
         case kPack: launch<kPack>(t, c, grid, stream); break;

@@ -102,16 +102,6 @@ typedef uint16_t u16_alias __attribute__((may_alias));
 typedef uint32_t u32_alias __attribute__((may_alias));
 typedef u32x4 u32x4_alias __attribute__((may_alias));
 
-// Lanes of one wavefront exchange data through LDS: its LDS operations complete in order, so all
-// that is needed is that the compiler neither moves accesses across nor takes a lane's own store for
-// what a later load of the lane returns.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-
 // The in-place step's image: the new master, m and v of the workgroup's sub-blocks as they lie in
 // their streams; behind them room for the last dword that a shifted read touches.
 constexpr int kImgF = kWavesPerBlock * kSubElems * 4;  // bytes of one fp32 stream of a workgroup
@@ -228,13 +218,13 @@ struct RowIn {
 
 // Stores the elements [lo, hi) of the image (its element 0 lies `at` elements behind the tile's
 // first, perhaps before it) to every fp32 output stream: in place, and to the snapshot.  The 1 KiB
-// rows of all streams form one list that is cut into `parts` equal runs, so a wavefront sweeps
-// contiguous memory.  Rows lie on the destination's 128-byte lines, whatever its alignment: the image
+// rows of all streams form one list that is cut into equal runs, so a wavefront sweeps contiguous
+// memory.  Rows lie on the destination's 128-byte lines, whatever its alignment: the image
 // is read at the offset that takes.  A stream's first and last row may be partial; a lane on such an
 // edge moves its bytes halfword by halfword.
 __device__ __forceinline__ void store_image(const WorkTile& t, const uint8_t* img, const int at,
                                             const int lo, const int hi, uint8_t* __restrict__ chunks,
-                                            const int part, const int parts, const int lane)
+                                            const int wave, const int lane)
 {
     constexpr int kOut = 6;  // output o: master, m, v in place, then in the snapshot
     auto stream_of = [](int o) { return o < 3 ? o + 1 : o - 2; };
@@ -255,8 +245,8 @@ __device__ __forceinline__ void store_image(const WorkTile& t, const uint8_t* im
         rows_of(o, a, b);
         total += b - a;
     });
-    const int per = (total + parts - 1) / parts;
-    int skip = part * per, left = per;  // rows of the list in front of this wavefront's run, rows of the run
+    const int per = (total + kWavesPerBlock - 1) / kWavesPerBlock;
+    int skip = wave * per, left = per;  // rows of the list in front of this wavefront's run, rows of the run
 #pragma unroll 1
     for (int o = 0; o < kOut; o++) {
         int first, last;
@@ -453,8 +443,8 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
             });
         });
     }
-    // The 16-bit weights go out from here, stream by stream, and so do the chained step's fp32
-    // streams.  The in-place step stores those by way of the workgroup's image in LDS.
+    // Stores from registers, stream by stream; but the fp32 streams of an in-place step whose whole
+    // workgroup is at this tile go by way of its image in LDS.
     auto store_w = [&](uint8_t* base) {
         static_for<kRows>([&](auto r) {
             if (mine(r)) store8_unaligned<true>(base + (lane8 + 2 * kRowElems * r), q[r].g);
@@ -462,40 +452,37 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         if (!WHOLE && has_edge)
             *as_global(reinterpret_cast<uint16_t*>(base + 2 * ej)) = static_cast<uint16_t>(edge_w);
     };
+    auto store_f = [&](uint8_t* base, u32x4 RowIn::*x, float e) {
+        static_for<kRows>([&](auto r) {
+            if (mine(r)) store16_unaligned<true>(base + (lane16 + 4 * kRowElems * r), q[r].*x);
+        });
+        if (!WHOLE && has_edge)
+            *as_global(reinterpret_cast<u32_a2*>(base + 4 * ej)) = f32_to_bits(e);
+    };
     __builtin_amdgcn_sched_barrier(0);
     store_w(tw);
     store_w(sw);
-    if constexpr (CHAINED) {
-        auto store_f = [&](uint8_t* base, u32x4 RowIn::*x, float e) {
-            static_for<kRows>([&](auto r) {
-                if (mine(r)) store16_unaligned<true>(base + (lane16 + 4 * kRowElems * r), q[r].*x);
-            });
-            if (!WHOLE && has_edge)
-                *as_global(reinterpret_cast<u32_a2*>(base + 4 * ej)) = f32_to_bits(e);
-        };
-        store_f(chunks + (static_cast<int64_t>(t.soff[1]) + 4 * at64), &RowIn::p, ep);
-        store_f(chunks + (static_cast<int64_t>(t.soff[2]) + 4 * at64), &RowIn::m, em);
-        store_f(chunks + (static_cast<int64_t>(t.soff[3]) + 4 * at64), &RowIn::v, ev);
-    } else {
+    if (!CHAINED && ((info >> 8) & 15u) == kWavesPerBlock) {
         uint8_t* const im = img + wave * (kSubElems * 4);  // this wavefront's share of every stream
         static_for<kRows>([&](auto r) {
             *reinterpret_cast<u32x4_alias*>(im + (lane16 + 4 * kRowElems * r)) = q[r].p;
             *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
             *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
         });
+        __syncthreads();  // (every wavefront of the workgroup comes here)
         constexpr int kAll = kWavesPerBlock * int(kSubElems);
-        if (((info >> 8) & 15u) == kWavesPerBlock) {
-            // the whole workgroup is at this tile: its image is one run of elements
-            __syncthreads();
-            const int from = at - wave * int(kSubElems);
-            const int end = static_cast<int>(t.n) - from;
-            store_image(t, img, from, from < 0 ? -from : 0, end < kAll ? end : kAll, chunks, wave,
-                        kWavesPerBlock, lane);
-        } else {
-            wave_sync();
-            const int base = wave * int(kSubElems);
-            store_image(t, img, at - base, base + lo, base + hi, chunks, 0, 1, lane);
+        const int from = at - wave * int(kSubElems);
+        const int end = static_cast<int>(t.n) - from;
+        store_image(t, img, from, from < 0 ? -from : 0, end < kAll ? end : kAll, chunks, wave, lane);
+    } else {
+        if constexpr (!CHAINED) {
+            store_f(tp, &RowIn::p, ep);
+            store_f(tm, &RowIn::m, em);
+            store_f(tv, &RowIn::v, ev);
         }
+        store_f(chunks + (static_cast<int64_t>(t.soff[1]) + 4 * at64), &RowIn::p, ep);
+        store_f(chunks + (static_cast<int64_t>(t.soff[2]) + 4 * at64), &RowIn::m, em);
+        store_f(chunks + (static_cast<int64_t>(t.soff[3]) + 4 * at64), &RowIn::v, ev);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -597,11 +584,15 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
 // The gradient pointers of the parameter groups [grad_base, grad_base + kGradsPerLaunch) travel by
 // value in the kernel arguments: the step keeps no per-call table in device memory, so calls on
 // one plan may overlap and a captured launch carries its own pointers.
-template <bool F16, bool CHAINED, bool BC2>
+//
+// N: room for so many.  A launch whose arguments hold 3 KiB of pointers costs the host half a microsecond more
+// than one of 512 bytes, and holds up the launches behind it (host side of the tiny shard's step 26.7
+// against 19.1 us), so few groups take the small form.
+template <bool F16, bool CHAINED, bool BC2, uint32_t N>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void fused_kernel(
     const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
     const uint32_t* __restrict__ tabs, uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs,
-    FusedConsts C, GradPtrs grads)
+    FusedConsts C, GradPtrsOf<N> grads)
 {
     __shared__ Lds lds;
     __shared__ __attribute__((aligned(16))) uint8_t img[CHAINED ? 16 : kImgBytes];
@@ -828,9 +819,12 @@ __global__ void fused_prepare_kernel(uint32_t* __restrict__ crcs, uint64_t n_chu
     if (i == 0 && n_nonfinite) *n_nonfinite = 0;
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
     for (uint64_t j = i; j < n_chunks; j += stride) crcs[j] = affine;
-    uint16_t* tail = reinterpret_cast<uint16_t*>(chunks + payload);  // payload is even
-    const uint64_t n_half = (buffer_bytes - payload) / 2;
-    for (uint64_t j = i; j < n_half; j += stride) tail[j] = 0;
+    // the tail: whole 16-byte slots, and the halfwords in front of the first (payload is even)
+    const uint64_t first = (payload + 15) & ~uint64_t(15);  // chunks is 16-byte aligned
+    if (i < (first - payload) / 2) reinterpret_cast<uint16_t*>(chunks + payload)[i] = 0;
+    u32x4* const slots = reinterpret_cast<u32x4*>(chunks + first);
+    const uint64_t n_slots = (buffer_bytes - first) / 16;
+    for (uint64_t j = i; j < n_slots; j += stride) slots[j] = u32x4{0, 0, 0, 0};
 }
 
 }  // namespace
@@ -855,6 +849,32 @@ void build_fused_tabs(uint32_t* tab)
     }
 }
 
+namespace {
+
+constexpr uint32_t kFewGrads = 64;
+
+template <uint32_t N>
+void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTile* tiles,
+                 const void* const* grads, uint32_t p0, uint32_t n_params, const uint32_t* tabs,
+                 uint8_t* chunks, uint32_t* crcs, const FusedConsts& consts, hipStream_t stream)
+{
+    using Kernel = decltype(&fused_kernel<false, false, false, N>);
+    static const Kernel kernels[8] = {
+        fused_kernel<false, false, false, N>, fused_kernel<false, false, true, N>,
+        fused_kernel<false, true, false, N>,  fused_kernel<false, true, true, N>,
+        fused_kernel<true, false, false, N>,  fused_kernel<true, false, true, N>,
+        fused_kernel<true, true, false, N>,   fused_kernel<true, true, true, N>};
+    const bool bc2 = consts.adam.bc2s != 1.0f;
+    const Kernel kernel = kernels[(f16 ? 4 : 0) + (consts.prev ? 2 : 0) + (bc2 ? 1 : 0)];
+    GradPtrsOf<N> g;
+    for (uint32_t i = 0; i < N; i++)
+        g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
+    hipLaunchKernelGGL(kernel, dim3(n_waves / kWavesPerGroup), dim3(kThreads), 0, stream, waves, tiles, p0,
+                       tabs, chunks, crcs, consts, g);
+}
+
+}  // namespace
+
 hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grads, uint32_t n_params,
                         const uint32_t* tabs, void* chunks, uint32_t* crcs, uint64_t n_chunks,
                         uint64_t payload, uint64_t buffer_bytes, uint32_t affine,
@@ -863,12 +883,11 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
     uint8_t* c = static_cast<uint8_t*>(chunks);
     hipError_t e = hipSuccess;
     if (!bare) {
-        const uint64_t prep_items = n_chunks > (buffer_bytes - payload) / 2
-                                        ? n_chunks
-                                        : (buffer_bytes - payload) / 2;
+        const uint64_t slots = (buffer_bytes - payload) / 16;
+        const uint64_t prep_items = n_chunks > slots ? n_chunks : slots;
         unsigned prep_blocks = static_cast<unsigned>((prep_items + 255) / 256);
         if (prep_blocks == 0) prep_blocks = 1;
-        if (prep_blocks > 4096) prep_blocks = 4096;
+        if (prep_blocks > 1024) prep_blocks = 1024;
         hipLaunchKernelGGL(fused_prepare_kernel, dim3(prep_blocks), dim3(256), 0, stream, crcs,
                            n_chunks, affine, c, payload, buffer_bytes,
                            f16 ? consts.n_nonfinite : nullptr);
@@ -876,22 +895,14 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
         if (e != hipSuccess) return e;
     }
     const bool chained = consts.prev != nullptr;
-    using Kernel = decltype(&fused_kernel<false, false, false>);
-    static const Kernel kernels[8] = {
-        fused_kernel<false, false, false>, fused_kernel<false, false, true>,
-        fused_kernel<false, true, false>,  fused_kernel<false, true, true>,
-        fused_kernel<true, false, false>,  fused_kernel<true, false, true>,
-        fused_kernel<true, true, false>,   fused_kernel<true, true, true>};
-    const bool bc2 = consts.adam.bc2s != 1.0f;
-    const Kernel kernel = kernels[(f16 ? 4 : 0) + (chained ? 2 : 0) + (bc2 ? 1 : 0)];
     // one launch per kGradsPerLaunch parameter groups; tiles and wavefronts are sorted by group
     for (uint32_t k = 0, p0 = 0; p0 < n_params; k++, p0 += kGradsPerLaunch) {
-        GradPtrs g;
-        for (uint32_t i = 0; i < kGradsPerLaunch; i++)
-            g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
         if (bare) {
             const uint32_t t0 = work.launch_tile[k], t1 = work.launch_tile[k + 1];
             if (t1 == t0) continue;
+            GradPtrs g;
+            for (uint32_t i = 0; i < kGradsPerLaunch; i++)
+                g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
             // two workgroups per tile, one per half
             if (chained)
                 hipLaunchKernelGGL(mix_ceiling_kernel<true>, dim3(2 * (t1 - t0)), dim3(kStageThreads),
@@ -903,8 +914,8 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
         } else {
             const uint32_t w0 = work.launch_wave[k], w1 = work.launch_wave[k + 1];
             if (w1 == w0) continue;
-            hipLaunchKernelGGL(kernel, dim3((w1 - w0) / kWavesPerGroup), dim3(kThreads), 0, stream,
-                               work.waves + w0, work.tiles, p0, tabs, c, crcs, consts, g);
+            const auto launch = n_params - p0 <= kFewGrads ? launch_step<kFewGrads> : launch_step<kGradsPerLaunch>;
+            launch(f16, work.waves + w0, w1 - w0, work.tiles, grads, p0, n_params, tabs, c, crcs, consts, stream);
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -34,9 +34,11 @@ void build_fused_tabs(uint32_t* tab);
 // Gradient pointers of up to kGradsPerLaunch consecutive parameter groups, handed to the kernel by
 // value in its arguments (3 KiB).
 constexpr uint32_t kGradsPerLaunch = 384;
-struct GradPtrs {
-    uint64_t p[kGradsPerLaunch];
+template <uint32_t N>
+struct GradPtrsOf {
+    uint64_t p[N];
 };
+using GradPtrs = GradPtrsOf<kGradsPerLaunch>;
 
 // A plan's work lists on the device, and on the host where the part of every launch begins (one
 // entry more than there are launches).

@@ -79,6 +79,10 @@ struct TileTables {
 
 enum TileMode { kPack = 0, kRestore = 1, kVerify = 2 };
 
+// The cache hint of a pass over a buffer small enough to be still in the 256 MiB last-level cache, from
+// where it was written or received: plain loads, non-temporal stores.
+constexpr uint32_t kHintWarm(TileMode mode) { return mode == kPack ? 2u : 1u; }
+
 // A list of chunks handed to a kernel by value, inside its arguments: a selective restore needs
 // no device memory of its own for it.  Longer lists are processed in several launches.
 constexpr uint32_t kMaxListedChunks = 254;
