@@ -26,11 +26,13 @@
  *     enqueued on it and the call returns without synchronising; results stay on the device.
  *   - Return value: FF_OK (0) or a negative ff_status.  Nothing throws, nothing aborts.
  *     Corruption found by ff_restore is reported through bad[] / n_bad, never as an error code.
- *   - A plan is immutable after ff_snapshot_plan has returned: no call writes to it or to its
- *     device tables.  Calls on one plan may run concurrently, from several host threads and on
- *     several streams, as long as their output arrays (chunks, crcs, bad, n_bad, and for restore
- *     and the optimizer steps the plan's tensors) differ.  Intermediate results live in the
- *     output arrays themselves: while a call is in flight crcs[] / bad[] hold partial sums.
+ *   - A plan's tables do not change after ff_snapshot_plan has returned.  Calls on one plan may run
+ *     concurrently, from several host threads and on several streams, as long as their output
+ *     arrays (chunks, crcs, bad, n_bad, and for restore and the optimizer steps the plan's tensors)
+ *     differ.  Intermediate results live in the output arrays themselves -- while a call is in flight
+ *     crcs[] / bad[] hold partial sums -- or, for the calls of one stream, the first that asks for
+ *     it, in a small tally of the plan that every call leaves as it found it; calls on other streams
+ *     and captured calls do without.  A stream is destroyed only after its calls have completed.
  *   - Segments must not overlap each other, the chunk buffer or the crc arrays.
  *   - ff_pack, ff_restore, ff_restore_chunks and the optimizer steps allocate nothing, copy nothing
  *     and only launch kernels; host arrays they are given (gradient pointers, chunk ids) are read

@@ -224,10 +224,15 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
                              : T.payload - s < uint64_t(kBlockBytes) ? static_cast<uint32_t>(T.payload - s)
                                                                      : uint32_t(kBlockBytes);
         uint32_t first = T.tile_first_seg[entry];
-        if (sub)
-            while (first + 1 < T.n_seg && T.seg_off[first + 1] <= s) first++;
         // the tensor of the next entry's first byte is the last that can touch this block
         const uint32_t last = entry + 1 < T.n_tiles >> T.block_log2 ? T.tile_first_seg[entry + 1] : T.n_seg - 1;
+        if (sub) {  // not the entry's first block: the last tensor that starts at or before it
+            uint32_t hi = last;
+            while (first < hi) {
+                const uint32_t mid = first + (hi - first + 1) / 2;
+                if (T.seg_off[mid] <= s) first = mid; else hi = mid - 1;
+            }
+        }
         const uint32_t n = last - first + 1;
         if (end == 0) {
             if (MODE == kPack) static_for<kRows>([&](auto r) { w[r] = u32x4{0, 0, 0, 0}; });

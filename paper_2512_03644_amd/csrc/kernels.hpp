@@ -116,7 +116,8 @@ inline TileTables as_blocks(TileTables t)
 }
 inline bool tiles_are_blocks(const TileTables& t)
 {
-    return t.tile_rows == kBlockBytes / 1024 && t.block_tab && !t.partial;
+    // (tiles grouped for a read-only pass may be as long, but their shifts lie shift_stride apart)
+    return t.tile_rows == kBlockBytes / 1024 && t.shift_stride == 1 && t.block_tab && !t.partial;
 }
 
 // Fills tab (host, kBlockTabWords entries): byte tables of multiplication by x^8192 and by x^32, then

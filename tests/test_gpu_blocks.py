@@ -128,3 +128,17 @@ def test_listed_chunks_of_any_plan(oracle, tile_log2, flags):
         a, b = j * chunk, min((j + 1) * chunk, plan.payload_bytes)
         want[a:b] = sent[a:b]
     assert np.array_equal(np.concatenate(_host_segments(shard)[0]), want)
+
+
+@pytest.mark.parametrize("chunk,tile_log2", [(1 << 13, 10), (1 << 13, 11), (1 << 13, 12), (1 << 12, 10),
+                                             (1 << 14, 11), (1 << 15, 10)])
+def test_verify_where_grouped_tiles_are_as_long_as_a_block(oracle, chunk, tile_log2):
+    # a read-only pass groups tiles up to 64 KiB or the chunk: groups of 8 KiB are not blocks
+    shard = _ragged(60, 8.0, 1.0, tile_log2, chunk)
+    plan, chunks, crcs, _, _, _, _ = _pack_and_compare(shard, oracle, tile_log2=tile_log2)
+    chunks[3 * chunk + 11] ^= 8
+    want = np.zeros(plan.num_chunks, np.uint32)
+    want[3] = 1
+    for stream in (None, torch.cuda.Stream()):
+        bad, n_bad = _verify(plan, chunks, crcs, stream)
+        assert np.array_equal(bad, want) and n_bad == 1
