@@ -26,7 +26,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 
 
-KERNEL_SOURCES = ("kernels.hip", "kernels.hpp", "fused.hip", "fused.hpp", "fold.h", "fold_taps.h",
+KERNEL_SOURCES = ("kernels.hip", "blocks.hip", "tally.h", "kernels.hpp", "fused.hip", "fused.hpp", "fold.h", "fold_taps.h",
                   "gf2.h", "layout.hpp", "xcd_order.h")
 
 
