@@ -30,9 +30,9 @@
  *     concurrently, from several host threads and on several streams, as long as their output
  *     arrays (chunks, crcs, bad, n_bad, and for restore and the optimizer steps the plan's tensors)
  *     differ.  Intermediate results live in the output arrays themselves -- while a call is in flight
- *     crcs[] / bad[] hold partial sums -- or, for the calls of one stream, the first that asks for
- *     it, in a small tally of the plan that every call leaves as it found it; calls on other streams
- *     and captured calls do without.  A stream is destroyed only after its calls have completed.
+ *     crcs[] / bad[] hold partial sums -- or, for calls on the default stream (hip_stream NULL, not
+ *     captured), in a small tally of the plan that every call leaves as it found it.  Those calls are
+ *     one kernel where the others are two or three: a few microseconds on a small snapshot.
  *   - Segments must not overlap each other, the chunk buffer or the crc arrays.
  *   - ff_pack, ff_restore, ff_restore_chunks and the optimizer steps allocate nothing, copy nothing
  *     and only launch kernels; host arrays they are given (gradient pointers, chunk ids) are read

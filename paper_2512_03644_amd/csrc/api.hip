@@ -2,7 +2,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -30,8 +29,8 @@ static __device__ __align__(256) uint32_t scratch[kTabWords + kNoallocMaxTiles];
 
 // Calls on a plan read it, and the device tables behind it.  What a call needs beyond them travels in
 // kernel arguments or lives in the caller's own output arrays, with one exception: the tally, where
-// the calls of one stream -- the first that asks for it -- sum up their chunks in a single launch.
-// Every call leaves it as it found it, all zero, and calls on one stream do not overlap.
+// the calls on the default stream sum up their chunks in a single launch.  Every call leaves it as it
+// found it, all zero, and calls on one stream do not overlap.
 struct ff_plan {
     Layout layout;
     bool host_only = false;
@@ -52,7 +51,6 @@ struct ff_plan {
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
     uint64_t* tally = nullptr;  // null: chunks too long for one
-    mutable std::atomic<uint64_t> tally_owner{0};  // 0: nobody yet, else the stream's handle + 1
 };
 
 namespace {
@@ -183,22 +181,21 @@ int upload_tables(ff_plan* p)
     return FF_OK;
 }
 
-// The plan's tally, if calls on stream s may use it: the stream owns it (the first one to ask does,
-// from then on), it names one queue, and the call is not being captured -- a captured launch may be
-// replayed on any stream, beside later calls on this one.
+// The plan's tally, if calls on stream s may use it: s is the default stream, and is not being captured
+// (a captured launch may be replayed on any stream, beside later calls).  Of any other stream there is
+// only a handle, and a handle does not name a queue: a stream may be destroyed while its work is in
+// flight, and the next one created may get the same handle and run beside it.  Two calls that overlap
+// on the tally would leave it with bits that no later call accounts for.  The default stream is one
+// queue (the per-thread one has a handle of its own) and is never destroyed.
 uint64_t* tally_for(const ff_plan* p, hipStream_t s)
 {
-    if (!p->tally || s == hipStreamPerThread) return nullptr;
+    if (s != nullptr) return nullptr;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
-    if (st != hipStreamCaptureStatusNone) return nullptr;
-    const uint64_t me = reinterpret_cast<uint64_t>(s) + 1;
-    uint64_t owner = 0;
-    if (p->tally_owner.compare_exchange_strong(owner, me)) owner = me;
-    return owner == me ? p->tally : nullptr;
+    return st == hipStreamCaptureStatusNone ? p->tally : nullptr;
 }
 
 // Cache hint of a pass of `mode` over `bytes` of the buffer.

@@ -11,7 +11,7 @@
 //
 // A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the
 // plan's tally, which starts at zero, and whoever completes the word writes the chunk's result and
-// sets the word back to zero.  Otherwise -- a call on another stream than the tally's, or under
+// sets the word back to zero.  Otherwise -- a call on another stream than the default one, or under
 // capture -- the sums are XORed into the caller's own array between a preset and a finishing kernel.
 //
 // A block that lies inside one tensor needs one address.  In any other the wavefront first puts the

@@ -20,8 +20,8 @@
 // chunk's word of the caller's own output array (crcs[] for pack, bad[] for restore/verify), which
 // a small kernel has preset with the preset/complement term of the CRC.  XOR commutes, so the
 // result does not depend on the order in which tiles finish, and no memory outside the caller's
-// arrays is written: calls on one plan may overlap in time.  The restore and verify calls of the one
-// stream that owns the plan's tally meet there instead (tally.h).
+// arrays is written: calls on one plan may overlap in time.  The registers of restore and verify calls
+// on the default stream meet in the plan's tally instead (tally.h).
 #include "kernels.hpp"
 
 #include "fold.h"

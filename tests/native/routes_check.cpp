@@ -1,0 +1,154 @@
+// Host-only check of which kernels a call enqueues, and which of them use the plan's tally.  The
+// library's host code runs on a recording stand-in for the HIP runtime: device memory is host memory,
+// a launch is noted with its kernel's name and arguments and not run.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "kernels.hpp"
+#include "layout.hpp"
+
+using namespace ffsnap;
+
+struct Launch {
+    std::string kernel;
+    TileTables t;
+    hipStream_t stream;
+};
+static std::vector<Launch> g_log;
+// (filled by the objects' constructors, before this file's own)
+static std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
+static hipStreamCaptureStatus g_capture = hipStreamCaptureStatusNone;
+static struct { dim3 g, b; size_t s; hipStream_t q; } g_config;
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* f, char* name, const char*, unsigned, void*, void*, dim3*, dim3*, int*) { names()[f] = name; }
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, hipStream_t q) { g_config = {g, b, s, q}; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* q) { *g = g_config.g; *b = g_config.b; *s = g_config.s; *q = g_config.q; return hipSuccess; }
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t q)
+{
+    Launch l{names()[f], TileTables(), q};
+    if (l.kernel.find("block_kernel") != std::string::npos) l.t = *static_cast<TileTables*>(args[0]);
+    if (l.kernel.find("tile_kernel") != std::string::npos) l.t = *static_cast<TileTables*>(args[5]);
+    g_log.push_back(l);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { *p = malloc(n); return hipSuccess; }
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void**, const void*) { return hipErrorNotFound; }
+const char* hipGetErrorString(hipError_t) { return "stand-in"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) { *st = g_capture; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+}
+
+#define CHECK(x) do { if (!(x)) { printf("line %d, checked from line %d: %s\n", __LINE__, g_line, #x); exit(1); } } while (0)
+static int g_line = 0;
+#define FROM_HERE(x) do { g_line = __LINE__; x; } while (0)
+
+static bool is(const Launch& l, const char* part) { return l.kernel.find(part) != std::string::npos; }
+
+// A plan over `n` tensors of `bytes` bytes each, and the outputs of its calls.
+struct Job {
+    ff_plan* plan = nullptr;
+    alignas(16) char chunks[16];
+    uint32_t crcs[4], bad[4];
+    uint64_t n_bad;
+    Job(uint64_t n, uint64_t bytes, uint64_t chunk, uint32_t flags = 0, uint64_t misaligned = 0)
+    {
+        std::vector<ff_segment> segs;
+        for (uint64_t i = 0; i < n; i++)
+            segs.push_back({reinterpret_cast<void*>((1ull << 40) + misaligned + i * ((bytes + 255) / 128 * 128)), bytes, FF_BF16, FF_KIND_RAW, 0, 0});
+        CHECK(ff_snapshot_plan(segs.data(), n, chunk, flags, &plan) == FF_OK);
+    }
+    ~Job() { ff_plan_destroy(plan); }
+    std::vector<Launch> pack(void* s) { g_log.clear(); CHECK(ff_pack(plan, chunks, crcs, s) == FF_OK); return g_log; }
+    std::vector<Launch> restore(uint32_t flags, void* s) { g_log.clear(); CHECK(ff_restore(plan, chunks, crcs, bad, &n_bad, flags, s) == FF_OK); return g_log; }
+    std::vector<Launch> listed(uint32_t flags, void* s)
+    {
+        const uint64_t ids[2] = {0, 1};
+        g_log.clear();
+        CHECK(ff_restore_chunks(plan, chunks, crcs, ids, 2, bad, &n_bad, flags, s) == FF_OK);
+        return g_log;
+    }
+    std::vector<Launch> to_host(void* s) { g_log.clear(); CHECK(ff_pack_to_host(plan, chunks, crcs, chunks, crcs, 1, s, s) == FF_OK); return g_log; }
+};
+
+// The registers of a call meet in the caller's array between a preset and, for a verdict, a finishing
+// kernel; no launch of the call knows the tally.
+static void check_without_tally(const std::vector<Launch>& log, bool verdict)
+{
+    bool preset = false, folded = false, finished = false;
+    for (const Launch& l : log) {
+        CHECK(l.t.tally == nullptr);
+        if (is(l, "preset")) preset = true;
+        if (l.t.acc) { CHECK(preset); folded = true; }
+        if (is(l, "finish_verify")) { CHECK(folded); finished = true; }
+    }
+    CHECK(folded && finished == verdict);
+}
+// One launch sums up and delivers.
+static void check_with_tally(const std::vector<Launch>& log)
+{
+    for (const Launch& l : log) {
+        CHECK(!is(l, "preset") && !is(l, "finish"));
+        CHECK((l.t.acc != nullptr) == (l.t.tally != nullptr));
+    }
+    CHECK(!log.empty() && log[0].t.tally);
+}
+
+static void every_call_without_tally(Job& j, void* s)
+{
+    check_without_tally(j.pack(s), false);
+    check_without_tally(j.to_host(s), false);
+    for (uint32_t flags : {0u, FF_RESTORE_VERIFY_ONLY, FF_RESTORE_SKIP_BAD}) {
+        check_without_tally(j.restore(flags, s), true);
+        check_without_tally(j.listed(flags, s), true);
+    }
+}
+static void every_call_with_tally(Job& j)
+{
+    check_with_tally(j.pack(nullptr));
+    check_with_tally(j.to_host(nullptr));
+    for (uint32_t flags : {0u, FF_RESTORE_VERIFY_ONLY, FF_RESTORE_SKIP_BAD}) {
+        check_with_tally(j.restore(flags, nullptr));
+        check_with_tally(j.listed(flags, nullptr));
+    }
+}
+
+// A handle says nothing about the queue behind it once its stream may have been destroyed with work in
+// flight and the handle given to another, so the tally belongs to the one stream that is never destroyed.
+static void only_the_default_stream_uses_the_tally()
+{
+    for (const bool default_first : {false, true}) {
+        Job j(4, 1 << 20, 1 << 16);
+        if (default_first) FROM_HERE(every_call_with_tally(j));
+        for (void* s : {reinterpret_cast<void*>(0x7f0012340000ull), static_cast<void*>(hipStreamPerThread),
+                        static_cast<void*>(hipStreamLegacy), reinterpret_cast<void*>(0x7f0012340000ull)})
+            FROM_HERE(every_call_without_tally(j, s));
+        FROM_HERE(every_call_with_tally(j));  // whoever called before
+        g_capture = hipStreamCaptureStatusActive;
+        FROM_HERE(every_call_without_tally(j, nullptr));
+        g_capture = hipStreamCaptureStatusNone;
+    }
+}
+
+int main()
+{
+    only_the_default_stream_uses_the_tally();
+    printf("ok\n");
+    return 0;
+}

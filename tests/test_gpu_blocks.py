@@ -1,7 +1,11 @@
 """Pack, restore and verify in 8 KiB blocks against the oracle: at the sizes where a block can go
 wrong (crowded blocks, slots that straddle boundaries, the payload's end, runs shorter than a
-workgroup, every level of the tally), and on every route a call can take -- the tally, a second
-stream without it, a replayed capture, listed chunks of a plan with larger tiles."""
+workgroup, every level of the tally), and on every route a call can take -- the tally of the default
+stream, other streams without it, a replayed capture, listed chunks of a plan with larger tiles."""
+import ctypes
+import threading
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -64,7 +68,7 @@ def test_every_level_of_the_tally_and_the_routes_without_it(oracle, chunk, n_chu
     want[damaged] = 1
     side = torch.cuda.Stream()
     for _ in range(2):                                       # the tally comes back to zero
-        for stream in (None, side):                          # the first stream's, and not its own
+        for stream in (None, side):                          # with it, and without
             bad, n_bad = _verify(plan, chunks, crcs, stream)
             assert np.array_equal(bad, want) and n_bad == len(damaged)
     _poison_segments(shard)
@@ -97,6 +101,50 @@ def test_replayed_capture_beside_eager_calls(oracle):
         for c, r in ((chunks, crcs), (chunks2, crcs2)):
             assert np.array_equal(c.cpu().numpy(), want_buf) and np.array_equal(_u32(r), want_crcs)
         assert int(n_bad.item()) == 0 and not _u32(bad).any()
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    maps = {l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l}
+    return ctypes.CDLL(sorted(maps)[0])
+
+
+def test_threads_and_streams_that_come_and_go(oracle):
+    # Two host threads on the default stream, two on their per-thread streams, and streams that are
+    # destroyed with their work in flight, whose handles the runtime may give to the next one: every call
+    # gets its own chunks, checksums and verdicts right.
+    shard = _ragged(3000, 8.0, 1.5, 21, 1 << 18)
+    plan, chunks, crcs, _, _, want_buf, want_crcs = _pack_and_compare(shard, oracle)
+    damaged = chunks.clone()
+    damaged[5 * (1 << 18) + 99] ^= 16
+    hip = _hip()
+    outs = [ff.alloc_outputs(plan, DEV) for _ in range(12)]
+    torch.cuda.synchronize()
+
+    def calls(stream, out, times):
+        for _ in range(times):
+            ff.ff_pack(plan, out[0], out[1], stream=stream)
+            ff.ff_restore(plan, damaged, crcs, out[2], out[3], ff.FF_RESTORE_VERIFY_ONLY, stream=stream)
+
+    per_thread = SimpleNamespace(cuda_stream=2)  # hipStreamPerThread
+    default = SimpleNamespace(cuda_stream=0)
+    workers = [threading.Thread(target=calls, args=(s, outs[k], 20))
+               for k, s in enumerate((default, default, per_thread, per_thread))]
+    for w in workers:
+        w.start()
+    for k in range(4, 12):
+        handle = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0
+        calls(SimpleNamespace(cuda_stream=handle.value), outs[k], 5)
+        assert hip.hipStreamDestroy(handle) == 0
+    for w in workers:
+        w.join()
+    torch.cuda.synchronize()
+    want_bad = np.zeros(plan.num_chunks, np.uint32)
+    want_bad[5] = 1
+    for c, r, bad, n_bad in outs:
+        assert np.array_equal(c.cpu().numpy(), want_buf) and np.array_equal(_u32(r), want_crcs)
+        assert np.array_equal(_u32(bad), want_bad) and int(n_bad.item()) == 1
 
 
 @pytest.mark.parametrize("tile_log2", [13, 14, 15, 17])
