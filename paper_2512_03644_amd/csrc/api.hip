@@ -109,8 +109,9 @@ int upload_tables(ff_plan* p)
     std::vector<WorkWave> waves;
     if (L.adam_ok && !L.params.empty()) {
         build_work_tiles(L, work);
-        if (work.size() > 0x1FFFFFF0ull) return FF_ERR_INVALID;  // at most 8 wavefronts each
-        build_work_waves(work, L.params.size(), kGradsPerLaunch, waves, p->work.launch_wave);
+        if (work.size() > kMaxWorkEntries ||
+            !build_work_waves(work, L.params.size(), kGradsPerLaunch, waves, p->work.launch_wave))
+            return FF_ERR_INVALID;
     }
     const uint64_t o_work = align_up(o_tab + kTabWords * 4, 256);
     const uint64_t o_waves = align_up(o_work + work.size() * sizeof(WorkTile), 256);

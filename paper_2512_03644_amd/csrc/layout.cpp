@@ -230,9 +230,9 @@ void build_work_tiles(const Layout& L, std::vector<WorkTile>& out)
     }
 }
 
-void build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
+bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
                       uint32_t groups_per_launch, std::vector<WorkWave>& out,
-                      std::vector<uint32_t>& begin)
+                      std::vector<uint32_t>& begin, uint64_t max_entries)
 {
     out.clear();
     begin.assign(1, 0);
@@ -265,9 +265,12 @@ void build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
                 out.push_back(WorkWave{static_cast<uint32_t>(i),
                                        static_cast<uint32_t>(s | (slot << 4) | (run << 8))});
         }
+        if (out.size() > max_entries) return false;
     }
     fill_group();
+    if (out.size() > max_entries) return false;
     while (begin.size() < launches + 1) begin.push_back(static_cast<uint32_t>(out.size()));
+    return true;
 }
 
 }  // namespace ffsnap

@@ -88,10 +88,12 @@ void build_work_tiles(const Layout& L, std::vector<WorkTile>& out);
 // The wavefronts of the tiles, launch by launch: launch k takes the parameter groups
 // [k * groups_per_launch, (k + 1) * groups_per_launch), the last launch the RAW tiles as well.
 // begin[k] is the first entry of launch k, one more entry the end; each a multiple of
-// kWavesPerGroup.
-void build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
+// kWavesPerGroup.  False, with out and begin unfinished, if there would be more than max_entries: the
+// kernels count tiles and entries in 32 bits, and a tile has up to 16 entries.
+constexpr uint64_t kMaxWorkEntries = 0xFFFFFFF0ull;
+bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
                       uint32_t groups_per_launch, std::vector<WorkWave>& out,
-                      std::vector<uint32_t>& begin);
+                      std::vector<uint32_t>& begin, uint64_t max_entries = kMaxWorkEntries);
 
 // Returns FF_OK or a negative ff_status; `out` is valid only on FF_OK.
 // tile_log2: 0 = default tile size, else log2 of the tile size in bytes (clamped to

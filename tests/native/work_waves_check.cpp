@@ -23,7 +23,12 @@ int main(){
     if(build_layout(segs.data(), segs.size(), chunk, 0, L)!=FF_OK) continue;
     std::vector<WorkTile> tiles; build_work_tiles(L,tiles);
     std::vector<WorkWave> w; std::vector<uint32_t> begin;
-    build_work_waves(tiles, L.params.size(), per_launch, w, begin);
+    if(!build_work_waves(tiles, L.params.size(), per_launch, w, begin)){ printf("refused\n"); return 1; }
+    { // the limit is on the entries themselves, whatever their number for each tile
+      std::vector<WorkWave> w2; std::vector<uint32_t> begin2;
+      if(!build_work_waves(tiles, L.params.size(), per_launch, w2, begin2, w.size()) || begin2!=begin ||
+         build_work_waves(tiles, L.params.size(), per_launch, w2, begin2, w.size()-1)){ printf("limit\n"); return 1; }
+    }
     const uint64_t launches = (L.params.size()+per_launch-1)/per_launch;
     if(begin.size()!=launches+1 || begin[0]!=0 || begin.back()!=w.size()){ printf("launches\n"); return 1; }
     std::vector<uint32_t> seen(tiles.size(), 0);
