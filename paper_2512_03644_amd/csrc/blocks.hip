@@ -189,7 +189,8 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
     return u32x4{d[0], d[1], d[2], d[3]};
 }
 
-// One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once.
+// One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once, each in
+// the branch it takes.
 template <int MODE, int HINT, class Ready>
 __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, GatherLds* gather,
                                            uint8_t* __restrict__ chunks, const uint32_t tile,
@@ -313,7 +314,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         static_assert(kThreads * 4 == 2048, "two tables");
         *(reinterpret_cast<u32x4*>(lds.tab16) + threadIdx.x) = tab;  // tab16, tab_d
         if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = 0;
-        __syncthreads();
+        workgroup_barrier();
     };
     const uint32_t slot = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWaves + wave;
     const uint32_t count = LISTED ? list->n << T.tpc_log2 : T.n_list ? T.n_list : T.n_tiles;

@@ -31,6 +31,19 @@ __device__ __forceinline__ FF_GLOBAL T* as_global(T* p)
 
 constexpr int kWaveSize = 64;
 
+// Barrier of the workgroup for kernels whose wavefronts take different branches (a branch per wavefront,
+// never per lane) and come to it in different places of the code.  __syncthreads() may stand only
+// where all threads of a workgroup reach the same call; this names what such kernels rely on, and is what
+// __syncthreads() compiles to here: s_barrier counts the wavefronts that have arrived, wherever their
+// program counters are, and fences on both sides order LDS.  Every wavefront has to execute it the
+// same number of times, or end.
+__device__ __forceinline__ void workgroup_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 template <class Fn, int... Is>
 __device__ __forceinline__ void static_for_impl(Fn&& fn, std::integer_sequence<int, Is...>)
 {

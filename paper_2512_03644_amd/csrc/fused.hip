@@ -130,7 +130,8 @@ __device__ __forceinline__ void add_head_piece(uint32_t* __restrict__ crcs, cons
 static_assert(2 * (sizeof(Lds) + kImgBytes) <= 160 * 1024, "two workgroups on a compute unit");
 
 // The byte tables on their way to LDS: fetched first thing, stored (put) behind the loads of the
-// wavefront's own data, so that the two latencies overlap.  put() is the workgroup's only barrier.
+// wavefront's own data, so that the two latencies overlap.  put() is a barrier of the workgroup; every
+// wavefront calls it exactly once, whether at a parameter, a RAW tile or none.
 struct TableFetch {
     static constexpr int kEach = 6 * 1024 / (4 * kThreads);
     u32x4 a[kEach];
@@ -148,7 +149,7 @@ struct TableFetch {
         });
         if (threadIdx.x < kWavesPerBlock * 4) (&lds.sum[0][0])[threadIdx.x] = 0;
         if (threadIdx.x < kWavesPerBlock) lds.arrived[threadIdx.x] = 0;
-        __syncthreads();
+        workgroup_barrier();
     }
 };
 
@@ -469,7 +470,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
             *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
             *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
         });
-        __syncthreads();  // (every wavefront of the workgroup comes here)
+        workgroup_barrier();  // every wavefront is at this tile, in this function's instantiation or the other
         constexpr int kAll = kWavesPerBlock * int(kSubElems);
         const int from = at - wave * int(kSubElems);
         const int end = static_cast<int>(t.n) - from;
