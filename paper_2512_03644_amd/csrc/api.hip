@@ -50,7 +50,7 @@ struct ff_plan {
     uint32_t fused_xcd_group = 64, chained_xcd_group = 16;
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
-    uint64_t* tally = nullptr;  // null: chunks too long for one
+    uint64_t* tally = nullptr;  // null: none (tally_size)
 };
 
 namespace {
@@ -416,7 +416,7 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
     }
     choose_hint(p, v, pass1 ? kVerify : kRestore, bytes);
     choose_hint(p, t, kRestore, bytes);
-    v.tally = tally_for(p, s);
+    if ((list ? list->n : L.n_chunks) <= kTallyChunks) v.tally = tally_for(p, s);
     v.want = crcs;
     v.n_bad = n_bad;
     v.n_bad_add = clear_n_bad ? 0 : 1;

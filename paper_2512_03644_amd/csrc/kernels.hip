@@ -639,7 +639,7 @@ __device__ __forceinline__ void deliver(const TileTables& T, RunLds& lds, uint32
     if (T.tile_shift) reg = gf2_mul(reg, shift);
     if (lane != 0) return;
     const uint32_t chunk = tile >> T.tpc_log2;
-    if (T.tally) {
+    if (MODE != kPack && T.tally) {  // (a pack has it in blocks only)
         const uint32_t run = T.tiles_per_chunk < uint32_t(kWavesPerBlock) ? T.tiles_per_chunk : uint32_t(kWavesPerBlock);
         const uint32_t lead = wave - (wave & (run - 1));
         if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, reg)) return;
@@ -666,7 +666,7 @@ tile_kernel(
     __shared__ RunLds run_lds;
     __shared__ __align__(16) uint32_t ring[MODE == kRestore ? kWavesPerBlock : 1][kRingWords];
     for (int i = threadIdx.x; i < 1024; i += blockDim.x) tab[i] = tab_u_global[i];
-    if (threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = run_lds.arrived[threadIdx.x] = 0;
+    if (MODE != kPack && threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = run_lds.arrived[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);

@@ -13,10 +13,19 @@ namespace ffsnap {
 constexpr uint32_t kDefaultXcdGroup = 2048;
 
 constexpr uint32_t kTallyFan = 32;
-// Words of a plan's tally (0: its chunks have more runs than there are levels for), enough for runs
-// of 8 blocks of 8 KiB and of 4 tiles of the plan's size or more.
+// A verdict on more chunks than this does without the tally: the returning atomics of a chunk hold its
+// workgroup up, and the last level counts a word per 32 chunks on one address, which the two launches that
+// the tally saves no longer pay for.  With it / without, us: 4096 chunks (64 MB) restore 27.6 / 28.1, verify
+// 18.8 / 21.3; 6080 (190 MB) 75.6 / 77.7, 41.1 / 41.6; 8000 (1 GB) 338.6 / 337.5, 166.1 / 164.2; 8192 (64 MB)
+// 31.0 / 28.1, 22.5 / 21.3; 64000 (1 GB) 476.8 / 464.1, 316 / 300.
+constexpr uint64_t kTallyChunks = 6144;
+// Words of a plan's tally (0: none), enough for runs of 8 blocks of 8 KiB and of 4 tiles of the plan's size
+// or more.  None if its chunks have more runs than there are levels for, or its tiles are smaller than a
+// block: those are bound by what a tile costs beyond its bytes, and a returning atomic each is too much
+// of it (restore of 4 MB in chunks of 4 KiB 15.8 us with, 14.0 without; 64 MB 80.2 / 74.7).
 inline uint64_t tally_size(uint64_t n_chunks, uint64_t chunk_bytes, uint64_t tile_bytes)
 {
+    if (tile_bytes < (1ull << 13)) return 0;
     const uint64_t run = 4 * tile_bytes < (8ull << 13) ? 4 * tile_bytes : (8ull << 13);
     const uint64_t runs = chunk_bytes > run ? chunk_bytes / run : 1;
     if (runs > kTallyFan * kTallyFan) return 0;

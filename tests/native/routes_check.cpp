@@ -146,9 +146,33 @@ static void only_the_default_stream_uses_the_tally()
     }
 }
 
+// Where the tally costs more than the launches it saves: tiles smaller than a block, verdicts on more than
+// 6144 chunks (a pack counts no chunks and keeps it).
+static void tally_where_it_pays()
+{
+    for (uint64_t chunk : {1024, 2048, 4096}) {
+        Job j(4, 1 << 20, chunk);
+        FROM_HERE(every_call_without_tally(j, nullptr));
+    }
+    Job fine(4, 1 << 20, 1 << 17, FF_PLAN_TILE_LOG2(12));
+    FROM_HERE(check_without_tally(fine.pack(nullptr), false));
+    FROM_HERE(check_without_tally(fine.restore(0, nullptr), true));
+    FROM_HERE(check_without_tally(fine.listed(0, nullptr), true));
+    for (uint32_t flags : {0u, FF_PLAN_TILE_LOG2(13)}) {
+        Job last(6144, 8192, 8192, flags), more(6145, 8192, 8192, flags);
+        for (uint32_t f : {0u, FF_RESTORE_VERIFY_ONLY, FF_RESTORE_SKIP_BAD}) {
+            FROM_HERE(check_with_tally(last.restore(f, nullptr)));
+            FROM_HERE(check_without_tally(more.restore(f, nullptr), true));
+            FROM_HERE(check_with_tally(more.listed(f, nullptr)));
+        }
+        FROM_HERE(check_with_tally(more.pack(nullptr)));
+    }
+}
+
 int main()
 {
     only_the_default_stream_uses_the_tally();
+    tally_where_it_pays();
     printf("ok\n");
     return 0;
 }
