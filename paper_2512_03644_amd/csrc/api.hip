@@ -37,7 +37,7 @@ struct ff_plan {
     int device = -1;
     void* dev_block = nullptr;  // one allocation holding every device table
     TileTables tables;
-    bool hint_given = false;    // by the plan's flags
+    bool hint_given = false, tile_given = false;  // by the plan's flags
     // A pass that only reads (verify) runs fastest on larger tiles than one that also writes:
     // it folds verify_group consecutive tiles as one.
     uint32_t verify_group = 1;
@@ -248,6 +248,7 @@ int ff_snapshot_plan(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_byt
     }
     const Layout& L = p->layout;
     p->host_only = (flags & FF_PLAN_HOST_ONLY) != 0;
+    p->tile_given = tile_log2 != 0;
     p->affine = crc_affine_term(L.chunk_bytes);
     while (L.tile_bytes * p->verify_group < kVerifyTileBytes &&
            p->verify_group * 2 <= L.tiles_per_chunk)
@@ -396,17 +397,20 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         return FF_OK;
     }
     // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan (28 chunks
-    // of 4 MiB: 48.5-49.6 us in blocks, 47.3 on the plan's tiles; one chunk of 512 KiB 11 against 19);
-    // but a read-only pass over more than a small buffer is faster on 64 KiB tiles (400 MB: 70 against
-    // 76 us).
+    // of 4 MiB: 48.5-49.6 us in blocks, 47.3 on the plan's tiles; one chunk of 512 KiB 11 against 19),
+    // and a read-only pass over no more than a medium-sized buffer; over more it is faster on 64 KiB tiles
+    // (400 MB: 70 against 76 us).
     const uint64_t bytes = list ? list->n * L.chunk_bytes : L.buffer_bytes;
-    const bool small = bytes <= kSmallBufferBytes;
     const bool pass1 = verify_only || skip_bad;
-    if (list && bytes <= kWarmBytes && L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes) t = as_blocks(t);
+    const bool divisible = L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes;  // into blocks
+    if (list && bytes <= kWarmBytes && divisible) t = as_blocks(t);
+    const bool read_in_blocks = bytes <= kMediumBufferBytes && (tiles_are_blocks(t) || (!p->tile_given && divisible));
     // The verifying pass.  With the tally it delivers bad[] and *n_bad itself; else the registers are
     // summed in bad[] between two small kernels.
     TileTables v = t;
-    if (pass1 && !list && !(tiles_are_blocks(t) && small)) {  // a long read-only pass: grouped tiles
+    if (pass1 && !list && read_in_blocks) {
+        v = as_blocks(t);
+    } else if (pass1 && !list) {  // a long read-only pass: grouped tiles
         v.tile_rows *= p->verify_group;
         v.n_tiles /= p->verify_group;
         v.tiles_per_chunk /= p->verify_group;

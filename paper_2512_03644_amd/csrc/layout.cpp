@@ -99,21 +99,27 @@ int build_layout(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_bytes, 
     };
     uint64_t tile = kDefaultTileBytes;
     if (tile_log2) tile = 1ull << std::min<unsigned>(std::max<unsigned>(tile_log2, 10), 30);
-    const bool small = !tile_log2 && L.buffer_bytes <= kSmallBufferBytes;
-    cut_tiles(std::min(small ? kSmallTileBytes : tile, chunk_bytes));
-    if (!tile_log2 && !small) {
-        uint64_t crowded = 0;
-        for (uint64_t k = 0; k + 1 < L.n_tiles; k++)
-            crowded += L.tile_first_seg[k + 1] - L.tile_first_seg[k] >= 4 ? 1 : 0;
-        if (crowded > L.n_tiles / kCrowdedShare) cut_tiles(std::min(kSmallTileBytes, chunk_bytes));
-    }
-    tile = L.tile_bytes;
-    L.tile_base.assign(L.n_tiles, 0);
-    for (uint64_t k = 0; k < L.n_tiles; k++) {
-        const uint64_t s = k * tile;
+    auto base_of = [&](uint64_t k) -> uint64_t {  // address of tile k if it lies inside one segment, else 0
+        const uint64_t s = k * L.tile_bytes;
         const Seg& g = L.segs[L.tile_first_seg[k]];
-        if (g.off <= s && s + tile <= g.off + g.nbytes) L.tile_base[k] = g.ptr + (s - g.off);
+        return g.off <= s && s + L.tile_bytes <= g.off + g.nbytes ? g.ptr + (s - g.off) : 0;
+    };
+    cut_tiles(std::min(tile, chunk_bytes));
+    if (!tile_log2) {
+        uint64_t crowded = 0, on_line = 0;
+        for (uint64_t k = 0; k < L.n_tiles; k++) {
+            if (k + 1 < L.n_tiles) crowded += L.tile_first_seg[k + 1] - L.tile_first_seg[k] >= 4 ? 1 : 0;
+            const uint64_t base = base_of(k);
+            on_line += base && base % 128 == 0 ? 1 : 0;
+        }
+        const bool small = L.buffer_bytes <= kSmallBufferBytes;
+        const bool medium = L.buffer_bytes <= kMediumBufferBytes &&
+                            (L.tile_bytes < kDefaultTileBytes || on_line < L.n_tiles / 2);
+        if (small || medium || crowded > L.n_tiles / kCrowdedShare)
+            cut_tiles(std::min(kSmallTileBytes, chunk_bytes));
     }
+    L.tile_base.resize(L.n_tiles);
+    for (uint64_t k = 0; k < L.n_tiles; k++) L.tile_base[k] = base_of(k);
     return FF_OK;
 }
 

@@ -104,15 +104,23 @@ int build_layout(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_bytes, 
 // Tile size when the caller names none.  32 KiB tiles keep the region the chip is sweeping at any
 // moment compact, which is what a pass that reads and writes needs; a read-only pass amortises the
 // per-tile reduction better on 64 KiB.  Tiles of 8 KiB (blocks, blocks.hip) are for two kinds of plan.
-// Small buffers, where 32 KiB per wavefront leaves the chip idle and launches count: pack of 8 / 32 /
-// 64 / 128 / 192 / 256 / 512 MB 17.6 / 21.3 / 33.8 / 56.4 / 75.5 / 97.3 / 181 us with 32 KiB tiles, 11.2 /
-// 17.1 / 29.8 / 53.2 / 75.5 / 98.0 / 188 with blocks.  And lists of small tensors, whose tiles of more
+// Small buffers, where 32 KiB per wavefront leaves the chip idle and launches count.  Three buffers in turn,
+// tensors on 128-byte lines, 32 KiB tiles against blocks, us: pack of 32 / 64 / 96 / 112 / 128 / 160 / 190 MB
+// 20.2 / 30.8 / 41.8 / 48.8 / 53.0 / 63.0 / 73.2 against 15.4 / 25.7 / 40.7 / 47.1 / 53.4 / 64.7 / 75.6, restore of
+// 96 / 112 / 128 / 190 MB 44.4 / 52.0 / 55.9 / 76.6 against 41.4 / 49.4 / 55.5 / 78.1 (on a stream without the
+// tally blocks take 1-2 us more).  Where most tiles are off the lines or hold a boundary blocks win for longer:
+// tensors 6 bytes off a line, restore of 128 / 160 / 190 MB 66.3 / 76.5 / 87.0 against 59.5 / 70.9 / 82.3,
+// pack 62.2 / 67.8 / 78.3 against 59.4 / 67.8 / 78.3; 300 ragged tensors in 186 MB 82.8 against 78.1 (pack); and
+// so they do where a chunk leaves no room for a 32 KiB tile.  A read-only pass is as fast or faster in
+// blocks up to there on any layout (verify of 96 / 128 / 144 / 160 / 190 MB 27.8 / 30.5 / 38.6 / 39.6 / 42.8
+// against 24.9 / 29.9 / 32.8 / 36.8 / 41.0).  And lists of small tensors, whose tiles of more
 // than four tensors take the tile kernel's row-by-row path: 5 KiB tensors (1 GB) 890 and 373 us; tensors
 // of 40 KB on average (0.8 GB) 302 and 291 us.  With 110 KB it is 318 and 312 for a pack but 459 and 483
 // for a restore that leaves bad chunks out: too few of those tiles are crowded.
 constexpr uint64_t kDefaultTileBytes = 1ull << 15;
 constexpr uint64_t kSmallTileBytes = 1ull << 13;
-constexpr uint64_t kSmallBufferBytes = 192ull << 20;
+constexpr uint64_t kSmallBufferBytes = 112ull << 20;   // blocks, whatever the layout
+constexpr uint64_t kMediumBufferBytes = 192ull << 20;  // blocks if fewer than half of the tiles are on lines
 constexpr uint64_t kCrowdedShare = 16;  // blocks if a tile in so many holds more than four tensors
 // Up to here a pass in blocks loads through the caches (unless the plan's flags say otherwise).  Three
 // buffers in turn, plain against non-temporal loads: pack of 8 / 32 / 64 / 128 MB 11.8 / 17.4 / 27.8 / 60.1

@@ -169,8 +169,48 @@ static void tally_where_it_pays()
     }
 }
 
+// The kernel that folds: of a pack and a restore (the scatter of a skipping one), and of a read-only pass.
+static const char* folding(const std::vector<Launch>& log)
+{
+    for (const Launch& l : log)
+        if (l.t.acc) return is(l, "block_kernel") ? "blocks" : is(l, "tile_kernel") ? "tiles" : "?";
+    return "none";
+}
+static void blocks_by_size_and_layout()
+{
+    const std::string blocks = "blocks", tiles = "tiles";
+    struct { uint64_t mb, chunk, misaligned; uint32_t flags; std::string moving, reading; } cases[] = {
+        {112, 1 << 20, 0, 0, blocks, blocks},        // small
+        {112, 1 << 20, 6, 0, blocks, blocks},
+        {113, 1 << 20, 0, 0, tiles, blocks},         // medium, on the lines
+        {192, 1 << 20, 0, 0, tiles, blocks},
+        {192, 1 << 20, 6, 0, blocks, blocks},        // medium, off the lines
+        {192, 1 << 20, 64, 0, blocks, blocks},
+        {192, 1 << 14, 0, 0, blocks, blocks},        // no room for 32 KiB
+        {193, 1 << 20, 0, 0, tiles, tiles},          // large
+        {193, 1 << 20, 6, 0, tiles, tiles},
+        {113, 1 << 20, 0, FF_PLAN_TILE_LOG2(15), tiles, tiles},  // a tile size that is asked for is kept
+        {8, 1 << 20, 6, FF_PLAN_TILE_LOG2(15), tiles, tiles},
+        {193, 1 << 20, 0, FF_PLAN_TILE_LOG2(13), blocks, tiles},
+    };
+    for (const auto& c : cases) {
+        Job j(1, c.mb << 20, c.chunk, c.flags, c.misaligned);
+        for (void* s : {static_cast<void*>(nullptr), reinterpret_cast<void*>(0x7f0012340000ull)}) {
+            g_line = static_cast<int>(c.mb);
+            CHECK(folding(j.pack(s)) == c.moving);
+            CHECK(folding(j.restore(0, s)) == c.moving);
+            CHECK(folding(j.restore(FF_RESTORE_VERIFY_ONLY, s)) == c.reading);
+            const auto skip = j.restore(FF_RESTORE_SKIP_BAD, s);
+            CHECK(folding(skip) == c.reading);
+            CHECK(is(skip.back(), c.moving == blocks ? "block_kernel" : "tile_kernel"));
+            CHECK(folding(j.listed(0, s)) == blocks);
+        }
+    }
+}
+
 int main()
 {
+    blocks_by_size_and_layout();
     only_the_default_stream_uses_the_tally();
     tally_where_it_pays();
     printf("ok\n");

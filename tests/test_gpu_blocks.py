@@ -80,6 +80,35 @@ def test_every_level_of_the_tally_and_the_routes_without_it(oracle, chunk, n_chu
         assert np.array_equal(got[a:b], np.full(b - a, 0xA5, np.uint8) if want[j] else want_buf[a:b])
 
 
+@pytest.mark.parametrize("mis", [0, 6])
+@pytest.mark.parametrize("chunk", [1 << 14, 1 << 15, 1 << 20])
+def test_medium_buffers_on_and_off_the_lines(oracle, mis, chunk):
+    # 113 MiB: moved in 32 KiB tiles if they lie on the tensors' lines (in chunks that have room), in blocks
+    # otherwise, and verified in blocks either way
+    n_chunks = (113 << 20) // chunk
+    shard = wl.fragmented_shard([(chunk * n_chunks // 2 - 7, 2, mis)], chunk, seed=chunk + mis, device=DEV,
+                                max_gap=0)
+    assert shard.segments[0].data_ptr() % 128 == mis
+    plan, chunks, crcs, bad, n_bad, want_buf, _ = _pack_and_compare(shard, oracle)
+    assert plan.num_chunks == n_chunks
+    _restore_and_compare(shard, plan, chunks, crcs, bad, n_bad, want_buf)
+    damaged = [0, n_chunks // 3, n_chunks - 1]
+    for j in damaged:
+        chunks[j * chunk + 1029 + j % 900] ^= 2
+    want = np.zeros(n_chunks, np.uint32)
+    want[damaged] = 1
+    for stream in (None, torch.cuda.Stream()):
+        for flags in (ff.FF_RESTORE_VERIFY_ONLY, ff.FF_RESTORE_SKIP_BAD):
+            _poison_segments(shard)
+            got_bad, got_n = _verify(plan, chunks, crcs, stream, flags)
+            assert np.array_equal(got_bad, want) and got_n == len(damaged)
+            got = _host_segments(shard)[0][0].reshape(-1)
+            kept = np.full(got.size, flags == ff.FF_RESTORE_VERIFY_ONLY)
+            for j in damaged:
+                kept[j * chunk:(j + 1) * chunk] = True
+            assert np.array_equal(got, np.where(kept, np.uint8(0xA5), want_buf[:got.size]))
+
+
 def test_replayed_capture_beside_eager_calls(oracle):
     shard = _ragged(800, 7.0, 1.5, 3, 1 << 16)
     plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle)
