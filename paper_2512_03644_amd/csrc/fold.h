@@ -177,6 +177,18 @@ __device__ __forceinline__ uint32_t quad_place_xor(uint32_t v)
     return b[0] ^ b[1];
 }
 
+// One lane per wavefront: adds v to the run's sum in LDS.  True in the wavefront that completes the
+// run; v is then the run's whole sum.  (LDS operations of a wavefront complete in order, so the
+// sum is complete when the count is.)
+__device__ __forceinline__ bool run_complete(uint32_t& sum, uint32_t& arrived, const uint32_t run, uint32_t& v)
+{
+    atomicXor(&sum, v);
+    asm volatile("" ::: "memory");
+    if (atomicAdd(&arrived, 1u) + 1 != run) return false;
+    v = *const_cast<volatile uint32_t*>(&sum);
+    return true;
+}
+
 // State of all lanes -> R / x^32, where R is the CRC register (run from 0) of the rows folded so
 // far; the factor x^32 that every register carries is applied once per chunk by the combine
 // step.  The result is valid in every lane.  tab: byte tables of x^(8*ROW_BYTES);

@@ -179,11 +179,12 @@ __device__ __forceinline__ uint32_t finish_streams(const uint32_t (&v)[4], const
     return quad_place_xor(gf2_mul(w, lane_c));
 }
 
-// Sum of the run's registers; in the run's last wavefront, on to memory.  v: lane l (l < n) holds
-// the register of stream x.
+// Sum of the registers of a parameter tile's run; in the run's last wavefront, on to memory.  v: lane l
+// (l < 4) holds the register of stream x.
 __device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info, uint32_t v, int x,
-                                        int n, uint32_t* __restrict__ crcs, int lane)
+                                        uint32_t* __restrict__ crcs, int lane)
 {
+    int n = 4;
     const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
     if (len > 1) {
         // LDS operations of a wavefront complete in order: the sum is complete when the count is
@@ -202,7 +203,7 @@ __device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t in
     v = gf2_mul(v, s);
     // all streams in one chunk (any parameter much smaller than a chunk)?
     const bool one = t.chunk[0] == t.chunk[1] && t.chunk[0] == t.chunk[2] && t.chunk[0] == t.chunk[3];
-    if (n == 4 && one) {
+    if (one) {
         v ^= __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
         v ^= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
         n = 1;
@@ -514,7 +515,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     });
     const uint32_t v[4] = {join_columns(rw, lds.tab_d), join_columns(rp, lds.tab_d),
                            join_columns(rm, lds.tab_d), join_columns(rv, lds.tab_d)};
-    deliver(lds, t, info, finish_streams(v, lds, lane_c, lane), stream_of_lane(lane), 4, crcs, lane);
+    deliver(lds, t, info, finish_streams(v, lds, lane_c, lane), stream_of_lane(lane), crcs, lane);
 
     if constexpr (F16) {
         if (C.n_nonfinite && __any(nonfinite != 0)) {
@@ -540,7 +541,7 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
 {
     const int sub = info & 15u;
     // x^(8 * bytes between the end of the lane's slot and the end of the block)
-    const uint32_t lane_c = lane_tab[(3 - sub) * 64 + lane];
+    const uint32_t to_block_end = lane_tab[(3 - sub) * 64 + lane];
     const uint8_t* const src = reinterpret_cast<const uint8_t*>(t.ptr[0]) + at;
     uint8_t* const dst = chunks + (static_cast<int64_t>(t.soff[0]) + at);
     auto mine = [&](int r) {
@@ -562,6 +563,10 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
             *as_global(reinterpret_cast<uint16_t*>(dst + x)) = static_cast<uint16_t>(eh);
         }
     }
+    // and on to the end of the chunk: the wavefronts of a run may be at different tiles of it.  (While the
+    // data is on its way.)
+    const uint32_t lane_c = gf2_mul(to_block_end, t.shift[0]);
+    __builtin_amdgcn_sched_barrier(0);
     tf.put(lds);
     u32x4 edge[2];  // the two slots, put together from the halfwords of lanes 0..15
     static_for<2>([&](auto e) {
@@ -578,8 +583,13 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
         const uint32_t d[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
         add_row<4, r == 0>(reg, lds.tab16, d);
     });
-    const uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
-    deliver(lds, t, info, v, 0, 1, crcs, lane);
+    // (With a run for every tile tensors of 2 KB are bound by the atomics on their chunk's word: 40 MB of
+    // them in chunks of 16 KiB / 1 MiB / 8 MiB 49 / 188 / 256 us, with runs across tiles 48 / 52 / 52.)
+    uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
+    if (lane != 0) return;
+    const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
+    if (len > 1 && !run_complete(lds.sum[run][0], lds.arrived[run], len, v)) return;
+    atomicXor(&crcs[t.chunk[0]], v);
 }
 
 // The gradient pointers of the parameter groups [grad_base, grad_base + kGradsPerLaunch) travel by

@@ -266,10 +266,19 @@ bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
         if (last - first + 1 >= kWavesPerGroup) fill_group();
         for (uint64_t s = first; s <= last;) {
             const uint64_t slot = out.size() % kWavesPerGroup;
-            const uint64_t run = std::min<uint64_t>(last - s + 1, kWavesPerGroup - slot);
-            for (uint64_t k = 0; k < run; k++, s++)
+            const uint64_t here = std::min<uint64_t>(last - s + 1, kWavesPerGroup - slot);
+            // a RAW tile goes on with the run in front of it, if that is of the same chunk
+            uint64_t begin = slot, run = here;
+            const WorkTile* before = slot && out.back().tile != kNoTile ? &tiles[out.back().tile] : nullptr;
+            if (t.kind == kWorkRaw && before && before->kind == kWorkRaw && before->chunk[0] == t.chunk[0]) {
+                begin = (out.back().info >> 4) & 7u;
+                run = slot + here - begin;
+                for (uint64_t k = out.size() - slot + begin; k < out.size(); k++)
+                    out[k].info = (out[k].info & 0xFFu) | static_cast<uint32_t>(run << 8);
+            }
+            for (uint64_t k = 0; k < here; k++, s++)
                 out.push_back(WorkWave{static_cast<uint32_t>(i),
-                                       static_cast<uint32_t>(s | (slot << 4) | (run << 8))});
+                                       static_cast<uint32_t>(s | (begin << 4) | (run << 8))});
         }
         if (out.size() > max_entries) return false;
     }

@@ -69,8 +69,9 @@ constexpr uint32_t kParamTileElems = 1u << 13;
 constexpr uint32_t kRawTileBytes = 1u << 15;
 
 // What one wavefront of the fused step works on: one sub-block of a tile.  kWavesPerGroup
-// consecutive entries make a workgroup; the entries of one tile that share a workgroup (a run) sum
-// their registers in LDS before they go to memory.
+// consecutive entries make a workgroup; the entries of a run, all in one workgroup, sum their registers in
+// LDS before they go to memory.  A run is the entries of one parameter tile; or, as RAW tiles lie in
+// stream order and have one stream, the neighbouring entries of all RAW tiles in one chunk.
 struct WorkWave {
     uint32_t tile;  // index into the tile list, or kNoTile: nothing to do
     uint32_t info;  // bits 0..3 sub-block of the tile's block, 4..6 place of the run's first

@@ -18,18 +18,6 @@ __device__ __forceinline__ void tally_reset(uint64_t* word)
     __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One lane per wavefront: adds v to the run's sum in LDS.  True in the wavefront that completes the
-// run; v is then the run's whole sum.  (LDS operations of a wavefront complete in order, so the
-// sum is complete when the count is.)
-__device__ __forceinline__ bool run_complete(uint32_t& sum, uint32_t& arrived, const uint32_t run, uint32_t& v)
-{
-    atomicXor(&sum, v);
-    asm volatile("" ::: "memory");
-    if (atomicAdd(&arrived, 1u) + 1 != run) return false;
-    v = *const_cast<volatile uint32_t*>(&sum);
-    return true;
-}
-
 // v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.
 template <int MODE>
 __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const uint32_t chunk,

@@ -1,6 +1,6 @@
 // host-only check of build_work_waves over random layouts: every sub-block of every tile belongs to
 // exactly one wavefront of the launch that carries its parameter group, runs name the wavefronts of
-// one tile that share a workgroup, launches begin at workgroups
+// one parameter tile, or of one chunk's RAW tiles, that share a workgroup, launches begin at workgroups
 #include "layout.hpp"
 #include <cstdio>
 #include <random>
@@ -18,6 +18,7 @@ int main(){
       segs.push_back({arena+2, 2*ne, FF_BF16, FF_KIND_W16, (uint32_t)p, 0});
       for(uint32_t k=FF_KIND_MASTER;k<=FF_KIND_V;k++) segs.push_back({arena+4, 4*ne, FF_F32, k, (uint32_t)p, 0});
       if(rng()%3==0) segs.push_back({arena+2, 2*(rng()%60000), FF_BF16, FF_KIND_RAW, 0, 0});
+      for(uint64_t k=rng()%30; k-- && rng()%8;) segs.push_back({arena+2, 2*(1+rng()%3000), FF_BF16, FF_KIND_RAW, 0, 0});
     }
     Layout L;
     if(build_layout(segs.data(), segs.size(), chunk, 0, L)!=FF_OK) continue;
@@ -45,7 +46,11 @@ int main(){
         if(slot<first || slot>=first+len || first+len>kWavesPerGroup){ printf("run place\n"); return 1; }
         for(uint32_t s=0;s<kWavesPerGroup;s++){
           const bool in = s>=first && s<first+len;
-          if(in != (w[base+s].tile==w[i].tile)){ printf("run members\n"); return 1; }
+          const uint32_t o=w[base+s].tile;
+          // RAW tiles of one chunk share a run, they are neighbours in the stream
+          const bool mates = o==w[i].tile || (o!=kNoTile && t.kind==kWorkRaw && tiles[o].kind==kWorkRaw && tiles[o].chunk[0]==t.chunk[0]);
+          if(in != mates){ printf("run members\n"); return 1; }
+          if(in && ((w[base+s].info>>4)!=(w[i].info>>4))){ printf("run of a mate\n"); return 1; }
         }
       }
     }

@@ -29,6 +29,16 @@ def test_block_edges_in_place_and_chained(oracle, chunk):
                          loss_scale=1024.0, extra_raw=extra)
 
 
+@pytest.mark.parametrize("chunk", [1024, 1 << 14, 1 << 20])
+def test_many_raw_tensors_in_a_chunk(oracle, chunk):
+    # workgroups whose wavefronts are at many RAW tensors of one chunk, or of two, some behind a parameter
+    sizes = torch.randint(1, 3000, (300,), generator=torch.Generator().manual_seed(chunk)).tolist()
+    raw = _raw(sizes + [1] * 40 + [20000], torch.bfloat16, chunk)
+    extra = [(12 if i >= 30 else 5, t) for i, t in enumerate(raw)]
+    _adam_and_compare(oracle, [700, 5, 9000], chunk, seed=chunk, hp=dict(HP, step=2), extra_raw=extra)
+    _chained_and_compare(oracle, [700, 5, 9000], chunk, seed=chunk, steps=2, extra_raw=extra)
+
+
 @pytest.mark.parametrize("shift", [1, 3, 7])
 def test_step_on_tensors_off_every_alignment(shift):
     """Tensors and gradients that start `shift` elements into an allocation give the same snapshot,
