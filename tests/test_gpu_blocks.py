@@ -44,6 +44,37 @@ def test_one_block_of_so_many_tensors(oracle, n_seg, end):
     _restore_and_compare(shard, *state[:6])
 
 
+# one tensor, a few, around the 64 lanes, around the 128 that the table of a block holds, beyond it
+@pytest.mark.parametrize("n_seg", [1, 2, 63, 64, 65, 127, 128, 129, 130, 170])
+@pytest.mark.parametrize("behind", [False, True])
+@pytest.mark.parametrize("tile_log2", [0, 13, 15])
+def test_exactly_so_many_tensors_in_one_block(oracle, n_seg, behind, tile_log2):
+    # a tensor that ends where the block begins, then n_seg in the block: all boundaries are inside a slot,
+    # each in one of its own, so there are as many straddling slots as there can be.  Behind them the
+    # payload ends inside a slot too, or a tensor begins where the next block does.
+    sizes = [2] + [48] * (n_seg - 2) if n_seg > 1 else []
+    last = (8192 if behind else 8192 - 16 * 3 - 6) - sum(sizes)
+    sizes.append(last)
+    assert len(sizes) == n_seg and last > 0
+    ends = 8192 + np.cumsum(sizes)
+    assert all(e % 16 for e in ends[:-1]) and len({e // 16 for e in ends}) == n_seg
+    starts = ends - sizes
+    assert sum(a < 16384 and e > 8192 for a, e in zip(starts, ends)) == n_seg
+    lay = [(4096, 2, 6)] + [(b // 2, 2, (2 * i) % 16) for i, b in enumerate(sizes)]
+    if behind:
+        lay += [(5000, 2, 10)]
+    shard = wl.fragmented_shard(lay, 1 << 15, seed=n_seg, device=DEV)
+    state = _pack_and_compare(shard, oracle, tile_log2)
+    _restore_and_compare(shard, *state[:6])
+    # and as a list of chunks, in blocks whatever the tiles are
+    plan, chunks, crcs, bad, n_bad, want_buf, _ = state
+    _poison_segments(shard)
+    ff.ff_restore_chunks(plan, chunks, crcs, list(range(plan.num_chunks)), bad, n_bad)
+    torch.cuda.synchronize()
+    assert int(n_bad.item()) == 0
+    assert np.array_equal(np.concatenate(_host_segments(shard)[0]), want_buf[:plan.payload_bytes])
+
+
 def _verify(plan, chunks, crcs, stream=None, flags=ff.FF_RESTORE_VERIFY_ONLY):
     bad = torch.full((plan.num_chunks,), 7, dtype=torch.int32, device=DEV)
     n_bad = torch.full((1,), 99, dtype=torch.int64, device=DEV)

@@ -10,6 +10,9 @@ from paper_2512_03644_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
+# Buffers of these sizes are cut into 8 KiB blocks by default; 15 has them in the 32 KiB tiles of large ones.
+TILES = (0, 15)
+
 
 def _host_segments(shard):
     """Host copies of the shard's segments as numpy arrays (uint8 views of the raw bytes)."""
@@ -98,26 +101,29 @@ def test_param_shard_chunk_and_tile_sizes(oracle, chunk, tile_log2):
     _restore_and_compare(shard, *state[:6])
 
 
+@pytest.mark.parametrize("tile_log2", TILES)
 @pytest.mark.parametrize("seed,mu,n", [(1, 3.0, 3000), (2, 6.0, 2000), (3, 9.0, 400)])
-def test_ragged_unaligned_segments(oracle, seed, mu, n):
+def test_ragged_unaligned_segments(oracle, seed, mu, n, tile_log2):
     # many tiny tensors (down to one element), 2-byte granularity, every misalignment
     lay = wl.fragmented_layout(seed=seed, n_tensors=n, mu=mu, sigma=2.0, max_numel=1 << 18)
     shard = wl.fragmented_shard(lay, 1 << 16, seed=seed, device=DEV)
     assert len({o % 16 for o, _ in shard.spans}) == 8
-    state = _pack_and_compare(shard, oracle)
+    state = _pack_and_compare(shard, oracle, tile_log2)
     _restore_and_compare(shard, *state[:6])
 
 
+@pytest.mark.parametrize("tile_log2", TILES)
 @pytest.mark.parametrize("seed", [11, 12, 13])
-def test_tiles_with_a_few_segment_boundaries(oracle, seed):
+def test_tiles_with_a_few_segment_boundaries(oracle, seed, tile_log2):
     # tensors of 4-40 KB at every 2-byte misalignment: most 32 KiB tiles hold 2-5 pieces
     lay = wl.fragmented_layout(seed=seed, n_tensors=1200, mu=8.6, sigma=0.6, max_numel=1 << 15)
     shard = wl.fragmented_shard(lay, 1 << 17, seed=seed, device=DEV)
-    state = _pack_and_compare(shard, oracle)
+    state = _pack_and_compare(shard, oracle, tile_log2)
     _restore_and_compare(shard, *state[:6])
 
 
-def test_whole_tiles_at_every_offset_within_a_line(oracle):
+@pytest.mark.parametrize("tile_log2", TILES)
+def test_whole_tiles_at_every_offset_within_a_line(oracle, tile_log2):
     # tensors of 3-4 tiles each, ragged, starting at every even offset within a 128-byte line:
     # most tiles lie inside one tensor, at every misalignment of the tensor side (on restore
     # these are the tiles whose stores are lined up with the tensor)
@@ -125,12 +131,13 @@ def test_whole_tiles_at_every_offset_within_a_line(oracle):
     lay = [(int(rng.integers(48000, 60000)), 2, int(rng.integers(0, 8)) * 2) for _ in range(320)]
     shard = wl.fragmented_shard(lay, 1 << 18, seed=5, device=DEV)
     assert len({o % 128 for o, _ in shard.spans}) == 64
-    state = _pack_and_compare(shard, oracle)
+    state = _pack_and_compare(shard, oracle, tile_log2)
     _restore_and_compare(shard, *state[:6])
 
 
+@pytest.mark.parametrize("tile_log2", TILES)
 @pytest.mark.parametrize("tail", [2, 14, 16, 18, 1022, 1024, 1026, 16384 + 6, 32766])
-def test_payload_end_inside_a_tile(oracle, tail):
+def test_payload_end_inside_a_tile(oracle, tail, tile_log2):
     # three full tiles, then `tail` bytes split over segments of 2-byte granularity: the payload
     # ends inside the fourth tile at every kind of position (inside a lane, on a lane or row edge)
     lay = [(3 * 16384 + 5, 2, 2), (max(tail // 2 - 5, 0), 2, 6)]
@@ -138,12 +145,13 @@ def test_payload_end_inside_a_tile(oracle, tail):
         lay = [(3 * 16384 + tail // 2, 2, 2)]
     shard = wl.fragmented_shard(lay, 1 << 17, seed=tail, device=DEV)
     assert shard.payload_bytes == 3 * 32768 + tail
-    state = _pack_and_compare(shard, oracle)
+    state = _pack_and_compare(shard, oracle, tile_log2)
     _restore_and_compare(shard, *state[:6])
 
 
+@pytest.mark.parametrize("tile_log2", TILES)
 @pytest.mark.parametrize("pieces", [2, 3, 4, 5, 6])
-def test_boundaries_at_every_offset_in_a_lane(oracle, pieces):
+def test_boundaries_at_every_offset_in_a_lane(oracle, pieces, tile_log2):
     # one 32 KiB tile cut into `pieces` segments; the cuts walk through all eight halfword
     # positions of a lane, include segments shorter than a lane, and two cuts inside one lane
     lay, used = [], 0
@@ -154,7 +162,7 @@ def test_boundaries_at_every_offset_in_a_lane(oracle, pieces):
         used = c
     lay.append((20000, 4, 4))                       # more tiles behind it
     shard = wl.fragmented_shard(lay, 1 << 16, seed=pieces, device=DEV)
-    state = _pack_and_compare(shard, oracle)
+    state = _pack_and_compare(shard, oracle, tile_log2)
     _restore_and_compare(shard, *state[:6])
 
 
@@ -165,10 +173,11 @@ def test_single_element_segments(oracle):
     _restore_and_compare(shard, *state[:6])
 
 
-def test_corruption_is_flagged_exactly(oracle):
+@pytest.mark.parametrize("tile_log2", TILES)
+def test_corruption_is_flagged_exactly(oracle, tile_log2):
     numels = [int(x) for x in np.random.default_rng(5).integers(1000, 90000, size=40)]
     shard = wl.param_shard("c", numels, 1 << 16, 5, DEV, tiny_recipe=True)
-    plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle)
+    plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle, tile_log2)
     hits = wl.corrupt_chunks(plan.num_chunks, shard.chunk_bytes, seed=8, fraction=0.05)
     dirty = chunks.clone()
     for c, off, bit in hits:
@@ -194,14 +203,16 @@ def test_corruption_is_flagged_exactly(oracle):
 
 
 @pytest.mark.parametrize("chunk,tile_log2", [(1 << 15, 0), (1 << 16, 0), (1 << 16, 12), (1 << 18, 0),
-                                             (1 << 20, 14), (1 << 17, 17)])
+                                             (1 << 20, 14), (1 << 17, 17), (1 << 15, 15),
+                                             (1 << 16, 15), (1 << 18, 15)])
 def test_verify_only_every_tile_position(oracle, chunk, tile_log2):
-    """A read-only pass folds several tiles as one; a flipped bit in any tile of a chunk, and at
-    the first and last byte of a chunk, must flag exactly that chunk."""
+    """A flipped bit in any tile of a chunk (8 KiB blocks by default), and at the first and last byte of
+    a chunk, must flag exactly that chunk; with a tile size named, a read-only pass folds several tiles
+    as one."""
     numels = [int(x) for x in np.random.default_rng(chunk + tile_log2).integers(20000, 200000, size=12)]
     shard = wl.param_shard("v", numels, chunk, 31, DEV, tiny_recipe=True)
     plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle, tile_log2)
-    tile = 1 << (tile_log2 or 15)
+    tile = 1 << (tile_log2 or 13)
     tile = min(tile, chunk)
     rng = np.random.default_rng(7)
     dirty = chunks.clone()
@@ -384,12 +395,13 @@ def test_mix_ceiling_moves_exactly_the_steps_bytes(chunk, chained):
     assert bool((got[~covered] == 0xA5).all())
 
 
-def test_one_plan_on_two_streams_at_once(oracle):
+@pytest.mark.parametrize("tile_log2", TILES)
+def test_one_plan_on_two_streams_at_once(oracle, tile_log2):
     """A plan is immutable: calls on ONE plan may overlap in time as long as their outputs differ.
     Two streams pack the same shard into two buffers and verify them concurrently, several times
     over (once with a corrupted chunk each); every result equals the oracle's."""
     shard = wl.param_shard("s", [1300000, 70001, 333, 250000], 1 << 18, 41, DEV, tiny_recipe=True)
-    plan = ff.plan_for_shard(shard)
+    plan = ff.plan_for_shard(shard, tile_log2=tile_log2)
     want_buf, want_crcs = oracle.pack(_host_segments(shard)[0], shard.chunk_bytes, threads=8)
     outs = [ff.alloc_outputs(plan, DEV) for _ in range(2)]
     streams = [torch.cuda.Stream() for _ in range(2)]
@@ -417,11 +429,12 @@ def test_one_plan_on_two_streams_at_once(oracle):
         assert int(dn.item()) == 1 and torch.nonzero(dbad).flatten().tolist() == [5 + k]
 
 
-def test_one_plan_two_host_threads(oracle):
+@pytest.mark.parametrize("tile_log2", TILES)
+def test_one_plan_two_host_threads(oracle, tile_log2):
     """The same from two host threads, each with its own stream and outputs, sharing the plan."""
     import threading
     shard = wl.param_shard("t", [900000, 12345, 400001], 1 << 17, 43, DEV, tiny_recipe=True)
-    plan = ff.plan_for_shard(shard)
+    plan = ff.plan_for_shard(shard, tile_log2=tile_log2)
     want_buf, want_crcs = oracle.pack(_host_segments(shard)[0], shard.chunk_bytes, threads=8)
     outs = [ff.alloc_outputs(plan, DEV) for _ in range(2)]
     streams = [torch.cuda.Stream() for _ in range(2)]
@@ -782,22 +795,22 @@ def test_fused_adam_random_cases(oracle, seed):
                              loss_scale=1024.0 if seed % 2 else 1.0)
 
 
-@pytest.mark.parametrize("seed", list(range(8)))
+@pytest.mark.parametrize("seed", list(range(14)))
 def test_pack_restore_random_layouts_and_tiles(oracle, seed):
     rng = np.random.default_rng(3000 + seed)
     mu = float(rng.uniform(4.0, 10.0))
     lay = wl.fragmented_layout(seed=3000 + seed, n_tensors=int(rng.integers(20, 800)), mu=mu,
                                sigma=float(rng.uniform(0.5, 2.5)), max_numel=1 << 17)
     chunk = int(rng.choice([1024, 8192, 1 << 15, 1 << 16, 1 << 19]))
-    tile_log2 = int(rng.choice([0, 0, 10, 12, 14, 16]))
+    tile_log2 = int(rng.choice([0, 0, 10, 12, 14, 16])) if seed < 8 else 15
     shard = wl.fragmented_shard(lay, chunk, seed=seed, device=DEV)
     state = _pack_and_compare(shard, oracle, tile_log2)
     _restore_and_compare(shard, *state[:6])
 
 
 def test_fused_adam_with_large_raw_segments(oracle):
-    # RAW segments long enough that the RAW kernel's XCD-aware order permutes complete rounds of
-    # tiles (8 MiB each), between and around parameter groups
+    # RAW segments long enough that the XCD-aware order permutes complete rounds of workgroups at RAW
+    # tiles, between and around parameter groups
     g = torch.Generator(device=DEV)
     g.manual_seed(31)
     raw1 = torch.randn(5 * (1 << 20) + 3, device=DEV, generator=g)                     # 20 MiB + 12 B
@@ -813,13 +826,15 @@ _TUNING = [ff.FF_PLAN_XCD_ORDER(1), ff.FF_PLAN_XCD_ORDER(2), ff.FF_PLAN_XCD_ORDE
            ff.FF_PLAN_CACHE_HINT(1) | ff.FF_PLAN_XCD_ORDER(1), ff.FF_PLAN_CACHE_HINT(2)]
 
 
+@pytest.mark.parametrize("tile_log2", TILES)
 @pytest.mark.parametrize("flags", _TUNING)
-def test_plan_tuning_flags_pack_restore(oracle, flags):
-    # 6 MiB in 32 KiB tiles: runs of 1, 2 and 4 workgroups per XCD permute several complete rounds
+def test_plan_tuning_flags_pack_restore(oracle, flags, tile_log2):
+    # 6 MiB in 32 KiB tiles (or 8 KiB blocks, 64 KiB a workgroup): runs of 1, 2 and 4 workgroups per XCD
+    # permute several complete rounds
     lay = wl.fragmented_layout(seed=77, n_tensors=120, mu=9.5, sigma=1.5, max_numel=1 << 18)
     shard = wl.fragmented_shard(lay, 1 << 18, seed=flags, device=DEV)
     assert sum(n for _, n in shard.spans) > 3 << 20
-    state = _pack_and_compare(shard, oracle, flags=flags)
+    state = _pack_and_compare(shard, oracle, tile_log2, flags)
     _restore_and_compare(shard, *state[:6])
     plan, chunks, crcs, bad, n_bad = state[:5]
     ff.ff_restore(plan, chunks, crcs, bad, n_bad, ff.FF_RESTORE_VERIFY_ONLY)
@@ -1063,7 +1078,8 @@ def _segments_as_stream(shard):
     return np.concatenate(_host_segments(shard)[0])
 
 
-@pytest.mark.parametrize("chunk,tile_log2", [(1024, 0), (1 << 14, 12), (1 << 16, 0), (1 << 20, 0)])
+@pytest.mark.parametrize("chunk,tile_log2", [(1024, 0), (1 << 14, 12), (1 << 16, 0), (1 << 20, 0),
+                                             (1 << 16, 15), (1 << 20, 15), (1 << 18, 17)])
 def test_restore_chunks_matches_oracle(oracle, chunk, tile_log2):
     numels = [int(x) for x in np.random.default_rng(chunk + 1).integers(1, 60000, size=30)]
     shard = wl.param_shard("sel", numels, chunk, 31, DEV, tiny_recipe=True)
@@ -1137,6 +1153,43 @@ def test_restore_chunks_long_list(oracle, flags):
         want_n = oracle.restore_chunks(host, chunk, dirty.cpu().numpy(), want_crcs, ids, want_bad,
                                        skip_bad=flags == ff.FF_RESTORE_SKIP_BAD)
     assert want_n == len(flipped) == int(n_bad.item())
+    assert np.array_equal(_u32(bad), want_bad)
+    assert np.array_equal(_segments_as_stream(shard), np.concatenate(host))
+
+
+@pytest.mark.parametrize("side", [False, True])
+@pytest.mark.parametrize("flags", [0, ff.FF_RESTORE_SKIP_BAD, ff.FF_RESTORE_VERIFY_ONLY])
+def test_restore_chunks_more_than_go_in_blocks(oracle, flags, side):
+    """Lists of more than 96 MiB are restored on the plan's own tiles, here 32 KiB: 100 chunks of
+    1 MiB of ragged tensors, and of tensors that start anywhere in a line, some of them corrupt."""
+    chunk = 1 << 20
+    lay = wl.fragmented_layout(seed=14, n_tensors=900, mu=10.0, sigma=1.2, max_numel=1 << 20)
+    lay += [(int(x), 2, 2 * (i % 8)) for i, x in enumerate(np.random.default_rng(14).integers(1 << 17, 1 << 18, 160))]
+    shard = wl.fragmented_shard(lay, chunk, seed=14, device=DEV)
+    plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle, 15)
+    n = plan.num_chunks
+    assert n >= 130
+    ids = sorted({int(x) for x in np.random.default_rng(9).choice(n, size=100, replace=False)})
+    flipped = [ids[0], ids[33], ids[98]]
+    for k, j in enumerate(flipped):
+        chunks[j * chunk + 32768 * (3 + 9 * k) + 17 * k] ^= 0x20
+    _poison_segments(shard)
+    bad.fill_(7)
+    n_bad.fill_(99)
+    torch.cuda.synchronize()
+    ff.ff_restore_chunks(plan, chunks, crcs, ids, bad, n_bad, flags=flags,
+                         stream=torch.cuda.Stream() if side else None)
+    torch.cuda.synchronize()
+    host = [np.full(h.size, 0xA5, dtype=np.uint8) for h in _host_segments(shard)[0]]
+    want_bad = np.full(n, 7, dtype=np.uint32)
+    want_bad[ids] = 0
+    want_bad[flipped] = 1
+    if flags != ff.FF_RESTORE_VERIFY_ONLY:
+        got = np.full(n, 7, dtype=np.uint32)
+        assert oracle.restore_chunks(host, chunk, chunks.cpu().numpy(), want_crcs, ids, got,
+                                     skip_bad=flags == ff.FF_RESTORE_SKIP_BAD) == len(flipped)
+        assert np.array_equal(got, want_bad)
+    assert int(n_bad.item()) == len(flipped)
     assert np.array_equal(_u32(bad), want_bad)
     assert np.array_equal(_segments_as_stream(shard), np.concatenate(host))
 
@@ -1218,10 +1271,14 @@ def test_restore_checked_refuses_another_layout(oracle):
     assert np.array_equal(got, want_buf[:got.size])
 
 
-def test_full_restore_skip_bad_on_ragged_layout(oracle):
-    lay = wl.fragmented_layout(seed=4, n_tensors=1500, mu=6.0, sigma=2.0, max_numel=1 << 16)
-    shard = wl.fragmented_shard(lay, 1 << 14, seed=4, device=DEV)
-    plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle)
+# The last two on 32 KiB tiles: ragged tensors (most tiles hold boundaries), and tensors of several tiles that
+# start anywhere in a line.
+@pytest.mark.parametrize("n,mu,chunk,tile_log2", [(1500, 6.0, 1 << 14, 0), (1500, 7.0, 1 << 16, 15),
+                                                  (400, 10.5, 1 << 17, 15)])
+def test_full_restore_skip_bad_on_ragged_layout(oracle, n, mu, chunk, tile_log2):
+    lay = wl.fragmented_layout(seed=4, n_tensors=n, mu=mu, sigma=2.0 if mu < 10 else 0.5, max_numel=1 << 16)
+    shard = wl.fragmented_shard(lay, chunk, seed=4, device=DEV)
+    plan, chunks, crcs, bad, n_bad, want_buf, want_crcs = _pack_and_compare(shard, oracle, tile_log2)
     n, C = plan.num_chunks, shard.chunk_bytes
     hits = wl.corrupt_chunks(n, C, seed=4, fraction=0.05)
     dirty = chunks.clone()
@@ -1244,16 +1301,19 @@ def test_full_restore_skip_bad_on_ragged_layout(oracle):
 
 # ---- snapshot into pinned host memory ----------------------------------------------------------------
 
+@pytest.mark.parametrize("tile_log2,default_stream", [(0, False), (0, True), (15, False)])
 @pytest.mark.parametrize("slice_chunks", [1, 5, 1000])
-def test_pack_to_host_equals_pack(oracle, slice_chunks):
+def test_pack_to_host_equals_pack(oracle, slice_chunks, tile_log2, default_stream):
     numels = [int(x) for x in np.random.default_rng(3).integers(1, 90000, size=40)]
     shard = wl.param_shard("h", numels, 1 << 16, 17, DEV, tiny_recipe=True)
-    plan = ff.plan_for_shard(shard)
+    plan = ff.plan_for_shard(shard, tile_log2=tile_log2)
     chunks, crcs, bad, n_bad = ff.alloc_outputs(plan, DEV)
     chunks.fill_(0xA5)
     h_chunks = torch.empty(plan.buffer_bytes, dtype=torch.uint8, pin_memory=True).fill_(0x5A)
     h_crcs = torch.empty(plan.num_chunks, dtype=torch.int32, pin_memory=True).fill_(-1)
     s_pack, s_copy = torch.cuda.Stream(), torch.cuda.Stream()
+    if default_stream:
+        s_pack = torch.cuda.default_stream()
     s_pack.wait_stream(torch.cuda.current_stream())
     ff.ff_pack_to_host(plan, chunks, crcs, h_chunks, h_crcs, slice_chunks, s_pack, s_copy)
     s_copy.synchronize()

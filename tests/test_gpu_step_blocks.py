@@ -1,6 +1,7 @@
-"""The optimizer step's sub-blocks of 1024 elements (8 KiB of a RAW segment) at the sizes where they
-can go wrong: around a lane's slot, a row, a sub-block and a block, with chunk boundaries that cut
-blocks anywhere, and on tensors that start off every alignment."""
+"""The optimizer step's sub-blocks of 512 elements (8 KiB of a RAW segment) at the sizes where they
+can go wrong: around a lane's slot, a row, a sub-block, a workgroup's eight of them (from where on an
+in-place step stores through LDS) and a block, with chunk boundaries that cut blocks anywhere, and on
+tensors that start off every alignment."""
 import pytest
 import torch
 
@@ -10,8 +11,8 @@ from test_gpu_parity import DEV, HP, _adam_and_compare, _chained_and_compare
 
 pytestmark = pytest.mark.gpu
 
-EDGES = [1, 2, 3, 4, 5, 7, 8, 9, 255, 256, 257, 259, 1023, 1024, 1025, 1027, 8188, 8191, 8192, 8193,
-         8197, 16384 + 1022]
+EDGES = [1, 2, 3, 4, 5, 7, 8, 9, 255, 256, 257, 259, 511, 512, 513, 1023, 1024, 1025, 1027, 3583, 3584, 3585,
+         4095, 4096, 4097, 8188, 8191, 8192, 8193, 8197, 16384 + 1022]
 
 
 def _raw(numels, dtype, seed):
