@@ -396,8 +396,11 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, nullptr));
         return FF_OK;
     }
-    // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan (28 chunks
-    // of 4 MiB: 48.5-49.6 us in blocks, 47.3 on the plan's tiles; one chunk of 512 KiB 11 against 19),
+    // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan (in blocks
+    // against the plan's 32 KiB tiles, us, tensors on / off the lines: 1 chunk of 4 MiB 10.4 / 10.9 against 11.2 /
+    // 14.6, 8 15.2 / 15.6 against 17.6 / 19.2, 16 26.3 / 27.2 against 29.6 / 32.5, 24 36.5 / 37.4 against 40.8 /
+    // 43.5; 26, with no warm loads above 96 MiB, 45.3 / 47.2 against 44.6 / 49.5, 40 66.1 / 69.5 against 62.5 /
+    // 67.0; verified only, 1-16 chunks 0-7 % behind, 20-48 1-10 % ahead),
     // and a read-only pass over no more than a medium-sized buffer; over more it is faster on 64 KiB tiles
     // (400 MB: 70 against 76 us).
     const uint64_t bytes = list ? list->n * L.chunk_bytes : L.buffer_bytes;

@@ -24,9 +24,11 @@
 // element instead of 28 and loses more by the two workgroups per compute unit that the image leaves
 // room for than it gains: it stores from registers, stream by stream.  One process, same tensors,
 // rows handed through LDS by workgroups of 8 / rows stored from registers / as now, ms:
-//   7B shard, 842 million elements      in place 6.70 / 6.86 / 6.60   chained 4.57 / 4.59 / 4.52
-//   30 odd-sized parameters, 354 million         3.34 / 3.05 / 2.78           2.15 / 2.07 / 2.02
-//   64 parameters, 2.1 million                  0.032 / 0.028 / 0.029        0.031 / 0.030 / 0.023
+//   7B shard, 842 million elements      in place 6.71 / 6.86 / 6.63   chained 4.62 / 4.59 / 4.54
+//   30 odd-sized parameters, 354 million         3.34 / 3.05 / 2.77           2.22 / 2.07 / 2.07
+//   64 parameters, 2.1 million                  0.033 / 0.028 / 0.026        0.031 / 0.030 / 0.023
+// On the 7B shard that is 1-2 %, whatever the values (zeros, denormals, NaNs), and is seen on the same
+// tensors only: where they lie moves either kernel between 5.7 and 6.7 ms from process to process.
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
@@ -596,9 +598,9 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
 // value in the kernel arguments: the step keeps no per-call table in device memory, so calls on
 // one plan may overlap and a captured launch carries its own pointers.
 //
-// N: room for so many.  A launch whose arguments hold 3 KiB of pointers costs the host half a microsecond more
-// than one of 512 bytes, and holds up the launches behind it (host side of the tiny shard's step 26.7
-// against 19.1 us), so few groups take the small form.
+// N: room for so many.  Arguments of 512 bytes instead of 3 KiB save the host 0.2-0.3 us a call (1 / 8 / 64
+// groups 7.4 / 7.9 / 11.0 against 7.7 / 8.1 / 11.2), which shows where a queue of steps is bound by that: 64
+// groups of 100 elements 10.7 against 11.2 us a step, fewer or larger groups the same within 1 %.
 template <bool F16, bool CHAINED, bool BC2, uint32_t N>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void fused_kernel(
     const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
