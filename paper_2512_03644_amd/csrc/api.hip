@@ -44,9 +44,10 @@ struct ff_plan {
     uint32_t affine = 0;  // preset/complement term of a chunk_bytes-long CRC
     // fused optimizer step (only when every parameter group is complete)
     FusedWork work;
-    // XCD-aware order (kernels.hpp) of the step's workgroups of 4096 elements, in place and chained;
-    // runs of 4 / 16 / 64 on the 7B shard 6.69 / 6.62 / 6.60 and 4.66 / 4.52 / 4.57 ms, on 360 million
-    // odd-sized elements 2.81 / 2.80 / 2.78 and 2.05 / 2.02 / 2.06 ms
+    // XCD-aware order (kernels.hpp) of the step's workgroups of 4096 elements, in place and chained; runs of
+    // 8 / 16 / 32 / 64 / 128 in place: 24 parameters of 1 million elements 205 / 200 / 194 / 195 / 195 us, 60 of 3
+    // million 1453 / 1461 / 1430 / 1416 / 1420, 7B in a better placement 5525 / 5716 / 5487 / 5483 / 5489; of
+    // 4 / 16 / 64 chained: 7B 4.66 / 4.52 / 4.57 ms, 360 million odd-sized elements 2.05 / 2.02 / 2.06 ms
     uint32_t fused_xcd_group = 64, chained_xcd_group = 16;
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
@@ -178,6 +179,8 @@ int upload_tables(ff_plan* p)
         while (lt.size() <= work[i].grad_index / kGradsPerLaunch) lt.push_back(i);
     while (lt.size() <= (L.params.size() + kGradsPerLaunch - 1) / kGradsPerLaunch)
         lt.push_back(n_param_tiles);
+    for (size_t k = 0; k + 1 < lt.size(); k++)
+        p->work.launch_off_lines.push_back(mostly_off_lines(work.data() + lt[k], lt[k + 1] - lt[k]) ? 1 : 0);
     p->fused_tabs = reinterpret_cast<const uint32_t*>(d + o_ftabs);
     return FF_OK;
 }

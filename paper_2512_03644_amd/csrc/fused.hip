@@ -16,22 +16,30 @@
 // an atomic; XOR is commutative, so the result does not depend on the order in which tiles finish.  A
 // prepare kernel sets crcs[] to the preset/complement term and writes the zero tail of the last chunk.
 //
-// What bounds it: the memory system's handling of 4 load and 8 (chained: 5) store streams at once, not
-// arithmetic or latency (one or two workgroups per compute unit, any order of the stores and any cache
-// policy of the accesses measured the same).  What helps is fewer, longer runs: the in-place step
-// lays the new master, m and v of a workgroup out in LDS and every wavefront then stores 12 KiB
-// of consecutive rows, on the destination's own 128-byte lines.  The chained step writes 16 bytes per
-// element instead of 28 and loses more by the two workgroups per compute unit that the image leaves
-// room for than it gains: it stores from registers, stream by stream.  One process, same tensors,
-// rows handed through LDS by workgroups of 8 / rows stored from registers / as now, ms:
-//   7B shard, 842 million elements      in place 6.71 / 6.86 / 6.63   chained 4.62 / 4.59 / 4.54
-//   30 odd-sized parameters, 354 million         3.34 / 3.05 / 2.77           2.22 / 2.07 / 2.07
-//   64 parameters, 2.1 million                  0.033 / 0.028 / 0.026        0.031 / 0.030 / 0.023
-// On the 7B shard that is 1-2 %, whatever the values (zeros, denormals, NaNs), and is seen on the same
-// tensors only: where they lie moves either kernel between 5.7 and 6.7 ms from process to process.
+// What bounds it: the memory system's handling of 4 load and 8 (chained: 5) store streams at once, and how
+// well it does depends on where the tensors lie: one 7B shard in place takes 5.5 or 6.5 ms from one
+// allocation to the next, with this kernel and any other tried.  Results are stored from registers, stream by
+// stream, by two workgroups on a compute unit (three where they hold the launch at once).  Where most
+// elements have an fp32 stream off its 128-byte lines, longer runs on the lines are worth a detour: the new
+// master, m and v of a workgroup are laid out in LDS, in the place of the tables when the folds are done
+// with them, and every wavefront stores 12 KiB of consecutive rows.  (An image of its own next to the
+// tables, used by every launch, is what the third column has: 3-6 % faster on aligned lists of 60-250
+// million elements in the worse placements, but 5-12 % slower from 400 million on or in the better
+// placements, 10 % slower in the first passes after a pause, 10-20 % on small launches.)  One process, same
+// tensors, ms: rows handed through LDS by workgroups of 8 / image for all / as now
+//   7B shard, 842 million elements, aligned: a worse placement   6.60 / 6.53 / 6.50   a better one 5.65 / 6.15 / 5.47
+//     the first pass after 0.3 s without work                    6.70 / 7.30 / 6.65                6.15 / 7.15 / 6.12
+//   128 parameters of 4 million, aligned: worse, better          4.19 / 4.16 / 4.28                3.62 / 3.90 / 3.55
+//   64 parameters of 4 million, aligned                          2.04 / 2.03 / 2.10                1.99 / 1.95 / 1.89
+//   64 parameters of 4194381, off the lines                      2.57 / 2.17 / 2.07
+//   30 odd-sized parameters, 354 million                         3.31 / 2.74 / 2.70
+//   2000 ragged groups in fp16, 190 MB                           1.25 / 1.07 / 1.03
+//   64 parameters, 2.1 million                                   0.032 / 0.026 / 0.023
+// Chained: 7B 4.60 / 4.53 / 4.53, odd-sized 2.15 / 2.02 / 2.02, 64 parameters 0.031 / 0.023 / 0.023.
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
+#include <stddef.h>
 
 #include "fold.h"
 
@@ -104,19 +112,35 @@ typedef uint16_t u16_alias __attribute__((may_alias));
 typedef uint32_t u32_alias __attribute__((may_alias));
 typedef u32x4 u32x4_alias __attribute__((may_alias));
 
-// The in-place step's image: the new master, m and v of the workgroup's sub-blocks as they lie in
-// their streams; behind them room for the last dword that a shifted read touches.
-constexpr int kImgF = kWavesPerBlock * kSubElems * 4;  // bytes of one fp32 stream of a workgroup
-constexpr int kImgBytes = 3 * kImgF + 16;
-
 struct Lds {
+    uint32_t sum[kWavesPerBlock][4];  // per run (at its first wavefront's place): XOR of its registers
+    uint32_t arrived[kWavesPerBlock]; // wavefronts of the run that have added theirs
     uint32_t tab16[1024];  // multiply by x^8192  (1 KiB rows)
     uint32_t tab8[1024];   // multiply by x^4096  (512 B rows)
     uint32_t tab_d[1024];  // multiply by x^32    (neighbouring dwords)
     uint32_t tab_s[3][1024];  // multiply by x^64, x^128, x^256 (neighbouring slots and pairs of them)
-    uint32_t sum[kWavesPerBlock][4];  // per run (at its first wavefront's place): XOR of its registers
-    uint32_t arrived[kWavesPerBlock]; // wavefronts of the run that have added theirs
 };
+
+// The in-place step's image: the new master, m and v of the workgroup's sub-blocks as they lie in
+// their streams; behind them room for the last dword that a shifted read touches.  It takes the place of
+// the tables, when they have been used.
+constexpr int kImgF = kWavesPerBlock * kSubElems * 4;  // bytes of one fp32 stream of a workgroup
+constexpr int kImgBytes = 3 * kImgF + 16;
+template <bool IMAGE>
+union __attribute__((aligned(16))) Shared {
+    Lds lds;
+    uint8_t bytes[IMAGE ? offsetof(Lds, tab16) + kImgBytes : sizeof(Lds)];
+};
+static_assert(offsetof(Lds, tab16) % 16 == 0, "the image's slots");
+
+// Workgroups of an in-place step on a compute unit: three if they hold the launch at once, else two, made so
+// by LDS that nobody uses.  Stored from registers, three against two, us: 30 parameters of 100,000 elements
+// (750 workgroups) 30.9 / 32.6, 40 of 340,000 (3320) 116.4 / 114.4, 30 odd-sized ones (86,000) 3003 / 2921; 7B
+// (205,000) 6640-6700 / 6470-6560 in worse placements, 5520-5540 / 5470-5480 in better ones.  Through the image 7B
+// 6650-6690 / 6400-6490, 5560 / 5550, odd-sized 2890 / 2700.
+constexpr unsigned kComputeUnits = 256, kSpareLds = 8192;
+static_assert(3 * sizeof(Shared<true>) <= 160 * 1024 && 3 * (sizeof(Shared<true>) + kSpareLds) > 160 * 1024 &&
+              2 * (sizeof(Shared<true>) + kSpareLds) <= 160 * 1024, "two or three");
 
 // Tile registers come out of the folds without the factor x^32 that a CRC register carries.
 constexpr uint32_t kX16 = gf2_xpow(16);
@@ -128,8 +152,6 @@ __device__ __forceinline__ void add_head_piece(uint32_t* __restrict__ crcs, cons
 {
     atomicXor(&crcs[t.chunk[piece]], gf2_mul_const<kX16>(low_half));
 }
-
-static_assert(2 * (sizeof(Lds) + kImgBytes) <= 160 * 1024, "two workgroups on a compute unit");
 
 // The byte tables on their way to LDS: fetched first thing, stored (put) behind the loads of the
 // wavefront's own data, so that the two latencies overlap.  put() is a barrier of the workgroup; every
@@ -447,8 +469,8 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
             });
         });
     }
-    // Stores from registers, stream by stream; but the fp32 streams of an in-place step whose whole
-    // workgroup is at this tile go by way of its image in LDS.
+    // Stores from registers, stream by stream; but the fp32 streams of a workgroup that is all at this tile
+    // may go by way of its image in LDS (C.image), which waits for the folds to be done with the tables.
     auto store_w = [&](uint8_t* base) {
         static_for<kRows>([&](auto r) {
             if (mine(r)) store8_unaligned<true>(base + (lane8 + 2 * kRowElems * r), q[r].g);
@@ -466,19 +488,8 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     __builtin_amdgcn_sched_barrier(0);
     store_w(tw);
     store_w(sw);
-    if (!CHAINED && ((info >> 8) & 15u) == kWavesPerBlock) {
-        uint8_t* const im = img + wave * (kSubElems * 4);  // this wavefront's share of every stream
-        static_for<kRows>([&](auto r) {
-            *reinterpret_cast<u32x4_alias*>(im + (lane16 + 4 * kRowElems * r)) = q[r].p;
-            *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
-            *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
-        });
-        workgroup_barrier();  // every wavefront is at this tile, in this function's instantiation or the other
-        constexpr int kAll = kWavesPerBlock * int(kSubElems);
-        const int from = at - wave * int(kSubElems);
-        const int end = static_cast<int>(t.n) - from;
-        store_image(t, img, from, from < 0 ? -from : 0, end < kAll ? end : kAll, chunks, wave, lane);
-    } else {
+    const bool by_image = !CHAINED && C.image && ((info >> 8) & 15u) == kWavesPerBlock;
+    if (!by_image) {
         if constexpr (!CHAINED) {
             store_f(tp, &RowIn::p, ep);
             store_f(tm, &RowIn::m, em);
@@ -518,6 +529,21 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     const uint32_t v[4] = {join_columns(rw, lds.tab_d), join_columns(rp, lds.tab_d),
                            join_columns(rm, lds.tab_d), join_columns(rv, lds.tab_d)};
     deliver(lds, t, info, finish_streams(v, lds, lane_c, lane), stream_of_lane(lane), crcs, lane);
+
+    if (by_image) {
+        workgroup_barrier();  // every wavefront is at this tile, in this function's instantiation or the other
+        uint8_t* const im = img + wave * (kSubElems * 4);  // this wavefront's share of every stream
+        static_for<kRows>([&](auto r) {
+            *reinterpret_cast<u32x4_alias*>(im + (lane16 + 4 * kRowElems * r)) = q[r].p;
+            *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
+            *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
+        });
+        workgroup_barrier();
+        constexpr int kAll = kWavesPerBlock * int(kSubElems);
+        const int from = at - wave * int(kSubElems);
+        const int end = static_cast<int>(t.n) - from;
+        store_image(t, img, from, from < 0 ? -from : 0, end < kAll ? end : kAll, chunks, wave, lane);
+    }
 
     if constexpr (F16) {
         if (C.n_nonfinite && __any(nonfinite != 0)) {
@@ -607,8 +633,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const uint32_t* __restrict__ tabs, uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs,
     FusedConsts C, GradPtrsOf<N> grads)
 {
-    __shared__ Lds lds;
-    __shared__ __attribute__((aligned(16))) uint8_t img[CHAINED ? 16 : kImgBytes];
+    __shared__ Shared<!CHAINED> shared;
+    Lds& lds = shared.lds;
+    uint8_t* const img = shared.bytes + offsetof(Lds, tab16);
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
@@ -869,7 +896,7 @@ constexpr uint32_t kFewGrads = 64;
 template <uint32_t N>
 void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTile* tiles,
                  const void* const* grads, uint32_t p0, uint32_t n_params, const uint32_t* tabs,
-                 uint8_t* chunks, uint32_t* crcs, const FusedConsts& consts, hipStream_t stream)
+                 uint8_t* chunks, uint32_t* crcs, const FusedConsts& consts, bool off_lines, hipStream_t stream)
 {
     using Kernel = decltype(&fused_kernel<false, false, false, N>);
     static const Kernel kernels[8] = {
@@ -879,11 +906,19 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
         fused_kernel<true, true, false, N>,   fused_kernel<true, true, true, N>};
     const bool bc2 = consts.adam.bc2s != 1.0f;
     const Kernel kernel = kernels[(f16 ? 4 : 0) + (consts.prev ? 2 : 0) + (bc2 ? 1 : 0)];
+    // The image only pays in launches of several rounds (aligned, in the one round that there is: 64 parameters
+    // of 5000 elements 12.0 us from registers, 13.9 through the image; 32 of 32,768 15.6 and 17.2; 64 of 30,011
+    // 23.5 and 23.4) and off the lines (30 odd-sized parameters 2921 from registers, 2700 through it; aligned, 64 of
+    // 100,000 58 and 64, 13 of 5 million 514 and 517).
+    const unsigned groups = n_waves / kWavesPerGroup;
+    const bool at_once = groups <= 3 * kComputeUnits;
+    FusedConsts c = consts;
+    c.image = !consts.prev && off_lines && !at_once;
     GradPtrsOf<N> g;
     for (uint32_t i = 0; i < N; i++)
         g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
-    hipLaunchKernelGGL(kernel, dim3(n_waves / kWavesPerGroup), dim3(kThreads), 0, stream, waves, tiles, p0,
-                       tabs, chunks, crcs, consts, g);
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), consts.prev || at_once ? 0 : kSpareLds, stream, waves,
+                       tiles, p0, tabs, chunks, crcs, c, g);
 }
 
 }  // namespace
@@ -928,7 +963,8 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
             const uint32_t w0 = work.launch_wave[k], w1 = work.launch_wave[k + 1];
             if (w1 == w0) continue;
             const auto launch = n_params - p0 <= kFewGrads ? launch_step<kFewGrads> : launch_step<kGradsPerLaunch>;
-            launch(f16, work.waves + w0, w1 - w0, work.tiles, grads, p0, n_params, tabs, c, crcs, consts, stream);
+            launch(f16, work.waves + w0, w1 - w0, work.tiles, grads, p0, n_params, tabs, c, crcs, consts,
+                   work.launch_off_lines[k] != 0, stream);
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -21,6 +21,7 @@ struct FusedConsts {
     // Chained step: master, m and v are read from this snapshot buffer (at the segments' stream
     // offsets) instead of their tensors, and those tensors are not written.  Null: in-place step.
     const uint8_t* prev = nullptr;
+    uint32_t image = 0;  // in-place step: whole workgroups store their fp32 streams through LDS
 };
 
 // Device table of the fused kernels (kFusedTabWords entries): byte tables of multiplication by
@@ -47,6 +48,7 @@ struct FusedWork {
     const WorkWave* waves = nullptr;
     std::vector<uint32_t> launch_tile;     // parameter tiles only
     std::vector<uint32_t> launch_wave;
+    std::vector<uint8_t> launch_off_lines; // most elements have an fp32 stream off the 128-byte lines
 };
 
 // Enqueues prepare (crcs = affine, zero tail, counter = 0) and the tile kernels.

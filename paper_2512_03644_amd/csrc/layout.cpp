@@ -288,4 +288,18 @@ bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
     return true;
 }
 
+bool mostly_off_lines(const WorkTile* tiles, uint64_t n)
+{
+    uint64_t off = 0, all = 0;
+    for (uint64_t i = 0; i < n; i++) {
+        const WorkTile& t = tiles[i];
+        bool line = true;
+        for (int x = 1; x < 4; x++)  // rows begin at multiples of 512 bytes from the parameter's first element
+            line = line && (t.ptr[x] - 4 * t.e0) % 128 == 0 && (t.soff[x] - 4 * t.e0) % 128 == 0;
+        all += t.n;
+        off += line ? 0 : t.n;
+    }
+    return 2 * off > all;
+}
+
 }  // namespace ffsnap

@@ -96,6 +96,10 @@ bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
                       uint32_t groups_per_launch, std::vector<WorkWave>& out,
                       std::vector<uint32_t>& begin, uint64_t max_entries = kMaxWorkEntries);
 
+// Do most elements of these parameter tiles have an fp32 stream, in place or in the snapshot, whose rows lie
+// off its 128-byte lines?  (A buffer that is itself on a line is assumed.)
+bool mostly_off_lines(const WorkTile* tiles, uint64_t n);
+
 // Returns FF_OK or a negative ff_status; `out` is valid only on FF_OK.
 // tile_log2: 0 = default tile size, else log2 of the tile size in bytes (clamped to
 // [10, log2(chunk_bytes)]).

@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "fused.hpp"
 #include "kernels.hpp"
 #include "layout.hpp"
 
@@ -17,6 +18,8 @@ struct Launch {
     std::string kernel;
     TileTables t;
     hipStream_t stream;
+    size_t spare_lds;
+    uint32_t groups, image;
 };
 static std::vector<Launch> g_log;
 // (filled by the objects' constructors, before this file's own)
@@ -31,9 +34,10 @@ void __hipRegisterFunction(void**, const void* f, char* name, const char*, unsig
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, hipStream_t q) { g_config = {g, b, s, q}; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* q) { *g = g_config.g; *b = g_config.b; *s = g_config.s; *q = g_config.q; return hipSuccess; }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t q)
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t lds, hipStream_t q)
 {
-    Launch l{names()[f], TileTables(), q};
+    Launch l{names()[f], TileTables(), q, lds, grid.x, 0};
+    if (l.kernel.find("fused_kernel") != std::string::npos) l.image = static_cast<FusedConsts*>(args[6])->image;
     if (l.kernel.find("block_kernel") != std::string::npos) l.t = *static_cast<TileTables*>(args[0]);
     if (l.kernel.find("tile_kernel") != std::string::npos) l.t = *static_cast<TileTables*>(args[5]);
     g_log.push_back(l);
@@ -208,8 +212,51 @@ static void blocks_by_size_and_layout()
     }
 }
 
+// The optimizer step: three workgroups on a compute unit for a launch of up to 768, else two; results through
+// an image in LDS for a longer launch that is mostly off the lines; neither for a chained step.
+static void step_by_size_and_alignment()
+{
+    struct { uint64_t n, numel, misaligned; bool off; } cases[] = {
+        {64, 32768, 0, false}, {96, 32768, 0, false}, {97, 32768, 0, false}, {400, 32768, 0, false},
+        {64, 32768, 4, true}, {97, 32768, 4, true}, {97, 32768, 64, true}, {97, 32769, 0, true}, {1000, 5, 4, true},
+    };
+    for (const auto& c : cases) {
+        std::vector<ff_segment> segs;
+        std::vector<const void*> grads(c.n, reinterpret_cast<void*>(1ull << 41));
+        uint64_t at = (1ull << 40) + c.misaligned;
+        for (uint32_t i = 0; i < c.n; i++)
+            for (uint32_t kind = FF_KIND_W16; kind <= FF_KIND_V; kind++) {
+                const bool w16 = kind == FF_KIND_W16;
+                segs.push_back({reinterpret_cast<void*>(at), (w16 ? 2 : 4) * c.numel, w16 ? FF_BF16 : FF_F32, kind, i, 0});
+                at += (4 * c.numel + 255) / 256 * 256;
+            }
+        ff_plan* plan = nullptr;
+        CHECK(ff_snapshot_plan(segs.data(), segs.size(), 1 << 20, 0, &plan) == FF_OK);
+        const ff_adam_hparams hp = {1e-3f, 0.9f, 0.95f, 1e-8f, 0.1f, 1};
+        alignas(16) static char chunks[16], prev_end[16];
+        uint32_t crcs[1];
+        for (const bool chained : {false, true}) {
+            g_log.clear();
+            const char* prev = prev_end + (1ull << 33);  // far away; never touched
+            CHECK((chained ? ff_adam_step_chained(plan, grads.data(), &hp, 1.0f, nullptr, prev, chunks, crcs, nullptr)
+                           : ff_adam_step_snapshot(plan, grads.data(), &hp, chunks, crcs, nullptr)) == FF_OK);
+            int launches = 0;
+            for (const Launch& l : g_log) {
+                if (!is(l, "fused_kernel")) continue;
+                launches++;
+                g_line = static_cast<int>(c.n);
+                CHECK((l.spare_lds != 0) == (!chained && l.groups > 768));
+                CHECK((l.image != 0) == (!chained && l.groups > 768 && c.off));
+            }
+            CHECK(launches == static_cast<int>((c.n + kGradsPerLaunch - 1) / kGradsPerLaunch));
+        }
+        ff_plan_destroy(plan);
+    }
+}
+
 int main()
 {
+    step_by_size_and_alignment();
     blocks_by_size_and_layout();
     only_the_default_stream_uses_the_tally();
     tally_where_it_pays();

@@ -1,6 +1,5 @@
 """The optimizer step's sub-blocks of 512 elements (8 KiB of a RAW segment) at the sizes where they
-can go wrong: around a lane's slot, a row, a sub-block, a workgroup's eight of them (from where on an
-in-place step stores through LDS) and a block, with chunk boundaries that cut blocks anywhere, and on
+can go wrong: around a lane's slot, a row, a sub-block, a workgroup's eight of them and a block, with chunk boundaries that cut blocks anywhere, and on
 tensors that start off every alignment."""
 import pytest
 import torch
@@ -28,6 +27,19 @@ def test_block_edges_in_place_and_chained(oracle, chunk):
     _adam_and_compare(oracle, EDGES, chunk, seed=chunk, hp=dict(HP, step=3), extra_raw=extra)
     _chained_and_compare(oracle, EDGES, chunk, seed=chunk + 1, steps=2, half=torch.float16,
                          loss_scale=1024.0, extra_raw=extra)
+
+
+@pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("chunk", [1 << 15, 1 << 17, 1 << 22])
+def test_results_through_the_image(oracle, chunk, half):
+    # a launch of more than 768 workgroups whose streams lie off the lines: whole workgroups store through LDS,
+    # at every edge and behind every cut
+    _adam_and_compare(oracle, EDGES + [3300001, 4096 * 3 + 512, 150001], chunk, seed=chunk + 3,
+                      hp=dict(HP, step=3), half=half, loss_scale=1024.0 if half == torch.float16 else 1.0)
+
+
+def test_results_of_a_long_launch_on_the_lines(oracle):
+    _adam_and_compare(oracle, [1 << 20] * 3 + [262144], 1 << 20, seed=31, hp=dict(HP, step=2))
 
 
 @pytest.mark.parametrize("chunk", [1024, 1 << 14, 1 << 20])
