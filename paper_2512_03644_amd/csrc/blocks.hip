@@ -2,12 +2,19 @@
 // tensors (launch_tiles in kernels.hip has the rule).
 //
 // One wavefront takes one block: 8 rows of 1 KiB, lane l of a row its 16 bytes ("slot") at 16 l.  All
-// 8 loads are up front, a further row is one Horner step of the block's CRC register through byte
-// tables in LDS, and the wavefronts of a workgroup that are at the same chunk sum their registers in
-// LDS before one of them delivers the sum with an atomic.  A block is a quarter of a default tile and
-// its chain of dependent steps is short: nothing is folded, the tables are fetched beside the data,
-// and the lane's constant covers the place in the run.  That is what a launch of a few
+// 8 loads are up front, the block's CRC register comes from the matrix cores (matrix_fold.h: a dword of
+// every lane at a time, weights in LDS), and the wavefronts of a workgroup that are at the same chunk
+// sum their registers in LDS before one of them delivers the sum with an atomic.  A block is a
+// quarter of a default tile and its chain of dependent steps is short: the weights are fetched beside
+// the data, and the lane's constant covers the place in the run.  That is what a launch of a few
 // thousand wavefronts or less is made of.
+//
+// What bounds a small call is that chain and the launch itself.  With Horner steps through byte tables in
+// place of the matrix product, 124 lookups a lane and block, the wavefronts of a compute unit queued at its
+// LDS, all at the same time: pack of 32 MB 18.9 us and 15.0 now (a copy of it 10.2-11.2), restore 18.9 and
+// 15.6, verify of 41 / 3.2 MB 16.6 / 9.6 and 12.6 / 7.3.  On 1 GB of 5 KiB tensors, where the lookups hid behind
+// the memory, both take 407 us, though the weights leave room for two workgroups on a compute unit and the
+// tables left it for three.
 //
 // A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the
 // plan's tally, which starts at zero, and whoever completes the word writes the chunk's result and
@@ -23,6 +30,7 @@
 #include "kernels.hpp"
 
 #include "fold.h"
+#include "matrix_fold.h"
 #include "tally.h"
 
 namespace ffsnap {
@@ -40,8 +48,7 @@ typedef uint16_t u16_alias __attribute__((may_alias));
 typedef u32x4 u32x4_alias __attribute__((may_alias));
 
 struct BlockLds {
-    uint32_t tab16[1024];  // multiply by x^8192 (1 KiB rows)
-    uint32_t tab_d[1024];  // multiply by x^32   (neighbouring dwords)
+    u32x4 weight[kRows * 4][kWaveSize];  // of every dword of a lane's slots
     uint32_t sum[kWaves];      // per run (at its first wavefront's place): XOR of its registers
     uint32_t arrived[kWaves];  // wavefronts of the run that have added theirs
 };
@@ -195,7 +202,7 @@ template <int MODE, int HINT, class Ready>
 __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, GatherLds* gather,
                                            uint8_t* __restrict__ chunks, const uint32_t tile,
                                            const bool folding, const int lane, Ready&& tables_ready,
-                                           uint32_t (&reg)[4])
+                                           f32x16& acc)
 {
     constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
     const uint64_t s = static_cast<uint64_t>(tile) * kBlockBytes;
@@ -204,6 +211,9 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
     u32x4 w[kRows];
     if (MODE != kPack)
         static_for<kRows>([&](auto r) { w[r] = load16_stream<kBufNT>(bp + (lane16 + 1024 * r)); });
+    auto fold = [&](auto r) {
+        static_for<4>([&](auto f) { matrix_add(acc, lds.weight[4 * r + f][lane], w[r][int(f)]); });
+    };
     const uint32_t entry = tile >> T.block_log2;  // of the plan's tables
     const uint32_t sub = tile - (entry << T.block_log2);
     const uint64_t tb = MODE == kVerify ? 0 : T.tile_base[entry];
@@ -214,12 +224,21 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
         if (MODE == kPack)
             static_for<kRows>([&](auto r) { w[r] = load16_unaligned<kSegNT>(tp + (lane16 + 1024 * r)); });
         tables_ready();
+        // Row by row, stored and folded as it arrives: the matrix cores are at work while later rows are on
+        // their way.  (Pack / restore of 32 MB with all stores in front of the fold 15.9 / 16.5 us, so
+        // 15.0 / 15.6.  In the blocks of several tensors below it is the other way round: restore of 5 KiB
+        // tensors, 1 GB, 407 us with the stores in front, 417 row by row.)
         static_for<kRows>([&](auto r) {
             if (MODE == kPack)
                 store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]);
             else
                 store16_unaligned<kSegNT>(tp + (lane16 + 1024 * r), w[r]);
+            if (!folding) return;
+            __builtin_amdgcn_sched_barrier(0);
+            fold(r);
+            __builtin_amdgcn_sched_barrier(0);
         });
+        return;
     } else {
         const uint32_t end = s >= T.payload ? 0u
                              : T.payload - s < uint64_t(kBlockBytes) ? static_cast<uint32_t>(T.payload - s)
@@ -294,11 +313,7 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
         if (MODE == kPack)
             static_for<kRows>([&](auto r) { store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]); });
     }
-    if (!folding) return;
-    static_for<kRows>([&](auto r) {
-        const uint32_t d[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
-        add_row<4, r == 0>(reg, lds.tab16, d);
-    });
+    if (folding) static_for<kRows>([&](auto r) { fold(r); });
 }
 
 template <int MODE, int HINT, bool LISTED>
@@ -309,10 +324,13 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     __shared__ GatherLds gather[MODE == kVerify ? 1 : kWaves];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const u32x4 tab = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + threadIdx.x);
+    constexpr int kEach = kRows * 4 * kWaveSize / kThreads;
+    u32x4 tab[kEach];
+    static_for<kEach>([&](auto i) {
+        tab[i] = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + i * kThreads + threadIdx.x);
+    });
     auto tables_ready = [&] {
-        static_assert(kThreads * 4 == 2048, "two tables");
-        *(reinterpret_cast<u32x4*>(lds.tab16) + threadIdx.x) = tab;  // tab16, tab_d
+        static_for<kEach>([&](auto i) { (&lds.weight[0][0])[i * kThreads + threadIdx.x] = tab[i]; });
         if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = 0;
         workgroup_barrier();
     };
@@ -338,17 +356,17 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     if (folding) {
         // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and the
         // run's own distance to the end of its chunk (times the x^32 that the register lacks)
-        lane_c = T.block_tab[2048 + (run - 1 - in_run) * kWaveSize + lane];
+        lane_c = T.block_tab[kRows * 4 * kWeightWords + (run - 1 - in_run) * kWaveSize + lane];
         shift = T.tile_shift[((tile & (T.tiles_per_chunk - 1)) | (run - 1)) >> T.block_log2];
     }
-    uint32_t reg[4];
+    f32x16 acc = {};
     if (active)
         block_rows<MODE, HINT>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
-                               tables_ready, reg);
+                               tables_ready, acc);
     else
         tables_ready();
     if (!active || !folding) return;
-    uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
+    uint32_t v = wave_xor(gf2_mul_half(matrix_halves(acc), lane_c));
     if (lane != 0) return;
     if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, v)) return;
     v = gf2_mul(v, shift);
@@ -359,17 +377,16 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         atomicXor(T.acc + chunk, v);
 }
 
-// (six wavefronts per SIMD are three workgroups per compute unit instead of two: restore of 5 KiB
-// tensors, 1 GB, 400 -> 381 us, ragged 425 -> 408)
+// (two workgroups on a compute unit: the weights and the scratch of blocks of several tensors leave room for no more)
 template <int MODE, int HINT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
 {
     block_body<MODE, HINT, false>(T, chunks, nullptr);
 }
 
 // The blocks of the chunks in `list`, which travels in the kernel arguments, instead of a range.
 template <int MODE, int HINT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void block_kernel_listed(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void block_kernel_listed(
     TileTables T, uint8_t* __restrict__ chunks, ChunkList list)
 {
     block_body<MODE, HINT, true>(T, chunks, &list);
@@ -393,19 +410,17 @@ void launch(const TileTables& t, uint8_t* chunks, unsigned grid, hipStream_t str
 
 void build_block_tab(uint32_t* tab)
 {
-    const uint64_t step[2] = {8192, 32};
-    for (int t = 0; t < 2; t++) {
-        const uint32_t u = gf2_xpow(step[t]);
-        for (int k = 0; k < 4; k++)
-            for (uint32_t b = 0; b < 256; b++) tab[t * 1024 + k * 256 + b] = gf2_mul(b << (8 * k), u);
-    }
-    // lane 63 of block 0 is the last slot; a slot earlier is 16 bytes further from the end
-    const uint32_t x_slot = gf2_xpow(8 * 16);
+    // a dword enters times x^(8 * bytes from its end to the end of the last row's slot of lane 31 or 63)
+    for (int r = 0; r < kRows; r++)
+        for (int f = 0; f < 4; f++) {
+            const uint32_t high = gf2_xpow(8ull * 1024 * (kRows - 1 - r) + 32 * (3 - f));
+            build_matrix_weights(tab + (4 * r + f) * kWeightWords, gf2_mul(high, gf2_xpow(8 * 512)), high);
+        }
     const uint32_t x_block = gf2_xpow(8ull * kBlockBytes);
-    uint32_t first = kOne;
-    for (int k = 0; k < kWaves; k++, first = gf2_mul(first, x_block)) {
-        uint32_t v = first;
-        for (int lane = kWaveSize; lane-- > 0; v = gf2_mul(v, x_slot)) tab[2048 + k * kWaveSize + lane] = v;
+    uint32_t* const lanes = tab + 4 * kRows * kWeightWords;
+    for (int lane = 0; lane < kWaveSize; lane++) {
+        uint32_t v = matrix_lane_factor(lane, 8 * 16);
+        for (int k = 0; k < kWaves; k++, v = gf2_mul(v, x_block)) lanes[k * kWaveSize + lane] = v;
     }
 }
 

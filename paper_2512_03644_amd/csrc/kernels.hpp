@@ -129,10 +129,9 @@ inline bool tiles_are_blocks(const TileTables& t)
     return t.tile_rows == kBlockBytes / 1024 && t.shift_stride == 1 && t.block_tab && !t.partial;
 }
 
-// Fills tab (host, kBlockTabWords entries): byte tables of multiplication by x^8192 and by x^32, then
-// for k = 0..7 and every lane x^(8 * bytes between the end of the lane's 16 bytes in a block's last
-// row and the end of that row, plus k blocks).
-constexpr int kBlockTabWords = 2048 + 8 * 64;
+// Fills tab (host, kBlockTabWords entries): the weights of the 32 dwords of a lane (matrix_fold.h), then
+// for k = 0..7 and every lane its factor for the place of its column in a row, plus k blocks.
+constexpr int kBlockTabWords = 32 * 4 * 64 + 8 * 64;
 void build_block_tab(uint32_t* tab);
 
 // out[j] = affine (crcs null: pack) or affine ^ crcs[j] (verify) for chunks [first, first + n), or

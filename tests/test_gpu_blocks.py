@@ -250,3 +250,24 @@ def test_verify_where_grouped_tiles_are_as_long_as_a_block(oracle, chunk, tile_l
     for stream in (None, torch.cuda.Stream()):
         bad, n_bad = _verify(plan, chunks, crcs, stream)
         assert np.array_equal(bad, want) and n_bad == 1
+
+
+@pytest.mark.parametrize("chunk", [1 << 13, 1 << 16])
+def test_every_weight_of_the_matrix_product(oracle, chunk):
+    # One bit per block: dword d of block d, bit (d / 4) mod 32 of it, so that every bit of every place in a
+    # lane's rows comes up in either half of the wavefront.  Then the largest counts: blocks of ones.
+    words = np.zeros((2048 + 16, 2048), np.uint32)
+    d = np.arange(2048)
+    words[d, d] = np.uint32(1) << (d // 4 % 32).astype(np.uint32)
+    words[2048:] = 0xFFFFFFFF
+    words[2048 + 8, 1000:] = 0
+    raw = words.view(np.uint8).reshape(-1)
+    t = torch.from_numpy(raw.view(np.int16).copy()).to(DEV).view(torch.bfloat16)
+    plan = ff.ff_snapshot_plan([t], chunk, tile_log2=13)
+    chunks, crcs, bad, n_bad = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+    ff.ff_restore(plan, chunks, crcs, bad, n_bad)
+    torch.cuda.synchronize()
+    assert np.array_equal(chunks.cpu().numpy(), raw) and int(n_bad.item()) == 0
+    want = [oracle.crc32c(raw[k:k + chunk]) for k in range(0, raw.size, chunk)]
+    assert np.array_equal(_u32(crcs), np.array(want, np.uint32))
