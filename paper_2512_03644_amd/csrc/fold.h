@@ -44,6 +44,29 @@ __device__ __forceinline__ void workgroup_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// A table of `bytes` on its way into LDS without passing through registers, 16 bytes a lane and load:
+// thread t of the workgroup's THREADS fetches slots t, t + THREADS, ...  wait_loads() waits for them.  (Buffer
+// loads: next to global loads into LDS the compiler takes no other load's completion for ordered, and
+// waits for all of them wherever it waits for one.)
+#define FF_LDS __attribute__((address_space(3)))
+template <int THREADS, int BYTES>
+__device__ __forceinline__ void table_to_lds(const uint32_t* table, u32x4* lds, const int wave, const int lane)
+{
+    static_assert(BYTES % (16 * THREADS) == 0, "whole rounds");
+    constexpr int kWords = 0x00027000;  // of 32 bits, no swizzle
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(table), 0, BYTES, kWords);
+    for (int i = 0; i < BYTES / (16 * THREADS); i++)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (FF_LDS void*)(lds + i * THREADS + wave * 64), 16, 16 * lane,
+                                                 16 * (i * THREADS + wave * 64), 0, 0);
+}
+// Until every load and store issued by this wavefront has completed.
+__device__ __forceinline__ void wait_loads()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters at their largest
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 template <class Fn, int... Is>
 __device__ __forceinline__ void static_for_impl(Fn&& fn, std::integer_sequence<int, Is...>)
 {
@@ -137,22 +160,6 @@ __device__ __forceinline__ uint32_t mul_tab_add(const uint32_t* tab, uint32_t a,
                 tab[768 + (a >> 24)], b);
 }
 
-// One more row of a stream: reg[f] holds column f (dword f of every lane's slot) of the rows so far.
-template <int DW, bool FIRST>
-__device__ __forceinline__ void add_row(uint32_t (&reg)[DW], const uint32_t* tab, const uint32_t (&d)[DW])
-{
-    static_for<DW>([&](auto f) { reg[f] = FIRST ? d[f] : mul_tab_add(tab, reg[f], d[f]); });
-}
-
-// Columns -> one value per lane and stream.
-template <int DW>
-__device__ __forceinline__ uint32_t join_columns(const uint32_t (&reg)[DW], const uint32_t* tab_d)
-{
-    uint32_t v = reg[0];
-    static_for<DW - 1>([&](auto f) { v = mul_tab_add(tab_d, v, reg[f + 1]); });
-    return v;
-}
-
 // XOR over the 64 lanes, the same value in every lane: inside each row of 16 lanes with DPP moves
 // (no LDS round trip as in a shuffle), across the four rows through scalar registers.
 __device__ __forceinline__ uint32_t wave_xor(uint32_t v)
@@ -163,18 +170,6 @@ __device__ __forceinline__ uint32_t wave_xor(uint32_t v)
     v ^= __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);  // row_mirror: the other eight
     return __builtin_amdgcn_readlane(v, 0) ^ __builtin_amdgcn_readlane(v, 16) ^
            __builtin_amdgcn_readlane(v, 32) ^ __builtin_amdgcn_readlane(v, 48);
-}
-
-// XOR over the lanes with the same lane mod 4, the same value in all of them.
-__device__ __forceinline__ uint32_t quad_place_xor(uint32_t v)
-{
-    v ^= __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, true);  // row_ror:4
-    v ^= __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror:8
-    // both halves of a swapped pair of copies: the neighbouring row of 16 lanes, the other 32 lanes
-    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = a[0] ^ a[1];
-    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return b[0] ^ b[1];
 }
 
 // One lane per wavefront: adds v to the run's sum in LDS.  True in the wavefront that completes the

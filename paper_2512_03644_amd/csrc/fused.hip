@@ -8,9 +8,9 @@
 // into the CRC of their stream, so the snapshot is never read back from memory.  Rows are aligned
 // to the tensors' elements; elements of a row that are not the tile's count as zeros.
 //
-// A sub-block is straight-line code with all its loads up front; each further row is one Horner step
-// of a stream's register through byte tables in LDS (x^8192 or x^4096 per row), and the lanes of a
-// quad share the four streams among themselves before the multiplication by the lane's constant.
+// A sub-block is straight-line code with all its loads up front; the registers of its four streams come
+// from the matrix cores (matrix_fold.h, weights in LDS) as eight bits of each in every lane, which are
+// multiplied by the lane's factors before the lanes share the streams out among themselves.
 // The sub-blocks of a tile that share a workgroup sum their registers in LDS; the last one to arrive
 // multiplies the sums by x^(8 * distance to the end of the chunk) and XORs them into crcs[chunk] with
 // an atomic; XOR is commutative, so the result does not depend on the order in which tiles finish.  A
@@ -21,9 +21,8 @@
 // allocation to the next, with this kernel and any other tried.  Results are stored from registers, stream by
 // stream, by two workgroups on a compute unit (three where they hold the launch at once).  Where most
 // elements have an fp32 stream off its 128-byte lines, longer runs on the lines are worth a detour: the new
-// master, m and v of a workgroup are laid out in LDS, in the place of the tables when the folds are done
-// with them, and every wavefront stores 12 KiB of consecutive rows.  (An image of its own next to the
-// tables, used by every launch, is what the third column has: 3-6 % faster on aligned lists of 60-250
+// master, m and v of a workgroup are laid out in LDS, and every wavefront stores 12 KiB of consecutive
+// rows.  (The image used by every launch is what the second column has: 3-6 % faster on aligned lists of 60-250
 // million elements in the worse placements, but 5-12 % slower from 400 million on or in the better
 // placements, 10 % slower in the first passes after a pause, 10-20 % on small launches.)  One process, same
 // tensors, ms: rows handed through LDS by workgroups of 8 / image for all / as now
@@ -36,12 +35,17 @@
 //   2000 ragged groups in fp16, 190 MB                           1.25 / 1.07 / 1.03
 //   64 parameters, 2.1 million                                   0.032 / 0.026 / 0.023
 // Chained: 7B 4.60 / 4.53 / 4.53, odd-sized 2.15 / 2.02 / 2.02, 64 parameters 0.031 / 0.023 / 0.023.
+// With the registers from the matrix cores (all of the above had 108 lookups a lane and sub-block in byte
+// tables, 64 random LDS addresses each), us: 35 fp16 parameters of 19,000 elements and 300 RAW tensors 27.7 ->
+// 24.5, 96 ragged ones 34.8 -> 31.9, 2000 ragged groups 1016 -> 988, chained 20 million elements 53.1 -> 52.0;
+// 64 parameters, 2.1 million, and the 7B shard the same within 0.5 %.
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
 #include <stddef.h>
 
 #include "fold.h"
+#include "matrix_fold.h"
 
 namespace ffsnap {
 
@@ -115,32 +119,26 @@ typedef u32x4 u32x4_alias __attribute__((may_alias));
 struct Lds {
     uint32_t sum[kWavesPerBlock][4];  // per run (at its first wavefront's place): XOR of its registers
     uint32_t arrived[kWavesPerBlock]; // wavefronts of the run that have added theirs
-    uint32_t tab16[1024];  // multiply by x^8192  (1 KiB rows)
-    uint32_t tab8[1024];   // multiply by x^4096  (512 B rows)
-    uint32_t tab_d[1024];  // multiply by x^32    (neighbouring dwords)
-    uint32_t tab_s[3][1024];  // multiply by x^64, x^128, x^256 (neighbouring slots and pairs of them)
+    u32x4 wide[kRows * 4][2][kWaveSize];  // weights of the dwords of two rows of 16-byte slots
+    u32x4 half[kRows * 2][2][kWaveSize];  // ... of 8-byte slots
 };
 
 // The in-place step's image: the new master, m and v of the workgroup's sub-blocks as they lie in
-// their streams; behind them room for the last dword that a shifted read touches.  It takes the place of
-// the tables, when they have been used.
+// their streams; behind them room for the last dword that a shifted read touches.  Dynamic LDS, so that
+// only the launches that use it pay for it.
 constexpr int kImgF = kWavesPerBlock * kSubElems * 4;  // bytes of one fp32 stream of a workgroup
 constexpr int kImgBytes = 3 * kImgF + 16;
-template <bool IMAGE>
-union __attribute__((aligned(16))) Shared {
-    Lds lds;
-    uint8_t bytes[IMAGE ? offsetof(Lds, tab16) + kImgBytes : sizeof(Lds)];
-};
-static_assert(offsetof(Lds, tab16) % 16 == 0, "the image's slots");
 
 // Workgroups of an in-place step on a compute unit: three if they hold the launch at once, else two, made so
 // by LDS that nobody uses.  Stored from registers, three against two, us: 30 parameters of 100,000 elements
 // (750 workgroups) 30.9 / 32.6, 40 of 340,000 (3320) 116.4 / 114.4, 30 odd-sized ones (86,000) 3003 / 2921; 7B
 // (205,000) 6640-6700 / 6470-6560 in worse placements, 5520-5540 / 5470-5480 in better ones.  Through the image 7B
 // 6650-6690 / 6400-6490, 5560 / 5550, odd-sized 2890 / 2700.
-constexpr unsigned kComputeUnits = 256, kSpareLds = 8192;
-static_assert(3 * sizeof(Shared<true>) <= 160 * 1024 && 3 * (sizeof(Shared<true>) + kSpareLds) > 160 * 1024 &&
-              2 * (sizeof(Shared<true>) + kSpareLds) <= 160 * 1024, "two or three");
+constexpr unsigned kComputeUnits = 256, kSpareLds = 30 * 1024;
+constexpr size_t kLds = 160 * 1024;
+static_assert(3 * sizeof(Lds) <= kLds && 3 * (sizeof(Lds) + kSpareLds) > kLds && 2 * (sizeof(Lds) + kSpareLds) <= kLds,
+              "two or three");
+static_assert(2 * (sizeof(Lds) + kImgBytes) <= kLds && 3 * (sizeof(Lds) + kImgBytes) > kLds, "two");
 
 // Tile registers come out of the folds without the factor x^32 that a CRC register carries.
 constexpr uint32_t kX16 = gf2_xpow(16);
@@ -153,61 +151,36 @@ __device__ __forceinline__ void add_head_piece(uint32_t* __restrict__ crcs, cons
     atomicXor(&crcs[t.chunk[piece]], gf2_mul_const<kX16>(low_half));
 }
 
-// The byte tables on their way to LDS: fetched first thing, stored (put) behind the loads of the
-// wavefront's own data, so that the two latencies overlap.  put() is a barrier of the workgroup; every
-// wavefront calls it exactly once, whether at a parameter, a RAW tile or none.
-struct TableFetch {
-    static constexpr int kEach = 6 * 1024 / (4 * kThreads);
-    u32x4 a[kEach];
-    __device__ __forceinline__ explicit TableFetch(const uint32_t* __restrict__ tabs)
-    {
-        static_for<kEach>([&](auto i) {
-            a[i] = *as_global(reinterpret_cast<const u32x4*>(tabs) + i * kThreads + threadIdx.x);
-        });
-    }
-    __device__ __forceinline__ void put(Lds& lds) const
-    {
-        static_assert(kEach * kThreads * 4 == 6 * 1024, "six tables");
-        static_for<kEach>([&](auto i) {  // tab16, tab8, tab_d, tab_s
-            *(reinterpret_cast<u32x4*>(lds.tab16) + i * kThreads + threadIdx.x) = a[i];
-        });
-        if (threadIdx.x < kWavesPerBlock * 4) (&lds.sum[0][0])[threadIdx.x] = 0;
-        if (threadIdx.x < kWavesPerBlock) lds.arrived[threadIdx.x] = 0;
-        workgroup_barrier();
-    }
-};
-
-// Four streams at once (v[0]: 8-byte slots, v[1..3]: 16-byte slots): the lanes of a quad first share
-// the streams out among themselves -- two exchanges, in each of which a lane keeps half of its values
-// and gets the neighbour's share of them -- so that the multiplication by the lane's constant, 130
-// instructions, is done once and not once per stream.  Lane l ends with stream kStreamOf(l mod 4),
-// summed over all lanes.
-__device__ __forceinline__ int stream_of_lane(int lane) { return (lane & 1) * 2 + ((lane >> 1) & 1); }
-__device__ __forceinline__ uint32_t finish_streams(const uint32_t (&v)[4], const Lds& lds,
-                                                   uint32_t lane_c, int lane)
+// The weights on their way to LDS, first thing.  tables_ready() is a barrier of the workgroup, behind a
+// wavefront's own loads (whose completion includes that of its part of the weights); every wavefront calls it
+// exactly once, whether at a parameter, a RAW tile or none.  (In front of the folds instead, behind the
+// stores, it costs 3 % on 50 million elements chained and 4 % on 64 small parameters.)
+__device__ __forceinline__ void fetch_tables(const uint32_t* __restrict__ tabs, Lds& lds, const int wave, const int lane)
 {
-    const bool odd = lane & 1, high = lane & 2;
-    // lane ^ 1: even lanes keep streams 0 and 1, odd lanes 2 and 3; the even lane's slot comes first
-    uint32_t u[2];
-    static_for<2>([&](auto k) {
-        const uint32_t keep = odd ? v[2 + k] : v[k], send = odd ? v[k] : v[2 + k];
-        const uint32_t got = __builtin_amdgcn_mov_dpp(send, 0xB1, 0xF, 0xF, true);
-        const uint32_t* tab = (k == 0) ? lds.tab_s[odd ? 1 : 0] : lds.tab_s[1];
-        u[k] = mul_tab_add(tab, odd ? got : keep, odd ? keep : got);
-    });
-    // lane ^ 2: the lower pair keeps u[0], the higher u[1]
-    const uint32_t keep = high ? u[1] : u[0], send = high ? u[0] : u[1];
-    const uint32_t got = __builtin_amdgcn_mov_dpp(send, 0x4E, 0xF, 0xF, true);
-    const uint32_t* tab = lds.tab_s[(odd || high) ? 2 : 1];
-    const uint32_t w = mul_tab_add(tab, high ? got : keep, high ? keep : got);
-    return quad_place_xor(gf2_mul(w, lane_c));
+    static_assert(4 * kFusedWeightWords == sizeof(lds.wide) + sizeof(lds.half), "all weights");
+    static_assert(offsetof(Lds, half) == offsetof(Lds, wide) + sizeof(lds.wide), "one behind the other");
+    table_to_lds<kThreads, 4 * kFusedWeightWords>(tabs, &lds.wide[0][0][0], wave, lane);
+    if (threadIdx.x < kWavesPerBlock * 4) (&lds.sum[0][0])[threadIdx.x] = 0;
+    if (threadIdx.x < kWavesPerBlock) lds.arrived[threadIdx.x] = 0;
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void tables_ready()
+{
+    wait_loads();
+    workgroup_barrier();
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// Sum of the registers of a parameter tile's run; in the run's last wavefront, on to memory.  v: lane l
-// (l < 4) holds the register of stream x.
-__device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info, uint32_t v, int x,
+// Sum of the registers of a parameter tile's run; in the run's last wavefront, on to memory.  v: the lanes
+// of row j (of 16) hold the register of stream j.
+__device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info, uint32_t v,
                                         uint32_t* __restrict__ crcs, int lane)
 {
+    const int x = lane & 3;  // from here on lane x has stream x
+    static_for<3>([&](auto k) {
+        const uint32_t u = __builtin_amdgcn_readlane(v, 16 * (k + 1));
+        v = lane == k + 1 ? u : v;
+    });
     int n = 4;
     const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
     if (len > 1) {
@@ -341,12 +314,12 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
                                                 const uint8_t* __restrict__ grad,
                                                 uint8_t* __restrict__ chunks,
                                                 uint32_t* __restrict__ crcs, const FusedConsts& C,
-                                                const TableFetch& tf, Lds& lds, uint8_t* img,
+                                                Lds& lds, uint8_t* img,
                                                 const uint32_t* __restrict__ lane_tab, int wave, int lane)
 {
     const int sub = info & 15u;
-    // x^(8 * bytes between the end of the lane's quad and the end of the block), in the lane's stream
-    const uint32_t lane_c = lane_tab[(15 - sub) * 64 + lane];
+    // x^(8 * bytes between the end of the lane's column and the end of the block), in the lane's stream
+    const uint32_t lane_c0 = lane_tab[(15 - sub) * 64 + lane], lane_c = lane_tab[(16 + 15 - sub) * 64 + lane];
     // wave-uniform addresses of the sub-block's element 0 in every stream; a lane adds 32 bits
     const int64_t at64 = at;
     uint8_t* const tw = reinterpret_cast<uint8_t*>(t.ptr[0]) + 2 * at64;
@@ -396,8 +369,8 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
             ev = f32_at(lv + 4 * ej);
         }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    tf.put(lds);
+    // (Waiting for the weights alone, vmcnt counted, and for the data row by row costs 0.7 % on the 7B shard.)
+    tables_ready();
 
     uint32_t nonfinite = 0;  // this lane's count of infinite or NaN gradient elements (fp16 only)
     uint32_t edge_w = 0;
@@ -470,7 +443,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         });
     }
     // Stores from registers, stream by stream; but the fp32 streams of a workgroup that is all at this tile
-    // may go by way of its image in LDS (C.image), which waits for the folds to be done with the tables.
+    // may go by way of its image in LDS (C.image).
     auto store_w = [&](uint8_t* base) {
         static_for<kRows>([&](auto r) {
             if (mine(r)) store8_unaligned<true>(base + (lane8 + 2 * kRowElems * r), q[r].g);
@@ -489,7 +462,14 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     store_w(tw);
     store_w(sw);
     const bool by_image = !CHAINED && C.image && ((info >> 8) & 15u) == kWavesPerBlock;
-    if (!by_image) {
+    if (by_image) {
+        uint8_t* const im = img + wave * (kSubElems * 4);  // this wavefront's share of every stream
+        static_for<kRows>([&](auto r) {
+            *reinterpret_cast<u32x4_alias*>(im + (lane16 + 4 * kRowElems * r)) = q[r].p;
+            *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
+            *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
+        });
+    } else {
         if constexpr (!CHAINED) {
             store_f(tp, &RowIn::p, ep);
             store_f(tm, &RowIn::m, em);
@@ -500,44 +480,53 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         store_f(chunks + (static_cast<int64_t>(t.soff[3]) + 4 * at64), &RowIn::v, ev);
     }
     __builtin_amdgcn_sched_barrier(0);
-
-    uint32_t rw[2], rp[4], rm[4], rv[4];
-    static_for<kRows>([&](auto r) {
-        uint32_t fw[2] = {q[r].g.x, q[r].g.y};
-        uint32_t fp[4] = {q[r].p.x, q[r].p.y, q[r].p.z, q[r].p.w};
-        uint32_t fm[4] = {q[r].m.x, q[r].m.y, q[r].m.z, q[r].m.w};
-        uint32_t fv[4] = {q[r].v.x, q[r].v.y, q[r].v.z, q[r].v.w};
-        if (!WHOLE) {
-            const int x = r * kRowElems + 4 * lane;
-            // split first element: its first two bytes close the previous chunk and must not
-            // enter this tile's CRC of that stream
-            if (t.head_split && at <= 0 && x == edge_lo) {
-#pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    if (s != (lo & 3)) continue;
-                    if (t.head_split & 2u) { add_head_piece(crcs, t, 4, fp[s] & 0xFFFFu); fp[s] &= 0xFFFF0000u; }
-                    if (t.head_split & 4u) { add_head_piece(crcs, t, 5, fm[s] & 0xFFFFu); fm[s] &= 0xFFFF0000u; }
-                    if (t.head_split & 8u) { add_head_piece(crcs, t, 6, fv[s] & 0xFFFFu); fv[s] &= 0xFFFF0000u; }
-                }
-            }
+    // Split first element: its first two bytes close the previous chunk and must not enter this tile's CRC
+    // of that stream.
+    const bool head = !WHOLE && t.head_split && at <= 0;
+    auto dword = [&](auto r, u32x4 RowIn::*x, auto stream, auto f) -> uint32_t {
+        uint32_t d = (q[r].*x)[int(f)];
+        if (!WHOLE && head && r * kRowElems + 4 * lane == edge_lo && f == (lo & 3) && (t.head_split >> stream & 1u)) {
+            add_head_piece(crcs, t, 3 + stream, d & 0xFFFFu);
+            d &= 0xFFFF0000u;
         }
-        add_row<2, r == 0>(rw, lds.tab8, fw);
-        add_row<4, r == 0>(rp, lds.tab16, fp);
-        add_row<4, r == 0>(rm, lds.tab16, fm);
-        add_row<4, r == 0>(rv, lds.tab16, fv);
-    });
-    const uint32_t v[4] = {join_columns(rw, lds.tab_d), join_columns(rp, lds.tab_d),
-                           join_columns(rm, lds.tab_d), join_columns(rv, lds.tab_d)};
-    deliver(lds, t, info, finish_streams(v, lds, lane_c, lane), stream_of_lane(lane), crcs, lane);
+        return d;
+    };
+    // Two streams at a time: the sums of all four would take the registers that a third workgroup on the
+    // compute unit needs.
+    uint32_t bits = 0;
+    {
+        QuarterSums w = {}, p = {};
+        static_for<kRows>([&](auto r) {
+            static_for<2>([&](auto f) {
+                const u32x4 k[2] = {lds.half[2 * r + f][0][lane], lds.half[2 * r + f][1][lane]};
+                matrix_add(w, k, q[r].g[int(f)]);
+            });
+            static_for<4>([&](auto f) {
+                const u32x4 k[2] = {lds.wide[4 * r + f][0][lane], lds.wide[4 * r + f][1][lane]};
+                matrix_add(p, k, dword(r, &RowIn::p, std::integral_constant<int, 1>{}, f));
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        matrix_take(bits, w);
+        matrix_take(bits, p);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        QuarterSums m = {}, v = {};
+        static_for<kRows>([&](auto r) {
+            static_for<4>([&](auto f) {
+                const u32x4 k[2] = {lds.wide[4 * r + f][0][lane], lds.wide[4 * r + f][1][lane]};
+                matrix_add(m, k, dword(r, &RowIn::m, std::integral_constant<int, 2>{}, f));
+                matrix_add(v, k, dword(r, &RowIn::v, std::integral_constant<int, 3>{}, f));
+                if (f % 2) __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        matrix_take(bits, m);
+        matrix_take(bits, v);
+    }
+    deliver(lds, t, info, row_xor(matrix_streams(bits, lane_c0, lane_c)), crcs, lane);
 
     if (by_image) {
-        workgroup_barrier();  // every wavefront is at this tile, in this function's instantiation or the other
-        uint8_t* const im = img + wave * (kSubElems * 4);  // this wavefront's share of every stream
-        static_for<kRows>([&](auto r) {
-            *reinterpret_cast<u32x4_alias*>(im + (lane16 + 4 * kRowElems * r)) = q[r].p;
-            *reinterpret_cast<u32x4_alias*>(im + kImgF + (lane16 + 4 * kRowElems * r)) = q[r].m;
-            *reinterpret_cast<u32x4_alias*>(im + 2 * kImgF + (lane16 + 4 * kRowElems * r)) = q[r].v;
-        });
         workgroup_barrier();
         constexpr int kAll = kWavesPerBlock * int(kSubElems);
         const int from = at - wave * int(kSubElems);
@@ -564,8 +553,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
 // slot that holds lo) and 8-15 (the one that holds hi), and handed to its owner for the CRC.
 __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t info, const int at,
                                               const int lo, const int hi, uint8_t* __restrict__ chunks,
-                                              uint32_t* __restrict__ crcs, const TableFetch& tf,
-                                              Lds& lds, const uint32_t* __restrict__ lane_tab, int lane)
+                                              uint32_t* __restrict__ crcs, Lds& lds, const uint32_t* __restrict__ lane_tab, int lane)
 {
     const int sub = info & 15u;
     // x^(8 * bytes between the end of the lane's slot and the end of the block)
@@ -594,26 +582,33 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
     // and on to the end of the chunk: the wavefronts of a run may be at different tiles of it.  (While the
     // data is on its way.)
     const uint32_t lane_c = gf2_mul(to_block_end, t.shift[0]);
-    __builtin_amdgcn_sched_barrier(0);
-    tf.put(lds);
+    tables_ready();
     u32x4 edge[2];  // the two slots, put together from the halfwords of lanes 0..15
     static_for<2>([&](auto e) {
         uint32_t h[8];
         static_for<8>([&](auto k) { h[k] = __builtin_amdgcn_readlane(eh, 8 * e + k); });
         edge[e] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
     });
-    uint32_t reg[4];
-    static_for<kRawRows>([&](auto r) {
-        const int x = r * 1024 + 16 * lane;
-        if (mine(r)) store16_stream<true>(dst + x, w[r]);
-        if (lo_cut && x == edge_lo) w[r] = edge[0];
-        if (hi_cut && x == edge_hi) w[r] = edge[1];
-        const uint32_t d[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
-        add_row<4, r == 0>(reg, lds.tab16, d);
+    uint32_t bits = 0;
+    static_for<kRawRows / 2>([&](auto pair) {  // two rows are a stream
+        QuarterSums sums = {};
+        static_for<2>([&](auto k) {
+            constexpr int r = 2 * pair + k;
+            const int x = r * 1024 + 16 * lane;
+            if (mine(r)) store16_stream<true>(dst + x, w[r]);
+            if (lo_cut && x == edge_lo) w[r] = edge[0];
+            if (hi_cut && x == edge_hi) w[r] = edge[1];
+            static_for<4>([&](auto f) {
+                const u32x4 weights[2] = {lds.wide[4 * k + f][0][lane], lds.wide[4 * k + f][1][lane]};
+                matrix_add(sums, weights, w[r][int(f)]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        matrix_take(bits, sums);
     });
     // (With a run for every tile tensors of 2 KB are bound by the atomics on their chunk's word: 40 MB of
     // them in chunks of 16 KiB / 1 MiB / 8 MiB 49 / 188 / 256 us, with runs across tiles 48 / 52 / 52.)
-    uint32_t v = wave_xor(gf2_mul(join_columns(reg, lds.tab_d), lane_c));
+    uint32_t v = wave_xor(gf2_mul(matrix_share(bits, lane), lane_c));
     if (lane != 0) return;
     const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
     if (len > 1 && !run_complete(lds.sum[run][0], lds.arrived[run], len, v)) return;
@@ -628,34 +623,33 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
 // groups 7.4 / 7.9 / 11.0 against 7.7 / 8.1 / 11.2), which shows where a queue of steps is bound by that: 64
 // groups of 100 elements 10.7 against 11.2 us a step, fewer or larger groups the same within 1 %.
 template <bool F16, bool CHAINED, bool BC2, uint32_t N>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void fused_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void fused_kernel(
     const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
     const uint32_t* __restrict__ tabs, uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs,
     FusedConsts C, GradPtrsOf<N> grads)
 {
-    __shared__ Shared<!CHAINED> shared;
-    Lds& lds = shared.lds;
-    uint8_t* const img = shared.bytes + offsetof(Lds, tab16);
+    __shared__ Lds lds;
+    extern __shared__ __attribute__((aligned(16))) uint8_t img[];  // of launches with C.image
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
-    const TableFetch tf(tabs);
+    fetch_tables(tabs, lds, wave, lane);
     const WorkWave e = waves[group * kWavesPerBlock + wave];
     if (e.tile == kNoTile) {
-        tf.put(lds);
+        tables_ready();
         return;
     }
     // the tile descriptor is uniform and read-only: the loads below go through scalar registers
     // (a private copy indexed by the stream number would live in scratch memory instead)
     const WorkTile& t = tiles[e.tile];
     const int sub = e.info & 15u;
-    const uint32_t* const lane_tab = tabs + 6 * 1024;
+    const uint32_t* const lane_tab = tabs + kFusedWeightWords;
     if (t.kind == kWorkRaw) {
         const int at = sub * int(kSubRawBytes) - static_cast<int>(t.soff[0] % kRawTileBytes);
         const int lo = at < 0 ? -at : 0;
         const int left = static_cast<int>(t.n) - at;
         raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
-                      crcs, tf, lds, lane_tab + 16 * 64, lane);
+                      crcs, lds, lane_tab + 32 * 64, lane);
         return;
     }
     const int at = sub * int(kSubElems) - static_cast<int>(t.e0 % kParamTileElems);
@@ -664,10 +658,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const int hi = left < int(kSubElems) ? left : int(kSubElems);
     const uint8_t* const grad = reinterpret_cast<const uint8_t*>(grads.p[t.grad_index - grad_base]);
     if (lo == 0 && hi == int(kSubElems) && !(t.head_split && at == 0))
-        param_sub_block<F16, CHAINED, BC2, true>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds, img,
+        param_sub_block<F16, CHAINED, BC2, true>(t, e.info, at, lo, hi, grad, chunks, crcs, C, lds, img,
                                             lane_tab, wave, lane);
     else
-        param_sub_block<F16, CHAINED, BC2, false>(t, e.info, at, lo, hi, grad, chunks, crcs, C, tf, lds, img,
+        param_sub_block<F16, CHAINED, BC2, false>(t, e.info, at, lo, hi, grad, chunks, crcs, C, lds, img,
                                              lane_tab, wave, lane);
 }
 
@@ -871,21 +865,28 @@ __global__ void fused_prepare_kernel(uint32_t* __restrict__ crcs, uint64_t n_chu
 
 void build_fused_tabs(uint32_t* tab)
 {
-    const uint64_t step[6] = {8192, 4096, 32, 64, 128, 256};
-    for (int t = 0; t < 6; t++) {
-        const uint32_t u = gf2_xpow(step[t]);
-        for (int k = 0; k < 4; k++)
-            for (uint32_t b = 0; b < 256; b++) tab[t * 1024 + k * 256 + b] = gf2_mul(b << (8 * k), u);
-    }
-    uint32_t* const lane_tab = tab + 6 * 1024;
+    for (int r = 0; r < kRows; r++)
+        for (int f = 0; f < 4; f++)
+            build_quarter_weights(tab + (4 * r + f) * kQuarterWords,
+                                  gf2_xpow(8ull * 1024 * (kRows - 1 - r) + 32 * (3 - f)), gf2_xpow(8 * 16 * 16));
+    tab += 4 * kRows * kQuarterWords;
+    for (int r = 0; r < kRows; r++)
+        for (int f = 0; f < 2; f++)
+            build_quarter_weights(tab + (2 * r + f) * kQuarterWords,
+                                  gf2_xpow(8ull * 512 * (kRows - 1 - r) + 32 * (1 - f)), gf2_xpow(8 * 8 * 16));
+    uint32_t* const lane_tab = tab + 2 * kRows * kQuarterWords;
     for (int lane = 0; lane < kWaveSize; lane++) {
-        const uint64_t slot = ((lane & 1) * 2 + ((lane >> 1) & 1)) == 0 ? 8 : 16;  // w16 : fp32
-        uint32_t v = gf2_xpow(8 * slot * 4 * (15 - lane / 4));
-        const uint32_t x_sub = gf2_xpow(8 * slot * kWaveSize * kRows);
-        for (int k = 0; k < 16; k++, v = gf2_mul(v, x_sub)) lane_tab[k * 64 + lane] = v;
-        v = gf2_xpow(8 * 16 * (63 - lane));
+        const int quarter = lane / 16, column = lane % 16, stream = quarter;
+        uint32_t v;
+        for (int wide = 0; wide < 2; wide++) {
+            const uint64_t slot = wide ? 16 : 8;
+            v = gf2_xpow(8 * slot * (15 - column) + 24 - 8 * quarter);
+            const uint32_t x_sub = gf2_xpow(8 * slot * kWaveSize * kRows);
+            for (int k = 0; k < 16; k++, v = gf2_mul(v, x_sub)) lane_tab[(16 * wide + k) * 64 + lane] = v;
+        }
+        v = gf2_xpow(8 * 16 * (15 - column) + 8ull * 2048 * (3 - stream));
         const uint32_t x_raw = gf2_xpow(8ull * kSubRawBytes);
-        for (int k = 0; k < 4; k++, v = gf2_mul(v, x_raw)) lane_tab[(16 + k) * 64 + lane] = v;
+        for (int k = 0; k < 4; k++, v = gf2_mul(v, x_raw)) lane_tab[(32 + k) * 64 + lane] = v;
     }
 }
 
@@ -917,7 +918,7 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
     GradPtrsOf<N> g;
     for (uint32_t i = 0; i < N; i++)
         g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), consts.prev || at_once ? 0 : kSpareLds, stream, waves,
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), consts.prev || at_once ? 0 : c.image ? kImgBytes : kSpareLds, stream, waves,
                        tiles, p0, tabs, chunks, crcs, c, g);
 }
 

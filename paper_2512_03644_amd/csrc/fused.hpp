@@ -24,12 +24,12 @@ struct FusedConsts {
     uint32_t image = 0;  // in-place step: whole workgroups store their fp32 streams through LDS
 };
 
-// Device table of the fused kernels (kFusedTabWords entries): byte tables of multiplication by
-// x^8192 (1 KiB rows), x^4096 (512 B rows), x^32 (dwords), x^64, x^128 and x^256 (slots of 8 and 16
-// bytes and pairs of them), then lane constants: for k = 0..15 and every lane of a parameter
-// sub-block, x^(8 * bytes between the end of the lane's quad in its stream and the end of a row, plus
-// k sub-blocks), and for k = 0..3 the same for a lane's slot of a RAW sub-block.
-constexpr int kFusedTabWords = 6 * 1024 + 16 * 64 + 4 * 64;
+// Device table of the fused kernels (kFusedTabWords entries): weights (matrix_fold.h) of the dwords of two
+// rows of 16-byte slots and of two rows of 8-byte slots, then lane constants: for k = 0..15 and every lane of a
+// parameter sub-block, x^(8 * bytes between the end of the lane's column in its stream and the end of a
+// row, plus k sub-blocks), and for k = 0..3 the same for the columns of a RAW sub-block's pairs of rows.
+constexpr int kFusedWeightWords = 12 * 2 * 4 * 64;
+constexpr int kFusedTabWords = kFusedWeightWords + 32 * 64 + 4 * 64;
 void build_fused_tabs(uint32_t* tab);
 
 // Gradient pointers of up to kGradsPerLaunch consecutive parameter groups, handed to the kernel by

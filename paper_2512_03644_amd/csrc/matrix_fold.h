@@ -19,19 +19,29 @@
 namespace ffsnap {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Words of the weights of one dword position: four for every lane.
 constexpr int kWeightWords = 4 * 64;
 
+// A dword's bits as 4-bit floats, and weights as an operand.
+__device__ __forceinline__ i32x8 matrix_bits(const uint32_t x)
+{
+    return i32x8{int(x & 0x11111111u), int(x & 0x22222222u), int(x & 0x44444444u),
+                 int((x >> 1) & 0x44444444u), 0, 0, 0, 0};
+}
+__device__ __forceinline__ i32x8 matrix_weights(const u32x4 w)
+{
+    return i32x8{int(w.x), int(w.y), int(w.z), int(w.w), 0, 0, 0, 0};
+}
+constexpr int kFloat4 = 4;  // the operands' format
+
 // One dword of every lane.
 __device__ __forceinline__ void matrix_add(f32x16& acc, const u32x4 weights, const uint32_t x)
 {
-    const i32x8 a = {int(weights.x), int(weights.y), int(weights.z), int(weights.w), 0, 0, 0, 0};
-    const i32x8 b = {int(x & 0x11111111u), int(x & 0x22222222u), int(x & 0x44444444u),
-                     int((x >> 1) & 0x44444444u), 0, 0, 0, 0};
-    constexpr int kFloat4 = 4;
-    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, kFloat4, kFloat4, 0, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(matrix_weights(weights), matrix_bits(x), acc, kFloat4,
+                                                          kFloat4, 0, 0, 0, 0);
 }
 
 // Half a register per lane, in the upper 16 bits: lane n < 32 bits 16..31 of column n's, lane n + 32
@@ -82,6 +92,104 @@ inline void build_matrix_weights(uint32_t* out, uint32_t low, uint32_t high)
             for (int b = 0; b < 32; b++)
                 if ((product[b] >> bit) & 1u) w[b % 4] |= kCode[b % 4] << (4 * (b / 4));
         }
+    }
+}
+
+// ---- four streams at once ------------------------------------------------------------------------
+//
+// v_mfma_f32_16x16x128_f8f6f4: lanes n, n + 16, n + 32 and n + 48 are the quarters of column n, a product
+// has 16 rows, so two of them make a register.  Twice the weights for a dword, but a product's sums
+// take 4 registers a lane and not 16, so that several streams can use weights that have been read
+// once; and a column's register comes out in four lanes, eight bits each, which suits four
+// streams: the lanes share the streams out among themselves, and the multiplication by a lane's own
+// factor, 130 instructions, is done once and not once per stream.
+
+// Words of the weights of one dword position: two products, four words for every lane.
+constexpr int kQuarterWords = 2 * 4 * 64;
+
+struct QuarterSums {
+    f32x4 p[2];  // the two products
+};
+__device__ __forceinline__ void matrix_add(QuarterSums& acc, const u32x4 (&weights)[2], const uint32_t x)
+{
+    const i32x8 b = matrix_bits(x);
+    static_for<2>([&](auto s) {
+        acc.p[s] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(matrix_weights(weights[s]), b, acc.p[s], kFloat4,
+                                                                    kFloat4, 0, 0, 0, 0);
+    });
+}
+
+// The eight bits of a stream's register that this lane has, from above into r.
+__device__ __forceinline__ void matrix_take(uint32_t& r, const QuarterSums& acc)
+{
+    static_for<2>([&](auto s) {
+        static_for<4>([&](auto g) {
+            r = __builtin_amdgcn_alignbit(__float_as_uint(acc.p[s][int(g)] + 16777216.0f), r, 1);
+        });
+    });
+}
+
+// r: taken from streams 0 to 3, so byte j has bits 8 q .. 8 q + 7 of stream j's register, q = lane / 16.
+// Lanes of row j (of 16) get what adds up over the row to the register of stream j, the columns
+// times their factors: c0 of this lane for stream 0, c for the others.
+__device__ __forceinline__ uint32_t matrix_streams(const uint32_t r, uint32_t c0, uint32_t c)
+{
+    uint32_t v[4] = {0, 0, 0, 0};
+    static_for<8>([&](auto i) {
+        static_for<4>([&](auto j) {
+            const uint32_t on = static_cast<uint32_t>(static_cast<int32_t>(r << (24 - 8 * j + i)) >> 31);
+            v[j] ^= on & (j == 0 ? c0 : c);
+        });
+        if constexpr (i < 7) { c0 = gf2_mulx(c0); c = gf2_mulx(c); }
+    });
+    const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+    const auto w = __builtin_amdgcn_permlane16_swap(a[0] ^ a[1], b[0] ^ b[1], false, false);
+    return w[0] ^ w[1];
+}
+
+// r: taken from streams 0 to 3, so byte j has bits 8 q .. 8 q + 7 of stream j's register, q = lane / 16.
+// Lane 16 j + n gets the register of stream j's column n.
+__device__ __forceinline__ uint32_t matrix_share(const uint32_t r, const int lane)
+{
+    // every lane gets r of all four quarters: the halves of a swapped pair of copies, twice
+    const auto h = __builtin_amdgcn_permlane32_swap(r, r, false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+    // and takes byte j of each (0x0C: a byte of zeros)
+    const uint32_t j = static_cast<uint32_t>(lane) >> 4, pick = j | (4 + j) << 8;
+    return __builtin_amdgcn_perm(lo[1], lo[0], pick | 0x0C0C0000u) |
+           __builtin_amdgcn_perm(hi[1], hi[0], pick << 16 | 0x0C0Cu);
+}
+
+// XOR over each 16 lanes, the same value in all of them.
+__device__ __forceinline__ uint32_t row_xor(uint32_t v)
+{
+    v ^= __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]: lane ^ 1
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]: lane ^ 2
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);  // row_half_mirror: the other quad
+    v ^= __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);  // row_mirror: the other eight
+    return v;
+}
+
+// Weights of one dword position (host; out: kQuarterWords words): the dwords of the lanes of quarter q
+// enter their column's register times factor * step^(3 - q).
+inline void build_quarter_weights(uint32_t* out, uint32_t factor, uint32_t step)
+{
+    constexpr uint32_t kCode[4] = {6, 4, 2, 2};
+    for (int quarter = 3; quarter >= 0; quarter--, factor = gf2_mul(factor, step)) {
+        uint32_t product[32];
+        uint32_t v = factor;
+        for (int b = 31; b >= 0; b--, v = gf2_mulx(v)) product[b] = v;
+        for (int s = 0; s < 2; s++)
+            for (int m = 0; m < 16; m++) {
+                // row m of product s comes out in the lanes of quarter m / 4, at place m % 4
+                const int bit = 8 * (m / 4) + 4 * s + m % 4;
+                uint32_t* const w = out + 4 * (64 * s + 16 * quarter + m);
+                w[0] = w[1] = w[2] = w[3] = 0;
+                for (int b = 0; b < 32; b++)
+                    if ((product[b] >> bit) & 1u) w[b % 4] |= kCode[b % 4] << (4 * (b / 4));
+            }
     }
 }
 

@@ -1,6 +1,7 @@
 """The optimizer step's sub-blocks of 512 elements (8 KiB of a RAW segment) at the sizes where they
 can go wrong: around a lane's slot, a row, a sub-block, a workgroup's eight of them and a block, with chunk boundaries that cut blocks anywhere, and on
 tensors that start off every alignment."""
+import numpy as np
 import pytest
 import torch
 
@@ -83,3 +84,37 @@ def test_step_on_tensors_off_every_alignment(shift):
     for x, y, (room, n) in zip(a.segments, segs_b, rooms):
         assert torch.equal(x, y)
         assert not room[:shift].any() and not room[shift + n:].any()  # nothing around it is touched
+
+
+@pytest.mark.parametrize("high", [0, 1])
+def test_every_weight_of_the_matrix_products(oracle, high):
+    # With lr = 0 the master weights stay, so the streams can be chosen bit by bit: one element with one bit
+    # in each sub-block of 512, so that every place of a lane's slots has every bit in every quarter of the
+    # wavefront (the 16-bit weights where the bit is in the upper half), and a RAW tensor likewise.
+    n = 512 * 512
+    e = np.arange(512)
+    master = np.zeros((512, 512), np.uint32)
+    master[e, e] = np.uint32(1) << (16 * high + e // 4 % 16).astype(np.uint32)
+    raw = np.zeros((2048, 2048), np.uint32)                    # sub-blocks of 8 KiB
+    d = np.arange(2048)
+    raw[d, d] = np.uint32(1) << (16 * high + d // 4 % 16).astype(np.uint32)
+
+    def f32(a):
+        return torch.from_numpy(a.reshape(-1).view(np.float32)).to(DEV)
+
+    p, m, v, x = f32(master), torch.zeros(n, device=DEV), torch.zeros(n, device=DEV), f32(raw)
+    w = torch.zeros(n, dtype=torch.bfloat16, device=DEV)
+    chunk = 1 << 20
+    plan = ff.ff_snapshot_plan([x, w, p, m, v], chunk, 0,
+                               [ff.FF_KIND_RAW, ff.FF_KIND_W16, ff.FF_KIND_MASTER, ff.FF_KIND_M, ff.FF_KIND_V],
+                               [0] * 5)
+    chunks, crcs, _, _ = ff.alloc_outputs(plan, DEV)
+    ff.ff_adam_step_snapshot(plan, [torch.zeros_like(w)], dict(HP, lr=0.0, weight_decay=0.0, step=1), chunks, crcs)
+    torch.cuda.synchronize()
+    got = chunks.cpu().numpy()
+    half = torch.from_numpy(master.reshape(-1).view(np.float32)).to(torch.bfloat16).view(torch.int16).numpy()
+    want = np.concatenate([raw.reshape(-1).view(np.uint8), half.view(np.uint8), master.reshape(-1).view(np.uint8),
+                           np.zeros(8 * n, np.uint8)])
+    assert np.array_equal(got[:want.size], want) and not got[want.size:].any()
+    want_crcs = [oracle.crc32c(got[k:k + chunk]) for k in range(0, got.size, chunk)]
+    assert np.array_equal(crcs.cpu().numpy().view(np.uint32), np.array(want_crcs, np.uint32))
