@@ -106,7 +106,8 @@ typedef struct {
 #define FF_RESTORE_VERIFY_ONLY 1u /* recompute and compare CRCs, write bad[]/n_bad, scatter nothing */
 #define FF_RESTORE_SKIP_BAD 2u    /* verify first, then scatter only the chunks whose CRC matched:
                                      tensor ranges covered by a bad chunk keep their old contents
-                                     (the buffer is read twice: 3 B of traffic per payload byte)  */
+                                     (read once on the default stream, twice on others, under
+                                     capture and with chunks of more than 16 MiB)                 */
 
 #define FF_MIN_CHUNK_BYTES 1024ull
 #define FF_MAX_CHUNK_BYTES (1ull << 30)
@@ -127,6 +128,11 @@ int ff_snapshot_plan(const ff_segment *segs, uint64_t n_segs, uint64_t chunk_byt
 /* Frees the plan and its device tables.  NULL is ignored.  The caller must have synchronised
  * every stream that still uses the plan. */
 void ff_plan_destroy(ff_plan *plan);
+
+/* A wavefront of a restore with FF_RESTORE_SKIP_BAD may keep what it has read until its chunk has been
+ * checked.  It looks `polls` times (4096 unless set: a few milliseconds), then checks the chunk by itself.  The
+ * results do not depend on it; 0 makes every wait end at once.  Not to be called beside other calls on the plan. */
+int ff_plan_set_polls(ff_plan *plan, uint32_t polls);
 
 uint64_t ff_plan_payload_bytes(const ff_plan *plan); /* N                                   */
 uint64_t ff_plan_num_chunks(const ff_plan *plan);    /* ceil(N / chunk_bytes)               */

@@ -89,6 +89,7 @@ def lib():
                                        ctypes.POINTER(vp)]
         L.ff_plan_destroy.restype = None
         L.ff_plan_destroy.argtypes = [vp]
+        L.ff_plan_set_polls.restype, L.ff_plan_set_polls.argtypes = i32, [vp, ctypes.c_uint32]
         for name in ("payload_bytes", "num_chunks", "buffer_bytes", "chunk_bytes", "num_segments",
                      "num_params"):
             fn = getattr(L, "ff_plan_" + name)

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -52,6 +53,9 @@ struct ff_plan {
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
     uint64_t* tally = nullptr;  // null: none (tally_size)
+    uint32_t* verdict = nullptr;
+    mutable std::atomic<uint32_t> epoch{0};  // of the last call that waits for verdicts
+    uint32_t polls = kHoldPolls;
 };
 
 namespace {
@@ -122,7 +126,8 @@ int upload_tables(ff_plan* p)
     const uint64_t o_btab = align_up(o_shift + uint64_t(L.tiles_per_chunk) * 4, 256);
     const uint64_t o_tally = align_up(o_btab + kBlockTabWords * 4, 256);
     const uint64_t tally_words = tally_size(L.n_chunks, L.chunk_bytes, L.tile_bytes);
-    const uint64_t total = align_up(o_tally + tally_words * 8, 256);
+    const uint64_t o_verdict = align_up(o_tally + tally_words * 8, 256);
+    const uint64_t total = align_up(o_verdict + (tally_words ? L.n_chunks * 4 : 0), 256);
 
     std::vector<unsigned char> host(total, 0);
     uint64_t* h_off = reinterpret_cast<uint64_t*>(host.data() + o_off);
@@ -167,7 +172,10 @@ int upload_tables(ff_plan* p)
     t.tile_shift = reinterpret_cast<const uint32_t*>(d + o_shift);
     t.tab_u = reinterpret_cast<const uint32_t*>(d + o_tab);
     t.block_tab = reinterpret_cast<const uint32_t*>(d + o_btab);
-    if (tally_words) p->tally = reinterpret_cast<uint64_t*>(d + o_tally);  // zeros
+    if (tally_words) {  // zeros
+        p->tally = reinterpret_cast<uint64_t*>(d + o_tally);
+        p->verdict = reinterpret_cast<uint32_t*>(d + o_verdict);
+    }
     p->work.tiles = reinterpret_cast<const WorkTile*>(d + o_work);
     p->work.waves = reinterpret_cast<const WorkWave*>(d + o_waves);
     // the parameter tiles are sorted by parameter group: where each launch of the step begins
@@ -310,6 +318,13 @@ void ff_plan_destroy(ff_plan* plan)
     delete plan;
 }
 
+int ff_plan_set_polls(ff_plan* p, uint32_t polls)
+{
+    if (!p) return FF_ERR_NULL;
+    p->polls = polls;
+    return FF_OK;
+}
+
 uint64_t ff_plan_payload_bytes(const ff_plan* p) { return p ? p->layout.payload : 0; }
 uint64_t ff_plan_num_chunks(const ff_plan* p) { return p ? p->layout.n_chunks : 0; }
 uint64_t ff_plan_buffer_bytes(const ff_plan* p) { return p ? p->layout.buffer_bytes : 0; }
@@ -386,6 +401,19 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
     void* buf = const_cast<void*>(chunks);
     const bool verify_only = (flags & FF_RESTORE_VERIFY_ONLY) != 0;
     const bool skip_bad = (flags & FF_RESTORE_SKIP_BAD) != 0;
+    if (skip_bad && !verify_only && !list && (t.tile_rows * 1024ull == kDefaultTileBytes || tiles_are_blocks(t)) &&
+        L.chunk_bytes <= hold_chunk_bytes(t) && (t.tally = tally_for(p, s))) {
+        // verified and scattered in one pass
+        t.want = crcs;
+        t.n_bad = n_bad;
+        t.verdict = p->verdict;
+        t.epoch = (p->epoch.fetch_add(1, std::memory_order_relaxed) + 1) & 0x7FFFFFFFu;
+        t.polls = p->polls;
+        t.xcd_group = kHoldXcdGroup;
+        choose_hint(p, t, kRestore, L.buffer_bytes);
+        FF_HIP_TRY(launch_hold(t, buf, s));
+        return FF_OK;
+    }
     if ((verify_only || skip_bad) && !list && verify_chunks_applicable(L.chunk_bytes, L.n_chunks) &&
         L.tile_bytes <= L.chunk_bytes / 8 && L.tile_bytes <= (1u << 16) &&
         (1u << 16) % L.tile_bytes == 0) {

@@ -51,6 +51,7 @@ struct BlockLds {
     u32x4 weight[kRows * 4][kWaveSize];  // of every dword of a lane's slots
     uint32_t sum[kWaves];      // per run (at its first wavefront's place): XOR of its registers
     uint32_t arrived[kWaves];  // wavefronts of the run that have added theirs
+    uint32_t verdict[kWaves];  // on the run's chunk, of a restore that waits for it: 0 none yet, 2 sound, 3 damaged
 };
 
 // A wavefront's own scratch for a block of several tensors.
@@ -197,12 +198,13 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
 }
 
 // One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once, each in
-// the branch it takes.
-template <int MODE, int HINT, class Ready>
+// the branch it takes.  HOLD (restore): the block is folded first, and stored only if permit(), which takes
+// the sums to the tally and waits for the chunk's verdict, says so.
+template <int MODE, int HINT, bool HOLD, class Ready, class Permit>
 __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, GatherLds* gather,
                                            uint8_t* __restrict__ chunks, const uint32_t tile,
                                            const bool folding, const int lane, Ready&& tables_ready,
-                                           f32x16& acc)
+                                           f32x16& acc, Permit&& permit)
 {
     constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
     const uint64_t s = static_cast<uint64_t>(tile) * kBlockBytes;
@@ -224,6 +226,10 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
         if (MODE == kPack)
             static_for<kRows>([&](auto r) { w[r] = load16_unaligned<kSegNT>(tp + (lane16 + 1024 * r)); });
         tables_ready();
+        if (HOLD) {
+            static_for<kRows>([&](auto r) { fold(r); });
+            if (!permit()) return;
+        }
         // Row by row, stored and folded as it arrives: the matrix cores are at work while later rows are on
         // their way.  (Pack / restore of 32 MB with all stores in front of the fold 15.9 / 16.5 us, so
         // 15.0 / 15.6.  In the blocks of several tensors below it is the other way round: restore of 5 KiB
@@ -233,7 +239,7 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
                 store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]);
             else
                 store16_unaligned<kSegNT>(tp + (lane16 + 1024 * r), w[r]);
-            if (!folding) return;
+            if (HOLD || !folding) return;
             __builtin_amdgcn_sched_barrier(0);
             fold(r);
             __builtin_amdgcn_sched_barrier(0);
@@ -254,9 +260,14 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
             }
         }
         const uint32_t n = last - first + 1;
+        if (HOLD && (end == 0 || n > kMaxSegs)) {
+            tables_ready();
+            static_for<kRows>([&](auto r) { fold(r); });
+            if (!permit()) return;
+        }
         if (end == 0) {
             if (MODE == kPack) static_for<kRows>([&](auto r) { w[r] = u32x4{0, 0, 0, 0}; });
-            tables_ready();
+            if (!HOLD) tables_ready();
         } else if (n > kMaxSegs) {
 #pragma unroll 1
             for (int r = 0; r < kRows; r++) {
@@ -266,11 +277,16 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
                                                     s + 1024 * r + lane16, T.payload, x);
                 if (MODE == kPack) static_for<kRows>([&](auto k) { if (k == r) w[k] = x; });
             }
-            tables_ready();
+            if (!HOLD) tables_ready();
         } else {
             GatherLds& G = *gather;
             Place P;
             locate(T, G, first, n, s, end, lane, P);
+            if (HOLD) {
+                tables_ready();
+                static_for<kRows>([&](auto r) { fold(r); });
+                if (!permit()) return;
+            }
             auto slot_in_list = [&](int r) {  // place of this lane's straddling slot of row r
                 uint32_t before = 0;
                 static_for<kRows>([&](auto k) { before += k < r ? __builtin_popcountll(P.straddle[k]) : 0; });
@@ -308,15 +324,15 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
                     if (addr) *as_global(reinterpret_cast<uint16_t*>(addr)) = reinterpret_cast<const u16_alias*>(G.fix)[i];
                 });
             }
-            tables_ready();
+            if (!HOLD) tables_ready();
         }
         if (MODE == kPack)
             static_for<kRows>([&](auto r) { store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]); });
     }
-    if (folding) static_for<kRows>([&](auto r) { fold(r); });
+    if (!HOLD && folding) static_for<kRows>([&](auto r) { fold(r); });
 }
 
-template <int MODE, int HINT, bool LISTED>
+template <int MODE, int HINT, bool LISTED, bool HOLD = false>
 __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restrict__ chunks,
                                            const ChunkList* list)
 {
@@ -331,7 +347,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     });
     auto tables_ready = [&] {
         static_for<kEach>([&](auto i) { (&lds.weight[0][0])[i * kThreads + threadIdx.x] = tab[i]; });
-        if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = 0;
+        if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
         workgroup_barrier();
     };
     const uint32_t slot = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWaves + wave;
@@ -360,21 +376,39 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         shift = T.tile_shift[((tile & (T.tiles_per_chunk - 1)) | (run - 1)) >> T.block_log2];
     }
     f32x16 acc = {};
+    // the block's register on its way; true in the wavefront (lane 0) that has taken the run's to the chunk
+    auto deliver = [&] {
+        uint32_t v = wave_xor(gf2_mul_half(matrix_halves(acc), lane_c));
+        if (lane != 0) return false;
+        if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, v)) return false;
+        v = gf2_mul(v, shift);
+        if (T.tally)
+            tally_run<MODE>(T, v, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run,
+                            (slot >> T.tpc_log2), count >> T.tpc_log2);
+        else
+            atomicXor(T.acc + chunk, v);
+        return true;
+    };
+    // (as in hold.hip: one wavefront of the run waits for the others, and not for ever)
+    auto permit = [&] {
+        volatile uint32_t* const said = &lds.verdict[lead];
+        uint32_t verdict = 0;
+        if (__builtin_amdgcn_readfirstlane(deliver() ? 1u : 0u)) {
+            verdict = await_verdict(T, chunk);
+            if (!verdict) verdict = chunk_is_bad(T, lds.weight, chunks, chunk,
+                                                 T.block_tab[kRows * 4 * kWeightWords + lane], lane) ? 3 : 2;
+            *said = verdict;
+        } else {
+            while (!(verdict = __builtin_amdgcn_readfirstlane(*said))) __builtin_amdgcn_s_sleep(1);
+        }
+        return verdict == 2;
+    };
     if (active)
-        block_rows<MODE, HINT>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
-                               tables_ready, acc);
+        block_rows<MODE, HINT, HOLD>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
+                                     tables_ready, acc, permit);
     else
         tables_ready();
-    if (!active || !folding) return;
-    uint32_t v = wave_xor(gf2_mul_half(matrix_halves(acc), lane_c));
-    if (lane != 0) return;
-    if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, v)) return;
-    v = gf2_mul(v, shift);
-    if (T.tally)
-        tally_run<MODE>(T, v, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run,
-                        (slot >> T.tpc_log2), count >> T.tpc_log2);
-    else
-        atomicXor(T.acc + chunk, v);
+    if (!HOLD && active && folding) deliver();
 }
 
 // (two workgroups on a compute unit: the weights and the scratch of blocks of several tensors leave room for no more)
@@ -382,6 +416,14 @@ template <int MODE, int HINT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
 {
     block_body<MODE, HINT, false>(T, chunks, nullptr);
+}
+
+// Restore of what verifies, in one pass: every wavefront holds its block until its chunk's verdict is there.
+template <int HINT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void block_kernel_held(
+    TileTables T, uint8_t* __restrict__ chunks)
+{
+    block_body<kRestore, HINT, false, true>(T, chunks, nullptr);
 }
 
 // The blocks of the chunks in `list`, which travels in the kernel arguments, instead of a range.
@@ -422,6 +464,15 @@ void build_block_tab(uint32_t* tab)
         uint32_t v = matrix_lane_factor(lane, 8 * 16);
         for (int k = 0; k < kWaves; k++, v = gf2_mul(v, x_block)) lanes[k * kWaveSize + lane] = v;
     }
+}
+
+hipError_t launch_hold_blocks(const TileTables& t, void* chunks, hipStream_t stream)
+{
+    if (!tiles_are_blocks(t) || !t.tally || !t.verdict || !t.acc || t.n_list || t.tile_begin) return hipErrorInvalidValue;
+    const unsigned grid = (t.n_tiles + kWaves - 1) / kWaves;
+    const auto kernel = t.hint == kHintWarm(kRestore) ? block_kernel_held<kHintWarm(kRestore)> : block_kernel_held<3>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, t, static_cast<uint8_t*>(chunks));
+    return hipGetLastError();
 }
 
 hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,

@@ -59,11 +59,13 @@ __device__ __forceinline__ void table_to_lds(const uint32_t* table, u32x4* lds, 
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (FF_LDS void*)(lds + i * THREADS + wave * 64), 16, 16 * lane,
                                                  16 * (i * THREADS + wave * 64), 0, 0);
 }
-// Until every load and store issued by this wavefront has completed.
+// Until no more than LATER of the loads and stores issued by this wavefront are under way.
+template <int LATER>
 __device__ __forceinline__ void wait_loads()
 {
+    static_assert(LATER >= 0 && LATER < 64, "six bits, in two places; the other counters at their largest");
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters at their largest
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (LATER & 15) | (LATER >> 4) << 14);
     __builtin_amdgcn_sched_barrier(0);
 }
 

@@ -166,7 +166,7 @@ __device__ __forceinline__ void fetch_tables(const uint32_t* __restrict__ tabs, 
 }
 __device__ __forceinline__ void tables_ready()
 {
-    wait_loads();
+    wait_loads<0>();
     workgroup_barrier();
     __builtin_amdgcn_sched_barrier(0);
 }

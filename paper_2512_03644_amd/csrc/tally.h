@@ -2,6 +2,7 @@
 #pragma once
 #include "fold.h"
 #include "kernels.hpp"
+#include "matrix_fold.h"
 
 namespace ffsnap {
 
@@ -51,6 +52,8 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
     }
     const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
     T.acc[chunk] = is_bad;
+    if (T.verdict)
+        __hip_atomic_store(T.verdict + chunk, T.epoch << 1 | is_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // how many chunks are done (low half) and how many of them are bad (high half)
     auto count = [](uint64_t* w, uint32_t bad) {
         const uint64_t mine = uint64_t(bad) << 32 | 1u;
@@ -68,6 +71,42 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
     if (static_cast<uint32_t>(now) != (n_groups > 1 ? n_groups : n)) return;
     tally_reset(T.tally);
     *T.n_bad = (T.n_bad_add ? *T.n_bad : 0) + (now >> 32);
+}
+
+// The chunk's verdict, when another wavefront has put it there: 2 sound, 3 damaged; 0 if patience ends.
+__device__ __forceinline__ uint32_t await_verdict(const TileTables& T, const uint32_t chunk)
+{
+    for (uint32_t n = 0; n < T.polls; n++) {
+        const uint32_t v = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(T.verdict + chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if ((v >> 1) == T.epoch) return 2 | (v & 1);
+        __builtin_amdgcn_s_sleep(8);  // 512 clocks
+    }
+    return 0;
+}
+
+// Is the chunk damaged?  By one wavefront alone.  weight: of the rows of an 8 KiB block, in LDS; lane_c: the
+// lane's factor in a block.
+__device__ __forceinline__ bool chunk_is_bad(const TileTables& T, const u32x4 (*weight)[kWaveSize],
+                                             const uint8_t* chunks, const uint32_t chunk, const uint32_t lane_c,
+                                             const int lane)
+{
+    constexpr uint32_t kXBlock = gf2_xpow(8ull * kBlockBytes);
+    constexpr int kBlockRows = kBlockBytes / 1024;
+    const uint32_t rows = static_cast<uint32_t>(T.tile_rows) << T.tpc_log2;
+    const uint8_t* p = chunks + static_cast<uint64_t>(chunk) * rows * 1024 + 16u * lane;
+    uint32_t reg = 0;
+#pragma unroll 1
+    for (uint32_t b = 0; b < rows / kBlockRows; b++) {
+        f32x16 acc = {};
+#pragma unroll 1
+        for (int r = 0; r < kBlockRows; r++, p += 1024) {
+            const u32x4 w = load16_stream<false>(p);
+            static_for<4>([&](auto f) { matrix_add(acc, weight[4 * r + f][lane], w[int(f)]); });
+        }
+        reg = gf2_mul_const<kXBlock>(reg) ^ wave_xor(gf2_mul_half(matrix_halves(acc), lane_c));
+    }
+    return (gf2_mul_const<kX32>(reg) ^ T.affine) != T.want[chunk];
 }
 
 }  // namespace ffsnap

@@ -271,3 +271,61 @@ def test_every_weight_of_the_matrix_product(oracle, chunk):
     assert np.array_equal(chunks.cpu().numpy(), raw) and int(n_bad.item()) == 0
     want = [oracle.crc32c(raw[k:k + chunk]) for k in range(0, raw.size, chunk)]
     assert np.array_equal(_u32(crcs), np.array(want, np.uint32))
+
+
+# Restores that leave damaged chunks out in one pass: tiles inside one tensor on and off the lines, of two to four
+# tensors, of more, at the payload's end and behind it; runs of 1, 2, 4 and 8 wavefronts; waits that end at
+# once; the routes that take two passes (other streams, larger chunks); more chunks than one word counts.
+_HELD = {
+    "whole": [(1 << 20, 2, 0), (3 << 18, 2, 0)],
+    "off": [(1 << 20, 2, 2), (700001, 4, 12), (1 << 19, 2, 14)],
+    "pieces": [(9001 + 7 * i, 2 if i % 3 else 4, (2 * i) % 16 if i % 3 else 4) for i in range(200)],
+    "crowded": [(1 << 19, 2, 6)] + [(900 + i, 2, (2 * i) % 16) for i in range(150)] + [(300000, 4, 8)],
+}
+
+
+@pytest.mark.parametrize("layout", list(_HELD))
+@pytest.mark.parametrize("chunk_log2", [13, 15, 16, 18, 20, 22])
+@pytest.mark.parametrize("tile_log2", [13, 15])
+def test_restore_without_damaged_chunks_in_one_pass(oracle, layout, chunk_log2, tile_log2):
+    chunk = 1 << chunk_log2
+    shard = wl.fragmented_shard(_HELD[layout], chunk, seed=chunk_log2, device=DEV)
+    plan, chunks, crcs, _, _, want_buf, _ = _pack_and_compare(shard, oracle, tile_log2=min(tile_log2, chunk_log2))
+    n = plan.num_chunks
+    damaged = sorted({0, n // 2, n - 1} if n > 3 else {n - 1})
+    for j in damaged:
+        chunks[j * chunk + (911 * j + 5) % chunk] ^= 64
+    want_bad = np.zeros(n, np.uint32)
+    want_bad[damaged] = 1
+    keep = np.repeat(want_bad != 0, chunk)[:plan.payload_bytes]
+    for polls, stream in ((4096, None), (0, None), (4096, torch.cuda.Stream()), (1, None)):
+        ff._check(ff.lib().ff_plan_set_polls(plan.handle, polls))
+        _poison_segments(shard)
+        before = np.concatenate(_host_segments(shard)[0])
+        bad, n_bad = _verify(plan, chunks, crcs, stream, ff.FF_RESTORE_SKIP_BAD)
+        assert np.array_equal(bad, want_bad) and n_bad == len(damaged)
+        got = np.concatenate(_host_segments(shard)[0])
+        assert np.array_equal(got, np.where(keep, before, want_buf[:plan.payload_bytes]))
+
+
+@pytest.mark.parametrize("chunk_log2,nbytes", [(15, 240 << 20), (24, 70 << 20), (25, 200 << 20), (26, 200 << 20)])
+def test_one_pass_over_many_and_over_large_chunks(chunk_log2, nbytes):
+    # 7680 chunks; chunks of 256 workgroups and of one more than the route takes
+    chunk = 1 << chunk_log2
+    g = torch.Generator(device=DEV)
+    g.manual_seed(chunk_log2)
+    t = torch.empty(nbytes // 2 - 1001, dtype=torch.int16, device=DEV).random_(generator=g)
+    src = t.clone()
+    plan = ff.ff_snapshot_plan([t.view(torch.bfloat16)], chunk)
+    chunks, crcs, bad, n_bad = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+    j = plan.num_chunks // 3
+    chunks[j * chunk + 12345] ^= 1
+    for rep in range(3):
+        t.fill_(rep)
+        ff.ff_restore(plan, chunks, crcs, bad, n_bad, ff.FF_RESTORE_SKIP_BAD)
+        torch.cuda.synchronize()
+        assert int(n_bad.item()) == 1 and int(bad.sum().item()) == 1 and int(bad[j].item()) == 1
+        want = src.clone()
+        want[j * chunk // 2:(j + 1) * chunk // 2] = rep
+        assert torch.equal(t, want)
