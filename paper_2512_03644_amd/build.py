@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libffsnap.so")
-SOURCES = ["api.hip", "kernels.hip", "blocks.hip", "hold.hip", "fused.hip", "layout.cpp"]
+SOURCES = ["api.hip", "kernels.hip", "blocks.hip", "fused.hip", "layout.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Wno-align-mismatch",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

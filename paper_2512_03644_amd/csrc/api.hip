@@ -222,6 +222,20 @@ void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
 // launches, gain up to 3 % (verify of 3.2 GB 483 -> 468 us).
 bool pack_takes_tally(const TileTables& t) { return tiles_are_blocks(t); }
 
+// Does a restore that leaves damaged chunks out take one pass (launch_held), given the tally?  In the plan's own
+// tiles, where its verifying pass would be in such tiles as well: blocks up to a medium-sized buffer, and of
+// lists of small tensors of any size (1 GB 544 us in two passes, 492 in one); 32 KiB tiles above.  (A medium
+// buffer on the lines is verified in blocks and scattered in tiles.)  In blocks with a word of the tally for every
+// 32 chunks at most; a tile's wavefronts wait anyway, and however many chunks there are (13,267: 1731 / 1247).
+bool held_in_one_pass(const ff_plan* p, const TileTables& t)
+{
+    const Layout& L = p->layout;
+    const bool medium = L.buffer_bytes <= kMediumBufferBytes;
+    if (L.chunk_bytes > hold_chunk_bytes(t)) return false;
+    if (tiles_are_blocks(t)) return (medium || !p->tile_given) && L.n_chunks <= kTallyChunks;
+    return t.tile_rows * 1024ull == kDefaultTileBytes && (!medium || p->tile_given) && (t.hint & 3) == 3;
+}
+
 int check_device_call(const ff_plan* p)
 {
     if (!p) return FF_ERR_NULL;
@@ -401,9 +415,7 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
     void* buf = const_cast<void*>(chunks);
     const bool verify_only = (flags & FF_RESTORE_VERIFY_ONLY) != 0;
     const bool skip_bad = (flags & FF_RESTORE_SKIP_BAD) != 0;
-    if (skip_bad && !verify_only && !list && (t.tile_rows * 1024ull == kDefaultTileBytes || tiles_are_blocks(t)) &&
-        L.chunk_bytes <= hold_chunk_bytes(t) && (t.tally = tally_for(p, s))) {
-        // verified and scattered in one pass
+    if (skip_bad && !verify_only && !list && held_in_one_pass(p, t) && (t.tally = tally_for(p, s))) {
         t.want = crcs;
         t.n_bad = n_bad;
         t.verdict = p->verdict;
@@ -411,7 +423,7 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         t.polls = p->polls;
         t.xcd_group = kHoldXcdGroup;
         choose_hint(p, t, kRestore, L.buffer_bytes);
-        FF_HIP_TRY(launch_hold(t, buf, s));
+        FF_HIP_TRY(launch_held(t, buf, s));
         return FF_OK;
     }
     if ((verify_only || skip_bad) && !list && verify_chunks_applicable(L.chunk_bytes, L.n_chunks) &&
@@ -427,17 +439,17 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, nullptr));
         return FF_OK;
     }
-    // In blocks: what the plan cuts into blocks anyway, and short lists of chunks of any plan (in blocks
-    // against the plan's 32 KiB tiles, us, tensors on / off the lines: 1 chunk of 4 MiB 10.4 / 10.9 against 11.2 /
-    // 14.6, 8 15.2 / 15.6 against 17.6 / 19.2, 16 26.3 / 27.2 against 29.6 / 32.5, 24 36.5 / 37.4 against 40.8 /
-    // 43.5; 26, with no warm loads above 96 MiB, 45.3 / 47.2 against 44.6 / 49.5, 40 66.1 / 69.5 against 62.5 /
-    // 67.0; verified only, 1-16 chunks 0-7 % behind, 20-48 1-10 % ahead),
+    // In blocks: what the plan cuts into blocks anyway, and lists of chunks of any plan up to 256 MiB a launch
+    // (in blocks against the plan's 32 KiB tiles, us: tensors on the lines 60 / 132 / 165 / 230 / 330 MB 26.3 / 51.1 /
+    // 60.4 / 81.6 / 115.5 against 29.6 / 53.0 / 62.0 / 83.1 / 114.3, 20,000 ragged ones 132 / 163 / 224 / 330 MB 58.4 /
+    // 69.9 / 89.6 / 125.8 against 72.4 / 77.8 / 100.8 / 129.2; verified only, 1-16 chunks of 4 MiB 0-7 % behind with the
+    // byte tables that blocks had, more 1-10 % ahead),
     // and a read-only pass over no more than a medium-sized buffer; over more it is faster on 64 KiB tiles
     // (400 MB: 70 against 76 us).
     const uint64_t bytes = list ? list->n * L.chunk_bytes : L.buffer_bytes;
     const bool pass1 = verify_only || skip_bad;
     const bool divisible = L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes;  // into blocks
-    if (list && bytes <= kWarmBytes && divisible) t = as_blocks(t);
+    if (list && bytes <= kListBytes && divisible) t = as_blocks(t);
     const bool read_in_blocks = bytes <= kMediumBufferBytes && (tiles_are_blocks(t) || (!p->tile_given && divisible));
     // The verifying pass.  With the tally it delivers bad[] and *n_bad itself; else the registers are
     // summed in bad[] between two small kernels.

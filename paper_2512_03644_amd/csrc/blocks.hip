@@ -30,6 +30,7 @@
 #include "kernels.hpp"
 
 #include "fold.h"
+#include "hold.h"
 #include "matrix_fold.h"
 #include "tally.h"
 
@@ -389,7 +390,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
             atomicXor(T.acc + chunk, v);
         return true;
     };
-    // (as in hold.hip: one wavefront of the run waits for the others, and not for ever)
+    // (as in hold.h: one wavefront of the run waits for the others, and not for ever)
     auto permit = [&] {
         volatile uint32_t* const said = &lds.verdict[lead];
         uint32_t verdict = 0;
@@ -466,12 +467,21 @@ void build_block_tab(uint32_t* tab)
     }
 }
 
-hipError_t launch_hold_blocks(const TileTables& t, void* chunks, hipStream_t stream)
+hipError_t launch_held(const TileTables& t, void* chunks, hipStream_t stream)
 {
-    if (!tiles_are_blocks(t) || !t.tally || !t.verdict || !t.acc || t.n_list || t.tile_begin) return hipErrorInvalidValue;
-    const unsigned grid = (t.n_tiles + kWaves - 1) / kWaves;
-    const auto kernel = t.hint == kHintWarm(kRestore) ? block_kernel_held<kHintWarm(kRestore)> : block_kernel_held<3>;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, t, static_cast<uint8_t*>(chunks));
+    if (!t.tally || !t.verdict || !t.acc || t.n_list || t.tile_begin) return hipErrorInvalidValue;
+    uint8_t* const c = static_cast<uint8_t*>(chunks);
+    if (tiles_are_blocks(t)) {
+        const unsigned grid = (t.n_tiles + kWaves - 1) / kWaves;
+        const auto kernel = t.hint == kHintWarm(kRestore) ? block_kernel_held<kHintWarm(kRestore)> : block_kernel_held<3>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, t, c);
+    } else if (t.tile_rows == hold::kRows) {
+        const unsigned grid = (t.n_tiles + hold::kWaves - 1) / hold::kWaves;
+        hipLaunchKernelGGL(hold::tile_kernel_held<3>, dim3(grid), dim3(hold::kThreads), 0, stream, t.seg_off, t.seg_ptr,
+                           t.tile_first_seg, t.tile_base, t.tile_shift, t, c);
+    } else {
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -10,15 +10,15 @@
 // A chunk's workgroups are dealt to the XCDs in short runs, so that they start at about the same time; but
 // nothing promises that all of them are in flight together (other kernels may hold compute units).  So a wait
 // is bounded, and a wavefront whose patience ends reads the whole chunk and finds the verdict by itself.
-#include "kernels.hpp"
-
+#pragma once
 #include "fold.h"
+#include "kernels.hpp"
 #include "matrix_fold.h"
 #include "tally.h"
 
 namespace ffsnap {
 
-namespace {
+namespace hold {
 
 constexpr int kRows = 32;          // of a tile
 constexpr int kBlocks = 4;         // of 8 rows, the unit of the weights
@@ -190,17 +190,16 @@ __device__ __forceinline__ void scatter_tile(const uint64_t* __restrict__ seg_of
 // (The tables as pointers of their own: what is read through them is then known not to change, and comes by
 // scalar loads, which no wait for the rows has to wait for.)
 template <int HINT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void hold_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void tile_kernel_held(
     const uint64_t* __restrict__ seg_off, const uint64_t* __restrict__ seg_ptr,
     const uint32_t* __restrict__ tile_first_seg, const uint64_t* __restrict__ tile_base,
-    const uint32_t* __restrict__ tile_shift, const uint32_t* __restrict__ block_tab, TileTables T,
-    const uint8_t* __restrict__ chunks)
+    const uint32_t* __restrict__ tile_shift, TileTables T, const uint8_t* __restrict__ chunks)
 {
     constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
     __shared__ HoldLds lds;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    table_to_lds<kThreads, sizeof(lds.weight)>(block_tab, &lds.weight[0][0], wave, lane);
+    table_to_lds<kThreads, sizeof(lds.weight)>(T.block_tab, &lds.weight[0][0], wave, lane);
     if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t tile = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWaves + wave;
@@ -210,7 +209,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
         return;
     }
     // the lane's factors in the four blocks, the tile's distance to the end of its chunk
-    const uint32_t* const lane_tab = block_tab + kBlockRows * 4 * kWeightWords + lane;
+    const uint32_t* const lane_tab = T.block_tab + kBlockRows * 4 * kWeightWords + lane;
     uint32_t c[kBlocks];
     static_for<kBlocks>([&](auto b) { c[b] = lane_tab[(kBlocks - 1 - b) * kWaveSize]; });
     const uint32_t in_chunk = tile & (T.tiles_per_chunk - 1), chunk = tile >> T.tpc_log2;
@@ -254,18 +253,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     scatter_tile<kSegNT>(seg_off, seg_ptr, tile_first_seg, T, tile, base, bp, w, lds.ring[wave], lane);
 }
 
-}  // namespace
-
-hipError_t launch_hold(const TileTables& t, void* chunks, hipStream_t stream)
-{
-    if (tiles_are_blocks(t)) return launch_hold_blocks(t, chunks, stream);
-    if (t.tile_rows != kRows || !t.tally || !t.verdict || !t.acc || t.n_list || t.tile_begin) return hipErrorInvalidValue;
-    const unsigned grid = (t.n_tiles + kWaves - 1) / kWaves;
-    const auto kernel = (t.hint & 1) ? ((t.hint & 2) ? hold_kernel<3> : hold_kernel<1>)
-                                     : ((t.hint & 2) ? hold_kernel<2> : hold_kernel<0>);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, t.seg_off, t.seg_ptr, t.tile_first_seg, t.tile_base, t.tile_shift,
-                       t.block_tab, t, static_cast<const uint8_t*>(chunks));
-    return hipGetLastError();
-}
+}  // namespace hold
 
 }  // namespace ffsnap

@@ -59,7 +59,7 @@ struct TileTables {
     const uint32_t* want = nullptr;
     uint64_t* n_bad = nullptr;
     uint32_t n_bad_add = 0;
-    // Who waits for verdicts (hold.hip) finds them here, [n_chunks] of the plan's own words: 2 * epoch, plus 1
+    // Who waits for verdicts (hold.h) finds them here, [n_chunks] of the plan's own words: 2 * epoch, plus 1
     // if the chunk is damaged.  No two calls have the same epoch, so nothing is ever set back.
     uint32_t* verdict = nullptr;
     uint32_t epoch = 0;
@@ -135,7 +135,7 @@ inline bool tiles_are_blocks(const TileTables& t)
 }
 
 // Verifies every chunk and scatters those that verify, reading the buffer once: tables with tiles of 32 KiB
-// (hold.hip) or of blocks (blocks.hip), T.acc, T.tally, T.verdict.  A wavefront keeps its tile until its chunk's
+// (hold.h) or of blocks (blocks.hip), T.acc, T.tally, T.verdict.  A wavefront keeps its tile until its chunk's
 // verdict is there, so the workgroups of a chunk should be in flight together: in runs of kHoldXcdGroup
 // workgroups an XCD (3.2 GB of 20,000 ragged tensors 1190 / 1179 / 1185 / 1248 us with runs of 1 / 8 / 16 / 32, of
 // 3.3 GB in chunks of 8 MiB 1145 / 1131 / 1207 with 4 / 8 / 16), and no more than a third (blocks: half) of
@@ -144,8 +144,7 @@ inline bool tiles_are_blocks(const TileTables& t)
 // and 9.2 / 12.0 / 28.6 / 47.0 / 72; small tensors 60 / 150 / 1000 MB 45.9 / 99 / 544 and 37.9 / 97 / 492.
 constexpr uint32_t kHoldXcdGroup = 8, kHoldPolls = 4096;
 inline uint64_t hold_chunk_bytes(const TileTables& t) { return tiles_are_blocks(t) ? 16ull << 20 : 32ull << 20; }
-hipError_t launch_hold(const TileTables& t, void* chunks, hipStream_t stream);
-hipError_t launch_hold_blocks(const TileTables& t, void* chunks, hipStream_t stream);
+hipError_t launch_held(const TileTables& t, void* chunks, hipStream_t stream);
 
 // Fills tab (host, kBlockTabWords entries): the weights of the 32 dwords of a lane (matrix_fold.h), then
 // for k = 0..7 and every lane its factor for the place of its column in a row, plus k blocks.

@@ -131,6 +131,7 @@ constexpr uint64_t kCrowdedShare = 16;  // blocks if a tile in so many holds mor
 // buffers in turn, plain against non-temporal loads: pack of 8 / 32 / 64 / 128 MB 11.8 / 17.4 / 27.8 / 60.1
 // against 12.1 / 20.9 / 35.7 / 58.5 us, restore 12.2 / 18.8 / 29.9 / 61.0 against 13.6 / 20.5 / 35.5 / 59.3.
 constexpr uint64_t kWarmBytes = 96ull << 20;
+constexpr uint64_t kListBytes = 256ull << 20;  // listed chunks of one launch go in blocks up to here
 constexpr uint64_t kVerifyTileBytes = 1ull << 16;
 
 }  // namespace ffsnap
