@@ -621,7 +621,8 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
 //
 // N: room for so many.  Arguments of 512 bytes instead of 3 KiB save the host 0.2-0.3 us a call (1 / 8 / 64
 // groups 7.4 / 7.9 / 11.0 against 7.7 / 8.1 / 11.2), which shows where a queue of steps is bound by that: 64
-// groups of 100 elements 10.7 against 11.2 us a step, fewer or larger groups the same within 1 %.
+// groups of 100 elements 10.7 against 11.2 us a step, fewer or larger groups the same within 1 %; those of 16 KiB
+// are for the steps that 3 KiB would cut into several launches.
 template <bool F16, bool CHAINED, bool BC2, uint32_t N>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void fused_kernel(
     const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
@@ -892,7 +893,7 @@ void build_fused_tabs(uint32_t* tab)
 
 namespace {
 
-constexpr uint32_t kFewGrads = 64;
+constexpr uint32_t kFewGrads = 64, kSomeGrads = 384;
 
 template <uint32_t N>
 void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTile* tiles,
@@ -963,7 +964,10 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
         } else {
             const uint32_t w0 = work.launch_wave[k], w1 = work.launch_wave[k + 1];
             if (w1 == w0) continue;
-            const auto launch = n_params - p0 <= kFewGrads ? launch_step<kFewGrads> : launch_step<kGradsPerLaunch>;
+            const uint32_t left = n_params - p0;
+            const auto launch = left <= kFewGrads    ? launch_step<kFewGrads>
+                                : left <= kSomeGrads ? launch_step<kSomeGrads>
+                                                     : launch_step<kGradsPerLaunch>;
             launch(f16, work.waves + w0, w1 - w0, work.tiles, grads, p0, n_params, tabs, c, crcs, consts,
                    work.launch_off_lines[k] != 0, stream);
         }

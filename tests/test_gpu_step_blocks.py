@@ -118,3 +118,44 @@ def test_every_weight_of_the_matrix_products(oracle, high):
     assert np.array_equal(got[:want.size], want) and not got[want.size:].any()
     want_crcs = [oracle.crc32c(got[k:k + chunk]) for k in range(0, got.size, chunk)]
     assert np.array_equal(crcs.cpu().numpy().view(np.uint32), np.array(want_crcs, np.uint32))
+
+
+# one room for the gradient pointers, the next, a launch's end and a second launch
+@pytest.mark.parametrize("n", [64, 65, 384, 385, 2047, 2048, 2049, 4100])
+def test_so_many_groups(oracle, n):
+    numels = torch.randint(1, 40, (n,), generator=torch.Generator().manual_seed(n)).tolist()
+    _adam_and_compare(oracle, numels, 1 << 14, seed=n)
+    _chained_and_compare(oracle, numels, 1 << 14, seed=n + 1, steps=2)
+
+
+def test_captured_step_over_many_groups():
+    # 16 KiB of kernel arguments in a graph node: every replay, with eager work between them, equals the eager step
+    numels = [7 + 3 * i for i in range(500)]
+    shard = wl.param_shard("a", numels, 1 << 16, 44, DEV, with_grads=True)
+    plan = ff.plan_for_shard(shard)
+    grads = [p.grad for p in shard.params]
+    chunks, crcs, _, _ = ff.alloc_outputs(plan, DEV)
+
+    def step():
+        ff.ff_adam_step_snapshot(plan, grads, HP, chunks, crcs)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for rep in range(3):
+        start = [t.clone() for t in shard.segments]
+        for t in grads:
+            t.mul_(0.5)
+        chunks.fill_(0xA5)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in shard.segments] + [chunks.clone(), crcs.clone()]
+        for t, s0 in zip(shard.segments, start):
+            t.copy_(s0)
+        chunks.fill_(0xA5)
+        step()
+        torch.cuda.synchronize()
+        for a, b in zip(got, list(shard.segments) + [chunks, crcs]):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), rep
