@@ -54,7 +54,8 @@ struct ff_plan {
     const uint32_t* fused_tabs = nullptr;
     uint64_t* tally = nullptr;  // null: none (tally_size)
     uint32_t* verdict = nullptr;
-    mutable std::atomic<uint32_t> epoch{0};  // of the last call that waits for verdicts
+    uint64_t* state = nullptr;
+    mutable std::atomic<uint64_t> epoch{0};  // of the last call with verdicts
     uint32_t polls = kHoldPolls;
 };
 
@@ -127,7 +128,12 @@ int upload_tables(ff_plan* p)
     const uint64_t o_tally = align_up(o_btab + kBlockTabWords * 4, 256);
     const uint64_t tally_words = tally_size(L.n_chunks, L.chunk_bytes, L.tile_bytes);
     const uint64_t o_verdict = align_up(o_tally + tally_words * 8, 256);
-    const uint64_t total = align_up(o_verdict + (tally_words ? L.n_chunks * 4 : 0), 256);
+    const uint64_t o_state = align_up(o_verdict + (tally_words ? L.n_chunks * 4 : 0), 256);
+    // runs of 8 blocks in a chunk of any plan whose tiles can be divided into blocks
+    const uint64_t run_bytes = std::min<uint64_t>(L.chunk_bytes, kMaxBlockTileBytes);
+    const uint64_t runs = L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes ? L.chunk_bytes / run_bytes : 0;
+    const uint64_t o_runs = align_up(o_state + 8, 256);
+    const uint64_t total = align_up(o_runs + runs * 32 * 4, 256);
 
     std::vector<unsigned char> host(total, 0);
     uint64_t* h_off = reinterpret_cast<uint64_t*>(host.data() + o_off);
@@ -152,6 +158,7 @@ int upload_tables(ff_plan* p)
     }
     build_tab_u(reinterpret_cast<uint32_t*>(host.data() + o_tab));
     build_block_tab(reinterpret_cast<uint32_t*>(host.data() + o_btab));
+    build_run_tab(reinterpret_cast<uint32_t*>(host.data() + o_runs), runs, run_bytes);
     if (!work.empty()) std::memcpy(host.data() + o_work, work.data(), work.size() * sizeof(WorkTile));
     if (!waves.empty())
         std::memcpy(host.data() + o_waves, waves.data(), waves.size() * sizeof(WorkWave));
@@ -172,9 +179,11 @@ int upload_tables(ff_plan* p)
     t.tile_shift = reinterpret_cast<const uint32_t*>(d + o_shift);
     t.tab_u = reinterpret_cast<const uint32_t*>(d + o_tab);
     t.block_tab = reinterpret_cast<const uint32_t*>(d + o_btab);
+    t.run_tab = reinterpret_cast<const uint32_t*>(d + o_runs);
     if (tally_words) {  // zeros
         p->tally = reinterpret_cast<uint64_t*>(d + o_tally);
         p->verdict = reinterpret_cast<uint32_t*>(d + o_verdict);
+        p->state = reinterpret_cast<uint64_t*>(d + o_state);
     }
     p->work.tiles = reinterpret_cast<const WorkTile*>(d + o_work);
     p->work.waves = reinterpret_cast<const WorkWave*>(d + o_waves);
@@ -221,6 +230,14 @@ void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
 // of ragged tensors 1.097 against 1.107, 256 MB 98.8 both).  Restore and verify, which save two
 // launches, gain up to 3 % (verify of 3.2 GB 483 -> 468 us).
 bool pack_takes_tally(const TileTables& t) { return tiles_are_blocks(t); }
+
+uint64_t next_epoch(const ff_plan* p) { return p->epoch.fetch_add(1, std::memory_order_relaxed) + 1; }
+void count_directly(const ff_plan* p, TileTables& t, uint64_t n)
+{
+    if (!tiles_are_blocks(t) || n > kDirectChunks) return;
+    t.direct = 1;
+    t.state = p->state;
+}
 
 // Does a restore that leaves damaged chunks out take one pass (launch_held), given the tally?  In the plan's own
 // tiles, where its verifying pass would be in such tiles as well: blocks up to a medium-sized buffer, and of
@@ -419,7 +436,8 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         t.want = crcs;
         t.n_bad = n_bad;
         t.verdict = p->verdict;
-        t.epoch = (p->epoch.fetch_add(1, std::memory_order_relaxed) + 1) & 0x7FFFFFFFu;
+        t.epoch = next_epoch(p);
+        count_directly(p, t, L.n_chunks);
         t.polls = p->polls;
         t.xcd_group = kHoldXcdGroup;
         choose_hint(p, t, kRestore, L.buffer_bytes);
@@ -470,6 +488,10 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
     v.want = crcs;
     v.n_bad = n_bad;
     v.n_bad_add = clear_n_bad ? 0 : 1;
+    if (v.tally) {
+        v.epoch = next_epoch(p);
+        count_directly(p, v, list ? list->n : L.n_chunks);
+    }
     if (!v.tally)
         FF_HIP_TRY(launch_preset(bad, crcs, 0, L.n_chunks, p->affine, clear_n_bad ? n_bad : nullptr, list, s));
     FF_HIP_TRY(launch_tiles(pass1 ? kVerify : kRestore, v, buf, s, list));

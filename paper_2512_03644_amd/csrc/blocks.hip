@@ -39,7 +39,8 @@ namespace ffsnap {
 namespace {
 
 constexpr int kRows = kBlockBytes / 1024;
-constexpr int kWaves = 8;
+constexpr int kWaves = 8, kWavesLog2 = 3;
+static_assert(kWaves == 1 << kWavesLog2);
 constexpr int kThreads = kWaves * kWaveSize;
 constexpr int kSlots = kBlockBytes / 16;
 constexpr uint32_t kMaxSegs = 128;  // tensors of a block that the table holds
@@ -366,25 +367,31 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         if (T.skip_bad) active = !__builtin_amdgcn_readfirstlane(T.skip_bad[chunk]);
     }
     // the wavefronts of this workgroup that are at the same chunk
-    const uint32_t run = T.tiles_per_chunk < uint32_t(kWaves) ? T.tiles_per_chunk : uint32_t(kWaves);
+    const uint32_t run_log2 = T.tpc_log2 < uint32_t(kWavesLog2) ? T.tpc_log2 : uint32_t(kWavesLog2);
+    const uint32_t run = 1u << run_log2, run_index = (tile & (T.tiles_per_chunk - 1)) >> run_log2;
     const uint32_t in_run = wave & (run - 1), lead = wave - in_run;
     const bool folding = T.acc != nullptr;
-    uint32_t lane_c = 0, shift = 0;
+    uint32_t lane_c = 0, bit_at_end = 0;
     if (folding) {
-        // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and the
-        // run's own distance to the end of its chunk (times the x^32 that the register lacks)
+        // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and what bit
+        // `lane` of the run's register is at the end of the chunk
         lane_c = T.block_tab[kRows * 4 * kWeightWords + (run - 1 - in_run) * kWaveSize + lane];
-        shift = T.tile_shift[((tile & (T.tiles_per_chunk - 1)) | (run - 1)) >> T.block_log2];
+        bit_at_end = T.run_tab[run_index * 32 + (lane & 31)];
     }
     f32x16 acc = {};
     // the block's register on its way; true in the wavefront (lane 0) that has taken the run's to the chunk
     auto deliver = [&] {
         uint32_t v = wave_xor(gf2_mul_half(matrix_halves(acc), lane_c));
+        if (run > 1) {
+            uint32_t complete = 0;
+            if (lane == 0) complete = run_complete(lds.sum[lead], lds.arrived[lead], run, v) ? 1u : 0u;
+            if (!__builtin_amdgcn_readfirstlane(complete)) return false;
+            v = __builtin_amdgcn_readfirstlane(v);
+        }
+        v = wave_xor(lane < 32 && ((v >> lane) & 1u) ? bit_at_end : 0u);
         if (lane != 0) return false;
-        if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, v)) return false;
-        v = gf2_mul(v, shift);
         if (T.tally)
-            tally_run<MODE>(T, v, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run,
+            tally_run<MODE>(T, v, chunk, run_index, T.tiles_per_chunk >> run_log2,
                             (slot >> T.tpc_log2), count >> T.tpc_log2);
         else
             atomicXor(T.acc + chunk, v);
@@ -404,6 +411,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         }
         return verdict == 2;
     };
+    if (MODE != kPack && T.direct && !T.n_bad_add && slot == gridDim.x * kWaves - 1 && lane == 0) open_count(T);
     if (active)
         block_rows<MODE, HINT, HOLD>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
                                      tables_ready, acc, permit);
@@ -451,6 +459,16 @@ void launch(const TileTables& t, uint8_t* chunks, unsigned grid, hipStream_t str
 
 }  // namespace
 
+void build_run_tab(uint32_t* tab, uint64_t runs, uint64_t run_bytes)
+{
+    uint32_t end = kX32;
+    const uint32_t x_run = gf2_xpow(8 * run_bytes);
+    for (uint64_t k = runs; k-- > 0; end = gf2_mul(end, x_run)) {
+        uint32_t v = end;
+        for (int i = 31; i >= 0; i--, v = gf2_mulx(v)) tab[32 * k + i] = v;
+    }
+}
+
 void build_block_tab(uint32_t* tab)
 {
     // a dword enters times x^(8 * bytes from its end to the end of the last row's slot of lane 31 or 63)
@@ -467,12 +485,19 @@ void build_block_tab(uint32_t* tab)
     }
 }
 
+// Workgroups for `count` blocks; with T.direct one more, whose last wavefront has nothing else to do than to open
+// the count.
+static unsigned grid_of(const TileTables& t, TileMode mode, uint64_t count)
+{
+    return static_cast<unsigned>((count + kWaves - 1) / kWaves) + (mode != kPack && t.direct && !t.n_bad_add ? 1u : 0u);
+}
+
 hipError_t launch_held(const TileTables& t, void* chunks, hipStream_t stream)
 {
     if (!t.tally || !t.verdict || !t.acc || t.n_list || t.tile_begin) return hipErrorInvalidValue;
     uint8_t* const c = static_cast<uint8_t*>(chunks);
     if (tiles_are_blocks(t)) {
-        const unsigned grid = (t.n_tiles + kWaves - 1) / kWaves;
+        const unsigned grid = grid_of(t, kRestore, t.n_tiles);
         const auto kernel = t.hint == kHintWarm(kRestore) ? block_kernel_held<kHintWarm(kRestore)> : block_kernel_held<3>;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, t, c);
     } else if (t.tile_rows == hold::kRows) {
@@ -493,7 +518,7 @@ hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipSt
     if (count == 0) return hipSuccess;
     if (t.tile_rows != kRows || (list && (list->n > kMaxListedChunks || mode == kPack)) || count > 0x7FFFFFF0ull)
         return hipErrorInvalidValue;
-    const unsigned grid = static_cast<unsigned>((count + kWaves - 1) / kWaves);
+    const unsigned grid = grid_of(t, mode, count);
     if (list) {
         const auto restore = t.hint == kHintWarm(kRestore) ? block_kernel_listed<kRestore, kHintWarm(kRestore)>
                                                            : block_kernel_listed<kRestore, 3>;

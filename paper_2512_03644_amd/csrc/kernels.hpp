@@ -19,6 +19,10 @@ constexpr uint32_t kTallyFan = 32;
 // 18.8 / 21.3; 6080 (190 MB) 75.6 / 77.7, 41.1 / 41.6; 8000 (1 GB) 338.6 / 337.5, 166.1 / 164.2; 8192 (64 MB)
 // 31.0 / 28.1, 22.5 / 21.3; 64000 (1 GB) 476.8 / 464.1, 316 / 300.
 constexpr uint64_t kTallyChunks = 6144;
+// Verdicts on so many chunks in blocks are not counted one by one, level above level at 0.7 us each: the damaged ones
+// alone are (7 chunks 6.7 us with the count, 6.0 without; 78 chunks 12.0 and 10.8).  On more chunks a buffer that is
+// damaged all over would be bound by the one word that they are counted on, at 50 ns each.
+constexpr uint32_t kDirectChunks = 128;
 // Words of a plan's tally (0: none), enough for runs of 8 blocks of 8 KiB and of 4 tiles of the plan's size
 // or more.  None if its chunks have more runs than there are levels for, or its tiles are smaller than a
 // block: those are bound by what a tile costs beyond its bytes, and a returning atomic each is too much
@@ -40,6 +44,8 @@ struct TileTables {
     const uint64_t* tile_base = nullptr;      // [n_tiles] tensor-side address of a tile that lies
                                               // inside one segment, else 0 (may be absent)
     const uint32_t* block_tab = nullptr;      // tables of the 8 KiB blocks (build_block_tab)
+    const uint32_t* run_tab = nullptr;        // [runs of 8 blocks in a chunk][32]: what bit i of a run's register
+                                              // is at the end of the chunk (build_run_tab)
     const uint32_t* tab_u = nullptr;          // [4][256] multiply-by-x^8192 byte tables, then
                                               // [64] lane constants x^(128 * (63 - lane))
     // Where a tile's register goes.  acc set: XORed (atomically) into acc[chunk of the tile], an
@@ -59,10 +65,15 @@ struct TileTables {
     const uint32_t* want = nullptr;
     uint64_t* n_bad = nullptr;
     uint32_t n_bad_add = 0;
-    // Who waits for verdicts (hold.h) finds them here, [n_chunks] of the plan's own words: 2 * epoch, plus 1
-    // if the chunk is damaged.  No two calls have the same epoch, so nothing is ever set back.
+    // The call's number in the plan: no two calls have the same, so what is marked with it is never set back.
+    // Who waits for verdicts (hold.h) finds them in verdict, [n_chunks] of the plan's own words: 2 * epoch, plus 1
+    // if the chunk is damaged (its low 31 bits do: every call writes every word).
+    uint64_t epoch = 0;
     uint32_t* verdict = nullptr;
-    uint32_t epoch = 0;
+    // Verdicts without the levels of the tally above its chunks (open_count in tally.h); state: a word of the
+    // plan's, 2 * epoch and more from when *n_bad is being set to zero.
+    uint64_t* state = nullptr;
+    uint32_t direct = 0;
     uint32_t polls = 0;       // how often one looks before it finds the verdict by itself
     uint32_t affine = 0;      // preset/complement term of a chunk
     uint32_t n_chunks = 0;
@@ -150,6 +161,13 @@ hipError_t launch_held(const TileTables& t, void* chunks, hipStream_t stream);
 // for k = 0..7 and every lane its factor for the place of its column in a row, plus k blocks.
 constexpr int kBlockTabWords = 32 * 4 * 64 + 8 * 64;
 void build_block_tab(uint32_t* tab);
+
+// Fills tab (host): for the k-th of `runs` runs of run_bytes bytes of a chunk, words 32 k + i = x^(31 - i) *
+// x^(32 + 8 * bytes from the run's end to the chunk's).  A run's register is one lane's, and a product of 32
+// dependent steps took it 0.5-0.7 us at the end of every small call; with its bits spread over the lanes it is one
+// word each and an XOR over the lanes (pack / restore of 32 MB 15.5 / 16.0 -> 14.9 / 15.3 us, verify of 3.2 MB 7.2 ->
+// 6.7).
+void build_run_tab(uint32_t* tab, uint64_t runs, uint64_t run_bytes);
 
 // out[j] = affine (crcs null: pack) or affine ^ crcs[j] (verify) for chunks [first, first + n), or
 // for the listed chunks; *n_bad = 0 if n_bad is not null.  The tiles then XOR their registers in.

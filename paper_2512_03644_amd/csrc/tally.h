@@ -14,9 +14,36 @@ __device__ __forceinline__ uint64_t tally_xor(uint64_t* word, uint32_t bit, uint
     const uint64_t mine = uint64_t(bit) << 32 | v;
     return atomicXor(reinterpret_cast<unsigned long long*>(word), mine) ^ mine;
 }
+__device__ __forceinline__ uint32_t verdict_word(const TileTables& T) { return static_cast<uint32_t>(T.epoch) << 1; }
 __device__ __forceinline__ void tally_reset(uint64_t* word)
 {
     __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The count of damaged chunks without a count of all (T.direct): whoever finds one adds it to *n_bad, which has to
+// be zero by then.  Whoever comes first and finds another call's number in the state puts this call's there, sets
+// *n_bad to zero and says so; who comes in between waits for that one, which is running and waits for nobody.
+// (Numbers are compared for equality only: two host threads may enqueue their calls in another order
+// than they got their numbers in.)
+__device__ __forceinline__ void open_count(const TileTables& T)
+{
+    unsigned long long* const state = reinterpret_cast<unsigned long long*>(T.state);
+    const unsigned long long claimed = 2 * T.epoch, ready = claimed + 1;
+    auto look = [&] { return __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    for (unsigned long long seen = look();;) {
+        if (seen == ready) return;
+        if (seen == claimed) {
+            __builtin_amdgcn_s_sleep(1);
+            seen = look();
+            continue;
+        }
+        const unsigned long long before = atomicCAS(state, seen, claimed);
+        if (before == seen) break;
+        seen = before;
+    }
+    const unsigned long long old = atomicExch(reinterpret_cast<unsigned long long*>(T.n_bad), 0ull);
+    asm volatile("" ::"v"(old) : "memory");  // the exchange has been done when its result is here
+    __hip_atomic_store(state, ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.
@@ -53,7 +80,13 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
     const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
     T.acc[chunk] = is_bad;
     if (T.verdict)
-        __hip_atomic_store(T.verdict + chunk, T.epoch << 1 | is_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(T.verdict + chunk, verdict_word(T) | is_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (T.direct) {
+        if (!is_bad) return;
+        if (!T.n_bad_add) open_count(T);
+        atomicAdd(reinterpret_cast<unsigned long long*>(T.n_bad), 1ull);
+        return;
+    }
     // how many chunks are done (low half) and how many of them are bad (high half)
     auto count = [](uint64_t* w, uint32_t bad) {
         const uint64_t mine = uint64_t(bad) << 32 | 1u;
@@ -79,7 +112,7 @@ __device__ __forceinline__ uint32_t await_verdict(const TileTables& T, const uin
     for (uint32_t n = 0; n < T.polls; n++) {
         const uint32_t v = __builtin_amdgcn_readfirstlane(
             __hip_atomic_load(T.verdict + chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if ((v >> 1) == T.epoch) return 2 | (v & 1);
+        if ((v & ~1u) == verdict_word(T)) return 2 | (v & 1);
         __builtin_amdgcn_s_sleep(8);  // 512 clocks
     }
     return 0;

@@ -329,3 +329,36 @@ def test_one_pass_over_many_and_over_large_chunks(chunk_log2, nbytes):
         want = src.clone()
         want[j * chunk // 2:(j + 1) * chunk // 2] = rep
         assert torch.equal(t, want)
+
+
+# verdicts counted one by one (128 chunks in a launch) and level by level (more), of which none, some or all are
+# damaged, in changing order; lists of more chunks than one launch takes add to the count
+@pytest.mark.parametrize("n_chunks", [1, 2, 127, 128, 129, 300])
+@pytest.mark.parametrize("chunk_log2", [13, 16])
+def test_count_of_damaged_chunks(n_chunks, chunk_log2):
+    chunk = 1 << chunk_log2
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n_chunks)
+    t = torch.empty(n_chunks * chunk // 2 - 3, dtype=torch.int16, device=DEV).random_(generator=g)
+    plan = ff.ff_snapshot_plan([t.view(torch.bfloat16)], chunk)
+    chunks, crcs, bad, n_bad = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+    rng = np.random.default_rng(n_chunks)
+    for share in (1.0, 0.0, 0.3, 1.0, 0.02, 0.0):
+        hit = np.flatnonzero(rng.random(n_chunks) < share)
+        at = torch.from_numpy(hit * chunk + rng.integers(0, chunk, hit.size)).to(DEV)
+        chunks[at] ^= 8
+        want = np.zeros(n_chunks, np.uint32)
+        want[hit] = 1
+        for flags in (ff.FF_RESTORE_VERIFY_ONLY, 0, ff.FF_RESTORE_SKIP_BAD):
+            bad.fill_(7)
+            n_bad.fill_(99)
+            ff.ff_restore(plan, chunks, crcs, bad, n_bad, flags)
+            torch.cuda.synchronize()
+            assert np.array_equal(_u32(bad), want) and int(n_bad.item()) == hit.size
+        bad.fill_(7)
+        n_bad.fill_(99)
+        ff.ff_restore_chunks(plan, chunks, crcs, list(range(n_chunks)), bad, n_bad, ff.FF_RESTORE_VERIFY_ONLY)
+        torch.cuda.synchronize()
+        assert np.array_equal(_u32(bad), want) and int(n_bad.item()) == hit.size
+        chunks[at] ^= 8
