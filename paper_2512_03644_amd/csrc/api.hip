@@ -29,8 +29,9 @@ constexpr uint64_t kNoallocMaxTiles = FF_CRC32C_NOALLOC_MAX_BYTES / (1024ull * k
 static __device__ __align__(256) uint32_t scratch[kTabWords + kNoallocMaxTiles];
 
 // Calls on a plan read it, and the device tables behind it.  What a call needs beyond them travels in
-// kernel arguments or lives in the caller's own output arrays, with one exception: the tally, where
-// the calls on the default stream sum up their chunks in a single launch.  Every call leaves it as it
+// kernel arguments or lives in the caller's own output arrays, with one exception: the tallies, where
+// the calls on the default stream sum up their chunks in a single launch (with the verdicts and states
+// beside them, which are marked with the call's number).  Every call leaves it as it
 // found it, all zero, and calls on one stream do not overlap.
 struct ff_plan {
     Layout layout;
@@ -54,7 +55,7 @@ struct ff_plan {
     const uint32_t* fused_tabs = nullptr;
     uint64_t* tally = nullptr;  // null: none (tally_size)
     uint32_t* verdict = nullptr;
-    uint64_t* state = nullptr;
+    uint64_t *state = nullptr, *step_state = nullptr;
     mutable std::atomic<uint64_t> epoch{0};  // of the last call with verdicts
     uint32_t polls = kHoldPolls;
 };
@@ -133,7 +134,20 @@ int upload_tables(ff_plan* p)
     const uint64_t run_bytes = std::min<uint64_t>(L.chunk_bytes, kMaxBlockTileBytes);
     const uint64_t runs = L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes ? L.chunk_bytes / run_bytes : 0;
     const uint64_t o_runs = align_up(o_state + 8, 256);
-    const uint64_t total = align_up(o_runs + runs * 32 * 4, 256);
+    // a step in one launch
+    std::vector<StepTicket> step_runs, step_heads;
+    uint64_t step_words = 0;
+    if (waves.empty() || waves.size() > kTallyStepGroups * kWavesPerGroup || L.params.size() > kGradsPerLaunch ||
+        !build_step_tickets(work, waves, L.n_chunks, step_runs, step_heads, step_words)) {
+        step_runs.clear();
+        step_heads.clear();
+        step_words = 0;
+    }
+    const uint64_t o_sruns = align_up(o_runs + runs * 32 * 4, 256);
+    const uint64_t o_sheads = align_up(o_sruns + step_runs.size() * sizeof(StepTicket), 256);
+    const uint64_t o_stally = align_up(o_sheads + step_heads.size() * sizeof(StepTicket), 256);
+    const uint64_t o_sstate = align_up(o_stally + step_words * 8, 256);
+    const uint64_t total = align_up(o_sstate + 8, 256);
 
     std::vector<unsigned char> host(total, 0);
     uint64_t* h_off = reinterpret_cast<uint64_t*>(host.data() + o_off);
@@ -163,6 +177,10 @@ int upload_tables(ff_plan* p)
     if (!waves.empty())
         std::memcpy(host.data() + o_waves, waves.data(), waves.size() * sizeof(WorkWave));
     build_fused_tabs(reinterpret_cast<uint32_t*>(host.data() + o_ftabs));
+    if (step_words) {
+        std::memcpy(host.data() + o_sruns, step_runs.data(), step_runs.size() * sizeof(StepTicket));
+        std::memcpy(host.data() + o_sheads, step_heads.data(), step_heads.size() * sizeof(StepTicket));
+    }
 
     FF_HIP_TRY(hipGetDevice(&p->device));
     hipError_t e = hipMalloc(&p->dev_block, total);
@@ -184,6 +202,12 @@ int upload_tables(ff_plan* p)
         p->tally = reinterpret_cast<uint64_t*>(d + o_tally);
         p->verdict = reinterpret_cast<uint32_t*>(d + o_verdict);
         p->state = reinterpret_cast<uint64_t*>(d + o_state);
+    }
+    if (step_words) {
+        p->work.runs = reinterpret_cast<const StepTicket*>(d + o_sruns);
+        p->work.heads = reinterpret_cast<const StepTicket*>(d + o_sheads);
+        p->work.tally = reinterpret_cast<uint64_t*>(d + o_stally);  // zeros
+        p->step_state = reinterpret_cast<uint64_t*>(d + o_sstate);
     }
     p->work.tiles = reinterpret_cast<const WorkTile*>(d + o_work);
     p->work.waves = reinterpret_cast<const WorkWave*>(d + o_waves);
@@ -208,16 +232,17 @@ int upload_tables(ff_plan* p)
 // flight, and the next one created may get the same handle and run beside it.  Two calls that overlap
 // on the tally would leave it with bits that no later call accounts for.  The default stream is one
 // queue (the per-thread one has a handle of its own) and is never destroyed.
-uint64_t* tally_for(const ff_plan* p, hipStream_t s)
+bool tally_allowed(hipStream_t s)
 {
-    if (s != nullptr) return nullptr;
+    if (s != nullptr) return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
-        return nullptr;
+        return false;
     }
-    return st == hipStreamCaptureStatusNone ? p->tally : nullptr;
+    return st == hipStreamCaptureStatusNone;
 }
+uint64_t* tally_for(const ff_plan* p, hipStream_t s) { return tally_allowed(s) ? p->tally : nullptr; }
 
 // Cache hint of a pass of `mode` over `bytes` of the buffer.
 void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
@@ -558,6 +583,16 @@ int adam_impl(const ff_plan* p, const void* const* grads, const ff_adam_hparams*
     c.xcd_group = bare ? p->mix_xcd_group : prev ? p->chained_xcd_group : p->fused_xcd_group;
     c.n_nonfinite = n_nonfinite;
     c.prev = static_cast<const uint8_t*>(prev);
+    if (!bare && p->work.tally && tally_allowed(s)) {
+        c.tally = p->work.tally;
+        c.runs = p->work.runs;
+        c.heads = p->work.heads;
+        c.state = p->step_state;
+        c.epoch = next_epoch(p);
+        c.payload = L.payload;
+        c.buffer_bytes = L.buffer_bytes;
+        c.affine = p->affine;
+    }
     FF_HIP_TRY(launch_fused(half_dtype == FF_F16, p->work, grads,
                             static_cast<uint32_t>(L.params.size()), p->fused_tabs, chunks, crcs,
                             L.n_chunks, L.payload, L.buffer_bytes, p->affine, c, bare, s));

@@ -411,7 +411,8 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         }
         return verdict == 2;
     };
-    if (MODE != kPack && T.direct && !T.n_bad_add && slot == gridDim.x * kWaves - 1 && lane == 0) open_count(T);
+    if (MODE != kPack && T.direct && !T.n_bad_add && slot == gridDim.x * kWaves - 1 && lane == 0)
+        open_count(T.state, T.epoch, T.n_bad);
     if (active)
         block_rows<MODE, HINT, HOLD>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
                                      tables_ready, acc, permit);

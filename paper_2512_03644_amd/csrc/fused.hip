@@ -14,7 +14,9 @@
 // The sub-blocks of a tile that share a workgroup sum their registers in LDS; the last one to arrive
 // multiplies the sums by x^(8 * distance to the end of the chunk) and XORs them into crcs[chunk] with
 // an atomic; XOR is commutative, so the result does not depend on the order in which tiles finish.  A
-// prepare kernel sets crcs[] to the preset/complement term and writes the zero tail of the last chunk.
+// prepare kernel sets crcs[] to the preset/complement term and writes the zero tail of the last chunk; a short
+// step on the default stream does without it: its contributions meet in the plan's tally (add_to_tally), and
+// workgroups of its own clear the tail.
 //
 // What bounds it: the memory system's handling of 4 load and 8 (chained: 5) store streams at once, and how
 // well it does depends on where the tensors lie: one 7B shard in place takes 5.5 or 6.5 ms from one
@@ -46,6 +48,7 @@
 
 #include "fold.h"
 #include "matrix_fold.h"
+#include "tally.h"
 
 namespace ffsnap {
 
@@ -143,12 +146,45 @@ static_assert(2 * (sizeof(Lds) + kImgBytes) <= kLds && 3 * (sizeof(Lds) + kImgBy
 // Tile registers come out of the folds without the factor x^32 that a CRC register carries.
 constexpr uint32_t kX16 = gf2_xpow(16);
 
+// A contribution to its chunk's checksum, by a lane: whoever completes the chunk writes it.
+__device__ __forceinline__ void add_to_tally(const FusedConsts& C, const StepTicket k, uint32_t* __restrict__ crcs,
+                                             const uint32_t chunk, uint32_t v)
+{
+    uint64_t now = tally_xor(C.tally + k.leaf, 1u << (k.bits & 31u), v);
+    if ((now >> 32) != k.leaf_full) return;
+    tally_reset(C.tally + k.leaf);
+    const uint32_t leaves = (k.bits >> 8) & 63u;
+    if (leaves > 1) {
+        now = tally_xor(C.tally + k.root, 1u << ((k.bits >> 16) & 31u), static_cast<uint32_t>(now));
+        if ((now >> 32) != (leaves == 32 ? 0xFFFFFFFFu : (1u << leaves) - 1)) return;
+        tally_reset(C.tally + k.root);
+    }
+    crcs[chunk] = static_cast<uint32_t>(now) ^ C.affine;
+}
+
+// The ticket of stream x of the run that begins at a wavefront entry (wave-uniform).  By scalar loads, whatever the
+// compiler can tell about the pointer: a vector load would wait for every store in front of it.
+__device__ __forceinline__ StepTicket run_ticket(const FusedConsts& C, const uint32_t run_entry, const int x)
+{
+    const auto* const t = (const __attribute__((address_space(4))) u32x4*)(C.runs + 4 * run_entry);
+    u32x4 k = t[0];
+    static_for<3>([&](auto i) {
+        const u32x4 other = t[i + 1];
+        static_for<4>([&](auto j) { k[int(j)] = x == i + 1 ? other[int(j)] : k[int(j)]; });
+    });
+    return StepTicket{k.x, k.y, k.z, k.w};
+}
+
 // Head piece: the first two bytes of a split element, which are the last two bytes of their
 // chunk.  In the low half of a dword they read M(x) * x^16, and their register is M(x) * x^32.
-__device__ __forceinline__ void add_head_piece(uint32_t* __restrict__ crcs, const WorkTile& t,
-                                               int piece, uint32_t low_half)
+__device__ __forceinline__ void add_head_piece(const FusedConsts& C, uint32_t* __restrict__ crcs, const WorkTile& t,
+                                               const uint32_t tile, int piece, uint32_t low_half)
 {
-    atomicXor(&crcs[t.chunk[piece]], gf2_mul_const<kX16>(low_half));
+    const uint32_t v = gf2_mul_const<kX16>(low_half);
+    if (C.tally)
+        add_to_tally(C, C.heads[3 * tile + piece - 4], crcs, t.chunk[piece], v);
+    else
+        atomicXor(&crcs[t.chunk[piece]], v);
 }
 
 // The weights on their way to LDS, first thing.  tables_ready() is a barrier of the workgroup, behind a
@@ -173,8 +209,8 @@ __device__ __forceinline__ void tables_ready()
 
 // Sum of the registers of a parameter tile's run; in the run's last wavefront, on to memory.  v: the lanes
 // of row j (of 16) hold the register of stream j.
-__device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t info, uint32_t v,
-                                        uint32_t* __restrict__ crcs, int lane)
+__device__ __forceinline__ void deliver(const FusedConsts& C, Lds& lds, const WorkTile& t, uint32_t info, uint32_t v,
+                                        const uint32_t run_entry, uint32_t* __restrict__ crcs, int lane)
 {
     const int x = lane & 3;  // from here on lane x has stream x
     static_for<3>([&](auto k) {
@@ -205,7 +241,12 @@ __device__ __forceinline__ void deliver(Lds& lds, const WorkTile& t, uint32_t in
         v ^= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
         n = 1;
     }
-    if (lane < n) atomicXor(&crcs[c], v);
+    if (lane < n) {
+        if (C.tally)
+            add_to_tally(C, run_ticket(C, run_entry, x), crcs, c, v);
+        else
+            atomicXor(&crcs[c], v);
+    }
 }
 
 // ---- parameter sub-block -------------------------------------------------------------------------
@@ -309,7 +350,8 @@ __device__ __forceinline__ void store_image(const WorkTile& t, const uint8_t* im
 // (the slot that holds lo) and 4-7 (the slot that holds hi), and handed to the lanes that own those
 // slots.  What is not the tile's counts as zero.
 template <bool F16, bool CHAINED, bool BC2, bool WHOLE>
-__device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_t info, const int at,
+__device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_t tile, const uint32_t info,
+                                                const uint32_t run_entry, const int at,
                                                 const int lo, const int hi,
                                                 const uint8_t* __restrict__ grad,
                                                 uint8_t* __restrict__ chunks,
@@ -486,7 +528,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     auto dword = [&](auto r, u32x4 RowIn::*x, auto stream, auto f) -> uint32_t {
         uint32_t d = (q[r].*x)[int(f)];
         if (!WHOLE && head && r * kRowElems + 4 * lane == edge_lo && f == (lo & 3) && (t.head_split >> stream & 1u)) {
-            add_head_piece(crcs, t, 3 + stream, d & 0xFFFFu);
+            add_head_piece(C, crcs, t, tile, 3 + stream, d & 0xFFFFu);
             d &= 0xFFFF0000u;
         }
         return d;
@@ -524,7 +566,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         matrix_take(bits, m);
         matrix_take(bits, v);
     }
-    deliver(lds, t, info, row_xor(matrix_streams(bits, lane_c0, lane_c)), crcs, lane);
+    deliver(C, lds, t, info, row_xor(matrix_streams(bits, lane_c0, lane_c)), run_entry, crcs, lane);
 
     if (by_image) {
         workgroup_barrier();
@@ -538,9 +580,11 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         if (C.n_nonfinite && __any(nonfinite != 0)) {
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) nonfinite += __shfl_xor(nonfinite, d);
-            if (lane == 0)
+            if (lane == 0) {
+                if (C.tally) open_count(C.state, C.epoch, C.n_nonfinite);
                 atomicAdd(reinterpret_cast<unsigned long long*>(C.n_nonfinite),
                           static_cast<unsigned long long>(nonfinite));
+            }
         }
     }
 }
@@ -553,7 +597,9 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
 // slot that holds lo) and 8-15 (the one that holds hi), and handed to its owner for the CRC.
 __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t info, const int at,
                                               const int lo, const int hi, uint8_t* __restrict__ chunks,
-                                              uint32_t* __restrict__ crcs, Lds& lds, const uint32_t* __restrict__ lane_tab, int lane)
+                                              uint32_t* __restrict__ crcs, const FusedConsts& C,
+                                              const uint32_t run_entry, Lds& lds,
+                                              const uint32_t* __restrict__ lane_tab, int lane)
 {
     const int sub = info & 15u;
     // x^(8 * bytes between the end of the lane's slot and the end of the block)
@@ -612,7 +658,27 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
     if (lane != 0) return;
     const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
     if (len > 1 && !run_complete(lds.sum[run][0], lds.arrived[run], len, v)) return;
-    atomicXor(&crcs[t.chunk[0]], v);
+    if (C.tally)
+        add_to_tally(C, run_ticket(C, run_entry, 0), crcs, t.chunk[0], v);
+    else
+        atomicXor(&crcs[t.chunk[0]], v);
+}
+
+// The buffer's end, workgroup by workgroup, and the counter.
+constexpr int kTailSlots = 8 * kThreads;
+__device__ __forceinline__ void clear_tail(const FusedConsts& C, uint8_t* __restrict__ chunks, const uint32_t part)
+{
+    const uint64_t first = (C.payload + 15) & ~uint64_t(15);  // chunks is 16-byte aligned, payload even
+    if (part == 0) {
+        if (threadIdx.x < (first - C.payload) / 2) reinterpret_cast<uint16_t*>(chunks + C.payload)[threadIdx.x] = 0;
+        if (threadIdx.x == kThreads - 1 && C.n_nonfinite) open_count(C.state, C.epoch, C.n_nonfinite);
+    }
+    u32x4* const slots = reinterpret_cast<u32x4*>(chunks + first);
+    const uint64_t n = (C.buffer_bytes - first) / 16;
+    static_for<kTailSlots / kThreads>([&](auto i) {
+        const uint64_t j = uint64_t(part) * kTailSlots + i * kThreads + threadIdx.x;
+        if (j < n) slots[j] = u32x4{0, 0, 0, 0};
+    });
 }
 
 // The gradient pointers of the parameter groups [grad_base, grad_base + kGradsPerLaunch) travel by
@@ -634,8 +700,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
+    if (C.tally && group >= C.n_groups) {
+        clear_tail(C, chunks, group - C.n_groups);
+        return;
+    }
     fetch_tables(tabs, lds, wave, lane);
     const WorkWave e = waves[group * kWavesPerBlock + wave];
+    const uint32_t run_entry = group * kWavesPerBlock + ((e.info >> 4) & 7u);
     if (e.tile == kNoTile) {
         tables_ready();
         return;
@@ -650,7 +721,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
         const int lo = at < 0 ? -at : 0;
         const int left = static_cast<int>(t.n) - at;
         raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
-                      crcs, lds, lane_tab + 32 * 64, lane);
+                      crcs, C, run_entry, lds, lane_tab + 32 * 64, lane);
         return;
     }
     const int at = sub * int(kSubElems) - static_cast<int>(t.e0 % kParamTileElems);
@@ -659,10 +730,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     const int hi = left < int(kSubElems) ? left : int(kSubElems);
     const uint8_t* const grad = reinterpret_cast<const uint8_t*>(grads.p[t.grad_index - grad_base]);
     if (lo == 0 && hi == int(kSubElems) && !(t.head_split && at == 0))
-        param_sub_block<F16, CHAINED, BC2, true>(t, e.info, at, lo, hi, grad, chunks, crcs, C, lds, img,
+        param_sub_block<F16, CHAINED, BC2, true>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
                                             lane_tab, wave, lane);
     else
-        param_sub_block<F16, CHAINED, BC2, false>(t, e.info, at, lo, hi, grad, chunks, crcs, C, lds, img,
+        param_sub_block<F16, CHAINED, BC2, false>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
                                              lane_tab, wave, lane);
 }
 
@@ -912,9 +983,15 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
     // of 5000 elements 12.0 us from registers, 13.9 through the image; 32 of 32,768 15.6 and 17.2; 64 of 30,011
     // 23.5 and 23.4) and off the lines (30 odd-sized parameters 2921 from registers, 2700 through it; aligned, 64 of
     // 100,000 58 and 64, 13 of 5 million 514 and 517).
-    const unsigned groups = n_waves / kWavesPerGroup;
-    const bool at_once = groups <= 3 * kComputeUnits;
+    unsigned groups = n_waves / kWavesPerGroup;
     FusedConsts c = consts;
+    if (c.tally) {
+        c.n_groups = groups;
+        const uint64_t tail = c.buffer_bytes - c.payload;
+        groups += static_cast<unsigned>((tail / 16 + kTailSlots - 1) / kTailSlots);
+        if (groups == c.n_groups && (tail || c.n_nonfinite)) groups++;
+    }
+    const bool at_once = groups <= 3 * kComputeUnits;
     c.image = !consts.prev && off_lines && !at_once;
     GradPtrsOf<N> g;
     for (uint32_t i = 0; i < N; i++)
@@ -932,7 +1009,7 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
 {
     uint8_t* c = static_cast<uint8_t*>(chunks);
     hipError_t e = hipSuccess;
-    if (!bare) {
+    if (!bare && !consts.tally) {
         const uint64_t slots = (buffer_bytes - payload) / 16;
         const uint64_t prep_items = n_chunks > slots ? n_chunks : slots;
         unsigned prep_blocks = static_cast<unsigned>((prep_items + 255) / 256);

@@ -22,6 +22,14 @@ struct FusedConsts {
     // offsets) instead of their tensors, and those tensors are not written.  Null: in-place step.
     const uint8_t* prev = nullptr;
     uint32_t image = 0;  // in-place step: whole workgroups store their fp32 streams through LDS
+    // A step in one launch (tally set): its contributions to crcs[] meet in words of the plan's, which are zero before
+    // and after; workgroups from n_groups on clear the buffer's end and *n_nonfinite (open_count in tally.h).
+    uint64_t* tally = nullptr;
+    const StepTicket* runs = nullptr;
+    const StepTicket* heads = nullptr;
+    uint64_t* state = nullptr;
+    uint64_t epoch = 0, payload = 0, buffer_bytes = 0;
+    uint32_t affine = 0, n_groups = 0;
 };
 
 // Device table of the fused kernels (kFusedTabWords entries): weights (matrix_fold.h) of the dwords of two
@@ -37,6 +45,12 @@ void build_fused_tabs(uint32_t* tab);
 // and its share of the host's time: with 384 to a launch / with 2048, us, 2000 ragged groups of 115 million elements in fp16
 // 1032 / 972, 27 million 292 / 235 (chained 224 / 171), 0.2 million 127 / 114, 500 groups of 6 million 70 / 63 (57 / 48).
 constexpr uint32_t kGradsPerLaunch = 2048;
+// Steps of up to so many workgroups go in one launch on the default stream, without the kernel that sets crcs[] and
+// clears the buffer's end (2 us).  With it / without, us, in place: 10 workgroups 11.3 / 9.5, 128 12.3 / 10.1, 35 fp16
+// parameters and 300 RAW tensors 24.6 / 23.5, 750 32.0 / 30.0, 1480 57.7 / 56.1, 2450 82.6 / 81.5, 2940 96.9 / 97.3;
+// chained 750 30.4 / 24.6, 1480 44.4 / 40.2, 2450 62.6 / 59.3, 2940 73.1 / 72.6.  In longer launches a workgroup's
+// returning atomics hold up the next one's start.
+constexpr uint64_t kTallyStepGroups = 2560;
 template <uint32_t N>
 struct GradPtrsOf {
     uint64_t p[N];
@@ -51,9 +65,14 @@ struct FusedWork {
     std::vector<uint32_t> launch_tile;     // parameter tiles only
     std::vector<uint32_t> launch_wave;
     std::vector<uint8_t> launch_off_lines; // most elements have an fp32 stream off the 128-byte lines
+    // of a plan whose step may go in one launch
+    const StepTicket* runs = nullptr;
+    const StepTicket* heads = nullptr;
+    uint64_t* tally = nullptr;
 };
 
-// Enqueues prepare (crcs = affine, zero tail, counter = 0) and the tile kernels.
+// Enqueues prepare (crcs = affine, zero tail, counter = 0) and the tile kernels; with consts.tally the tile kernel
+// alone.
 // tabs: device table (build_fused_tabs).  grads: HOST array of n_params device pointers, read
 // during the call only.  f16: gradients and working weights are fp16 (else bf16).  bare: the
 // step's traffic alone -- every parameter tile's loads and stores with no arithmetic and no CRC

@@ -288,6 +288,50 @@ bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
     return true;
 }
 
+bool build_step_tickets(const std::vector<WorkTile>& tiles, const std::vector<WorkWave>& waves, uint64_t n_chunks,
+                        std::vector<StepTicket>& runs, std::vector<StepTicket>& heads, uint64_t& words)
+{
+    runs.assign(4 * waves.size(), StepTicket{});
+    heads.assign(3 * tiles.size(), StepTicket{});
+    std::vector<uint32_t> count(n_chunks, 0);
+    // in two passes: a contribution's place in its chunk first (in root, for now), with the chunk in leaf
+    auto take = [&](StepTicket& t, uint32_t chunk) {
+        t.leaf = chunk;
+        t.root = count[chunk]++;
+        t.leaf_full = 1;  // taken
+    };
+    for (size_t i = 0; i < waves.size(); i++) {
+        if (waves[i].tile == kNoTile || i % kWavesPerGroup != ((waves[i].info >> 4) & 7u)) continue;
+        const WorkTile& t = tiles[waves[i].tile];
+        const bool one = t.kind == kWorkRaw ||
+                         (t.chunk[0] == t.chunk[1] && t.chunk[0] == t.chunk[2] && t.chunk[0] == t.chunk[3]);
+        for (int x = 0; x < (one ? 1 : 4); x++) take(runs[4 * i + x], t.chunk[x]);
+    }
+    for (size_t i = 0; i < tiles.size(); i++)
+        for (int x = 1; x < 4; x++)
+            if (tiles[i].kind == kWorkParam && (tiles[i].head_split >> x & 1u)) take(heads[3 * i + x - 1], tiles[i].chunk[3 + x]);
+    std::vector<uint32_t> base(n_chunks);
+    words = 0;
+    for (uint64_t c = 0; c < n_chunks; c++) {
+        const uint32_t leaves = (count[c] + 31) / 32;
+        if (leaves > 32) return false;
+        base[c] = static_cast<uint32_t>(words);
+        words += leaves + (leaves > 1 ? 1 : 0);
+    }
+    auto place = [&](StepTicket& t) {
+        if (!t.leaf_full) return;
+        const uint32_t chunk = t.leaf, k = t.root, n = count[chunk], leaves = (n + 31) / 32, leaf = k / 32;
+        const uint32_t here = leaf + 1 < leaves ? 32 : n - 32 * leaf;
+        t.leaf = base[chunk] + leaf;
+        t.leaf_full = here == 32 ? 0xFFFFFFFFu : (1u << here) - 1;
+        t.bits = k % 32 | leaves << 8 | leaf << 16;
+        t.root = base[chunk] + leaves;
+    };
+    for (StepTicket& t : runs) place(t);
+    for (StepTicket& t : heads) place(t);
+    return true;
+}
+
 bool mostly_off_lines(const WorkTile* tiles, uint64_t n)
 {
     uint64_t off = 0, all = 0;

@@ -96,6 +96,19 @@ bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
                       uint32_t groups_per_launch, std::vector<WorkWave>& out,
                       std::vector<uint32_t>& begin, uint64_t max_entries = kMaxWorkEntries);
 
+// Where a contribution to a chunk's checksum goes in a step that sums them up in 64-bit words (tally.h): leaf words of
+// up to 32 contributions each, and above a chunk's leaves, if there are several, a root.
+struct StepTicket {
+    uint32_t leaf, leaf_full;  // the word, and its upper half when everything is there
+    uint32_t bits;             // bits 0..4 the contribution's bit in it, 8..13 leaves of the chunk, 16..20 the leaf's bit in the root
+    uint32_t root;             // the word above, if there are several leaves
+};
+// Contributions of the step with these work lists: for every wavefront entry that begins a run four tickets (streams
+// 0 to 3; the first alone if all streams are in one chunk, or for RAW), for every tile three (its head pieces, streams
+// 1 to 3), others left at zero.  words: how many words there are.  False if a chunk has more than 1024 contributions.
+bool build_step_tickets(const std::vector<WorkTile>& tiles, const std::vector<WorkWave>& waves, uint64_t n_chunks,
+                        std::vector<StepTicket>& runs, std::vector<StepTicket>& heads, uint64_t& words);
+
 // Do most elements of these parameter tiles have an fp32 stream, in place or in the snapshot, whose rows lie
 // off its 128-byte lines?  (A buffer that is itself on a line is assumed.)
 bool mostly_off_lines(const WorkTile* tiles, uint64_t n);

@@ -25,10 +25,10 @@ __device__ __forceinline__ void tally_reset(uint64_t* word)
 // *n_bad to zero and says so; who comes in between waits for that one, which is running and waits for nobody.
 // (Numbers are compared for equality only: two host threads may enqueue their calls in another order
 // than they got their numbers in.)
-__device__ __forceinline__ void open_count(const TileTables& T)
+__device__ __forceinline__ void open_count(uint64_t* state_word, const uint64_t epoch, uint64_t* n)
 {
-    unsigned long long* const state = reinterpret_cast<unsigned long long*>(T.state);
-    const unsigned long long claimed = 2 * T.epoch, ready = claimed + 1;
+    unsigned long long* const state = reinterpret_cast<unsigned long long*>(state_word);
+    const unsigned long long claimed = 2 * epoch, ready = claimed + 1;
     auto look = [&] { return __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     for (unsigned long long seen = look();;) {
         if (seen == ready) return;
@@ -41,7 +41,7 @@ __device__ __forceinline__ void open_count(const TileTables& T)
         if (before == seen) break;
         seen = before;
     }
-    const unsigned long long old = atomicExch(reinterpret_cast<unsigned long long*>(T.n_bad), 0ull);
+    const unsigned long long old = atomicExch(reinterpret_cast<unsigned long long*>(n), 0ull);
     asm volatile("" ::"v"(old) : "memory");  // the exchange has been done when its result is here
     __hip_atomic_store(state, ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -83,7 +83,7 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
         __hip_atomic_store(T.verdict + chunk, verdict_word(T) | is_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (T.direct) {
         if (!is_bad) return;
-        if (!T.n_bad_add) open_count(T);
+        if (!T.n_bad_add) open_count(T.state, T.epoch, T.n_bad);
         atomicAdd(reinterpret_cast<unsigned long long*>(T.n_bad), 1ull);
         return;
     }

@@ -159,3 +159,52 @@ def test_captured_step_over_many_groups():
         torch.cuda.synchronize()
         for a, b in zip(got, list(shard.segments) + [chunks, crcs]):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), rep
+
+
+# one launch on the default stream, two on others: chunks of one contribution, of one word of 32, of several, and of
+# more than the words take (a parameter of 1221 workgroups in one chunk); a long end to clear; again and again
+@pytest.mark.parametrize("chunk,numels", [(1 << 10, [100, 3]), (1 << 19, [4096 * 31 + 5]), (1 << 22, [4096 * 40 + 1, 77, 4096 * 12]),
+                                          (1 << 25, [4096 * 300 + 9, 2]), (1 << 27, [5000001])])
+@pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
+def test_step_in_one_launch_and_in_two(chunk, numels, half):
+    kinds = [ff.FF_KIND_W16, ff.FF_KIND_MASTER, ff.FF_KIND_M, ff.FF_KIND_V] * len(numels) + [ff.FF_KIND_RAW]
+    pids = [k for k in range(len(numels)) for _ in range(4)] + [0]
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(chunk)
+
+    def rand(n, std, dtype=torch.float32):
+        return torch.randn(n, device=DEV, generator=gen).mul_(std).to(dtype)
+
+    segs = []
+    for n in numels:
+        segs += [rand(n, 0.02, half), rand(n, 0.02), rand(n, 1e-3), rand(n, 1e-3).square_()]
+    segs.append(rand(1001, 1.0, torch.bfloat16))
+    grads = [rand(n, 1e-3, half) for n in numels]
+    n_inf = 0
+    if half == torch.float16:
+        grads[0][::3].fill_(float("inf"))
+        n_inf = (numels[0] + 2) // 3
+    plan = ff.ff_snapshot_plan(segs, chunk, 0, kinds, pids)
+    start, got = [t.clone() for t in segs], []
+    side = torch.cuda.Stream()
+    count = torch.zeros(1, dtype=torch.int64, device=DEV)
+    chunks, crcs, _, _ = ff.alloc_outputs(plan, DEV)
+    for stream in (None, None, side, None, side):
+        for t, s0 in zip(segs, start):
+            t.copy_(s0)
+        chunks.fill_(0xA5)
+        crcs.fill_(7)
+        count.fill_(99)
+        torch.cuda.synchronize()
+        if half == torch.float16:
+            ff.ff_adam_step_snapshot_f16(plan, grads, HP, 1.0, count, chunks, crcs, stream=stream)
+        else:
+            ff.ff_adam_step_snapshot(plan, grads, HP, chunks, crcs, stream=stream)
+        torch.cuda.synchronize()
+        if half == torch.float16:
+            assert int(count.item()) == n_inf
+        assert not chunks[plan.payload_bytes:].any()
+        out = [chunks.clone(), crcs.clone()] + [t.clone() for t in segs]
+        got = got or out
+        for a, b in zip(got, out):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
