@@ -104,6 +104,20 @@ int scratch_for_current_device(uint32_t** out)
 }
 
 
+// The tables that do not depend on a plan, made once: the tile kernels', the blocks' and the step's, one behind the
+// other (0.4 ms of work).
+const std::vector<uint32_t>& common_tables()
+{
+    static const std::vector<uint32_t> all = [] {
+        std::vector<uint32_t> t(kTabWords + kBlockTabWords + kFusedTabWords);
+        build_tab_u(t.data());
+        build_block_tab(t.data() + kTabWords);
+        build_fused_tabs(t.data() + kTabWords + kBlockTabWords);
+        return t;
+    }();
+    return all;
+}
+
 int upload_tables(ff_plan* p)
 {
     const Layout& L = p->layout;
@@ -170,13 +184,14 @@ int upload_tables(ff_plan* p)
             v = gf2_mul(v, x_tile);
         }
     }
-    build_tab_u(reinterpret_cast<uint32_t*>(host.data() + o_tab));
-    build_block_tab(reinterpret_cast<uint32_t*>(host.data() + o_btab));
+    const uint32_t* const common = common_tables().data();
+    std::memcpy(host.data() + o_tab, common, kTabWords * 4);
+    std::memcpy(host.data() + o_btab, common + kTabWords, kBlockTabWords * 4);
     build_run_tab(reinterpret_cast<uint32_t*>(host.data() + o_runs), runs, run_bytes);
     if (!work.empty()) std::memcpy(host.data() + o_work, work.data(), work.size() * sizeof(WorkTile));
     if (!waves.empty())
         std::memcpy(host.data() + o_waves, waves.data(), waves.size() * sizeof(WorkWave));
-    build_fused_tabs(reinterpret_cast<uint32_t*>(host.data() + o_ftabs));
+    std::memcpy(host.data() + o_ftabs, common + kTabWords + kBlockTabWords, kFusedTabWords * 4);
     if (step_words) {
         std::memcpy(host.data() + o_sruns, step_runs.data(), step_runs.size() * sizeof(StepTicket));
         std::memcpy(host.data() + o_sheads, step_heads.data(), step_heads.size() * sizeof(StepTicket));
