@@ -49,8 +49,13 @@ static_assert(kMaxSegs <= 256, "a place in the table is 8 bits");
 typedef uint16_t u16_alias __attribute__((may_alias));
 typedef u32x4 u32x4_alias __attribute__((may_alias));
 
+// LEAN: the weights of the last four rows alone.  The first four are taken on their own with the same, as a register
+// that lies four rows further from the end; 110 instructions more for a block, but room for a third workgroup
+// on a compute unit beside the scratch of blocks of several tensors.
+template <bool LEAN>
 struct BlockLds {
-    u32x4 weight[kRows * 4][kWaveSize];  // of every dword of a lane's slots
+    static constexpr int kFirstRow = LEAN ? kRows / 2 : 0;
+    u32x4 weight[(kRows - kFirstRow) * 4][kWaveSize];  // of every dword of a lane's slots, from that row on
     uint32_t sum[kWaves];      // per run (at its first wavefront's place): XOR of its registers
     uint32_t arrived[kWaves];  // wavefronts of the run that have added theirs
     uint32_t verdict[kWaves];  // on the run's chunk, of a restore that waits for it: 0 none yet, 2 sound, 3 damaged
@@ -202,11 +207,11 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
 // One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once, each in
 // the branch it takes.  HOLD (restore): the block is folded first, and stored only if permit(), which takes
 // the sums to the tally and waits for the chunk's verdict, says so.
-template <int MODE, int HINT, bool HOLD, class Ready, class Permit>
-__device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, GatherLds* gather,
+template <int MODE, int HINT, bool HOLD, bool LEAN, class Ready, class Permit>
+__device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& lds, GatherLds* gather,
                                            uint8_t* __restrict__ chunks, const uint32_t tile,
                                            const bool folding, const int lane, Ready&& tables_ready,
-                                           f32x16& acc, Permit&& permit)
+                                           f32x16& acc, uint32_t& first_half, Permit&& permit)
 {
     constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
     const uint64_t s = static_cast<uint64_t>(tile) * kBlockBytes;
@@ -216,7 +221,13 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
     if (MODE != kPack)
         static_for<kRows>([&](auto r) { w[r] = load16_stream<kBufNT>(bp + (lane16 + 1024 * r)); });
     auto fold = [&](auto r) {
-        static_for<4>([&](auto f) { matrix_add(acc, lds.weight[4 * r + f][lane], w[r][int(f)]); });
+        constexpr int first = BlockLds<LEAN>::kFirstRow, row = r < first ? r : r - first;
+        static_for<4>([&](auto f) { matrix_add(acc, lds.weight[4 * row + f][lane], w[r][int(f)]); });
+        if constexpr (LEAN && r == first - 1) {
+            first_half = matrix_halves(acc);
+            acc = f32x16{};
+        }
+        if (LEAN) __builtin_amdgcn_sched_barrier(0);  // (the weights of one row at a time)
     };
     const uint32_t entry = tile >> T.block_log2;  // of the plan's tables
     const uint32_t sub = tile - (entry << T.block_log2);
@@ -334,18 +345,19 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds& lds, G
     if (!HOLD && folding) static_for<kRows>([&](auto r) { fold(r); });
 }
 
-template <int MODE, int HINT, bool LISTED, bool HOLD = false>
+template <int MODE, int HINT, bool LISTED, bool HOLD = false, bool LEAN = false>
 __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restrict__ chunks,
                                            const ChunkList* list)
 {
-    __shared__ BlockLds lds;
+    __shared__ BlockLds<LEAN> lds;
+    constexpr int kFirst = BlockLds<LEAN>::kFirstRow * 4 * kWaveSize;  // of the weights, as 16-byte words
     __shared__ GatherLds gather[MODE == kVerify ? 1 : kWaves];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    constexpr int kEach = kRows * 4 * kWaveSize / kThreads;
+    constexpr int kEach = (kRows * 4 * kWaveSize - kFirst) / kThreads;
     u32x4 tab[kEach];
     static_for<kEach>([&](auto i) {
-        tab[i] = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + i * kThreads + threadIdx.x);
+        tab[i] = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + kFirst + i * kThreads + threadIdx.x);
     });
     auto tables_ready = [&] {
         static_for<kEach>([&](auto i) { (&lds.weight[0][0])[i * kThreads + threadIdx.x] = tab[i]; });
@@ -371,17 +383,21 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     const uint32_t run = 1u << run_log2, run_index = (tile & (T.tiles_per_chunk - 1)) >> run_log2;
     const uint32_t in_run = wave & (run - 1), lead = wave - in_run;
     const bool folding = T.acc != nullptr;
-    uint32_t lane_c = 0, bit_at_end = 0;
+    uint32_t lane_c = 0, lane_c_first = 0, bit_at_end = 0;
     if (folding) {
         // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and what bit
         // `lane` of the run's register is at the end of the chunk
         lane_c = T.block_tab[kRows * 4 * kWeightWords + (run - 1 - in_run) * kWaveSize + lane];
+        if (LEAN) lane_c_first = T.block_tab[kRows * 4 * kWeightWords + (kWaves + run - 1 - in_run) * kWaveSize + lane];
         bit_at_end = T.run_tab[run_index * 32 + (lane & 31)];
     }
     f32x16 acc = {};
+    uint32_t first_half = 0;
     // the block's register on its way; true in the wavefront (lane 0) that has taken the run's to the chunk
     auto deliver = [&] {
-        uint32_t v = wave_xor(gf2_mul_half(matrix_halves(acc), lane_c));
+        uint32_t v = gf2_mul_half(matrix_halves(acc), lane_c);
+        if (LEAN) v ^= gf2_mul_half(first_half, lane_c_first);
+        v = wave_xor(v);
         if (run > 1) {
             uint32_t complete = 0;
             if (lane == 0) complete = run_complete(lds.sum[lead], lds.arrived[lead], run, v) ? 1u : 0u;
@@ -403,6 +419,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         uint32_t verdict = 0;
         if (__builtin_amdgcn_readfirstlane(deliver() ? 1u : 0u)) {
             verdict = await_verdict(T, chunk);
+            static_assert(!HOLD || !LEAN, "all weights");
             if (!verdict) verdict = chunk_is_bad(T, lds.weight, chunks, chunk,
                                                  T.block_tab[kRows * 4 * kWeightWords + lane], lane) ? 3 : 2;
             *said = verdict;
@@ -414,8 +431,8 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     if (MODE != kPack && T.direct && !T.n_bad_add && slot == gridDim.x * kWaves - 1 && lane == 0)
         open_count(T.state, T.epoch, T.n_bad);
     if (active)
-        block_rows<MODE, HINT, HOLD>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
-                                     tables_ready, acc, permit);
+        block_rows<MODE, HINT, HOLD, LEAN>(T, lds, &gather[MODE == kVerify ? 0 : wave], chunks, tile, folding, lane,
+                                     tables_ready, acc, first_half, permit);
     else
         tables_ready();
     if (!HOLD && active && folding) deliver();
@@ -426,6 +443,15 @@ template <int MODE, int HINT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void block_kernel(TileTables T, uint8_t* __restrict__ chunks)
 {
     block_body<MODE, HINT, false>(T, chunks, nullptr);
+}
+
+// Three of them, for packs of several rounds: two / three, us, 600-byte tensors 150 / 300 MB 69.3 / 65.5, 127.1 / 120.4 (with
+// byte tables, three workgroups, 68.8, 125.3), ragged ones of 3.3 KB 123.0 / 116.7, 60 of 2.5 MB off the lines 62.4 / 60.8,
+// 1 GB of 2.5 KB 374 / 372.  A restore spills for it and is 0-4 % slower.
+template <int MODE, int HINT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void block_kernel_lean(TileTables T, uint8_t* __restrict__ chunks)
+{
+    block_body<MODE, HINT, false, false, true>(T, chunks, nullptr);
 }
 
 // Restore of what verifies, in one pass: every wavefront holds its block until its chunk's verdict is there.
@@ -482,7 +508,11 @@ void build_block_tab(uint32_t* tab)
     uint32_t* const lanes = tab + 4 * kRows * kWeightWords;
     for (int lane = 0; lane < kWaveSize; lane++) {
         uint32_t v = matrix_lane_factor(lane, 8 * 16);
-        for (int k = 0; k < kWaves; k++, v = gf2_mul(v, x_block)) lanes[k * kWaveSize + lane] = v;
+        const uint32_t x_half = gf2_xpow(4ull * kBlockBytes);
+        for (int k = 0; k < kWaves; k++, v = gf2_mul(v, x_block)) {
+            lanes[k * kWaveSize + lane] = v;
+            lanes[(kWaves + k) * kWaveSize + lane] = gf2_mul(v, x_half);
+        }
     }
 }
 
@@ -527,6 +557,10 @@ hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipSt
                                                          : block_kernel_listed<kVerify, 3>;
         hipLaunchKernelGGL(mode == kRestore ? restore : verify, dim3(grid), dim3(kThreads), 0, stream, t, c, *list);
     } else {
+        if (mode == kPack && count > kLeanBlocks && t.hint == 3) {
+            hipLaunchKernelGGL((block_kernel_lean<kPack, 3>), dim3(grid), dim3(kThreads), 0, stream, t, c);
+            return hipGetLastError();
+        }
         switch (mode) {
         case kPack: launch<kPack>(t, c, grid, stream); break;
         case kRestore: launch<kRestore>(t, c, grid, stream); break;

@@ -158,8 +158,10 @@ inline uint64_t hold_chunk_bytes(const TileTables& t) { return tiles_are_blocks(
 hipError_t launch_held(const TileTables& t, void* chunks, hipStream_t stream);
 
 // Fills tab (host, kBlockTabWords entries): the weights of the 32 dwords of a lane (matrix_fold.h), then
-// for k = 0..7 and every lane its factor for the place of its column in a row, plus k blocks.
-constexpr int kBlockTabWords = 32 * 4 * 64 + 8 * 64;
+// for k = 0..7 and every lane its factor for the place of its column in a row, plus k blocks, and the same
+// plus half a block.
+constexpr int kBlockTabWords = 32 * 4 * 64 + 2 * 8 * 64;
+constexpr uint64_t kLeanBlocks = 16384;  // packs of more blocks take half the weights (block_kernel_lean)
 void build_block_tab(uint32_t* tab);
 
 // Fills tab (host): for the k-th of `runs` runs of run_bytes bytes of a chunk, words 32 k + i = x^(31 - i) *

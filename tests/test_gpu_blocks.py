@@ -362,3 +362,24 @@ def test_count_of_damaged_chunks(n_chunks, chunk_log2):
         torch.cuda.synchronize()
         assert np.array_equal(_u32(bad), want) and int(n_bad.item()) == hit.size
         chunks[at] ^= 8
+
+
+def test_pack_of_more_blocks_with_half_the_weights(oracle):
+    # one bit in every block of 160 MB, at every place of a block in turn, and tensors that begin anywhere
+    n = 20000
+    words = torch.zeros((n, 2048), dtype=torch.int32, device=DEV)
+    k = torch.arange(n, device=DEV)
+    at = k % 2048
+    words[k, at] = (torch.ones_like(k) << ((at // 4 + k // 2048) % 31)).to(torch.int32)
+    flat = words.view(torch.int16).reshape(-1).view(torch.bfloat16)
+    cuts = [0, 700001, 700002, 3000000] + list(range(3100001, 3400000, 1501)) + [flat.numel()]
+    segs = [flat[a:b] for a, b in zip(cuts[:-1], cuts[1:])]
+    chunk = 1 << 20
+    plan = ff.ff_snapshot_plan(segs, chunk, tile_log2=13)
+    chunks, crcs, _, _ = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+    torch.cuda.synchronize()
+    assert torch.equal(chunks[:plan.payload_bytes], flat.view(torch.uint8)) and not chunks[plan.payload_bytes:].any()
+    raw = chunks.cpu().numpy()
+    want = [oracle.crc32c(raw[j:j + chunk]) for j in range(0, raw.size, chunk)]
+    assert np.array_equal(_u32(crcs), np.array(want, np.uint32))
