@@ -26,8 +26,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 
 
-KERNEL_SOURCES = ("kernels.hip", "blocks.hip", "tally.h", "kernels.hpp", "fused.hip", "fused.hpp", "fold.h", "fold_taps.h",
-                  "gf2.h", "layout.hpp", "xcd_order.h")
+KERNEL_SOURCES = ("kernels.hip", "blocks.hip", "hold.h", "matrix_fold.h", "tally.h", "kernels.hpp", "fused.hip",
+                  "fused.hpp", "fold.h", "fold_taps.h", "gf2.h", "layout.hpp", "xcd_order.h")
 
 
 # Workloads that the library moves in 8 KiB blocks: a small buffer, and lists of small tensors.

@@ -15,7 +15,7 @@ constexpr uint32_t kDefaultXcdGroup = 2048;
 constexpr uint32_t kTallyFan = 32;
 // A verdict on more chunks than this does without the tally: the returning atomics of a chunk hold its
 // workgroup up, and the last level counts a word per 32 chunks on one address, which the two launches that
-// the tally saves no longer pay for.  With it / without, us: 4096 chunks (64 MB) restore 27.6 / 28.1, verify
+// the tally saves no longer pay for.  With it / without, us (blocks with byte tables): 4096 chunks (64 MB) restore 27.6 / 28.1, verify
 // 18.8 / 21.3; 6080 (190 MB) 75.6 / 77.7, 41.1 / 41.6; 8000 (1 GB) 338.6 / 337.5, 166.1 / 164.2; 8192 (64 MB)
 // 31.0 / 28.1, 22.5 / 21.3; 64000 (1 GB) 476.8 / 464.1, 316 / 300.
 constexpr uint64_t kTallyChunks = 6144;

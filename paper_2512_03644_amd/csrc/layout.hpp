@@ -135,6 +135,10 @@ int build_layout(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_bytes, 
 // than four tensors take the tile kernel's row-by-row path: 5 KiB tensors (1 GB) 890 and 373 us; tensors
 // of 40 KB on average (0.8 GB) 302 and 291 us.  With 110 KB it is 318 and 312 for a pack but 459 and 483
 // for a restore that leaves bad chunks out: too few of those tiles are crowded.
+// (All of this with byte tables in LDS in the blocks, before the matrix product.  With it blocks lead further up: tensors
+// on the lines, tiles / blocks, pack of 128 / 160 / 192 / 256 / 400 MB 66.4 / 68.2 / 82.8 / 100.5 / 142 against 49.8 / 62.1 /
+// 72.6 / 93.9 / 139, restore 55.7 / 67.6 / 77.1 / 97.4 / 142 against 51.4 / 64.4 / 75.0 / 95.8 / 141, 1 GB 327 against 331.
+// The limits have stayed where they were: which kernel a plan's calls take is pinned at them.)
 constexpr uint64_t kDefaultTileBytes = 1ull << 15;
 constexpr uint64_t kSmallTileBytes = 1ull << 13;
 constexpr uint64_t kSmallBufferBytes = 112ull << 20;   // blocks, whatever the layout
