@@ -54,9 +54,9 @@ struct ff_plan {
     uint32_t mix_xcd_group = 16;   // ... and of the bare traffic pattern (its own best)
     const uint32_t* fused_tabs = nullptr;
     uint64_t* tally = nullptr;  // null: none (tally_size)
-    uint32_t* verdict = nullptr;
+    uint64_t* verdict = nullptr;
     uint64_t *state = nullptr, *step_state = nullptr;
-    mutable std::atomic<uint64_t> epoch{0};  // of the last call with verdicts
+    mutable std::atomic<uint64_t> epoch{0};  // of the last call that has a number
     uint32_t polls = kHoldPolls;
 };
 
@@ -143,7 +143,7 @@ int upload_tables(ff_plan* p)
     const uint64_t o_tally = align_up(o_btab + kBlockTabWords * 4, 256);
     const uint64_t tally_words = tally_size(L.n_chunks, L.chunk_bytes, L.tile_bytes);
     const uint64_t o_verdict = align_up(o_tally + tally_words * 8, 256);
-    const uint64_t o_state = align_up(o_verdict + (tally_words ? L.n_chunks * 4 : 0), 256);
+    const uint64_t o_state = align_up(o_verdict + (tally_words ? L.n_chunks * 8 : 0), 256);
     // runs of 8 blocks in a chunk of any plan whose tiles can be divided into blocks
     const uint64_t run_bytes = std::min<uint64_t>(L.chunk_bytes, kMaxBlockTileBytes);
     const uint64_t runs = L.tile_bytes >= kBlockBytes && L.tile_bytes <= kMaxBlockTileBytes ? L.chunk_bytes / run_bytes : 0;
@@ -215,7 +215,7 @@ int upload_tables(ff_plan* p)
     t.run_tab = reinterpret_cast<const uint32_t*>(d + o_runs);
     if (tally_words) {  // zeros
         p->tally = reinterpret_cast<uint64_t*>(d + o_tally);
-        p->verdict = reinterpret_cast<uint32_t*>(d + o_verdict);
+        p->verdict = reinterpret_cast<uint64_t*>(d + o_verdict);
         p->state = reinterpret_cast<uint64_t*>(d + o_state);
     }
     if (step_words) {

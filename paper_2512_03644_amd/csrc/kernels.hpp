@@ -65,11 +65,10 @@ struct TileTables {
     const uint32_t* want = nullptr;
     uint64_t* n_bad = nullptr;
     uint32_t n_bad_add = 0;
-    // The call's number in the plan: no two calls have the same, so what is marked with it is never set back.
-    // Who waits for verdicts (hold.h) finds them in verdict, [n_chunks] of the plan's own words: 2 * epoch, plus 1
-    // if the chunk is damaged (its low 31 bits do: every call writes every word).
+    // The call's number in the plan, from 1: no two calls have the same, so what is marked with it is never set back.
+    // Who waits for verdicts (hold.h) finds them in verdict, [n_chunks] of the plan's own words (verdict_word).
     uint64_t epoch = 0;
-    uint32_t* verdict = nullptr;
+    uint64_t* verdict = nullptr;
     // Verdicts without the levels of the tally above its chunks (open_count in tally.h); state: a word of the
     // plan's, 2 * epoch and more from when *n_bad is being set to zero.
     uint64_t* state = nullptr;
@@ -101,6 +100,10 @@ struct TileTables {
     uint32_t xcd_group = kDefaultXcdGroup;  // measured: 8 .. 2048 within 0.5 % on a 12 GB shard, 2048 best
                                 // (by 1-2 %) on a 15 GB one; 0 (launch order) costs 5-7 %
 };
+
+// What the word of a chunk holds when the call has found it sound (0) or damaged (1).  The whole number: calls
+// that write no verdicts, and those are most, count as well, so a word may be as old as the plan.
+__host__ __device__ inline uint64_t verdict_word(uint64_t epoch, uint32_t bad) { return epoch << 1 | bad; }
 
 enum TileMode { kPack = 0, kRestore = 1, kVerify = 2 };
 

@@ -14,7 +14,6 @@ __device__ __forceinline__ uint64_t tally_xor(uint64_t* word, uint32_t bit, uint
     const uint64_t mine = uint64_t(bit) << 32 | v;
     return atomicXor(reinterpret_cast<unsigned long long*>(word), mine) ^ mine;
 }
-__device__ __forceinline__ uint32_t verdict_word(const TileTables& T) { return static_cast<uint32_t>(T.epoch) << 1; }
 __device__ __forceinline__ void tally_reset(uint64_t* word)
 {
     __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -80,7 +79,7 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
     const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
     T.acc[chunk] = is_bad;
     if (T.verdict)
-        __hip_atomic_store(T.verdict + chunk, verdict_word(T) | is_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(T.verdict + chunk, verdict_word(T.epoch, is_bad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (T.direct) {
         if (!is_bad) return;
         if (!T.n_bad_add) open_count(T.state, T.epoch, T.n_bad);
@@ -110,9 +109,9 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
 __device__ __forceinline__ uint32_t await_verdict(const TileTables& T, const uint32_t chunk)
 {
     for (uint32_t n = 0; n < T.polls; n++) {
-        const uint32_t v = __builtin_amdgcn_readfirstlane(
-            __hip_atomic_load(T.verdict + chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if ((v & ~1u) == verdict_word(T)) return 2 | (v & 1);
+        const uint64_t v = __hip_atomic_load(T.verdict + chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t about = v == verdict_word(T.epoch, 0) ? 2 : v == verdict_word(T.epoch, 1) ? 3 : 0;
+        if (const uint32_t verdict = __builtin_amdgcn_readfirstlane(about)) return verdict;
         __builtin_amdgcn_s_sleep(8);  // 512 clocks
     }
     return 0;

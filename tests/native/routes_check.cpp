@@ -6,6 +6,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "fused.hpp"
@@ -254,8 +255,28 @@ static void step_by_size_and_alignment()
     }
 }
 
+// A verdict is known by the number of its call, which every call of a plan advances though few write verdicts: no two
+// numbers may look the same in a word, and none like a word that has never been written.
+static void verdicts_of_two_calls_differ()
+{
+    Job j(4, 1 << 20, 1 << 16);
+    const auto log = j.restore(FF_RESTORE_SKIP_BAD, nullptr);
+    CHECK(log.size() == 1 && log[0].t.verdict && log[0].t.epoch > 0);
+    using Word = std::remove_reference_t<decltype(*log[0].t.verdict)>;
+    for (const uint64_t later : {1ull, 1ull << 30, 1ull << 31, 1ull << 32, 1ull << 40})
+        for (const uint64_t bad : {0, 1})
+            for (const uint64_t bad_later : {0, 1}) {
+                const Word a = static_cast<Word>(verdict_word(log[0].t.epoch, bad));
+                const Word b = static_cast<Word>(verdict_word(log[0].t.epoch + later, bad_later));
+                CHECK((a | 1) != (b | 1));
+                CHECK(static_cast<Word>(verdict_word(later, bad)) > 1);
+            }
+    for (uint64_t i = 0; i < 16; i++) CHECK(log[0].t.verdict[i] == 0);  // of the plan's chunks, from the start
+}
+
 int main()
 {
+    verdicts_of_two_calls_differ();
     step_by_size_and_alignment();
     blocks_by_size_and_layout();
     only_the_default_stream_uses_the_tally();
