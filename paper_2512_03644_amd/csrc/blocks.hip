@@ -204,6 +204,15 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
     return u32x4{d[0], d[1], d[2], d[3]};
 }
 
+// The tensor-side address of an entry of the plan's tables, or zero.  By a scalar load, whatever the compiler can tell
+// about stores in front of it (open_count): a vector load is done when the rows in front of it are, and the barrier
+// waits for it.  By vector / by scalar load, us: restore of 2 / 27 / 40 / 110 MB 6.9 / 9.6 / 16.1 / 43.5 and 6.7 / 9.3 /
+// 15.8 / 43.0, of 4 / 112 MB listed 7.5 / 45.9 and 7.2 / 45.7, held blocks of tensors of 5 KiB, 1 GB, 497 and 489.
+__device__ __forceinline__ uint64_t entry_base(const TileTables& T, const uint32_t entry)
+{
+    return ((const __attribute__((address_space(4))) uint64_t*)T.tile_base)[entry];
+}
+
 // One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once, each in
 // the branch it takes.  HOLD (restore): the block is folded first, and stored only if permit(), which takes
 // the sums to the tally and waits for the chunk's verdict, says so.
@@ -231,7 +240,7 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
     };
     const uint32_t entry = tile >> T.block_log2;  // of the plan's tables
     const uint32_t sub = tile - (entry << T.block_log2);
-    const uint64_t tb = MODE == kVerify ? 0 : T.tile_base[entry];
+    const uint64_t tb = MODE == kVerify ? 0 : entry_base(T, entry);
     if (MODE == kVerify) {
         tables_ready();
     } else if (tb) {
