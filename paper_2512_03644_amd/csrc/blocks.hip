@@ -226,6 +226,12 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
     const uint64_t s = static_cast<uint64_t>(tile) * kBlockBytes;
     uint8_t* const bp = chunks + s;
     const uint32_t lane16 = 16u * lane;
+    // A row's place for a lane.  Held: from a copy of lane16 as old as its use, or 64-bit offsets wait in scratch memory.
+    auto lane_offset = [&](auto r) {
+        uint32_t v = lane16;
+        if (HOLD) asm volatile("" : "+v"(v));
+        return v + 1024 * r;
+    };
     u32x4 w[kRows];
     if (MODE != kPack)
         static_for<kRows>([&](auto r) { w[r] = load16_stream<kBufNT>(bp + (lane16 + 1024 * r)); });
@@ -260,7 +266,7 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
             if (MODE == kPack)
                 store16_stream<kBufNT>(bp + (lane16 + 1024 * r), w[r]);
             else
-                store16_unaligned<kSegNT>(tp + (lane16 + 1024 * r), w[r]);
+                store16_unaligned<kSegNT>(tp + lane_offset(r), w[r]);
             if (HOLD || !folding) return;
             __builtin_amdgcn_sched_barrier(0);
             fold(r);
@@ -318,7 +324,7 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
             // (an address per row would be 16 registers; the table is still there)
             auto addr = [&](auto r) {
                 const u32x4 e = G.seg[(P.seg[r / 4] >> (8 * (r % 4))) & 255u];
-                return reinterpret_cast<uint8_t*>((uint64_t(e.y) << 32 | e.x) + (r * 1024 + lane16));
+                return reinterpret_cast<uint8_t*>((uint64_t(e.y) << 32 | e.x) + lane_offset(r));
             };
             if (MODE == kPack) {
                 static_for<kRows>([&](auto r) {
@@ -429,8 +435,11 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         if (__builtin_amdgcn_readfirstlane(deliver() ? 1u : 0u)) {
             verdict = await_verdict(T, chunk);
             static_assert(!HOLD || !LEAN, "all weights");
-            if (!verdict) verdict = chunk_is_bad(T, lds.weight, chunks, chunk,
-                                                 T.block_tab[kRows * 4 * kWeightWords + lane], lane) ? 3 : 2;
+            if (!verdict)  // (the block stays in its registers meanwhile: room for two rows)
+                verdict = find_verdict<2>(T.verdict + chunk, T.epoch, T.want + chunk, T.affine,
+                                          (const FF_LDS u32x4*)&lds.weight[0][0],
+                                          chunks + (uint64_t(chunk) << T.tpc_log2) * kBlockBytes, 1u << T.tpc_log2,
+                                          T.block_tab[kRows * 4 * kWeightWords + lane], lane);
             *said = verdict;
         } else {
             while (!(verdict = __builtin_amdgcn_readfirstlane(*said))) __builtin_amdgcn_s_sleep(1);

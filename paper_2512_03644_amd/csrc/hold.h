@@ -9,7 +9,8 @@
 //
 // A chunk's workgroups are dealt to the XCDs in short runs, so that they start at about the same time; but
 // nothing promises that all of them are in flight together (other kernels may hold compute units).  So a wait
-// is bounded, and a wavefront whose patience ends reads the whole chunk and finds the verdict by itself.
+// is bounded, and a wavefront whose patience ends reads the chunk and finds the verdict by itself, unless it comes
+// meanwhile (find_verdict).
 #pragma once
 #include "fold.h"
 #include "kernels.hpp"
@@ -46,6 +47,14 @@ __device__ __forceinline__ f32x16 block_sums(const HoldLds& lds, const int lane,
         __builtin_amdgcn_sched_barrier(0);
     });
     return acc;
+}
+
+// As a function of its own, so that its rows cost the kernel no registers.
+__device__ __noinline__ uint32_t find_verdict_apart(uint64_t* word, uint64_t epoch, const uint32_t* want, uint32_t affine,
+                                                    const FF_LDS u32x4* weight, const uint8_t* at, uint32_t n,
+                                                    uint32_t lane_c, int lane)
+{
+    return find_verdict<kBlockRows>(word, epoch, want, affine, weight, at, n, lane_c, lane);
 }
 
 // 16 bytes of the stream at pos to wherever they belong, by a lane on its own.
@@ -240,7 +249,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     if (__builtin_amdgcn_readfirstlane(speaks)) {
         verdict = await_verdict(T, chunk);
         if (!verdict) {  // alone, and with rows read again: this rare case would need the registers of both
-            verdict = chunk_is_bad(T, lds.weight, chunks, chunk, c[kBlocks - 1], lane) ? 3 : 2;
+            const uint32_t n = T.tiles_per_chunk * kBlocks;
+            verdict = __builtin_amdgcn_readfirstlane(find_verdict_apart(
+                T.verdict + chunk, T.epoch, T.want + chunk, T.affine, (const FF_LDS u32x4*)&lds.weight[0][0],
+                chunks + static_cast<uint64_t>(chunk) * n * kBlockBytes, n, c[kBlocks - 1], lane));
             *said = verdict;
             if (verdict == 2) scatter_slots(seg_off, seg_ptr, tile_first_seg, T, tile, bp, lane);
             return;

@@ -383,3 +383,29 @@ def test_pack_of_more_blocks_with_half_the_weights(oracle):
     raw = chunks.cpu().numpy()
     want = [oracle.crc32c(raw[j:j + chunk]) for j in range(0, raw.size, chunk)]
     assert np.array_equal(_u32(crcs), np.array(want, np.uint32))
+
+
+@pytest.mark.parametrize("chunk_log2,nbytes", [(24, 64 << 20), (25, 200 << 20)])
+def test_waits_that_end_at_once_cost_a_chunk_and_not_its_square(chunk_log2, nbytes):
+    # blocks, tiles of 32 KiB.  Every workgroup of a chunk reading all of it is 256 times the work (it took 600 times as
+    # long); one verdict for all costs each about what it reads until then.
+    chunk = 1 << chunk_log2
+    t = torch.zeros(nbytes // 2 - 1001, dtype=torch.bfloat16, device=DEV)
+    plan = ff.ff_snapshot_plan([t], chunk)
+    chunks, crcs, bad, n_bad = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+
+    def best(polls):
+        ff._check(ff.lib().ff_plan_set_polls(plan.handle, polls))
+        times = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ff.ff_restore(plan, chunks, crcs, bad, n_bad, ff.FF_RESTORE_SKIP_BAD)
+            b.record()
+            torch.cuda.synchronize()
+            assert int(n_bad.item()) == 0
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    assert best(0) < 30 * best(4096)
