@@ -58,6 +58,7 @@ struct ff_plan {
     uint64_t *state = nullptr, *step_state = nullptr;
     mutable std::atomic<uint64_t> epoch{0};  // of the last call that has a number
     uint32_t polls = kHoldPolls;
+    uint64_t compute_units = 0;  // of the device
 };
 
 namespace {
@@ -198,6 +199,9 @@ int upload_tables(ff_plan* p)
     }
 
     FF_HIP_TRY(hipGetDevice(&p->device));
+    int units = 0;
+    FF_HIP_TRY(hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, p->device));
+    p->compute_units = units > 0 ? static_cast<uint64_t>(units) : 0;
     hipError_t e = hipMalloc(&p->dev_block, total);
     if (e == hipErrorOutOfMemory) return FF_ERR_NOMEM;
     FF_HIP_TRY(e);
@@ -288,7 +292,7 @@ bool held_in_one_pass(const ff_plan* p, const TileTables& t)
 {
     const Layout& L = p->layout;
     const bool medium = L.buffer_bytes <= kMediumBufferBytes;
-    if (L.chunk_bytes > hold_chunk_bytes(t)) return false;
+    if (L.chunk_bytes > hold_chunk_bytes(t, p->compute_units)) return false;
     if (tiles_are_blocks(t)) return (medium || !p->tile_given) && L.n_chunks <= kTallyChunks;
     return t.tile_rows * 1024ull == kDefaultTileBytes && (!medium || p->tile_given) && (t.hint & 3) == 3;
 }

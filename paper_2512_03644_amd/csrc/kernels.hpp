@@ -157,7 +157,10 @@ inline bool tiles_are_blocks(const TileTables& t)
 // ragged in chunks of 32 KiB 1632 / 1188, 4 MiB 1572 / 1184; 4 / 16 / 64 / 100 / 180 MB 15.8 / 18.5 / 40.9 / 55.9 / 100
 // and 9.2 / 12.0 / 28.6 / 47.0 / 72; small tensors 60 / 150 / 1000 MB 45.9 / 99 / 544 and 37.9 / 97 / 492.
 constexpr uint32_t kHoldXcdGroup = 8, kHoldPolls = 4096;
-inline uint64_t hold_chunk_bytes(const TileTables& t) { return tiles_are_blocks(t) ? 16ull << 20 : 32ull << 20; }
+inline uint64_t hold_chunk_bytes(const TileTables& t, uint64_t compute_units)
+{
+    return compute_units * (tiles_are_blocks(t) ? 8 * kBlockBytes : 128u << 10);  // 256: 16 and 32 MiB
+}
 hipError_t launch_held(const TileTables& t, void* chunks, hipStream_t stream);
 
 // Fills tab (host, kBlockTabWords entries): the weights of the 32 dwords of a lane (matrix_fold.h), then

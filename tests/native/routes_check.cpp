@@ -25,6 +25,7 @@ struct Launch {
 static std::vector<Launch> g_log;
 // (filled by the objects' constructors, before this file's own)
 static std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
+static int g_units = 256;  // compute units
 static hipStreamCaptureStatus g_capture = hipStreamCaptureStatusNone;
 static struct { dim3 g, b; size_t s; hipStream_t q; } g_config;
 
@@ -45,6 +46,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t l
     return hipSuccess;
 }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_units; return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) { *p = malloc(n); return hipSuccess; }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
@@ -274,8 +276,32 @@ static void verdicts_of_two_calls_differ()
     for (uint64_t i = 0; i < 16; i++) CHECK(log[0].t.verdict[i] == 0);  // of the plan's chunks, from the start
 }
 
+// A restore that leaves damaged chunks out is one launch where the workgroups of a chunk can be in flight together: no
+// more of them than the device has compute units, the whole chip's 256 or a partition's.
+static void one_pass_where_a_chunk_fits_the_device()
+{
+    struct { int units; uint64_t mb, chunk; uint32_t flags; bool one; } cases[] = {
+        {256, 100, 16 << 20, 0, true},  {256, 100, 32 << 20, 0, false},   // blocks
+        {256, 400, 32 << 20, 0, true},  {256, 400, 64 << 20, 0, false},   // tiles
+        {128, 100, 8 << 20, 0, true},   {128, 100, 16 << 20, 0, false},  {128, 400, 16 << 20, 0, true}, {128, 400, 32 << 20, 0, false},
+        {32, 100, 2 << 20, 0, true},    {32, 100, 4 << 20, 0, false},    {32, 400, 4 << 20, 0, true},   {32, 400, 8 << 20, 0, false},
+        {304, 100, 16 << 20, 0, true},  {304, 100, 32 << 20, 0, false},
+    };
+    for (const auto& c : cases) {
+        g_units = c.units;
+        Job j(1, c.mb << 20, c.chunk, c.flags, 6);
+        g_line = static_cast<int>(c.mb * 1000 + c.units);
+        const auto log = j.restore(FF_RESTORE_SKIP_BAD, nullptr);
+        CHECK((log.size() == 1) == c.one);
+        CHECK(is(log[0], "kernel_held") == c.one);
+        CHECK(c.one || is(log.back(), "block_kernel") || is(log.back(), "tile_kernel"));
+    }
+    g_units = 256;
+}
+
 int main()
 {
+    one_pass_where_a_chunk_fits_the_device();
     verdicts_of_two_calls_differ();
     step_by_size_and_alignment();
     blocks_by_size_and_layout();
