@@ -476,7 +476,8 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
     void* buf = const_cast<void*>(chunks);
     const bool verify_only = (flags & FF_RESTORE_VERIFY_ONLY) != 0;
     const bool skip_bad = (flags & FF_RESTORE_SKIP_BAD) != 0;
-    if (skip_bad && !verify_only && !list && held_in_one_pass(p, t) && (t.tally = tally_for(p, s))) {
+    // (A wavefront that holds its tile may read its chunk's checksum behind the flag that another has written.)
+    if (skip_bad && !verify_only && !list && bad != crcs && held_in_one_pass(p, t) && (t.tally = tally_for(p, s))) {
         t.want = crcs;
         t.n_bad = n_bad;
         t.verdict = p->verdict;

@@ -299,9 +299,25 @@ static void one_pass_where_a_chunk_fits_the_device()
     g_units = 256;
 }
 
+// The flags may take the place of the checksums that they are found with.  A wavefront that holds a chunk may look at
+// its checksum after another has written the flag, so such a restore takes two passes.
+static void flags_in_place_of_the_checksums()
+{
+    for (const uint64_t mb : {8, 400}) {
+        Job j(1, mb << 20, 1 << 20);
+        g_line = static_cast<int>(mb);
+        CHECK(j.restore(FF_RESTORE_SKIP_BAD, nullptr).size() == 1);
+        g_log.clear();
+        CHECK(ff_restore(j.plan, j.chunks, j.crcs, j.crcs, &j.n_bad, FF_RESTORE_SKIP_BAD, nullptr) == FF_OK);
+        CHECK(g_log.size() > 1);
+        for (const Launch& l : g_log) CHECK(!is(l, "kernel_held"));
+    }
+}
+
 int main()
 {
     one_pass_where_a_chunk_fits_the_device();
+    flags_in_place_of_the_checksums();
     verdicts_of_two_calls_differ();
     step_by_size_and_alignment();
     blocks_by_size_and_layout();

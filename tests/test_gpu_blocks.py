@@ -409,3 +409,22 @@ def test_waits_that_end_at_once_cost_a_chunk_and_not_its_square(chunk_log2, nbyt
         return min(times)
 
     assert best(0) < 30 * best(4096)
+
+
+@pytest.mark.parametrize("nbytes", [8 << 20, 200 << 20])
+def test_flags_written_over_the_checksums(nbytes):
+    chunk = 1 << 20
+    t = torch.arange(nbytes // 2 - 77, dtype=torch.int32, device=DEV).to(torch.int16).view(torch.bfloat16)
+    src = t.clone()
+    plan = ff.ff_snapshot_plan([t], chunk)
+    chunks, crcs, _, n_bad = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+    chunks[3 * chunk + 4321] ^= 2
+    t.zero_()
+    ff._check(ff.lib().ff_plan_set_polls(plan.handle, 0))
+    ff.ff_restore(plan, chunks, crcs, crcs, n_bad, ff.FF_RESTORE_SKIP_BAD)
+    torch.cuda.synchronize()
+    want = src.clone()
+    want[3 * chunk // 2:4 * chunk // 2] = 0
+    assert int(n_bad.item()) == 1 and np.array_equal(np.flatnonzero(_u32(crcs)), [3])
+    assert torch.equal(t.view(torch.int16), want.view(torch.int16))
