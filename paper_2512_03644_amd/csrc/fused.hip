@@ -984,6 +984,10 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
     // 23.5 and 23.4) and off the lines (30 odd-sized parameters 2921 from registers, 2700 through it; aligned, 64 of
     // 100,000 58 and 64, 13 of 5 million 514 and 517).
     unsigned groups = n_waves / kWavesPerGroup;
+    // (Without those that clear the buffer's end: 760 and 6.6 MB to clear, aligned / off the lines, 26.9 / 31.3 us where
+    // they counted, 26.8 / 27.8 where they do not; 732 and 8.1 MB 28.8 / 32.0 and 27.1 / 27.4; 720 and 25 MB 33.7 / 37.0
+    // and 34.9 / 35.5.)
+    const bool at_once = groups <= 3 * kComputeUnits;
     FusedConsts c = consts;
     if (c.tally) {
         c.n_groups = groups;
@@ -991,7 +995,6 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
         groups += static_cast<unsigned>((tail / 16 + kTailSlots - 1) / kTailSlots);
         if (groups == c.n_groups && (tail || c.n_nonfinite)) groups++;
     }
-    const bool at_once = groups <= 3 * kComputeUnits;
     c.image = !consts.prev && off_lines && !at_once;
     GradPtrsOf<N> g;
     for (uint32_t i = 0; i < N; i++)

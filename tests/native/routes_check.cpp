@@ -21,6 +21,7 @@ struct Launch {
     hipStream_t stream;
     size_t spare_lds;
     uint32_t groups, image;
+    FusedConsts step;  // of the optimizer step
 };
 static std::vector<Launch> g_log;
 // (filled by the objects' constructors, before this file's own)
@@ -38,8 +39,11 @@ hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, hipStream_t q) {
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* q) { *g = g_config.g; *b = g_config.b; *s = g_config.s; *q = g_config.q; return hipSuccess; }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t lds, hipStream_t q)
 {
-    Launch l{names()[f], TileTables(), q, lds, grid.x, 0};
-    if (l.kernel.find("fused_kernel") != std::string::npos) l.image = static_cast<FusedConsts*>(args[6])->image;
+    Launch l{names()[f], TileTables(), q, lds, grid.x, 0, FusedConsts()};
+    if (l.kernel.find("fused_kernel") != std::string::npos) {
+        l.step = *static_cast<FusedConsts*>(args[6]);
+        l.image = l.step.image;
+    }
     if (l.kernel.find("block_kernel") != std::string::npos) l.t = *static_cast<TileTables*>(args[0]);
     if (l.kernel.find("tile_kernel") != std::string::npos) l.t = *static_cast<TileTables*>(args[5]);
     g_log.push_back(l);
@@ -314,8 +318,62 @@ static void flags_in_place_of_the_checksums()
     }
 }
 
+// Groups of parameters for the optimizer step, w16, master, m, v of each, and RAW tensors behind them.
+struct Step {
+    ff_plan* plan = nullptr;
+    std::vector<const void*> grads;
+    alignas(16) char chunks[16];
+    uint32_t crcs[1];
+    uint64_t n_nonfinite;
+    uint32_t half;
+    Step(uint64_t n, uint64_t numel, uint64_t chunk, uint64_t misaligned = 0, uint32_t half = FF_BF16, uint64_t n_raw = 0)
+        : grads(n, reinterpret_cast<void*>(1ull << 41)), half(half)
+    {
+        std::vector<ff_segment> segs;
+        uint64_t at = (1ull << 40) + misaligned;
+        for (uint32_t i = 0; i < n; i++)
+            for (uint32_t kind = FF_KIND_W16; kind <= FF_KIND_V; kind++) {
+                const bool w16 = kind == FF_KIND_W16;
+                segs.push_back({reinterpret_cast<void*>(at), (w16 ? 2 : 4) * numel, w16 ? half : FF_F32, kind, i, 0});
+                at += (4 * numel + 255) / 256 * 256;
+            }
+        for (uint64_t i = 0; i < n_raw; i++) segs.push_back({reinterpret_cast<void*>(at + (i << 12)), 1000, FF_BF16, FF_KIND_RAW, 0, 0});
+        CHECK(ff_snapshot_plan(segs.data(), segs.size(), chunk, 0, &plan) == FF_OK);
+    }
+    ~Step() { ff_plan_destroy(plan); }
+    std::vector<Launch> run(bool chained, void* s)
+    {
+        const ff_adam_hparams hp = {1e-3f, 0.9f, 0.95f, 1e-8f, 0.1f, 1};
+        const char* prev = chunks + (1ull << 40);  // far away; never touched
+        g_log.clear();
+        CHECK((chained ? ff_adam_step_chained(plan, grads.data(), &hp, 1.0f, half == FF_F16 ? &n_nonfinite : nullptr, prev, chunks, crcs, s)
+               : half == FF_F16 ? ff_adam_step_snapshot_f16(plan, grads.data(), &hp, 1.0f, &n_nonfinite, chunks, crcs, s)
+                                : ff_adam_step_snapshot(plan, grads.data(), &hp, chunks, crcs, s)) == FF_OK);
+        return g_log;
+    }
+};
+
+// How a step's workgroups share a compute unit hangs on how many of them there are, not on how much of the last chunk
+// is left to clear.
+static void room_by_the_working_groups()
+{
+    for (const uint64_t chunk : {1ull << 16, 8ull << 20, 64ull << 20})
+        for (const uint64_t misaligned : {0, 4})
+            for (const uint64_t n : {150, 191, 193, 250}) {  // of four workgroups each
+                Step j(n, 16384, chunk, misaligned);
+                g_line = static_cast<int>(n);
+                for (void* s : {static_cast<void*>(nullptr), reinterpret_cast<void*>(0x7f0012340000ull)}) {
+                    const Launch l = j.run(false, s).back();
+                    CHECK((l.spare_lds != 0) == (4 * n > 768));
+                    CHECK((l.image != 0) == (4 * n > 768 && misaligned));
+                    CHECK(j.run(true, s).back().spare_lds == 0);
+                }
+            }
+}
+
 int main()
 {
+    room_by_the_working_groups();
     one_pass_where_a_chunk_fits_the_device();
     flags_in_place_of_the_checksums();
     verdicts_of_two_calls_differ();
