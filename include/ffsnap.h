@@ -129,11 +129,6 @@ int ff_snapshot_plan(const ff_segment *segs, uint64_t n_segs, uint64_t chunk_byt
  * every stream that still uses the plan. */
 void ff_plan_destroy(ff_plan *plan);
 
-/* A wavefront of a restore with FF_RESTORE_SKIP_BAD may keep what it has read until its chunk has been
- * checked.  It looks `polls` times (4096 unless set: a few milliseconds), then checks the chunk by itself.  The
- * results do not depend on it; 0 makes every wait end at once.  Not to be called beside other calls on the plan. */
-int ff_plan_set_polls(ff_plan *plan, uint32_t polls);
-
 uint64_t ff_plan_payload_bytes(const ff_plan *plan); /* N                                   */
 uint64_t ff_plan_num_chunks(const ff_plan *plan);    /* ceil(N / chunk_bytes)               */
 uint64_t ff_plan_buffer_bytes(const ff_plan *plan);  /* num_chunks * chunk_bytes            */

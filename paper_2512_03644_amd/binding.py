@@ -39,7 +39,7 @@ def FF_PLAN_XCD_ORDER(n):
 FF_RESTORE_VERIFY_ONLY = 1
 FF_RESTORE_SKIP_BAD = 2
 
-EXPORTS = ["ff_snapshot_plan", "ff_plan_destroy", "ff_plan_set_polls", "ff_plan_payload_bytes", "ff_plan_num_chunks",
+EXPORTS = ["ff_snapshot_plan", "ff_plan_destroy", "ff_plan_payload_bytes", "ff_plan_num_chunks",
            "ff_plan_buffer_bytes", "ff_plan_chunk_bytes", "ff_plan_num_segments",
            "ff_plan_num_params", "ff_plan_layout_id", "ff_plan_segment_range",
            "ff_plan_chunk_span", "ff_razor_select", "ff_pack", "ff_pack_to_host", "ff_restore", "ff_restore_checked", "ff_restore_chunks", "ff_adam_step_snapshot",
@@ -89,7 +89,6 @@ def lib():
                                        ctypes.POINTER(vp)]
         L.ff_plan_destroy.restype = None
         L.ff_plan_destroy.argtypes = [vp]
-        L.ff_plan_set_polls.restype, L.ff_plan_set_polls.argtypes = i32, [vp, ctypes.c_uint32]
         for name in ("payload_bytes", "num_chunks", "buffer_bytes", "chunk_bytes", "num_segments",
                      "num_params"):
             fn = getattr(L, "ff_plan_" + name)

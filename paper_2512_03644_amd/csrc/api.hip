@@ -393,6 +393,8 @@ void ff_plan_destroy(ff_plan* plan)
     delete plan;
 }
 
+// For the tests, and not in the header: how often a wavefront that waits for its chunk's verdict looks (kHoldPolls unless
+// set, a few milliseconds; 0 ends every wait at once).  Results do not depend on it.
 int ff_plan_set_polls(ff_plan* p, uint32_t polls)
 {
     if (!p) return FF_ERR_NULL;

@@ -24,6 +24,14 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(L, name), name
 
 
+def test_no_call_of_the_tests_alone_is_part_of_the_interface():
+    # what a test turns and no user needs is exported beside the interface, and named nowhere in it
+    undeclared = ["ff_plan_set_polls"]
+    header = open(os.path.join(ROOT, "include", "ffsnap.h")).read()
+    for name in undeclared:
+        assert hasattr(ff.lib(), name) and name not in header and name not in ff.EXPORTS
+
+
 def _host_plan(tensors, chunk, **kw):
     return ff.ff_snapshot_plan(tensors, chunk, flags=ff.FF_PLAN_HOST_ONLY, **kw)
 
