@@ -371,8 +371,113 @@ static void room_by_the_working_groups()
             }
 }
 
+// A step is one launch that sums up in the plan's tally on the default stream, eager, where it is short, its gradients
+// are one launch's and no chunk has more contributions than the tally's words take.  Else it knows no tally, and a
+// kernel in front of it presets the checksums, clears the buffer's end and counter.
+static void step_in_one_launch()
+{
+    void* const named = reinterpret_cast<void*>(0x7f0012340000ull);
+    auto one = [](const std::vector<Launch>& log) {
+        CHECK(log.size() == 1 && is(log[0], "fused_kernel"));
+        const FusedConsts& c = log[0].step;
+        CHECK(c.tally && c.runs && c.heads && c.state && c.epoch && c.affine);
+        CHECK(c.n_groups && c.n_groups <= log[0].groups);
+        // every 64 KiB behind the payload has a workgroup, and the counter has one in any case
+        CHECK((log[0].groups - c.n_groups) * 65536ull >= c.buffer_bytes - c.payload);
+        CHECK(log[0].groups > c.n_groups || (c.buffer_bytes == c.payload && !c.n_nonfinite));
+        return c.epoch;
+    };
+    auto several = [](const std::vector<Launch>& log, size_t n) {
+        CHECK(log.size() == n + 1 && is(log[0], "fused_prepare"));
+        for (size_t i = 1; i <= n; i++) CHECK(is(log[i], "fused_kernel") && !log[i].step.tally && !log[i].step.state);
+    };
+    for (const uint32_t half : {FF_BF16, FF_F16})
+        for (const bool chained : {false, true}) {
+            Step j(10, 30011, 1 << 18, 4, half, 7);
+            uint64_t before = 0;
+            for (int i = 0; i < 3; i++) {
+                g_line = __LINE__;
+                const uint64_t epoch = one(j.run(chained, nullptr));
+                CHECK(epoch > before);
+                before = epoch;
+            }
+            for (void* s : {named, static_cast<void*>(hipStreamPerThread), static_cast<void*>(hipStreamLegacy)})
+                FROM_HERE(several(j.run(chained, s), 1));
+            for (const auto st : {hipStreamCaptureStatusActive, hipStreamCaptureStatusInvalidated}) {
+                g_capture = st;
+                FROM_HERE(several(j.run(chained, nullptr), 1));
+                FROM_HERE(several(j.run(chained, named), 1));
+            }
+            g_capture = hipStreamCaptureStatusNone;
+            FROM_HERE(one(j.run(chained, nullptr)));
+        }
+    for (const bool chained : {false, true}) {
+        FROM_HERE(one(Step(640, 16384, 1 << 20).run(chained, nullptr)));         // 2560 workgroups
+        FROM_HERE(several(Step(641, 16384, 1 << 20).run(chained, nullptr), 1));
+        FROM_HERE(one(Step(2048, 5, 1 << 14).run(chained, nullptr)));            // gradients of one launch
+        FROM_HERE(several(Step(2049, 5, 1 << 14).run(chained, nullptr), 2));
+        FROM_HERE(one(Step(1, 1024 * 4096, 64 << 20).run(chained, nullptr)));    // contributions to one chunk
+        FROM_HERE(several(Step(1, 1025 * 4096, 64 << 20).run(chained, nullptr), 1));
+    }
+}
+
+// A restore that leaves damaged chunks out is one launch by the rules of held_in_one_pass, both sides of each: on the
+// default stream, eager, with tiles large enough for a tally.
+static void skipping_restore_in_one_pass()
+{
+    const uint32_t t13 = FF_PLAN_TILE_LOG2(13), t14 = FF_PLAN_TILE_LOG2(14), t15 = FF_PLAN_TILE_LOG2(15);
+    struct { uint64_t n, bytes, chunk, misaligned; uint32_t flags; bool one; } cases[] = {
+        {1, 112ull << 20, 1 << 20, 0, 0, true},          // small: blocks
+        {1, 113ull << 20, 1 << 20, 0, 0, false},         // medium, on the lines: verified in blocks, scattered in tiles
+        {1, 192ull << 20, 1 << 20, 0, 0, false},
+        {1, 192ull << 20, 1 << 20, 6, 0, true},          // medium, off the lines: blocks
+        {1, 193ull << 20, 1 << 20, 0, 0, true},          // large: tiles
+        {1, 193ull << 20, 1 << 20, 6, 0, true},
+        {100000, 2560, 1 << 20, 6, 0, true},             // large, crowded: blocks
+        {1, 100ull << 20, 1 << 20, 0, t15, true},        // tiles that are asked for
+        {1, 150ull << 20, 1 << 20, 0, t15, true},
+        {1, 192ull << 20, 1 << 20, 0, t13, true},        // blocks that are asked for
+        {1, 193ull << 20, 1 << 20, 0, t13, false},
+        {1, 20ull << 20, 1 << 20, 0, t14, false},        // neither
+        {1, 20ull << 20, 1 << 20, 0, FF_PLAN_TILE_LOG2(12), false},
+        {1, 20ull << 20, 1 << 12, 0, 0, false},
+        {6144, 8192, 8192, 0, 0, true},                  // words of the tally for so many chunks
+        {6145, 8192, 8192, 0, 0, false},
+        {1, 400ull << 20, 1 << 15, 0, 0, true},          // in tiles any number
+        {1, 400ull << 20, 1 << 20, 0, FF_PLAN_CACHE_HINT(3), true},
+        {1, 400ull << 20, 1 << 20, 0, FF_PLAN_CACHE_HINT(1), false},
+        {1, 400ull << 20, 1 << 18, 0, 0, true},          // 1600 chunks of 256 KiB: two passes have a kernel of their own
+    };
+    for (const auto& c : cases) {
+        Job j(c.n, c.bytes, c.chunk, c.flags, c.misaligned);
+        for (void* s : {static_cast<void*>(nullptr), reinterpret_cast<void*>(0x7f0012340000ull), static_cast<void*>(hipStreamPerThread)})
+            for (const auto capture : {hipStreamCaptureStatusNone, hipStreamCaptureStatusActive}) {
+                g_capture = capture;
+                g_line = static_cast<int>(&c - cases);
+                const bool one = c.one && !s && capture == hipStreamCaptureStatusNone;
+                const auto log = j.restore(FF_RESTORE_SKIP_BAD, s);
+                CHECK((log.size() == 1) == one);
+                CHECK(is(log[0], "kernel_held") == one);
+                if (one) {
+                    CHECK(log[0].t.verdict && log[0].t.epoch && log[0].t.polls && log[0].t.tally && log[0].t.want && !log[0].t.skip_bad);
+                    CHECK((log[0].t.direct != 0) == (is(log[0], "block_kernel") && log[0].t.n_chunks <= kDirectChunks));
+                } else {
+                    for (const Launch& l : log) CHECK(!is(l, "kernel_held") && !l.t.verdict);
+                    const TileTables& last = log.back().t;
+                    CHECK(last.skip_bad == j.bad && !last.acc && !last.tally);
+                }
+            }
+        g_capture = hipStreamCaptureStatusNone;
+        for (const uint32_t flags : {0u, FF_RESTORE_VERIFY_ONLY, FF_RESTORE_VERIFY_ONLY | FF_RESTORE_SKIP_BAD})
+            for (const Launch& l : j.restore(flags, nullptr)) CHECK(!is(l, "kernel_held"));
+        for (const Launch& l : j.listed(FF_RESTORE_SKIP_BAD, nullptr)) CHECK(!is(l, "kernel_held"));
+    }
+}
+
 int main()
 {
+    step_in_one_launch();
+    skipping_restore_in_one_pass();
     room_by_the_working_groups();
     one_pass_where_a_chunk_fits_the_device();
     flags_in_place_of_the_checksums();
