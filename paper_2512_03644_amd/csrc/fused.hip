@@ -689,14 +689,22 @@ __device__ __forceinline__ void clear_tail(const FusedConsts& C, uint8_t* __rest
 // groups 7.4 / 7.9 / 11.0 against 7.7 / 8.1 / 11.2), which shows where a queue of steps is bound by that: 64
 // groups of 100 elements 10.7 against 11.2 us a step, fewer or larger groups the same within 1 %; those of 16 KiB
 // are for the steps that 3 KiB would cut into several launches.
-template <bool F16, bool CHAINED, bool BC2, uint32_t N>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void fused_kernel(
+//
+// TALLY: with C.tally or without; else without.  The long chained steps have code of their own, whose 70 registers
+// leave a SIMD room for seven wavefronts: still three workgroups, but the next one starts before the last of the third
+// is gone.  With the tally's code in it (76 registers, six wavefronts) the first pass of a 7B shard on a new state, when
+// every load takes longer, was 2-3 % slower (4810 / 4726 us on one machine, 5026 / 4950 on another), and repeated ones
+// 1 % faster (4397-4440 / 4463-4475); 500 ragged parameters 523 / 512, 64 of 600,000 248 / 247.  Two workgroups, made so by
+// LDS, 5142 and 4471.  In fp16 seven wavefronts need scratch memory and gain nothing (7B new 5060 with, 5038 without).
+template <bool F16, bool CHAINED, bool BC2, uint32_t N, bool TALLY = true>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TALLY || F16 ? 6 : 7))) void fused_kernel(
     const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
     const uint32_t* __restrict__ tabs, uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs,
     FusedConsts C, GradPtrsOf<N> grads)
 {
     __shared__ Lds lds;
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];  // of launches with C.image
+    if (!TALLY) C.tally = nullptr;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
@@ -977,8 +985,12 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
         fused_kernel<false, true, false, N>,  fused_kernel<false, true, true, N>,
         fused_kernel<true, false, false, N>,  fused_kernel<true, false, true, N>,
         fused_kernel<true, true, false, N>,   fused_kernel<true, true, true, N>};
+    static const Kernel chained[4] = {  // without a tally
+        fused_kernel<false, true, false, N, false>, fused_kernel<false, true, true, N, false>,
+        fused_kernel<true, true, false, N, false>,  fused_kernel<true, true, true, N, false>};
     const bool bc2 = consts.adam.bc2s != 1.0f;
-    const Kernel kernel = kernels[(f16 ? 4 : 0) + (consts.prev ? 2 : 0) + (bc2 ? 1 : 0)];
+    const Kernel kernel = consts.prev && !consts.tally ? chained[(f16 ? 2 : 0) + (bc2 ? 1 : 0)]
+                                                       : kernels[(f16 ? 4 : 0) + (consts.prev ? 2 : 0) + (bc2 ? 1 : 0)];
     // The image only pays in launches of several rounds (aligned, in the one round that there is: 64 parameters
     // of 5000 elements 12.0 us from registers, 13.9 through the image; 32 of 32,768 15.6 and 17.2; 64 of 30,011
     // 23.5 and 23.4) and off the lines (30 odd-sized parameters 2921 from registers, 2700 through it; aligned, 64 of

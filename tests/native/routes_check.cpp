@@ -380,6 +380,7 @@ static void step_in_one_launch()
     auto one = [](const std::vector<Launch>& log) {
         CHECK(log.size() == 1 && is(log[0], "fused_kernel"));
         const FusedConsts& c = log[0].step;
+        CHECK(log[0].kernel.find("ELb0EEEv") == std::string::npos);  // not the kernel that knows no tally
         CHECK(c.tally && c.runs && c.heads && c.state && c.epoch && c.affine);
         CHECK(c.n_groups && c.n_groups <= log[0].groups);
         // every 64 KiB behind the payload has a workgroup, and the counter has one in any case

@@ -1,4 +1,4 @@
-"""What the compiler makes of the block kernels, where their speed hangs on it and no result shows it."""
+"""What the compiler makes of the kernels, where their speed hangs on it and no result shows it."""
 import os
 import re
 import shutil
@@ -32,3 +32,24 @@ def test_restored_blocks_know_their_address_before_their_rows(tmp_path):
     for k in restores:
         text = " ".join(loads[k])
         assert re.search("(^| )" + " ".join(["global_load_dwordx4"] * 8) + " s_barrier", text), k
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_long_chained_steps_leave_room_for_seven_wavefronts_on_a_simd(tmp_path):
+    # 512 registers a SIMD, handed out in eights: 72 for seven wavefronts, none of them in scratch memory.
+    asm = str(tmp_path / "fused.s")
+    subprocess.run(["hipcc"] + build.FLAGS + ["--offload-device-only", "-S", "-o", asm,
+                                              os.path.join(build.CSRC, "fused.hip")],
+                   check=True, capture_output=True, text=True)
+    used, name = {}, None
+    for line in open(asm):
+        m = re.match(r"\s+\.amdhsa_(kernel|next_free_vgpr|private_segment_fixed_size) (\S+)", line)
+        if m and m.group(1) == "kernel":
+            name = m.group(2)
+        elif m:
+            used.setdefault(name, {})[m.group(1)] = int(m.group(2))
+    # <F16, CHAINED, BC2, N, TALLY>
+    bf16 = {k: v for k, v in used.items() if re.search(r"fused_kernelILb0ELb1ELb[01]ELj\d+ELb0EE", k)}
+    assert len(bf16) == 6
+    for k, v in bf16.items():
+        assert v["next_free_vgpr"] <= 72 and v["private_segment_fixed_size"] == 0, (k, v)
