@@ -11,10 +11,10 @@
 //
 // What bounds a small call is that chain and the launch itself.  With Horner steps through byte tables in
 // place of the matrix product, 124 lookups a lane and block, the wavefronts of a compute unit queued at its
-// LDS, all at the same time: pack of 32 MB 18.9 us and 15.0 now (a copy of it 10.2-11.2), restore 18.9 and
-// 15.6, verify of 41 / 3.2 MB 16.6 / 9.6 and 12.6 / 7.3.  On 1 GB of 5 KiB tensors, where the lookups hid behind
-// the memory, both take 407 us, though the weights leave room for two workgroups on a compute unit and the
-// tables left it for three.
+// LDS, all at the same time: pack of 32 MB 18.9 us and 14.9 now (a copy of it 10.2-11.2), restore 18.9 and
+// 14.6, verify of 41 / 3.2 MB 16.6 / 9.6 and 11.5 / 6.1.  On 1 GB of 5 KiB tensors, where the lookups hid behind
+// the memory, a restore takes 396 us and took 407, though the weights leave room for two workgroups on a compute
+// unit and the tables left it for three; a long pack takes half the weights, and has three (block_kernel_lean).
 //
 // A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the
 // plan's tally, which starts at zero, and whoever completes the word writes the chunk's result and
@@ -320,13 +320,15 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
         } else {
             GatherLds& G = *gather;
             Place P;
-            // The tensors' entries are on their way beside the rows, and no wavefront of a restore waits for another's
-            // stores: asked for one after the other behind the rows, and with the barrier behind the stores, pack / restore
-            // of 2 KB tensors, 40 / 200 MB, 19.8 / 23.1, 79.3 / 87.9 us, and so 19.4 / 20.8, 77.7 / 84.6; of 5 KiB, 1 GB, 367 /
-            // 397 and 357 / 396, 24 listed chunks of them 41.6 and 38.7; 27 MB off the lines 12.3 / 12.4 and 11.9 / 11.4.
+            // The tensors' entries are on their way beside the rows.  A wavefront of a restore passes the barrier when it
+            // knows where its rows go: others, whose stores are behind it, wait for no stores of this one's.  With the
+            // entries asked for one after the other behind the rows and the barrier behind the stores / so, us, restore of
+            // 2 KB tensors, 40 / 200 MB, 24.2 / 94.0 and 22.4 / 90.8, of 5 KiB, 1 GB, 409 and 404, 24 listed chunks of them 48.2
+            // and 45.5, 60 MB off the lines 28.5 and 25.3; pack of 2 KB tensors 19.8 / 79.3 and 19.4 / 77.7, of 5 KiB 367 and
+            // 357.  (The barrier in front of locate(): 21.8 / 91.1, 406, 44.4, 24.6, but 32 MB on the lines 14.8 and 15.0.)
             const Tensor mine = tensor_entry(T, first, n, lane);
-            if (!HOLD && MODE == kRestore) tables_ready();
             locate(T, G, first, n, s, end, lane, mine, P);
+            if (!HOLD && MODE == kRestore) tables_ready();
             if (HOLD) {
                 tables_ready();
                 static_for<kRows>([&](auto r) { fold(r); });
