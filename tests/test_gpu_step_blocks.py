@@ -128,6 +128,13 @@ def test_so_many_groups(oracle, n):
     _chained_and_compare(oracle, numels, 1 << 14, seed=n + 1, steps=2)
 
 
+# chained steps that know no tally have kernels of their own: every edge, and more groups than one launch takes
+@pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
+def test_block_edges_of_long_chained_steps(oracle, half):
+    _chained_and_compare(oracle, EDGES * 67, 1 << 15, seed=67, steps=2, half=half,
+                         loss_scale=1024.0 if half == torch.float16 else 1.0)
+
+
 def test_captured_step_over_many_groups():
     # 16 KiB of kernel arguments in a graph node: every replay, with eager work between them, equals the eager step
     numels = [7 + 3 * i for i in range(500)]
