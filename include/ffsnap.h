@@ -105,9 +105,12 @@ typedef struct {
 /* ff_restore flags */
 #define FF_RESTORE_VERIFY_ONLY 1u /* recompute and compare CRCs, write bad[]/n_bad, scatter nothing */
 #define FF_RESTORE_SKIP_BAD 2u    /* verify first, then scatter only the chunks whose CRC matched:
-                                     tensor ranges covered by a bad chunk keep their old contents
-                                     (read once on the default stream, twice on others, under
-                                     capture and with chunks of more than 16 MiB)                 */
+                                     tensor ranges covered by a bad chunk keep their old contents.
+                                     The buffer is read once on the default stream, where the device
+                                     has room for all of a chunk (16 or 32 MiB on a whole MI355X) and
+                                     the plan is of a layout, size and flags that keep their tiles in
+                                     registers (README); else twice, 3 B of traffic per payload byte:
+                                     always on other streams, under capture and with bad == crcs   */
 
 #define FF_MIN_CHUNK_BYTES 1024ull
 #define FF_MAX_CHUNK_BYTES (1ull << 30)

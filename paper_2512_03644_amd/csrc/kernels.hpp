@@ -127,7 +127,7 @@ hipError_t launch_tiles(TileMode mode, const TileTables& t, void* chunks, hipStr
 
 // The same in blocks of kBlockBytes, one wavefront each (blocks.hip): what launch_tiles does for
 // tables whose tiles have that size.  as_blocks() makes such tables of a plan's with larger tiles, up
-// to the 8 blocks of a run: tile_shift has to know the distance of every run's end.
+// to the 8 blocks of a run: run_tab knows the ends of runs of that size.
 constexpr uint32_t kBlockBytes = 8192;
 constexpr uint32_t kMaxBlockTileBytes = 8 * kBlockBytes;
 hipError_t launch_blocks(TileMode mode, const TileTables& t, void* chunks, hipStream_t stream,
