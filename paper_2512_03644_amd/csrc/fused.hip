@@ -693,9 +693,9 @@ __device__ __forceinline__ void clear_tail(const FusedConsts& C, uint8_t* __rest
 // TALLY: with C.tally or without; else without.  The long chained steps have code of their own, whose 70 registers
 // leave a SIMD room for seven wavefronts: still three workgroups, but the next one starts before the last of the third
 // is gone.  With the tally's code in it (76 registers, six wavefronts) the first pass of a 7B shard on a new state, when
-// every load takes longer, was 2-3 % slower (4810 / 4726 us on one machine, 5026 / 4950 on another), and repeated ones
-// 1 % faster (4397-4440 / 4463-4475); 500 ragged parameters 523 / 512, 64 of 600,000 248 / 247.  Two workgroups, made so by
-// LDS, 5142 and 4471.  In fp16 seven wavefronts need scratch memory and gain nothing (7B new 5060 with, 5038 without).
+// every load takes longer, was 1.5 % slower (4952 / 4869 us on one machine, 5026 / 4954 on another), and repeated ones
+// 1 % faster (4426-4440 / 4468-4479); 500 ragged parameters 523 / 512, 64 of 600,000 248 / 247.  Two workgroups, made so by
+// LDS, 5208 and 4494.  In fp16 seven wavefronts need scratch memory and gain nothing (7B new 5060 with, 5038 without).
 template <bool F16, bool CHAINED, bool BC2, uint32_t N, bool TALLY = true>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TALLY || F16 ? 6 : 7))) void fused_kernel(
     const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grad_base,
