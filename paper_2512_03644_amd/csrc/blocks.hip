@@ -214,16 +214,6 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
     return u32x4{d[0], d[1], d[2], d[3]};
 }
 
-// An entry of one of the plan's tables, for the whole wavefront.  By a scalar load, whatever the compiler can tell
-// about stores in front of it (open_count): a vector load is done when the rows in front of it are, and the barrier
-// waits for it.  By vector / by scalar load, us: restore of 2 / 27 / 40 / 110 MB 6.9 / 9.6 / 16.1 / 43.5 and 6.7 / 9.3 /
-// 15.8 / 43.0, of 4 / 112 MB listed 7.5 / 45.9 and 7.2 / 45.7, held blocks of tensors of 5 KiB, 1 GB, 497 and 489.
-template <class V>
-__device__ __forceinline__ V table_entry(const V* table, const uint32_t i)
-{
-    return ((const __attribute__((address_space(4))) V*)table)[i];
-}
-
 // One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once, each in
 // the branch it takes.  HOLD (restore): the block is folded first, and stored only if permit(), which takes
 // the sums to the tally and waits for the chunk's verdict, says so.
@@ -379,10 +369,14 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
     if (!HOLD && folding) static_for<kRows>([&](auto r) { fold(r); });
 }
 
+// The tables, the buffer and, behind them, the size of the grid (or of the list).
+constexpr int kBlockArgs = sizeof(TileTables) + sizeof(uint8_t*) + 4;
+
 template <int MODE, int HINT, bool LISTED, bool HOLD = false, bool LEAN = false>
 __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restrict__ chunks,
                                            const ChunkList* list)
 {
+    const uint32_t block = block_behind_args<0, kBlockArgs>();
     __shared__ BlockLds<LEAN> lds;
     constexpr int kFirst = BlockLds<LEAN>::kFirstRow * 4 * kWaveSize;  // of the weights, as 16-byte words
     __shared__ GatherLds gather[MODE == kVerify ? 1 : kWaves];
@@ -398,7 +392,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
         workgroup_barrier();
     };
-    const uint32_t slot = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWaves + wave;
+    const uint32_t slot = xcd_place(block, gridDim.x, T.xcd_group) * kWaves + wave;
     const uint32_t count = LISTED ? list->n << T.tpc_log2 : T.n_list ? T.n_list : T.n_tiles;
     bool active = slot < count;
     uint32_t chunk = 0, tile = 0;
@@ -410,20 +404,22 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
             tile = T.tile_begin + slot;
             chunk = tile >> T.tpc_log2;
         }
-        if (T.skip_bad) active = !__builtin_amdgcn_readfirstlane(T.skip_bad[chunk]);
+        if (T.skip_bad) active = !table_entry(T.skip_bad, chunk);
     }
     // the wavefronts of this workgroup that are at the same chunk
     const uint32_t run_log2 = T.tpc_log2 < uint32_t(kWavesLog2) ? T.tpc_log2 : uint32_t(kWavesLog2);
     const uint32_t run = 1u << run_log2, run_index = (tile & (T.tiles_per_chunk - 1)) >> run_log2;
     const uint32_t in_run = wave & (run - 1), lead = wave - in_run;
     const bool folding = T.acc != nullptr;
-    uint32_t lane_c = 0, lane_c_first = 0, bit_at_end = 0;
+    uint32_t lane_c = 0, lane_c_first = 0, bit_at_end = 0, want = 0;
     if (folding) {
         // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and what bit
         // `lane` of the run's register is at the end of the chunk
         lane_c = T.block_tab[kRows * 4 * kWeightWords + (run - 1 - in_run) * kWaveSize + lane];
         if (LEAN) lane_c_first = T.block_tab[kRows * 4 * kWeightWords + (kWaves + run - 1 - in_run) * kWaveSize + lane];
         bit_at_end = T.run_tab[run_index * 32 + (lane & 31)];
+        // (asked for by all, though the chunk's last run alone needs it: it is there by then)
+        if (MODE != kPack && T.tally) want = table_entry(T.want, chunk);
     }
     f32x16 acc = {};
     uint32_t first_half = 0;
@@ -442,7 +438,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         if (lane != 0) return false;
         if (T.tally)
             tally_run<MODE>(T, v, chunk, run_index, T.tiles_per_chunk >> run_log2,
-                            (slot >> T.tpc_log2), count >> T.tpc_log2);
+                            (slot >> T.tpc_log2), count >> T.tpc_log2, want);
         else
             atomicXor(T.acc + chunk, v);
         return true;

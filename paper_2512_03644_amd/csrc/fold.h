@@ -80,6 +80,34 @@ __device__ __forceinline__ void static_for(Fn&& fn)
     static_for_impl(fn, std::make_integer_sequence<int, N>{});
 }
 
+// The workgroup's number, known when bytes [FROM, TO) of the kernel's arguments are in the scalar cache.  The compiler
+// loads arguments where they are used, and the first wavefronts of a launch wait for memory at every line of them
+// that is new, one line after the other; so all are asked for at once.  With the order of the XCDs in closed form and a
+// chunk's checksum asked for beforehand, us, before / now: pack of 3 / 28 / 60 MB 9.05 / 14.50 / 23.6 and 8.21 / 14.07 /
+// 23.2, verify of 3 / 28 / 100 MB 6.2 / 10.0 / 25.8 and 5.3 / 9.2 / 21.9, pack of 300 MB in tiles 119.5 and 118.4, a skipping
+// restore of 20,000 ragged tensors 1151 and 1136.
+template <int FROM, int TO>
+__device__ __forceinline__ uint32_t block_behind_args()
+{
+    constexpr int kLine = 64, kFirst = FROM / kLine, kLines = (TO - 1) / kLine - kFirst + 1;
+    const auto* const args = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t all = 0, block = blockIdx.x;
+    static_for<kLines>([&](auto i) { all |= args[(kFirst + i) * (kLine / 4)]; });
+    asm("" : "+s"(block) : "s"(all));  // (not volatile: table reads behind it remain scalar loads)
+    __builtin_amdgcn_sched_barrier(0);
+    return block;
+}
+
+// An entry of one of the plan's tables, for the whole wavefront.  By a scalar load, whatever the compiler can tell
+// about stores in front of it (open_count): a vector load is done when the rows in front of it are, and the barrier
+// waits for it.  By vector / by scalar load, us: restore of 2 / 27 / 40 / 110 MB 6.9 / 9.6 / 16.1 / 43.5 and 6.7 / 9.3 /
+// 15.8 / 43.0, of 4 / 112 MB listed 7.5 / 45.9 and 7.2 / 45.7, held blocks of tensors of 5 KiB, 1 GB, 497 and 489.
+template <class V>
+__device__ __forceinline__ V table_entry(const V* table, const uint32_t i)
+{
+    return ((const __attribute__((address_space(4))) V*)table)[i];
+}
+
 // Tensor side: 16 (or 8) bytes at any even address.  Buffer side: 16-byte aligned.  NT marks
 // the access non-temporal (streaming data that will not be reused).
 template <bool NT = false>

@@ -205,13 +205,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const uint32_t* __restrict__ tile_shift, TileTables T, const uint8_t* __restrict__ chunks)
 {
     constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
+    const uint32_t block = block_behind_args<0, 5 * sizeof(void*) + sizeof(TileTables) + sizeof(void*) + 4>();
     __shared__ HoldLds lds;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     table_to_lds<kThreads, sizeof(lds.weight)>(T.block_tab, &lds.weight[0][0], wave, lane);
     if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
     __builtin_amdgcn_sched_barrier(0);
-    const uint32_t tile = xcd_order(blockIdx.x, gridDim.x, T.xcd_group) * kWaves + wave;
+    const uint32_t tile = xcd_place(block, gridDim.x, T.xcd_group) * kWaves + wave;
     if (tile >= T.n_tiles) {
         wait_loads<0>();
         workgroup_barrier();
@@ -224,6 +225,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const uint32_t in_chunk = tile & (T.tiles_per_chunk - 1), chunk = tile >> T.tpc_log2;
     const uint32_t shift = tile_shift[in_chunk];
     const uint64_t base = tile_base[tile];
+    const uint32_t want = table_entry(T.want, chunk);
     const uint8_t* const bp = chunks + static_cast<uint64_t>(tile) * kTileBytes + 16u * lane;
     u32x4 w[kRows];
     static_for<kRows>([&](auto r) { w[r] = load16_stream<kBufNT>(bp + r * kRowBytes); });
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const uint32_t lead = wave - (wave & (run - 1));
     uint32_t speaks = 0;
     if (lane == 0 && (run == 1 || run_complete(lds.sum[lead], lds.arrived[lead], run, reg))) {
-        tally_run<kRestore>(T, reg, chunk, in_chunk / run, T.tiles_per_chunk / run, chunk, T.n_chunks);
+        tally_run<kRestore>(T, reg, chunk, in_chunk / run, T.tiles_per_chunk / run, chunk, T.n_chunks, want);
         speaks = 1;
     }
     volatile uint32_t* const said = &lds.verdict[lead];

@@ -45,11 +45,12 @@ __device__ __forceinline__ void open_count(uint64_t* state_word, const uint64_t 
     __hip_atomic_store(state, ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.
+// v: register of one run, at the end of its chunk.  place: of the chunk among the n of this launch.  want: the chunk's
+// checksum, of a verdict.
 template <int MODE>
 __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const uint32_t chunk,
                                           const uint32_t run_index, const uint32_t runs,
-                                          const uint32_t place, const uint32_t n)
+                                          const uint32_t place, const uint32_t n, const uint32_t want)
 {
     constexpr uint32_t kFan = kTallyFan;
     auto all = [](uint32_t bits) { return bits == 32 ? 0xFFFFFFFFu : (1u << bits) - 1; };
@@ -76,7 +77,7 @@ __device__ __forceinline__ void tally_run(const TileTables& T, uint32_t v, const
         T.acc[chunk] = v;
         return;
     }
-    const uint32_t is_bad = v != T.want[chunk] ? 1u : 0u;
+    const uint32_t is_bad = v != want ? 1u : 0u;
     T.acc[chunk] = is_bad;
     if (T.verdict)
         __hip_atomic_store(T.verdict + chunk, verdict_word(T.epoch, is_bad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
