@@ -21,8 +21,8 @@
 // sets the word back to zero.  Otherwise -- a call on another stream than the default one, or under
 // capture -- the sums are XORed into the caller's own array between a preset and a finishing kernel.
 //
-// A block that lies inside one tensor needs one address.  In any other the wavefront first puts the
-// block's tensors into a table in LDS (base address and end of each); every tensor marks the first
+// A block that lies inside one tensor needs one address, one of up to four tensors (few_tensors) a comparison with
+// each boundary.  In any other the wavefront first puts the block's tensors into a table in LDS (base address and end of each); every tensor marks the first
 // slot that starts in it, and a running maximum over the slots gives every lane its tensor: no
 // search.  Slots that straddle a boundary are listed and moved by groups of eight lanes, a halfword
 // each, all of the block's at once.  The cost is the same for 2 or 100 tensors in a block; with the
@@ -44,6 +44,7 @@ static_assert(kWaves == 1 << kWavesLog2);
 constexpr int kThreads = kWaves * kWaveSize;
 constexpr int kSlots = kBlockBytes / 16;
 constexpr uint32_t kMaxSegs = 128;  // tensors of a block that the table holds
+constexpr int kPieces = 4;          // tensors of a block that need no table
 static_assert(kMaxSegs <= 256, "a place in the table is 8 bits");
 
 typedef uint16_t u16_alias __attribute__((may_alias));
@@ -214,6 +215,91 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
     return u32x4{d[0], d[1], d[2], d[3]};
 }
 
+// A block of up to kPieces tensors, the payload's end included: the boundaries stand in scalar registers and every lane
+// finds its tensors' addresses by comparing.  w: the rows (restore).
+// A small call ends when its last boundary block does, and by way of the table in LDS that one has two more loads and a
+// microsecond of LDS between its number and its rows.  By the table / so, us: pack of 3 / 28 / 60 / 100 MB 8.2 / 14.1 /
+// 23.2 / 46.2 and 7.1 / 13.3 / 22.0 / 44.1, restore of 28 / 60 MB 14.3 / 23.8 and 13.7 / 23.1, 60 MB off the lines 25.5 and
+// 23.4, tensors of 5 KiB, 100 MB, pack 46.6 and 44.2, 300 MB, restore 126.9 and 123.8, 1 GB 406 and 400.  Not where a block
+// is held, nor in packs with half the weights: they have no registers for it (300 MB of 5 KiB 147 and 181, pack 116 and 126).
+template <int MODE, int HINT, class Ready, class Fold>
+__device__ __forceinline__ void few_tensors(const TileTables& T, GatherLds& G, uint8_t* bp, u32x4 (&w)[kRows],
+                                            const uint32_t first, const uint64_t s, const uint32_t end,
+                                            const bool folding, const int lane, Ready&& tables_ready, Fold&& fold)
+{
+    constexpr bool kSegNT = (HINT & 1) != 0, kBufNT = (HINT & 2) != 0;
+    static_assert(kPieces == 4, "the sums below are written out");
+    uint64_t a[kPieces], p[kPieces];  // where the tensors begin in the stream, and their addresses
+    static_for<kPieces>([&](auto k) {
+        a[k] = table_entry(T.seg_off, first + k < T.n_seg ? first + k : T.n_seg);
+        p[k] = table_entry(T.seg_ptr, first + k < T.n_seg ? first + k : T.n_seg - 1);
+    });
+    // address of the block's byte 0 if it were in the tensor; where the next ones begin in the block (kBlockBytes: not in
+    // it)
+    auto base = [&](int k) { return p[k] + (s - a[k]); };
+    auto bound = [&](int k) {
+        return a[k] <= s ? 0u : a[k] - s < uint64_t(kBlockBytes) ? static_cast<uint32_t>(a[k] - s) : uint32_t(kBlockBytes);
+    };
+    const uint64_t b0 = base(0), step1 = base(1) - b0, step2 = base(2) - base(1), step3 = base(3) - base(2);
+    const uint32_t c1 = bound(1), c2 = bound(2), c3 = bound(3);
+    auto at = [&](uint32_t rel) {
+        return reinterpret_cast<uint8_t*>(b0 + (rel >= c1 ? step1 : 0) + (rel >= c2 ? step2 : 0) + (rel >= c3 ? step3 : 0) + rel);
+    };
+    // the slots that hold a boundary in their middle, the last one that of the payload's end; kNone where there is none, or
+    // it is in the list already (0 <= c1 <= c2 <= c3 <= end or kBlockBytes)
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    auto cut = [&](uint32_t before, uint32_t c) {
+        return c < kBlockBytes && (c & 15u) && before <= (c & ~15u) ? c & ~15u : kNone;
+    };
+    const uint32_t q0 = cut(0, c1), q1 = cut(c1, c2), q2 = cut(c2, c3), q3 = cut(c3, end);
+    // lane 8 k + u has halfword u of the k-th of them
+    const uint32_t q = lane < 8 ? q0 : lane < 16 ? q1 : lane < 24 ? q2 : lane < 32 ? q3 : kNone;
+    const uint32_t half = q + 2u * (lane & 7);
+    const bool moves = q != kNone && half < end;
+    u16_alias* const fix = reinterpret_cast<u16_alias*>(G.fix);
+    const uint32_t lane16 = 16u * lane;
+    auto rel = [&](auto r) { return r * 1024 + lane16; };
+    auto cut_row = [&](auto r) {  // (wave-uniform)
+        return q0 / 1024 == uint32_t(r) || q1 / 1024 == uint32_t(r) || q2 / 1024 == uint32_t(r) || q3 / 1024 == uint32_t(r);
+    };
+    auto slot = [&](uint32_t x) { return x == q0 ? 0u : x == q1 ? 1u : x == q2 ? 2u : x == q3 ? 3u : kNone; };
+    auto plain = [&](uint32_t x) { return x < end && x != q0 && x != q1 && x != q2 && x != q3; };
+    if (MODE == kPack) {
+        uint32_t h = 0;
+        if (moves) h = *as_global(reinterpret_cast<const uint16_t*>(at(half)));
+        static_for<kRows>([&](auto r) {
+            w[r] = u32x4{0, 0, 0, 0};
+            if (plain(rel(r))) w[r] = load16_unaligned<kSegNT>(at(rel(r)));
+        });
+        tables_ready();
+        if (lane < 32) fix[lane] = static_cast<uint16_t>(h);
+        wave_sync();
+        static_for<kRows>([&](auto r) {
+            if (cut_row(r)) {
+                const uint32_t k = slot(rel(r));
+                if (k != kNone) w[r] = G.fix[k];
+            }
+            store16_stream<kBufNT>(bp + rel(r), w[r]);
+            if (!folding) return;
+            __builtin_amdgcn_sched_barrier(0);
+            fold(r);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        return;
+    }
+    tables_ready();
+    static_for<kRows>([&](auto r) {
+        if (cut_row(r)) {
+            const uint32_t k = slot(rel(r));
+            if (k != kNone) G.fix[k] = w[r];
+        }
+        if (plain(rel(r))) store16_unaligned<kSegNT>(at(rel(r)), w[r]);
+    });
+    wave_sync();
+    if (moves) *as_global(reinterpret_cast<uint16_t*>(at(half))) = fix[lane];
+    if (folding) static_for<kRows>([&](auto r) { fold(r); });
+}
+
 // One block.  tables_ready() is the workgroup's barrier; every wavefront calls it exactly once, each in
 // the branch it takes.  HOLD (restore): the block is folded first, and stored only if permit(), which takes
 // the sums to the tally and waits for the chunk's verdict, says so.
@@ -247,7 +333,16 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
     };
     const uint32_t entry = tile >> T.block_log2;  // of the plan's tables
     const uint32_t sub = tile - (entry << T.block_log2);
+    // Where the block lies, whichever way that is: all asked for at once.
     const uint64_t tb = MODE == kVerify ? 0 : table_entry(T.tile_base, entry);
+    uint32_t first = 0, last = 0;
+    if (MODE != kVerify) {
+        first = table_entry(T.tile_first_seg, entry);
+        // the tensor of the next entry's first byte is the last that can touch this block
+        const bool more = entry + 1 < T.n_tiles >> T.block_log2;
+        last = table_entry(T.tile_first_seg, more ? entry + 1 : entry);
+        if (!more) last = T.n_seg - 1;
+    }
     if (MODE == kVerify) {
         tables_ready();
     } else if (tb) {
@@ -278,9 +373,12 @@ __device__ __forceinline__ void block_rows(const TileTables& T, BlockLds<LEAN>& 
         const uint32_t end = s >= T.payload ? 0u
                              : T.payload - s < uint64_t(kBlockBytes) ? static_cast<uint32_t>(T.payload - s)
                                                                      : uint32_t(kBlockBytes);
-        uint32_t first = table_entry(T.tile_first_seg, entry);
-        // the tensor of the next entry's first byte is the last that can touch this block
-        const uint32_t last = entry + 1 < T.n_tiles >> T.block_log2 ? table_entry(T.tile_first_seg, entry + 1) : T.n_seg - 1;
+        if constexpr (!HOLD && !LEAN) {
+            if (last - first < uint32_t(kPieces) && end) {
+                few_tensors<MODE, HINT>(T, *gather, bp, w, first, s, end, folding, lane, tables_ready, fold);
+                return;
+            }
+        }
         if (sub) {  // not the entry's first block: the last tensor that starts at or before it
             uint32_t hi = last;
             while (first < hi) {

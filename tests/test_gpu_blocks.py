@@ -75,6 +75,28 @@ def test_exactly_so_many_tensors_in_one_block(oracle, n_seg, behind, tile_log2):
     assert np.array_equal(np.concatenate(_host_segments(shard)[0]), want_buf[:plan.payload_bytes])
 
 
+# up to four tensors in a block go without its table
+@pytest.mark.parametrize("tile_log2", [0, 13, 15, 16])
+@pytest.mark.parametrize("sizes", [
+    [2, 2, 2], [6, 2, 4, 2], [16, 2, 14], [14, 2, 16], [18, 30, 16], [1022, 2, 1024], [1024, 8, 1016], [1030, 1024, 2042],
+    [8190], [8190, 2], [8192, 2], [8186, 4], [2, 8190, 2], [4098, 4094, 8192], [2, 2, 2, 2], [2048, 2, 2, 2], [3000, 3000, 2188],
+    [30000], [30000, 2, 2], [40960, 2, 24576]])
+def test_blocks_of_a_few_tensors(oracle, sizes, tile_log2):
+    # boundaries at the start of a slot, of a row, of a block and inside them, several in one slot, blocks of a larger tile that
+    # its first tensors do not reach; behind them a payload that goes on for many blocks, or ends inside a slot
+    for front, back in ((4096, 20000), (4096, 3), (4095, 0), (1, 0)):
+        lay = [(front, 2, 6)] + [(b // 2, 2, (2 * i) % 16) for i, b in enumerate(sizes)] + ([(back, 2, 10)] if back else [])
+        shard = wl.fragmented_shard(lay, 1 << 16, seed=sum(sizes), device=DEV)
+        state = _pack_and_compare(shard, oracle, tile_log2)
+        _restore_and_compare(shard, *state[:6])
+        plan, chunks, crcs, bad, n_bad, want_buf, _ = state
+        _poison_segments(shard)
+        ff.ff_restore_chunks(plan, chunks, crcs, list(range(plan.num_chunks)), bad, n_bad)
+        torch.cuda.synchronize()
+        assert int(n_bad.item()) == 0
+        assert np.array_equal(np.concatenate(_host_segments(shard)[0]), want_buf[:plan.payload_bytes])
+
+
 def _verify(plan, chunks, crcs, stream=None, flags=ff.FF_RESTORE_VERIFY_ONLY):
     bad = torch.full((plan.num_chunks,), 7, dtype=torch.int32, device=DEV)
     n_bad = torch.full((1,), 99, dtype=torch.int64, device=DEV)
