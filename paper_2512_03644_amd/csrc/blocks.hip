@@ -57,8 +57,7 @@ template <bool LEAN>
 struct BlockLds {
     static constexpr int kFirstRow = LEAN ? kRows / 2 : 0;
     u32x4 weight[(kRows - kFirstRow) * 4][kWaveSize];  // of every dword of a lane's slots, from that row on
-    uint32_t sum[kWaves];      // per run (at its first wavefront's place): XOR of its registers
-    uint32_t arrived[kWaves];  // wavefronts of the run that have added theirs
+    uint64_t sum[kWaves];      // per run (at its first wavefront's place): its registers, and who has added them
     uint32_t verdict[kWaves];  // on the run's chunk, of a restore that waits for it: 0 none yet, 2 sound, 3 damaged
 };
 
@@ -485,9 +484,15 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     static_for<kEach>([&](auto i) {
         tab[i] = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + kFirst + i * kThreads + threadIdx.x);
     });
+    // Of the multiplication that a wavefront ends with, what does not need its data: while that is on its way.  (Behind it,
+    // with a run's sum and the count of its wavefronts in two LDS words instead of one: pack / restore of 28 MB 13.3 / 13.7
+    // us, now 13.0 / 13.4, verify of 3 / 28 MB 5.3 / 9.2 and 5.05 / 9.0.  Not where registers are short.)
+    constexpr bool kAhead = !HOLD && !LEAN;
+    uint32_t lane_c = 0, times[16];
     auto tables_ready = [&] {
+        if (kAhead) gf2_multiples(times, lane_c);
         static_for<kEach>([&](auto i) { (&lds.weight[0][0])[i * kThreads + threadIdx.x] = tab[i]; });
-        if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
+        if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
         workgroup_barrier();
     };
     const uint32_t slot = xcd_place(block, gridDim.x, T.xcd_group) * kWaves + wave;
@@ -509,7 +514,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     const uint32_t run = 1u << run_log2, run_index = (tile & (T.tiles_per_chunk - 1)) >> run_log2;
     const uint32_t in_run = wave & (run - 1), lead = wave - in_run;
     const bool folding = T.acc != nullptr;
-    uint32_t lane_c = 0, lane_c_first = 0, bit_at_end = 0, want = 0;
+    uint32_t lane_c_first = 0, bit_at_end = 0, want = 0;
     if (folding) {
         // x^(8 * bytes between the end of the lane's slot in a row and the end of the run), and what bit
         // `lane` of the run's register is at the end of the chunk
@@ -523,12 +528,12 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     uint32_t first_half = 0;
     // the block's register on its way; true in the wavefront (lane 0) that has taken the run's to the chunk
     auto deliver = [&] {
-        uint32_t v = gf2_mul_half(matrix_halves(acc), lane_c);
+        uint32_t v = kAhead ? gf2_mul_half(matrix_halves(acc), times) : gf2_mul_half(matrix_halves(acc), lane_c);
         if (LEAN) v ^= gf2_mul_half(first_half, lane_c_first);
         v = wave_xor(v);
         if (run > 1) {
             uint32_t complete = 0;
-            if (lane == 0) complete = run_complete(lds.sum[lead], lds.arrived[lead], run, v) ? 1u : 0u;
+            if (lane == 0) complete = run_complete(lds.sum[lead], in_run, run, v) ? 1u : 0u;
             if (!__builtin_amdgcn_readfirstlane(complete)) return false;
             v = __builtin_amdgcn_readfirstlane(v);
         }

@@ -202,16 +202,14 @@ __device__ __forceinline__ uint32_t wave_xor(uint32_t v)
            __builtin_amdgcn_readlane(v, 32) ^ __builtin_amdgcn_readlane(v, 48);
 }
 
-// One lane per wavefront: adds v to the run's sum in LDS.  True in the wavefront that completes the
-// run; v is then the run's whole sum.  (LDS operations of a wavefront complete in order, so the
-// sum is complete when the count is.)
-__device__ __forceinline__ bool run_complete(uint32_t& sum, uint32_t& arrived, const uint32_t run, uint32_t& v)
+// One lane per wavefront: adds v to the run's sum in LDS (low half of the word; the high half has a bit for each of
+// its wavefronts, `who` of `all`).  True in the wavefront that completes the run; v is then the run's whole sum.
+__device__ __forceinline__ bool run_complete(uint64_t& word, const uint32_t who, const uint32_t all, uint32_t& v)
 {
-    atomicXor(&sum, v);
-    asm volatile("" ::: "memory");
-    if (atomicAdd(&arrived, 1u) + 1 != run) return false;
-    v = *const_cast<volatile uint32_t*>(&sum);
-    return true;
+    const uint64_t mine = uint64_t(1u << who) << 32 | v;
+    const uint64_t now = atomicXor(reinterpret_cast<unsigned long long*>(&word), mine) ^ mine;
+    v = static_cast<uint32_t>(now);
+    return (now >> 32) == (1u << all) - 1;
 }
 
 // State of all lanes -> R / x^32, where R is the CRC register (run from 0) of the rows folded so

@@ -122,6 +122,7 @@ typedef u32x4 u32x4_alias __attribute__((may_alias));
 struct Lds {
     uint32_t sum[kWavesPerBlock][4];  // per run (at its first wavefront's place): XOR of its registers
     uint32_t arrived[kWavesPerBlock]; // wavefronts of the run that have added theirs
+    uint64_t raw_sum[kWavesPerBlock]; // per run of RAW sub-blocks (run_complete)
     u32x4 wide[kRows * 4][2][kWaveSize];  // weights of the dwords of two rows of 16-byte slots
     u32x4 half[kRows * 2][2][kWaveSize];  // ... of 8-byte slots
 };
@@ -197,7 +198,7 @@ __device__ __forceinline__ void fetch_tables(const uint32_t* __restrict__ tabs, 
     static_assert(offsetof(Lds, half) == offsetof(Lds, wide) + sizeof(lds.wide), "one behind the other");
     table_to_lds<kThreads, 4 * kFusedWeightWords>(tabs, &lds.wide[0][0][0], wave, lane);
     if (threadIdx.x < kWavesPerBlock * 4) (&lds.sum[0][0])[threadIdx.x] = 0;
-    if (threadIdx.x < kWavesPerBlock) lds.arrived[threadIdx.x] = 0;
+    if (threadIdx.x < kWavesPerBlock) lds.raw_sum[threadIdx.x] = lds.arrived[threadIdx.x] = 0;
     __builtin_amdgcn_sched_barrier(0);
 }
 __device__ __forceinline__ void tables_ready()
@@ -599,7 +600,7 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
                                               const int lo, const int hi, uint8_t* __restrict__ chunks,
                                               uint32_t* __restrict__ crcs, const FusedConsts& C,
                                               const uint32_t run_entry, Lds& lds,
-                                              const uint32_t* __restrict__ lane_tab, int lane)
+                                              const uint32_t* __restrict__ lane_tab, int wave, int lane)
 {
     const int sub = info & 15u;
     // x^(8 * bytes between the end of the lane's slot and the end of the block)
@@ -657,7 +658,7 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
     uint32_t v = wave_xor(gf2_mul(matrix_share(bits, lane), lane_c));
     if (lane != 0) return;
     const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
-    if (len > 1 && !run_complete(lds.sum[run][0], lds.arrived[run], len, v)) return;
+    if (len > 1 && !run_complete(lds.raw_sum[run], wave - run, len, v)) return;
     if (C.tally)
         add_to_tally(C, run_ticket(C, run_entry, 0), crcs, t.chunk[0], v);
     else
@@ -729,7 +730,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TALLY 
         const int lo = at < 0 ? -at : 0;
         const int left = static_cast<int>(t.n) - at;
         raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
-                      crcs, C, run_entry, lds, lane_tab + 32 * 64, lane);
+                      crcs, C, run_entry, lds, lane_tab + 32 * 64, wave, lane);
         return;
     }
     const int at = sub * int(kSubElems) - static_cast<int>(t.e0 % kParamTileElems);

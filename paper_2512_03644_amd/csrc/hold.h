@@ -32,7 +32,7 @@ constexpr int kRingWords = 520;    // two rows and 16 bytes, padded to a multipl
 struct HoldLds {
     u32x4 weight[kBlockRows * 4][kWaveSize];
     uint32_t ring[kWaves][kRingWords];
-    uint32_t sum[kWaves], arrived[kWaves];  // per run, at its first wavefront's place
+    uint64_t sum[kWaves];                   // per run, at its first wavefront's place (run_complete)
     uint32_t verdict[kWaves];               // ... 0: none yet, 2: sound, 3: damaged
 };
 
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     table_to_lds<kThreads, sizeof(lds.weight)>(T.block_tab, &lds.weight[0][0], wave, lane);
-    if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.arrived[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
+    if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t tile = xcd_place(block, gridDim.x, T.xcd_group) * kWaves + wave;
     if (tile >= T.n_tiles) {
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const uint32_t run = T.tiles_per_chunk < uint32_t(kWaves) ? T.tiles_per_chunk : uint32_t(kWaves);
     const uint32_t lead = wave - (wave & (run - 1));
     uint32_t speaks = 0;
-    if (lane == 0 && (run == 1 || run_complete(lds.sum[lead], lds.arrived[lead], run, reg))) {
+    if (lane == 0 && (run == 1 || run_complete(lds.sum[lead], wave - lead, run, reg))) {
         tally_run<kRestore>(T, reg, chunk, in_chunk / run, T.tiles_per_chunk / run, chunk, T.n_chunks, want);
         speaks = 1;
     }

@@ -629,7 +629,7 @@ __device__ __forceinline__ void tile_body(
 // factor x^32 that the register lacks comes along), then by the tally with the workgroup's other
 // tiles of the chunk, or by an atomic into the caller's array; or, of a buffer CRC, to its own word.
 struct RunLds {
-    uint32_t sum[kWavesPerBlock], arrived[kWavesPerBlock];
+    uint64_t sum[kWavesPerBlock];
 };
 template <int MODE>
 __device__ __forceinline__ void deliver(const TileTables& T, RunLds& lds, uint32_t reg, const uint32_t shift,
@@ -642,7 +642,7 @@ __device__ __forceinline__ void deliver(const TileTables& T, RunLds& lds, uint32
     if (MODE != kPack && T.tally) {  // (a pack has it in blocks only)
         const uint32_t run = T.tiles_per_chunk < uint32_t(kWavesPerBlock) ? T.tiles_per_chunk : uint32_t(kWavesPerBlock);
         const uint32_t lead = wave - (wave & (run - 1));
-        if (run > 1 && !run_complete(lds.sum[lead], lds.arrived[lead], run, reg)) return;
+        if (run > 1 && !run_complete(lds.sum[lead], wave - lead, run, reg)) return;
         tally_run<MODE>(T, reg, chunk, (tile & (T.tiles_per_chunk - 1)) / run, T.tiles_per_chunk / run, place, n,
                         T.want[chunk]);
     } else if (T.acc) {
@@ -674,7 +674,7 @@ tile_kernel(
         for (int i = threadIdx.x; i < 1024; i += kWaveSize * kWavesPerBlock) tab[i] = tab_u_global[i];
     else
         reinterpret_cast<u32x4*>(tab)[threadIdx.x] = *as_global(reinterpret_cast<const u32x4*>(tab_u_global) + threadIdx.x);
-    if (MODE != kPack && threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = run_lds.arrived[threadIdx.x] = 0;
+    if (MODE != kPack && threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(kWaveSize* kWavesPerBlock) void tile_kernel_listed(
     __shared__ uint32_t tab[1024];
     __shared__ RunLds run_lds;
     for (int i = threadIdx.x; i < 1024; i += blockDim.x) tab[i] = tab_u_global[i];
-    if (threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = run_lds.arrived[threadIdx.x] = 0;
+    if (threadIdx.x < kWavesPerBlock) run_lds.sum[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);

@@ -68,6 +68,21 @@ __device__ __forceinline__ uint32_t gf2_mul_half(uint32_t a, uint32_t b)
     return p;
 }
 
+// The same with the multiples of b known beforehand: times[i] = b * x^i.
+__device__ __forceinline__ void gf2_multiples(uint32_t (&times)[16], uint32_t b)
+{
+    static_for<16>([&](auto i) {
+        times[i] = b;
+        b = gf2_mulx(b);
+    });
+}
+__device__ __forceinline__ uint32_t gf2_mul_half(const uint32_t a, const uint32_t (&times)[16])
+{
+    uint32_t p[2] = {0, 0};
+    static_for<16>([&](auto i) { p[i % 2] ^= static_cast<uint32_t>(static_cast<int32_t>(a << i) >> 31) & times[i]; });
+    return p[0] ^ p[1];
+}
+
 // The factor that lane `lane`'s half of its column's register still needs, where a column (lanes n
 // and n + 32) is multiplied by x^(shift * (31 - n)).
 inline uint32_t matrix_lane_factor(int lane, uint64_t shift)
