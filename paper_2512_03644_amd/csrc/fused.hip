@@ -41,6 +41,8 @@
 // tables, 64 random LDS addresses each), us: 35 fp16 parameters of 19,000 elements and 300 RAW tensors 27.7 ->
 // 24.5, 96 ragged ones 34.8 -> 31.9, 2000 ragged groups 1016 -> 988, chained 20 million elements 53.1 -> 52.0;
 // 64 parameters, 2.1 million, and the 7B shard the same within 0.5 %.
+// Short steps since, in a kernel of their own (fused_kernel_warm), before / now, us, three sets in turn: 0.2 million elements
+// 8.7 / 8.3, 2.1 million 25.2 / 21.2, chained 22.4 / 18.4, 3.2 million 33.3 / 30.7, chained 4.3 million 32.5 / 26.5.
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
@@ -250,6 +252,51 @@ __device__ __forceinline__ void deliver(const FusedConsts& C, Lds& lds, const Wo
     }
 }
 
+// s * x^(30 - 2 i), i < 16.
+__device__ __forceinline__ uint32_t spread_factor(uint32_t s, const int i)
+{
+    const int n = 30 - 2 * i;
+    static_for<4>([&](auto k) {
+        uint32_t v = s;
+        static_for<(2 << k)>([&](auto) { v = gf2_mulx(v); });
+        s = n & (2 << k) ? v : s;
+    });
+    return s;
+}
+
+// Sum of the registers of a parameter tile's run; in the run's last wavefront, on to the tally.  v: the lanes of row j (of 16)
+// hold the register of stream j; f: lane i of a row has spread_factor(the stream's distance to the end of its chunk, i),
+// made while the data was on its way, so that the product takes two bits of v in every lane and an XOR over the row.  (One
+// lane's 32 dependent steps at the end of a short step, us: 200,000 / 2.1 million elements 8.3 / 21.7, so 8.25 / 21.3,
+// chained 2.1 million 19.2 and 18.6.)
+__device__ __forceinline__ void deliver_to_tally(const FusedConsts& C, Lds& lds, const WorkTile& t, uint32_t info, uint32_t v,
+                                                 const uint32_t f, const uint32_t run_entry, uint32_t* __restrict__ crcs,
+                                                 const int lane)
+{
+    const int x = lane >> 4, i = lane & 15;
+    const uint32_t run = (info >> 4) & 7u, len = (info >> 8) & 15u;
+    if (len > 1) {
+        // LDS operations of a wavefront complete in order: the sum is complete when the count is
+        uint32_t before = 0;
+        if (i == 0) atomicXor(&lds.sum[run][x], v);
+        asm volatile("" ::: "memory");
+        if (lane == 0) before = atomicAdd(&lds.arrived[run], 1u);
+        if (__builtin_amdgcn_readfirstlane(before) + 1 != len) return;
+        v = *const_cast<volatile uint32_t*>(&lds.sum[run][x]);
+    }
+    v = row_xor((((v >> (2 * i + 1)) & 1u) ? f : 0u) ^ (((v >> (2 * i)) & 1u) ? gf2_mulx(f) : 0u));
+    // all streams in one chunk (any parameter much smaller than a chunk)?
+    const bool one = t.chunk[0] == t.chunk[1] && t.chunk[0] == t.chunk[2] && t.chunk[0] == t.chunk[3];
+    if (one)
+        v = __builtin_amdgcn_readlane(v, 0) ^ __builtin_amdgcn_readlane(v, 16) ^ __builtin_amdgcn_readlane(v, 32) ^
+            __builtin_amdgcn_readlane(v, 48);
+    if (lane == 0 || (i == 0 && !one)) {
+        uint32_t c = t.chunk[0];
+        static_for<3>([&](auto k) { c = (x == k + 1) ? t.chunk[k + 1] : c; });
+        add_to_tally(C, run_ticket(C, run_entry, x), crcs, c, v);
+    }
+}
+
 // ---- parameter sub-block -------------------------------------------------------------------------
 
 struct RowIn {
@@ -350,7 +397,8 @@ __device__ __forceinline__ void store_image(const WorkTile& t, const uint8_t* im
 // three elements at either end that do not fill a lane's slot are updated one per lane, by lanes 0-3
 // (the slot that holds lo) and 4-7 (the slot that holds hi), and handed to the lanes that own those
 // slots.  What is not the tile's counts as zero.
-template <bool F16, bool CHAINED, bool BC2, bool WHOLE>
+// WARM: of a short step (fused_kernel_warm).
+template <bool F16, bool CHAINED, bool BC2, bool WHOLE, bool WARM>
 __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_t tile, const uint32_t info,
                                                 const uint32_t run_entry, const int at,
                                                 const int lo, const int hi,
@@ -385,10 +433,10 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     static_for<kRows>([&](auto r) {
         if (!WHOLE) q[r] = RowIn{u32x2{0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}};
         if (mine(r)) {
-            q[r].g = load8_unaligned<true>(tg + (lane8 + 2 * kRowElems * r));
-            q[r].p = load16_unaligned<true>(lp + (lane16 + 4 * kRowElems * r));
-            q[r].m = load16_unaligned<true>(lm + (lane16 + 4 * kRowElems * r));
-            q[r].v = load16_unaligned<true>(lv + (lane16 + 4 * kRowElems * r));
+            q[r].g = load8_unaligned<!WARM>(tg + (lane8 + 2 * kRowElems * r));
+            q[r].p = load16_unaligned<!WARM>(lp + (lane16 + 4 * kRowElems * r));
+            q[r].m = load16_unaligned<!WARM>(lm + (lane16 + 4 * kRowElems * r));
+            q[r].v = load16_unaligned<!WARM>(lv + (lane16 + 4 * kRowElems * r));
         }
     });
     // edge elements: lane 0..3 element lane of the slot that holds lo, 4..7 of the slot that holds hi
@@ -410,6 +458,14 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
             ep = f32_at(lp + 4 * ej);
             em = f32_at(lm + 4 * ej);
             ev = f32_at(lv + 4 * ej);
+        }
+    }
+    uint32_t f = 0;  // deliver_to_tally
+    if constexpr (WARM) {
+        if (C.tally) {
+            uint32_t shift = t.shift[0];
+            static_for<3>([&](auto k) { shift = (lane >> 4) == k + 1 ? t.shift[k + 1] : shift; });
+            f = spread_factor(shift, lane & 15);
         }
     }
     // (Waiting for the weights alone, vmcnt counted, and for the data row by row costs 0.7 % on the 7B shard.)
@@ -567,7 +623,11 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
         matrix_take(bits, m);
         matrix_take(bits, v);
     }
-    deliver(C, lds, t, info, row_xor(matrix_streams(bits, lane_c0, lane_c)), run_entry, crcs, lane);
+    const uint32_t reg = row_xor(matrix_streams(bits, lane_c0, lane_c));
+    if (WARM && C.tally)
+        deliver_to_tally(C, lds, t, info, reg, f, run_entry, crcs, lane);
+    else
+        deliver(C, lds, t, info, reg, run_entry, crcs, lane);
 
     if (by_image) {
         workgroup_barrier();
@@ -739,11 +799,71 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TALLY 
     const int hi = left < int(kSubElems) ? left : int(kSubElems);
     const uint8_t* const grad = reinterpret_cast<const uint8_t*>(grads.p[t.grad_index - grad_base]);
     if (lo == 0 && hi == int(kSubElems) && !(t.head_split && at == 0))
-        param_sub_block<F16, CHAINED, BC2, true>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
+        param_sub_block<F16, CHAINED, BC2, true, false>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
                                             lane_tab, wave, lane);
     else
-        param_sub_block<F16, CHAINED, BC2, false>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
+        param_sub_block<F16, CHAINED, BC2, false, false>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
                                              lane_tab, wave, lane);
+}
+
+// Steps over small buffers (kWarmStepBytes): they load through the caches; and what the first wavefronts wait for, the
+// arguments' lines, then the descriptor's, the gradient's address and the run's tickets, they ask for at once, and the end of the
+// chain is shorter (deliver_to_tally).  A kernel of its own, as long steps lose by each: the choice of loads by a branch costs
+// lists of 7 million elements and more 3-5 % in place, the earlier start 0.6 % on the 7B shard, chained 0.9 %.
+template <bool F16, bool CHAINED, bool BC2, uint32_t N>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void fused_kernel_warm(
+    const WorkWave* __restrict__ waves, const WorkTile* __restrict__ tiles, uint32_t grid,
+    const uint32_t* __restrict__ tabs, uint8_t* __restrict__ chunks, uint32_t* __restrict__ crcs,
+    FusedConsts C, GradPtrsOf<N> grads)
+{
+    const uint32_t block = block_behind_args<0, 6 * sizeof(void*) + sizeof(FusedConsts)>();  // up to the gradients'
+    __shared__ Lds lds;
+    extern __shared__ __attribute__((aligned(16))) uint8_t img[];  // of launches with C.image
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
+    const uint32_t group = xcd_place(block, grid, C.xcd_group);
+    if (C.tally && group >= C.n_groups) {
+        clear_tail(C, chunks, group - C.n_groups);
+        return;
+    }
+    fetch_tables(tabs, lds, wave, lane);
+    WorkWave e = waves[group * kWavesPerBlock + wave];
+    const uint32_t run_entry = group * kWavesPerBlock + ((e.info >> 4) & 7u);
+    if (e.tile == kNoTile) {
+        tables_ready();
+        return;
+    }
+    const WorkTile& t = tiles[e.tile];
+    const uint64_t grad_at = grads.p[e.info >> 16];
+    {
+        typedef const __attribute__((address_space(4))) uint32_t Word;
+        Word* const words = (Word*)&t;
+        Word* const ticket = C.tally ? (Word*)(C.runs + 4 * run_entry) : words;
+        const uint32_t all = words[0] | words[16] | words[32] | words[sizeof(WorkTile) / 4 - 1] | *ticket;
+        asm("" : "+s"(e.info) : "s"(all), "s"(grad_at));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const int sub = e.info & 15u;
+    const uint32_t* const lane_tab = tabs + kFusedWeightWords;
+    if (t.kind == kWorkRaw) {
+        const int at = sub * int(kSubRawBytes) - static_cast<int>(t.soff[0] % kRawTileBytes);
+        const int lo = at < 0 ? -at : 0;
+        const int left = static_cast<int>(t.n) - at;
+        raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
+                      crcs, C, run_entry, lds, lane_tab + 32 * 64, wave, lane);
+        return;
+    }
+    const int at = sub * int(kSubElems) - static_cast<int>(t.e0 % kParamTileElems);
+    const int lo = at < 0 ? -at : 0;
+    const int left = static_cast<int>(t.n) - at;
+    const int hi = left < int(kSubElems) ? left : int(kSubElems);
+    const uint8_t* const grad = reinterpret_cast<const uint8_t*>(grad_at);
+    if (lo == 0 && hi == int(kSubElems) && !(t.head_split && at == 0))
+        param_sub_block<F16, CHAINED, BC2, true, true>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
+                                                       lane_tab, wave, lane);
+    else
+        param_sub_block<F16, CHAINED, BC2, false, true>(t, e.tile, e.info, run_entry, at, lo, hi, grad, chunks, crcs, C, lds, img,
+                                                        lane_tab, wave, lane);
 }
 
 // ---- the step's traffic alone (bench helper) -------------------------------------------------------
@@ -978,7 +1098,7 @@ constexpr uint32_t kFewGrads = 64, kSomeGrads = 384;
 template <uint32_t N>
 void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTile* tiles,
                  const void* const* grads, uint32_t p0, uint32_t n_params, const uint32_t* tabs,
-                 uint8_t* chunks, uint32_t* crcs, const FusedConsts& consts, bool off_lines, hipStream_t stream)
+                 uint8_t* chunks, uint32_t* crcs, const FusedConsts& consts, bool off_lines, bool warm, hipStream_t stream)
 {
     using Kernel = decltype(&fused_kernel<false, false, false, N>);
     static const Kernel kernels[8] = {
@@ -986,12 +1106,19 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
         fused_kernel<false, true, false, N>,  fused_kernel<false, true, true, N>,
         fused_kernel<true, false, false, N>,  fused_kernel<true, false, true, N>,
         fused_kernel<true, true, false, N>,   fused_kernel<true, true, true, N>};
+    static const Kernel kernels_warm[8] = {
+        fused_kernel_warm<false, false, false, N>, fused_kernel_warm<false, false, true, N>,
+        fused_kernel_warm<false, true, false, N>,  fused_kernel_warm<false, true, true, N>,
+        fused_kernel_warm<true, false, false, N>,  fused_kernel_warm<true, false, true, N>,
+        fused_kernel_warm<true, true, false, N>,   fused_kernel_warm<true, true, true, N>};
     static const Kernel chained[4] = {  // without a tally
         fused_kernel<false, true, false, N, false>, fused_kernel<false, true, true, N, false>,
         fused_kernel<true, true, false, N, false>,  fused_kernel<true, true, true, N, false>};
     const bool bc2 = consts.adam.bc2s != 1.0f;
-    const Kernel kernel = consts.prev && !consts.tally ? chained[(f16 ? 2 : 0) + (bc2 ? 1 : 0)]
-                                                       : kernels[(f16 ? 4 : 0) + (consts.prev ? 2 : 0) + (bc2 ? 1 : 0)];
+    const int which = (f16 ? 4 : 0) + (consts.prev ? 2 : 0) + (bc2 ? 1 : 0);
+    const Kernel kernel = warm                            ? kernels_warm[which]
+                          : consts.prev && !consts.tally ? chained[(f16 ? 2 : 0) + (bc2 ? 1 : 0)]
+                                                          : kernels[which];
     // The image only pays in launches of several rounds (aligned, in the one round that there is: 64 parameters
     // of 5000 elements 12.0 us from registers, 13.9 through the image; 32 of 32,768 15.6 and 17.2; 64 of 30,011
     // 23.5 and 23.4) and off the lines (30 odd-sized parameters 2921 from registers, 2700 through it; aligned, 64 of
@@ -1013,7 +1140,7 @@ void launch_step(bool f16, const WorkWave* waves, uint32_t n_waves, const WorkTi
     for (uint32_t i = 0; i < N; i++)
         g.p[i] = p0 + i < n_params ? reinterpret_cast<uint64_t>(grads[p0 + i]) : 0;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), consts.prev || at_once ? 0 : c.image ? kImgBytes : kSpareLds, stream, waves,
-                       tiles, p0, tabs, chunks, crcs, c, g);
+                       tiles, warm ? groups : p0, tabs, chunks, crcs, c, g);
 }
 
 }  // namespace
@@ -1062,7 +1189,7 @@ hipError_t launch_fused(bool f16, const FusedWork& work, const void* const* grad
                                 : left <= kSomeGrads ? launch_step<kSomeGrads>
                                                      : launch_step<kGradsPerLaunch>;
             launch(f16, work.waves + w0, w1 - w0, work.tiles, grads, p0, n_params, tabs, c, crcs, consts,
-                   work.launch_off_lines[k] != 0, stream);
+                   work.launch_off_lines[k] != 0, buffer_bytes <= kWarmStepBytes, stream);
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -51,6 +51,13 @@ constexpr uint32_t kGradsPerLaunch = 2048;
 // chained 750 30.4 / 24.6, 1480 44.4 / 40.2, 2450 62.6 / 59.3, 2940 73.1 / 72.6.  In longer launches a workgroup's
 // returning atomics hold up the next one's start.
 constexpr uint64_t kTallyStepGroups = 2560;
+// Steps over buffers up to here load through the caches: what they read was written not long ago, and is still in the
+// 256 MiB last-level cache, or would be by the next step.  Non-temporal / plain loads, us, one set of tensors and snapshots (as in a
+// training program) and three in turn, in place 30 / 45 / 60 / 80 / 100 MB 24.4 / 33.6 / 44.1 / 55.2 / 66.4 against 21.0 / 31.8 /
+// 39.2 / 48.4 / 57.6, in turn 24.4 / 33.8 / 44.4 / 55.4 / 66.7 against 21.3 / 32.3 / 39.5 / 53.1 / 71.5; chained 30 / 60 / 80 / 100 MB
+// 22.1 / 32.3 / 41.4 / 49.5 against 17.5 / 27.7 / 34.1 / 41.1, in turn 22.6 / 33.3 / 42.4 / 50.8 against 18.6 / 27.6 / 38.6 /
+// 51.9.  (The gradients alone non-temporal: 2-7 % behind either.)
+constexpr uint64_t kWarmStepBytes = 80ull << 20;
 template <uint32_t N>
 struct GradPtrsOf {
     uint64_t p[N];

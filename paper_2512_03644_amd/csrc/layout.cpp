@@ -276,9 +276,10 @@ bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,
                 for (uint64_t k = out.size() - slot + begin; k < out.size(); k++)
                     out[k].info = (out[k].info & 0xFFu) | static_cast<uint32_t>(run << 8);
             }
+            const uint32_t grad = t.kind == kWorkParam ? t.grad_index % groups_per_launch : 0;
             for (uint64_t k = 0; k < here; k++, s++)
                 out.push_back(WorkWave{static_cast<uint32_t>(i),
-                                       static_cast<uint32_t>(s | (begin << 4) | (run << 8))});
+                                       static_cast<uint32_t>(s | (begin << 4) | (run << 8)) | grad << 16});
         }
         if (out.size() > max_entries) return false;
     }

@@ -75,7 +75,8 @@ constexpr uint32_t kRawTileBytes = 1u << 15;
 struct WorkWave {
     uint32_t tile;  // index into the tile list, or kNoTile: nothing to do
     uint32_t info;  // bits 0..3 sub-block of the tile's block, 4..6 place of the run's first
-                    // wavefront in the workgroup, 8..11 wavefronts in the run
+                    // wavefront in the workgroup, 8..11 wavefronts in the run, 16..31 of a parameter tile
+                    // the group's number in its launch
 };
 constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 constexpr uint32_t kWavesPerGroup = 8;
@@ -89,7 +90,7 @@ void build_work_tiles(const Layout& L, std::vector<WorkTile>& out);
 // The wavefronts of the tiles, launch by launch: launch k takes the parameter groups
 // [k * groups_per_launch, (k + 1) * groups_per_launch), the last launch the RAW tiles as well.
 // begin[k] is the first entry of launch k, one more entry the end; each a multiple of
-// kWavesPerGroup.  False, with out and begin unfinished, if there would be more than max_entries: the
+// kWavesPerGroup.  groups_per_launch <= 65536.  False, with out and begin unfinished, if there would be more than max_entries: the
 // kernels count tiles and entries in 32 bits, and a tile has up to 16 entries.
 constexpr uint64_t kMaxWorkEntries = 0xFFFFFFF0ull;
 bool build_work_waves(const std::vector<WorkTile>& tiles, uint64_t n_params,

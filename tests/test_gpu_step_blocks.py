@@ -135,6 +135,18 @@ def test_block_edges_of_long_chained_steps(oracle, half):
                          loss_scale=1024.0 if half == torch.float16 else 1.0)
 
 
+# steps over more than 80 MiB have kernels of their own: every edge in place, behind cuts and, with a tally, in one chunk
+@pytest.mark.parametrize("times,chunk", [(55, 1 << 15), (1, 1 << 27)])
+@pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
+def test_block_edges_of_long_steps(oracle, times, chunk, half):
+    scale = 1024.0 if half == torch.float16 else 1.0
+    extra = [(5 * i, t) for i, t in enumerate(_raw([1, 7, 511, 4096, 16385 + 4096], torch.bfloat16, times))]
+    _adam_and_compare(oracle, EDGES * times, chunk, seed=times, hp=dict(HP, step=3), half=half, loss_scale=scale,
+                      extra_raw=extra)
+    if times == 1:
+        _chained_and_compare(oracle, EDGES, chunk, seed=3, steps=2, half=half, loss_scale=scale, extra_raw=extra)
+
+
 def test_captured_step_over_many_groups():
     # 16 KiB of kernel arguments in a graph node: every replay, with eager work between them, equals the eager step
     numels = [7 + 3 * i for i in range(500)]
