@@ -266,7 +266,11 @@ uint64_t* tally_for(const ff_plan* p, hipStream_t s) { return tally_allowed(s) ?
 // Cache hint of a pass of `mode` over `bytes` of the buffer.
 void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
 {
-    if (tiles_are_blocks(t) && !p->hint_given && bytes <= kWarmBytes) t.hint = kHintWarm(mode);
+    if (!tiles_are_blocks(t) || p->hint_given) return;
+    if (bytes <= kWarmBytes)
+        t.hint = kHintWarm(mode);
+    else if (mode == kRestore && bytes > kColdBytes && !p->tile_given)
+        t.hint = 0;
 }
 
 // A pack on the tile kernel keeps the preset kernel and fire-and-forget atomics: waiting for a returning
