@@ -486,8 +486,9 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
     });
     // Of the multiplication that a wavefront ends with, what does not need its data: while that is on its way.  (Behind it,
     // with a run's sum and the count of its wavefronts in two LDS words instead of one: pack / restore of 28 MB 13.3 / 13.7
-    // us, now 13.0 / 13.4, verify of 3 / 28 MB 5.3 / 9.2 and 5.05 / 9.0.  Not where registers are short.)
-    constexpr bool kAhead = !HOLD && !LEAN;
+    // us, now 13.0 / 13.4.  Not where registers are short: a verify has room for three workgroups on a compute unit without,
+    // for two with: 100 / 180 MB 21.4 / 36.3 and 23.8 / 38.5, 3 MB 5.17 and 5.09.)
+    constexpr bool kAhead = !HOLD && !LEAN && MODE != kVerify;
     uint32_t lane_c = 0, times[16];
     auto tables_ready = [&] {
         if (kAhead) gf2_multiples(times, lane_c);

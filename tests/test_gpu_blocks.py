@@ -450,3 +450,31 @@ def test_flags_written_over_the_checksums(nbytes):
     want[3 * chunk // 2:4 * chunk // 2] = 0
     assert int(n_bad.item()) == 1 and np.array_equal(np.flatnonzero(_u32(crcs)), [3])
     assert torch.equal(t.view(torch.int16), want.view(torch.int16))
+
+
+# a restore of small tensors goes through the caches above 384 MiB, and around them below
+@pytest.mark.parametrize("nbytes", [(384 << 20) - 4096, (384 << 20) + 4096])
+def test_restore_of_small_tensors_on_both_sides_of_384_mib(nbytes):
+    arena = torch.empty(nbytes + (64 << 20), dtype=torch.uint8, device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(nbytes % 1000003)
+    arena.view(torch.int64).random_(generator=gen)
+    half, segs, at, left, k = arena.view(torch.bfloat16), [], 0, nbytes // 2, 0
+    while left:  # 2.4 to 6.9 KB, off every line
+        n = min(left, 1201 + 37 * (k % 61))
+        segs.append(half[at:at + n])
+        at, left, k = at + n + 1 + k % 5, left - n, k + 1
+    plan = ff.ff_snapshot_plan(segs, 1 << 20)
+    chunks, crcs, bad, n_bad = ff.alloc_outputs(plan, DEV)
+    ff.ff_pack(plan, chunks, crcs)
+    want, gaps = arena.clone(), torch.ones_like(half, dtype=torch.bool)
+    for t in segs:
+        gaps[(t.data_ptr() - half.data_ptr()) // 2:][:t.numel()] = False
+        t.zero_()
+    half.view(torch.int16)[gaps] ^= 0x55
+    want.view(torch.int16)[gaps] ^= 0x55
+    for flags in (0, ff.FF_RESTORE_SKIP_BAD):
+        ff.ff_restore(plan, chunks, crcs, bad, n_bad, flags)
+        torch.cuda.synchronize()
+        assert int(n_bad.item()) == 0 and torch.equal(arena, want)
+        half[~gaps] = 0
