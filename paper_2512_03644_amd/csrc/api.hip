@@ -39,7 +39,7 @@ struct ff_plan {
     int device = -1;
     void* dev_block = nullptr;  // one allocation holding every device table
     TileTables tables;
-    bool hint_given = false, tile_given = false;  // by the plan's flags
+    bool hint_given = false, tile_given = false, order_given = false;  // by the plan's flags
     // A pass that only reads (verify) runs fastest on larger tiles than one that also writes:
     // it folds verify_group consecutive tiles as one.
     uint32_t verify_group = 1;
@@ -273,6 +273,16 @@ void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
         t.hint = 0;
 }
 
+// Run length of the XCDs' order of a pass that moves `bytes` of the buffer: short runs for restores and packs in blocks
+// (kShortXcdGroup).
+void choose_order(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
+{
+    const bool blocks = tiles_are_blocks(t);
+    if (p->order_given || mode == kVerify || (mode == kPack && !blocks)) return;
+    if (bytes <= kShortRunsFrom || bytes > kShortRunsTo) return;
+    t.xcd_group = blocks && bytes > kColdBytes ? 2 * kShortXcdGroup : kShortXcdGroup;
+}
+
 // A pack on the tile kernel keeps the preset kernel and fire-and-forget atomics: waiting for a returning
 // one at the end of every workgroup costs more than the launch (7B shard 3.677 against 3.684 ms, 3.2 GB
 // of ragged tensors 1.097 against 1.107, 256 MB 98.8 both).  Restore and verify, which save two
@@ -362,6 +372,7 @@ int ff_snapshot_plan(const ff_segment* segs, uint64_t n_segs, uint64_t chunk_byt
     // bits 19..23: 0 = default, else log2(xcd_group) + 1, 31 = no regrouping (tuning knob)
     {
         const unsigned xg = (flags >> 19) & 31u;
+        p->order_given = xg != 0;
         if (xg == 30u) {  // 8 * 2^29 workgroups per round does not fit the 32-bit launch index
             delete p;
             return FF_ERR_INVALID;
@@ -459,6 +470,7 @@ int ff_pack(const ff_plan* p, void* chunks, uint32_t* crcs, void* hip_stream)
     TileTables t = p->tables;
     t.acc = crcs;
     choose_hint(p, t, kPack, p->layout.buffer_bytes);
+    choose_order(p, t, kPack, p->layout.buffer_bytes);
     if (pack_takes_tally(t)) t.tally = tally_for(p, s);
     if (!t.tally)
         FF_HIP_TRY(launch_preset(crcs, nullptr, 0, p->layout.n_chunks, p->affine, nullptr, nullptr, s));
@@ -505,6 +517,7 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         if (verify_only) return FF_OK;
         t.acc = nullptr;
         t.skip_bad = bad;
+        choose_order(p, t, kRestore, L.buffer_bytes);
         FF_HIP_TRY(launch_tiles(kRestore, t, buf, s, nullptr));
         return FF_OK;
     }
@@ -535,6 +548,8 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
     }
     choose_hint(p, v, pass1 ? kVerify : kRestore, bytes);
     choose_hint(p, t, kRestore, bytes);
+    choose_order(p, v, pass1 ? kVerify : kRestore, bytes);
+    choose_order(p, t, kRestore, bytes);
     if ((list ? list->n : L.n_chunks) <= kTallyChunks) v.tally = tally_for(p, s);
     v.want = crcs;
     v.n_bad = n_bad;
@@ -654,6 +669,7 @@ int ff_pack_to_host(const ff_plan* p, void* chunks, uint32_t* crcs, void* host_c
         if (pack_takes_tally(t)) t.tally = tally_for(p, ps);
         t.tile_begin = static_cast<uint32_t>(j0 * L.tiles_per_chunk);
         t.n_list = static_cast<uint32_t>(nj * L.tiles_per_chunk);
+        choose_order(p, t, kPack, nj * L.chunk_bytes);
         if (!t.tally) FF_HIP_TRY(launch_preset(crcs, nullptr, j0, nj, p->affine, nullptr, nullptr, ps));
         FF_HIP_TRY(launch_tiles(kPack, t, chunks, ps));
         // the copy stream waits for this slice; the event belongs to this call alone and is

@@ -475,8 +475,36 @@ static void skipping_restore_in_one_pass()
     }
 }
 
+// Runs of the XCDs' order: short in restores and in packs in blocks of more than 80 MiB, up to 4 GiB, unless the flags name one.
+static void order_by_size()
+{
+    const uint32_t rule = kDefaultXcdGroup, brief = kShortXcdGroup;
+    struct { uint64_t n, bytes, misaligned; uint32_t flags, pack, restore; } cases[] = {
+        {1, 80ull << 20, 0, 0, rule, rule},
+        {1, 81ull << 20, 0, 0, brief, brief},              // blocks
+        {1, 192ull << 20, 0, 0, rule, brief},              // tiles
+        {1, 192ull << 20, 6, 0, brief, brief},             // blocks
+        {1, 4096ull << 20, 0, 0, rule, brief},
+        {1, 4097ull << 20, 0, 0, rule, rule},
+        {100000, 2560, 6, 0, brief, brief},                // blocks, whatever the size
+        {200000, 2560, 6, 0, 2 * brief, 2 * brief},
+        {1, 100ull << 20, 0, FF_PLAN_XCD_ORDER(7), 64, 64},
+        {1, 100ull << 20, 0, FF_PLAN_XCD_ORDER(31), 0, 0},
+    };
+    for (const auto& c : cases) {
+        Job j(c.n, c.bytes, 1 << 20, c.flags, c.misaligned);
+        g_line = static_cast<int>(&c - cases);
+        CHECK(j.pack(nullptr).back().t.xcd_group == c.pack);
+        CHECK(j.restore(0, nullptr)[0].t.xcd_group == c.restore);
+        const uint32_t given = c.flags ? c.pack : rule;
+        CHECK(j.restore(FF_RESTORE_VERIFY_ONLY, nullptr)[0].t.xcd_group == given);
+        CHECK(j.listed(0, nullptr)[0].t.xcd_group == given);  // 2 MiB of it
+    }
+}
+
 int main()
 {
+    order_by_size();
     step_in_one_launch();
     skipping_restore_in_one_pass();
     room_by_the_working_groups();
