@@ -11,10 +11,13 @@
 //
 // What bounds a small call is that chain and the launch itself.  With Horner steps through byte tables in
 // place of the matrix product, 124 lookups a lane and block, the wavefronts of a compute unit queued at its
-// LDS, all at the same time: pack of 32 MB 18.9 us and 14.9 now (a copy of it 10.2-11.2), restore 18.9 and
-// 14.6, verify of 41 / 3.2 MB 16.6 / 9.6 and 11.5 / 6.1.  On 1 GB of 5 KiB tensors, where the lookups hid behind
-// the memory, a restore takes 396 us and took 407, though the weights leave room for two workgroups on a compute
-// unit and the tables left it for three; a long pack takes half the weights, and has three (block_kernel_lean).
+// LDS, all at the same time: pack of 28 MB 18.9 us and 14.5 with the product, restore 18.9 and 14.8, verify of 41 / 3.2 MB
+// 16.6 / 9.6 and 11.5 / 6.1.  With the chain's ends shorter (block_behind_args, few_tensors, kAhead) 13.0, 13.4, and verify of
+// 3 MB 5.2, where a copy in this shape takes 9.0 for 28 MB and 3.0 for 3: the rest is the fold behind the last rows (1.1 us), the
+// way to the chunk's word (0.7) and the table entry in front of a pack's rows.  On 1 GB of 5 KiB tensors, where the lookups
+// hid behind the memory, a restore took 407 us, 396 with the product, and takes 379 (kColdBytes, kShortXcdGroup), though the
+// weights leave room for two workgroups on a compute unit and the tables left it for three; a long pack takes half
+// the weights, and has three (block_kernel_lean).
 //
 // A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the
 // plan's tally, which starts at zero, and whoever completes the word writes the chunk's result and

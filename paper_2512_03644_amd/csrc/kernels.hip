@@ -668,9 +668,9 @@ tile_kernel(
     __shared__ __align__(16) uint32_t tab[1024];
     __shared__ RunLds run_lds;
     __shared__ __align__(16) uint32_t ring[MODE == kRestore ? kWavesPerBlock : 1][kRingWords];
-    // In one round of loads.  (A restore is faster for the pause of four: 600 MB 223.2 us, in one round 225.6, 7B shard 3644 and
-    // 3670; pack of 600 MB 223.5 and 222.5, of 20,000 ragged tensors 1114 and 1111, verify of 300 MB 57.3 and 57.0.)
-    if (MODE == kRestore)
+    // Packs and restores are faster for the pause of four rounds of loads (in one, 7B shard 3672 and 3689 us, 3644 and 3670; 70B
+    // pack 4842 and 4862; restore of 600 MB 223.2 and 225.5), a verify is not (300 / 600 MB 57.3 / 103.2 and 57.0 / 102.8).
+    if (MODE != kVerify)
         for (int i = threadIdx.x; i < 1024; i += kWaveSize * kWavesPerBlock) tab[i] = tab_u_global[i];
     else
         reinterpret_cast<u32x4*>(tab)[threadIdx.x] = *as_global(reinterpret_cast<const u32x4*>(tab_u_global) + threadIdx.x);
