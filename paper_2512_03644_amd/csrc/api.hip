@@ -269,7 +269,7 @@ void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
     if (!tiles_are_blocks(t) || p->hint_given) return;
     if (bytes <= kWarmBytes)
         t.hint = kHintWarm(mode);
-    else if (mode == kRestore && bytes > kColdBytes && !p->tile_given)
+    else if (mode == kRestore && bytes > kCachedRestoreBytes && !p->tile_given)
         t.hint = 0;
 }
 
@@ -280,7 +280,7 @@ void choose_order(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes
     const bool blocks = tiles_are_blocks(t);
     if (p->order_given || mode == kVerify || (mode == kPack && !blocks)) return;
     if (bytes <= kShortRunsFrom || bytes > kShortRunsTo) return;
-    t.xcd_group = blocks && bytes > kColdBytes ? 2 * kShortXcdGroup : kShortXcdGroup;
+    t.xcd_group = blocks && bytes > kLongerRunsFrom ? 2 * kShortXcdGroup : kShortXcdGroup;
 }
 
 // A pack on the tile kernel keeps the preset kernel and fire-and-forget atomics: waiting for a returning

@@ -15,7 +15,7 @@
 // 16.6 / 9.6 and 11.5 / 6.1.  With the chain's ends shorter (block_behind_args, few_tensors, kAhead) 13.0, 13.4, and verify of
 // 3 MB 5.2, where a copy in this shape takes 9.0 for 28 MB and 3.0 for 3: the rest is the fold behind the last rows (1.1 us), the
 // way to the chunk's word (0.7) and the table entry in front of a pack's rows.  On 1 GB of 5 KiB tensors, where the lookups
-// hid behind the memory, a restore took 407 us, 396 with the product, and takes 379 (kColdBytes, kShortXcdGroup), though the
+// hid behind the memory, a restore took 407 us, 396 with the product, and takes 382 (kShortXcdGroup), though the
 // weights leave room for two workgroups on a compute unit and the tables left it for three; a long pack takes half
 // the weights, and has three (block_kernel_lean).
 //

@@ -13,14 +13,14 @@ namespace ffsnap {
 constexpr uint32_t kDefaultXcdGroup = 2048;
 
 // Restores, and packs in blocks, of more than kShortRunsFrom bytes take short runs instead, in tiles of 1 MB, in blocks of 512 KB
-// (of 1 MB above kColdBytes), so that the XCDs sweep one region and not eight.  Default / short, us: pack of 75 / 90 / 100 / 130 /
+// (of 1 MB above kLongerRunsFrom), so that the XCDs sweep one region and not eight.  Default / short, us: pack of 75 / 90 / 100 / 130 /
 // 180 MB 24.9 / 32.6 / 45.4 / 54.1 / 74.3 and 25.1 / 31.2 / 41.8 / 50.9 / 70.7, of 5 KiB tensors 0.15 / 0.3 / 1 GB 61.9 / 113.8 /
 // 356.8 and 59.4 / 110.6 / 348.4; restore of 60 / 110 / 150 / 300 / 600 MB 22.7 / 44.8 / 60.7 / 123.3 / 223 and 22.8 / 42.6 / 56.5 /
 // 116.2 / 213, of 1 / 2 / 4 GB 354 / 667 / 1345 and 342 / 650 / 1334, 11.8 GB 3642 both; of 5 KiB tensors 0.3 / 1 GB 121.6 / 386.8 and
 // 116.5 / 379.2; 24 listed chunks of them 44.3 and 43.5.  A pack on tiles gains or loses as the tensors lie (0.3 / 0.6 GB 117.6 / 222.9
 // and 115.2 / 213.2, of large tensors in one allocation 112.2 / 207.8 and 120.9 / 215.0; 15 GB 4862 and 4928), a verify nothing.
 constexpr uint32_t kShortXcdGroup = 8;
-constexpr uint64_t kShortRunsFrom = 80ull << 20, kShortRunsTo = 4096ull << 20;
+constexpr uint64_t kShortRunsFrom = 80ull << 20, kLongerRunsFrom = 384ull << 20, kShortRunsTo = 4096ull << 20;
 
 constexpr uint32_t kTallyFan = 32;
 // A verdict on more chunks than this does without the tally: the returning atomics of a chunk hold its

@@ -502,8 +502,34 @@ static void order_by_size()
     }
 }
 
+// The caches that a pass in blocks goes through: warm up to 96 MiB; a restore of small tensors through them again above 1 GiB.
+static void caches_by_size()
+{
+    const uint32_t around = 3, mid = FF_PLAN_TILE_LOG2(13);
+    struct { uint64_t n, bytes, misaligned; uint32_t flags, restore; } cases[] = {
+        {1, 96ull << 20, 0, 0, kHintWarm(kRestore)},
+        {1, 97ull << 20, 0, 0, around},
+        {100000, 4096, 6, 0, around},                       // 390 MiB, in blocks
+        {262144, 4096, 6, 0, around},                       // 1 GiB
+        {262145, 4096, 6, 0, 0},
+        {262145, 4096, 6, mid, around},                     // blocks that are asked for
+        {262145, 4096, 6, FF_PLAN_CACHE_HINT(1), 1},
+        {1, 1100ull << 20, 0, 0, around},                   // tiles
+    };
+    for (const auto& c : cases) {
+        Job j(c.n, c.bytes, 1 << 20, c.flags, c.misaligned);
+        g_line = static_cast<int>(&c - cases);
+        const auto log = j.restore(0, nullptr);
+        CHECK(log[0].t.hint == c.restore);
+        CHECK(is(log[0], "block_kernel") == (c.n > 1 || c.bytes <= 97ull << 20));
+        if (!is(log[0], "block_kernel")) continue;
+        CHECK(is(log[0], ("block_kernelILi1ELi" + std::to_string(c.restore) + "E").c_str()));
+    }
+}
+
 int main()
 {
+    caches_by_size();
     order_by_size();
     step_in_one_launch();
     skipping_restore_in_one_pass();
