@@ -263,13 +263,14 @@ bool tally_allowed(hipStream_t s)
 }
 uint64_t* tally_for(const ff_plan* p, hipStream_t s) { return tally_allowed(s) ? p->tally : nullptr; }
 
-// Cache hint of a pass of `mode` over `bytes` of the buffer.
-void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes)
+// Cache hint of a pass of `mode` over `bytes` of the buffer.  plain: by block_kernel, not one that holds its chunks or takes a
+// list of them, which exist for warm buffers and for access around the caches only.
+void choose_hint(const ff_plan* p, TileTables& t, TileMode mode, uint64_t bytes, bool plain)
 {
     if (!tiles_are_blocks(t) || p->hint_given) return;
     if (bytes <= kWarmBytes)
         t.hint = kHintWarm(mode);
-    else if (mode == kRestore && bytes > kCachedRestoreBytes && !p->tile_given)
+    else if (mode == kRestore && plain && bytes > kCachedRestoreBytes && !p->tile_given)
         t.hint = 0;
 }
 
@@ -469,7 +470,7 @@ int ff_pack(const ff_plan* p, void* chunks, uint32_t* crcs, void* hip_stream)
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     TileTables t = p->tables;
     t.acc = crcs;
-    choose_hint(p, t, kPack, p->layout.buffer_bytes);
+    choose_hint(p, t, kPack, p->layout.buffer_bytes, true);
     choose_order(p, t, kPack, p->layout.buffer_bytes);
     if (pack_takes_tally(t)) t.tally = tally_for(p, s);
     if (!t.tally)
@@ -503,7 +504,7 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         count_directly(p, t, L.n_chunks);
         t.polls = p->polls;
         t.xcd_group = kHoldXcdGroup;
-        choose_hint(p, t, kRestore, L.buffer_bytes);
+        choose_hint(p, t, kRestore, L.buffer_bytes, false);
         FF_HIP_TRY(launch_held(t, buf, s));
         return FF_OK;
     }
@@ -546,8 +547,8 @@ int restore_impl(const ff_plan* p, const void* chunks, const uint32_t* crcs, uin
         while ((1u << v.tpc_log2) < v.tiles_per_chunk) v.tpc_log2++;
         v.shift_stride = p->verify_group;
     }
-    choose_hint(p, v, pass1 ? kVerify : kRestore, bytes);
-    choose_hint(p, t, kRestore, bytes);
+    choose_hint(p, v, pass1 ? kVerify : kRestore, bytes, !list);
+    choose_hint(p, t, kRestore, bytes, !list);
     choose_order(p, v, pass1 ? kVerify : kRestore, bytes);
     choose_order(p, t, kRestore, bytes);
     if ((list ? list->n : L.n_chunks) <= kTallyChunks) v.tally = tally_for(p, s);

@@ -525,6 +525,18 @@ static void caches_by_size()
         if (!is(log[0], "block_kernel")) continue;
         CHECK(is(log[0], ("block_kernelILi1ELi" + std::to_string(c.restore) + "E").c_str()));
     }
+    // A restore that holds its chunks, or of a list of them, has no kernel that goes through the caches both ways: its tables say
+    // what its kernel does.
+    auto check = [](const std::vector<Launch>& log, const std::string& part, uint32_t hint) {
+        int n = 0;
+        for (const Launch& l : log)
+            if (is(l, (part + std::to_string(hint) + "E").c_str())) { CHECK(l.t.hint == hint); n++; }
+        CHECK(n == 1);
+    };
+    Job small(300000, 4096, 1 << 20, 0, 6), large(600000, 4096, 1 << 30, 0, 6);
+    FROM_HERE(check(small.restore(FF_RESTORE_SKIP_BAD, nullptr), "block_kernel_heldILi", around));
+    FROM_HERE(check(small.listed(0, nullptr), "block_kernel_listedILi1ELi", kHintWarm(kRestore)));  // 2 MiB
+    FROM_HERE(check(large.listed(0, nullptr), "block_kernel_listedILi1ELi", around));               // 2 GiB
 }
 
 int main()
