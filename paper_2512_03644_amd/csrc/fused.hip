@@ -42,7 +42,9 @@
 // 24.5, 96 ragged ones 34.8 -> 31.9, 2000 ragged groups 1016 -> 988, chained 20 million elements 53.1 -> 52.0;
 // 64 parameters, 2.1 million, and the 7B shard the same within 0.5 %.
 // Short steps since, in a kernel of their own (fused_kernel_warm), before / now, us, three sets in turn: 0.2 million elements
-// 8.7 / 8.3, 2.1 million 25.2 / 21.2, chained 22.4 / 18.4, 3.2 million 33.3 / 30.7, chained 4.3 million 32.5 / 26.5.
+// 8.7 / 8.3, 2.1 million 25.2 / 21.2, chained 22.4 / 18.4, 3.2 million 33.3 / 30.7, chained 4.3 million 32.5 / 26.5.  In fp16, one
+// set, before / now / now but with two registers in scratch memory, 0.1 / 1 / 2 million chained - / - / 22.2, 9.55 / 13.00 /
+// 17.5 and 9.70 / 13.04 / 17.8, in place 0.2 / 1 / 5 million 10.0 / - / 51.0, 9.37 / 13.33 / 43.7 and 9.42 / 13.51 / 43.7.
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
@@ -472,11 +474,13 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     tables_ready();
 
     uint32_t nonfinite = 0;  // this lane's count of infinite or NaN gradient elements (fp16 only)
-    uint32_t edge_w = 0;
+    uint32_t edge_w = 0, edge_nonfinite = 0;  // (of the whole wavefront)
     if (!WHOLE) {
         uint32_t wb = 0;
+        // (WARM: in a scalar register; the eighty others are taken, and it went to scratch memory and back)
+        if (F16 && WARM) edge_nonfinite = __popcll(__ballot(f16_nonfinite(eg)));
         if (has_edge) {
-            if constexpr (F16) nonfinite += f16_nonfinite(eg) ? 1u : 0u;
+            if constexpr (F16 && !WARM) nonfinite += f16_nonfinite(eg) ? 1u : 0u;
             adam_element<F16, BC2>(C, eg, ep, em, ev);
             ep = canonical_nan(ep);
             em = canonical_nan(em);
@@ -638,9 +642,10 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     }
 
     if constexpr (F16) {
-        if (C.n_nonfinite && __any(nonfinite != 0)) {
+        if (C.n_nonfinite && (__any(nonfinite != 0) || edge_nonfinite)) {
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) nonfinite += __shfl_xor(nonfinite, d);
+            nonfinite += edge_nonfinite;
             if (lane == 0) {
                 if (C.tally) open_count(C.state, C.epoch, C.n_nonfinite);
                 atomicAdd(reinterpret_cast<unsigned long long*>(C.n_nonfinite),
