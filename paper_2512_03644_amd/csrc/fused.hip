@@ -43,8 +43,9 @@
 // 64 parameters, 2.1 million, and the 7B shard the same within 0.5 %.
 // Short steps since, in a kernel of their own (fused_kernel_warm), before / now, us, three sets in turn: 0.2 million elements
 // 8.7 / 8.3, 2.1 million 25.2 / 21.2, chained 22.4 / 18.4, 3.2 million 33.3 / 30.7, chained 4.3 million 32.5 / 26.5.  In fp16, one
-// set, before / now / now but with two registers in scratch memory, 0.1 / 1 / 2 million chained - / - / 22.2, 9.55 / 13.00 /
-// 17.5 and 9.70 / 13.04 / 17.8, in place 0.2 / 1 / 5 million 10.0 / - / 51.0, 9.37 / 13.33 / 43.7 and 9.42 / 13.51 / 43.7.
+// set, 0.2 / 2.1 / 5 million 10.0 / 9.4, 22.6 / 19.7, 51.0 / 43.7, chained 10.0 / 9.4, 22.2 / 17.5, 38.4 / 31.1 (with two registers
+// in scratch memory 0.1 / 1 / 2.1 million 9.50 / 13.51 / 19.7 against 9.44 / 13.33 / 19.7, chained 9.70 / 13.04 / 17.8 against 9.55 /
+// 13.00 / 17.5).
 #include "fused.hpp"
 
 #include <hip/hip_fp16.h>
@@ -477,7 +478,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
     uint32_t edge_w = 0, edge_nonfinite = 0;  // (of the whole wavefront)
     if (!WHOLE) {
         uint32_t wb = 0;
-        // (WARM: in a scalar register; the eighty others are taken, and it went to scratch memory and back)
+        // (a scalar register: a short step has no other left, and the count went to scratch memory and back)
         if (F16 && WARM) edge_nonfinite = __popcll(__ballot(f16_nonfinite(eg)));
         if (has_edge) {
             if constexpr (F16 && !WARM) nonfinite += f16_nonfinite(eg) ? 1u : 0u;
@@ -661,6 +662,7 @@ __device__ __forceinline__ void param_sub_block(const WorkTile& t, const uint32_
 // are the tile's, and its first byte is `at` bytes behind the tile's first (perhaps before it).  A
 // slot of 16 bytes that is the tile's only in part is moved halfword by halfword, by lanes 0-7 (the
 // slot that holds lo) and 8-15 (the one that holds hi), and handed to its owner for the CRC.
+template <bool WARM>
 __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t info, const int at,
                                               const int lo, const int hi, uint8_t* __restrict__ chunks,
                                               uint32_t* __restrict__ crcs, const FusedConsts& C,
@@ -679,7 +681,7 @@ __device__ __forceinline__ void raw_sub_block(const WorkTile& t, const uint32_t 
     u32x4 w[kRawRows];
     static_for<kRawRows>([&](auto r) {
         w[r] = u32x4{0, 0, 0, 0};
-        if (mine(r)) w[r] = load16_unaligned<true>(src + r * 1024 + 16 * lane);
+        if (mine(r)) w[r] = load16_unaligned<!WARM>(src + r * 1024 + 16 * lane);
     });
     const int edge_lo = lo & ~15, edge_hi = hi & ~15;
     const bool lo_cut = (lo & 15) || edge_lo + 16 > hi, hi_cut = (hi & 15) && edge_hi > edge_lo;
@@ -794,7 +796,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TALLY 
         const int at = sub * int(kSubRawBytes) - static_cast<int>(t.soff[0] % kRawTileBytes);
         const int lo = at < 0 ? -at : 0;
         const int left = static_cast<int>(t.n) - at;
-        raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
+        raw_sub_block<false>(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
                       crcs, C, run_entry, lds, lane_tab + 32 * 64, wave, lane);
         return;
     }
@@ -854,7 +856,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
         const int at = sub * int(kSubRawBytes) - static_cast<int>(t.soff[0] % kRawTileBytes);
         const int lo = at < 0 ? -at : 0;
         const int left = static_cast<int>(t.n) - at;
-        raw_sub_block(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
+        raw_sub_block<true>(t, e.info, at, lo, left < int(kSubRawBytes) ? left : int(kSubRawBytes), chunks,
                       crcs, C, run_entry, lds, lane_tab + 32 * 64, wave, lane);
         return;
     }

@@ -56,7 +56,9 @@ constexpr uint64_t kTallyStepGroups = 2560;
 // training program) and three in turn, in place 30 / 45 / 60 / 80 / 100 MB 24.4 / 33.6 / 44.1 / 55.2 / 66.4 against 21.0 / 31.8 /
 // 39.2 / 48.4 / 57.6, in turn 24.4 / 33.8 / 44.4 / 55.4 / 66.7 against 21.3 / 32.3 / 39.5 / 53.1 / 71.5; chained 30 / 60 / 80 / 100 MB
 // 22.1 / 32.3 / 41.4 / 49.5 against 17.5 / 27.7 / 34.1 / 41.1, in turn 22.6 / 33.3 / 42.4 / 50.8 against 18.6 / 27.6 / 38.6 /
-// 51.9.  (The gradients alone non-temporal: 2-7 % behind either.)
+// 51.9.  (The gradients alone non-temporal: 2-7 % behind either.)  RAW tensors as well, us: 0.2 million elements and 32 MB of them
+// 19.6 / 18.9, chained 19.7 / 17.9, 2.1 million and 9 / 32 MB 22.8 / 36.9 against 21.5 / 32.0, chained 20.7 / 31.9 against 18.7 / 26.7;
+// first passes over a new state 50.9 / 52.0 / 65.0 against 46.4 / 51.1 / 63.8, chained 47.4 / 52.0 / 56.8 against 44.6 / 52.8 / 54.3.
 constexpr uint64_t kWarmStepBytes = 80ull << 20;
 template <uint32_t N>
 struct GradPtrsOf {

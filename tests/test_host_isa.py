@@ -72,3 +72,22 @@ def test_steps_keep_nothing_in_scratch_memory(step_registers):
     assert sum("fused_kernel_warm" in k for k in steps) == 24 and len(steps) == 60
     for k, v in steps.items():
         assert v["next_free_vgpr"] <= 80 and v["private_segment_fixed_size"] == 0, (k, v)
+
+
+def test_short_steps_load_through_the_caches(step_asm):
+    # what a short step reads, its tensors that are only copied included, is in the last-level cache or would be by the next step
+    nt, name = {}, None
+    for line in open(step_asm):
+        m = re.match(r"(_Z\S+):", line)
+        if m:
+            name = m.group(1)
+        m = re.match(r"\s+(global|flat|buffer)_load_\w+", line)
+        if m and name:
+            nt.setdefault(name, []).append(bool(re.search(r"\bnt\b", line)))
+    warm = [k for k in nt if "fused_kernel_warm" in k]
+    long = [k for k in nt if re.search(r"fused_kernelILb", k)]
+    assert len(warm) == 24 and len(long) == 36
+    for k in warm:
+        assert not any(nt[k]), k
+    for k in long:
+        assert any(nt[k]), k
