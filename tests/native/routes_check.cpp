@@ -371,6 +371,44 @@ static void room_by_the_working_groups()
             }
 }
 
+// The step's kernel: of a short step, and of a long one with or without the code of the tally.
+static const char* step_kernel(const Launch& l)
+{
+    const bool is_short = is(l, "fused_kernel_warmILb"), is_long = is(l, "fused_kernelILb");
+    CHECK(is_short != is_long);
+    if (is_short) return "short";
+    CHECK(is(l, "ELb0EEEv") != is(l, "ELb1EEEv"));
+    return is(l, "ELb0EEEv") ? "long, no tally" : "long";
+}
+// ... hangs on the buffer's size, 80 MiB or more, and on whether a long chained step has a tally.
+static void step_kernel_by_size()
+{
+    void* const named = reinterpret_cast<void*>(0x7f0012340000ull);
+    struct { uint64_t n, numel, chunk; bool is_short; } cases[] = {
+        {10, 30011, 1 << 18, true},
+        {1, 5991862, 1 << 20, true}, {1, 5991863, 1 << 20, false},  // 80 and 81 MiB
+        {2049, 2900, 1 << 14, true}, {2049, 2930, 1 << 14, false},  // two launches
+        {3, 5000, 1 << 27, false},                                  // one chunk of 128 MiB
+    };
+    for (const auto& c : cases)
+        for (const uint32_t half : {FF_BF16, FF_F16})
+            for (const bool chained : {false, true})
+                for (void* s : {static_cast<void*>(nullptr), named}) {
+                    g_line = static_cast<int>(&c - cases);
+                    Step j(c.n, c.numel, c.chunk, 4, half);
+                    CHECK((ff_plan_buffer_bytes(j.plan) <= 80ull << 20) == c.is_short);
+                    int n = 0;
+                    for (const Launch& l : j.run(chained, s)) {
+                        if (!is(l, "fused_kernel")) continue;
+                        n++;
+                        CHECK((l.step.tally != nullptr) == (!s && c.n <= kGradsPerLaunch));
+                        const std::string want = c.is_short ? "short" : chained && !l.step.tally ? "long, no tally" : "long";
+                        CHECK(step_kernel(l) == want);
+                    }
+                    CHECK(n == (c.n > kGradsPerLaunch ? 2 : 1));
+                }
+}
+
 // A step is one launch that sums up in the plan's tally on the default stream, eager, where it is short, its gradients
 // are one launch's and no chunk has more contributions than the tally's words take.  Else it knows no tally, and a
 // kernel in front of it presets the checksums, clears the buffer's end and counter.
@@ -380,7 +418,7 @@ static void step_in_one_launch()
     auto one = [](const std::vector<Launch>& log) {
         CHECK(log.size() == 1 && is(log[0], "fused_kernel"));
         const FusedConsts& c = log[0].step;
-        CHECK(log[0].kernel.find("ELb0EEEv") == std::string::npos);  // not the kernel that knows no tally
+        CHECK(step_kernel(log[0]) != std::string("long, no tally"));
         CHECK(c.tally && c.runs && c.heads && c.state && c.epoch && c.affine);
         CHECK(c.n_groups && c.n_groups <= log[0].groups);
         // every 64 KiB behind the payload has a workgroup, and the counter has one in any case
@@ -544,6 +582,7 @@ int main()
     caches_by_size();
     order_by_size();
     step_in_one_launch();
+    step_kernel_by_size();
     skipping_restore_in_one_pass();
     room_by_the_working_groups();
     one_pass_where_a_chunk_fits_the_device();
