@@ -135,6 +135,8 @@ int main(){
         if(w[i].tile==kNoTile) continue;
         const WorkTile& t=tiles[w[i].tile];
         if(t.kind==kWorkParam ? t.grad_index/per_launch!=k : k+1!=launches){ printf("launch of a tile\n"); return 1; }
+        // the place of its gradient among the launch's (a RAW tile has none)
+        if(w[i].info>>16 != (t.kind==kWorkParam ? t.grad_index-k*per_launch : 0)){ printf("group\n"); return 1; }
         const uint32_t sub=w[i].info&15, first=(w[i].info>>4)&7, len=(w[i].info>>8)&15;
         if(seen[w[i].tile]&(1u<<sub)){ printf("twice\n"); return 1; }
         seen[w[i].tile]|=1u<<sub;
