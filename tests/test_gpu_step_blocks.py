@@ -11,6 +11,7 @@ from test_gpu_parity import DEV, HP, _adam_and_compare, _chained_and_compare
 
 pytestmark = pytest.mark.gpu
 
+SHORT_STEP = 80 << 20  # a step over a larger buffer has kernels of its own
 EDGES = [1, 2, 3, 4, 5, 7, 8, 9, 255, 256, 257, 259, 511, 512, 513, 1023, 1024, 1025, 1027, 3583, 3584, 3585,
          4095, 4096, 4097, 8188, 8191, 8192, 8193, 8197, 16384 + 1022]
 
@@ -30,17 +31,25 @@ def test_block_edges_in_place_and_chained(oracle, chunk):
                          loss_scale=1024.0, extra_raw=extra)
 
 
+# of a short step, of a long one with a tally, and of one without
 @pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("chunk", [1 << 15, 1 << 17, 1 << 22])
-def test_results_through_the_image(oracle, chunk, half):
+@pytest.mark.parametrize("chunk,largest", [(1 << 15, 3300001), (1 << 17, 3300001), (1 << 22, 3300001), (1 << 15, 6000001),
+                                           (1 << 22, 6000001), (1 << 17, 10500001)])
+def test_results_through_the_image(oracle, chunk, largest, half):
     # a launch of more than 768 workgroups whose streams lie off the lines: whole workgroups store through LDS,
     # at every edge and behind every cut
-    _adam_and_compare(oracle, EDGES + [3300001, 4096 * 3 + 512, 150001], chunk, seed=chunk + 3,
+    numels = EDGES + [largest, 4096 * 3 + 512, 150001]
+    assert (14 * sum(numels) > SHORT_STEP) == (largest > 3300001)
+    assert (sum(numels) > 2560 * 4096) == (largest > 6000001)
+    _adam_and_compare(oracle, numels, chunk, seed=chunk + 3,
                       hp=dict(HP, step=3), half=half, loss_scale=1024.0 if half == torch.float16 else 1.0)
 
 
-def test_results_of_a_long_launch_on_the_lines(oracle):
-    _adam_and_compare(oracle, [1 << 20] * 3 + [262144], 1 << 20, seed=31, hp=dict(HP, step=2))
+@pytest.mark.parametrize("n", [3, 6])
+def test_results_of_a_long_launch_on_the_lines(oracle, n):
+    numels = [1 << 20] * n + [262144]
+    assert (14 * sum(numels) > SHORT_STEP) == (n == 6)
+    _adam_and_compare(oracle, numels, 1 << 20, seed=31, hp=dict(HP, step=2))
 
 
 @pytest.mark.parametrize("chunk", [1024, 1 << 14, 1 << 20])
@@ -128,17 +137,24 @@ def test_so_many_groups(oracle, n):
     _chained_and_compare(oracle, numels, 1 << 14, seed=n + 1, steps=2)
 
 
-# chained steps that know no tally have kernels of their own: every edge, and more groups than one launch takes
+# long chained steps that know no tally have kernels of their own: every edge, with RAW tensors between and more groups than one
+# launch takes; and the same of a short step
+@pytest.mark.parametrize("times", [67, 70])
 @pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
-def test_block_edges_of_long_chained_steps(oracle, half):
-    _chained_and_compare(oracle, EDGES * 67, 1 << 15, seed=67, steps=2, half=half,
-                         loss_scale=1024.0 if half == torch.float16 else 1.0)
+def test_block_edges_of_long_chained_steps(oracle, half, times):
+    numels = EDGES * times
+    assert len(numels) > 2048 and (14 * sum(numels) > SHORT_STEP) == (times == 70)
+    extra = [(5 * i, t) for i, t in enumerate(_raw([1, 7, 511, 4096, 16385 + 4096], torch.bfloat16, times))] if times == 70 else None
+    _chained_and_compare(oracle, numels, 1 << 15, seed=67, steps=2, half=half,
+                         loss_scale=1024.0 if half == torch.float16 else 1.0, extra_raw=extra)
 
 
-# steps over more than 80 MiB have kernels of their own: every edge in place, behind cuts and, with a tally, in one chunk
-@pytest.mark.parametrize("times,chunk", [(55, 1 << 15), (1, 1 << 27)])
+# steps over more than 80 MiB have kernels of their own: every edge in place, behind cuts without a tally and, with one, in one
+# chunk; and cuts in a short step
+@pytest.mark.parametrize("times,chunk", [(55, 1 << 15), (69, 1 << 15), (1, 1 << 27)])
 @pytest.mark.parametrize("half", [torch.bfloat16, torch.float16])
 def test_block_edges_of_long_steps(oracle, times, chunk, half):
+    assert (max(14 * sum(EDGES * times), chunk) > SHORT_STEP) == (times != 55) and (31 * times > 2048) == (times == 69)
     scale = 1024.0 if half == torch.float16 else 1.0
     extra = [(5 * i, t) for i, t in enumerate(_raw([1, 7, 511, 4096, 16385 + 4096], torch.bfloat16, times))]
     _adam_and_compare(oracle, EDGES * times, chunk, seed=times, hp=dict(HP, step=3), half=half, loss_scale=scale,
