@@ -499,7 +499,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
         workgroup_barrier();
     };
-    const uint32_t slot = xcd_place(block, gridDim.x, T.xcd_group) * kWaves + wave;
+    const uint32_t slot = xcd_order(block, gridDim.x, T.xcd_group) * kWaves + wave;
     const uint32_t count = LISTED ? list->n << T.tpc_log2 : T.n_list ? T.n_list : T.n_tiles;
     bool active = slot < count;
     uint32_t chunk = 0, tile = 0;

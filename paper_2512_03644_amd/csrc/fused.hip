@@ -775,7 +775,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TALLY 
     if (!TALLY) C.tally = nullptr;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const uint32_t group = xcd_place(blockIdx.x, gridDim.x, C.xcd_group);
+    const uint32_t group = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
     if (C.tally && group >= C.n_groups) {
         clear_tail(C, chunks, group - C.n_groups);
         return;
@@ -828,7 +828,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];  // of launches with C.image
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const uint32_t group = xcd_place(block, grid, C.xcd_group);
+    const uint32_t group = xcd_order(block, grid, C.xcd_group);
     if (C.tally && group >= C.n_groups) {
         clear_tail(C, chunks, group - C.n_groups);
         return;
@@ -919,7 +919,7 @@ __global__ __launch_bounds__(kStageThreads) void mix_ceiling_kernel(
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
     // workgroup position p: half p mod 2 of tile p div 2
-    const uint32_t pos = xcd_place(blockIdx.x, gridDim.x, C.xcd_group);
+    const uint32_t pos = xcd_order(blockIdx.x, gridDim.x, C.xcd_group);
     const uint32_t ti = pos / 2;
     if (ti >= n_tiles) return;
     const WorkTile& t = tiles[ti];

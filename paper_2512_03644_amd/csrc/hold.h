@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     table_to_lds<kThreads, sizeof(lds.weight)>(T.block_tab, &lds.weight[0][0], wave, lane);
     if (threadIdx.x < kWaves) lds.sum[threadIdx.x] = lds.verdict[threadIdx.x] = 0;
     __builtin_amdgcn_sched_barrier(0);
-    const uint32_t tile = xcd_place(block, gridDim.x, T.xcd_group) * kWaves + wave;
+    const uint32_t tile = xcd_order(block, gridDim.x, T.xcd_group) * kWaves + wave;
     if (tile >= T.n_tiles) {
         wait_loads<0>();
         workgroup_barrier();

@@ -678,7 +678,7 @@ tile_kernel(
     __syncthreads();
     const int lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const uint32_t slot = xcd_place(block, gridDim.x, T.xcd_group) * kWavesPerBlock + wave;
+    const uint32_t slot = xcd_order(block, gridDim.x, T.xcd_group) * kWavesPerBlock + wave;
     const uint32_t count = T.n_list ? T.n_list : T.n_tiles;
     if (slot >= count) return;
     const uint32_t tile = T.tile_begin + slot;
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(kWaveSize * kWavesPerBlock) void copy_kernel(
 {
     const uint32_t lane = threadIdx.x & (kWaveSize - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWaveSize);
-    const uint64_t tile = uint64_t(xcd_place(blockIdx.x, gridDim.x, kDefaultXcdGroup)) * kWavesPerBlock + wave;
+    const uint64_t tile = uint64_t(xcd_order(blockIdx.x, gridDim.x, kDefaultXcdGroup)) * kWavesPerBlock + wave;
     const uint64_t i0 = tile * (kCopyRows * kWaveSize);
     if (i0 >= n16) return;
     if (i0 + kCopyRows * kWaveSize <= n16) {
