@@ -11,13 +11,14 @@
 //
 // What bounds a small call is that chain and the launch itself.  With Horner steps through byte tables in
 // place of the matrix product, 124 lookups a lane and block, the wavefronts of a compute unit queued at its
-// LDS, all at the same time: pack of 28 MB 18.9 us and 14.5 with the product, restore 18.9 and 14.8, verify of 41 / 3.2 MB
-// 16.6 / 9.6 and 11.5 / 6.1.  With the chain's ends shorter (block_behind_args, few_tensors, kAhead) 13.0, 13.4, and verify of
-// 3 MB 5.2, where a copy in this shape takes 9.0 for 28 MB and 3.0 for 3: the rest is the fold behind the last rows (1.1 us), the
-// way to the chunk's word (0.7) and the table entry in front of a pack's rows.  On 1 GB of 5 KiB tensors, where the lookups
-// hid behind the memory, a restore took 407 us, 396 with the product, and takes 382 (kShortXcdGroup), though the
-// weights leave room for two workgroups on a compute unit and the tables left it for three; a long pack takes half
-// the weights, and has three (block_kernel_lean).
+// LDS, all at the same time: pack of 32 MB 18.9 us and 14.5 with the product, restore 18.9 and 14.8, verify of 41 / 3.2 MB
+// 16.6 / 9.6 and 11.5 / 6.1.  With the chain's ends shorter (block_behind_args, few_tensors, kAhead) 12.9, 13.4 and 10.7 / 5.5.  A
+// copy of so many bytes in this shape, with these loads, stores and order, takes 12.3 for 32 MB (three sets in turn, as those;
+// one set 10.8, where a pack takes 11.4 and a restore 11.9) and 4.6 for 3 MB, which pack and restore do in 7.1 / 7.4: what a call
+// of a few MB spends behind and in front of its rows hides behind other wavefronts' rows in one of 32.
+// On 1 GB of 5 KiB tensors, where the lookups hid behind the memory, a restore took 407 us, 396 with the product, and on
+// another machine 433 so and 401 now (kShortXcdGroup), though the weights leave room for two workgroups on a compute unit and
+// the tables left it for three; a long pack takes half the weights, and has three (block_kernel_lean).
 //
 // A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the
 // plan's tally, which starts at zero, and whoever completes the word writes the chunk's result and
@@ -220,8 +221,8 @@ __device__ __noinline__ u32x4 move_crowded_row(const uint64_t* __restrict__ seg_
 // A block of up to kPieces tensors, the payload's end included: the boundaries stand in scalar registers and every lane
 // finds its tensors' addresses by comparing.  w: the rows (restore).
 // A small call ends when its last boundary block does, and by way of the table in LDS that one has two more loads and a
-// microsecond of LDS between its number and its rows.  By the table / so, us: pack of 3 / 28 / 60 / 100 MB 8.2 / 14.1 /
-// 23.2 / 46.2 and 7.1 / 13.3 / 22.0 / 44.1, restore of 28 / 60 MB 14.3 / 23.8 and 13.7 / 23.1, 60 MB off the lines 25.5 and
+// microsecond of LDS between its number and its rows.  By the table / so, us: pack of 3 / 32 / 60 / 100 MB 8.2 / 14.1 /
+// 23.2 / 46.2 and 7.1 / 13.3 / 22.0 / 44.1, restore of 32 / 60 MB 14.3 / 23.8 and 13.7 / 23.1, 60 MB off the lines 25.5 and
 // 23.4, tensors of 5 KiB, 100 MB, pack 46.6 and 44.2, 300 MB, restore 126.9 and 123.8, 1 GB 406 and 400.  Not where a block
 // is held, nor in packs with half the weights: they have no registers for it (300 MB of 5 KiB 147 and 181, pack 116 and 126).
 template <int MODE, int HINT, class Ready, class Fold>
@@ -488,7 +489,7 @@ __device__ __forceinline__ void block_body(const TileTables& T, uint8_t* __restr
         tab[i] = *as_global(reinterpret_cast<const u32x4*>(T.block_tab) + kFirst + i * kThreads + threadIdx.x);
     });
     // Of the multiplication that a wavefront ends with, what does not need its data: while that is on its way.  (Behind it,
-    // with a run's sum and the count of its wavefronts in two LDS words instead of one: pack / restore of 28 MB 13.3 / 13.7
+    // with a run's sum and the count of its wavefronts in two LDS words instead of one: pack / restore of 32 MB 13.3 / 13.7
     // us, now 13.0 / 13.4.  Not where registers are short: a verify has room for three workgroups on a compute unit without,
     // for two with: 100 / 180 MB 21.4 / 36.3 and 23.8 / 38.5, 3 MB 5.17 and 5.09.)
     constexpr bool kAhead = !HOLD && !LEAN && MODE != kVerify;

@@ -83,8 +83,8 @@ __device__ __forceinline__ void static_for(Fn&& fn)
 // The workgroup's number, known when bytes [FROM, TO) of the kernel's arguments are in the scalar cache.  The compiler
 // loads arguments where they are used, and the first wavefronts of a launch wait for memory at every line of them
 // that is new, one line after the other; so all are asked for at once.  With the order of the XCDs in closed form and a
-// chunk's checksum asked for beforehand, us, before / now: pack of 3 / 28 / 60 MB 9.05 / 14.50 / 23.6 and 8.21 / 14.07 /
-// 23.2, verify of 3 / 28 / 100 MB 6.2 / 10.0 / 25.8 and 5.3 / 9.2 / 21.9, pack of 300 MB in tiles 119.5 and 118.4, a skipping
+// chunk's checksum asked for beforehand, us, before / now: pack of 3 / 32 / 60 MB 9.05 / 14.50 / 23.6 and 8.21 / 14.07 /
+// 23.2, verify of 3 / 32 / 100 MB 6.2 / 10.0 / 25.8 and 5.3 / 9.2 / 21.9, pack of 300 MB in tiles 119.5 and 118.4, a skipping
 // restore of 20,000 ragged tensors 1151 and 1136.
 template <int FROM, int TO>
 __device__ __forceinline__ uint32_t block_behind_args()
