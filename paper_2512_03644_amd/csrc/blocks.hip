@@ -17,7 +17,7 @@
 // one set 10.8, where a pack takes 11.4 and a restore 11.9) and 4.6 for 3 MB, which pack and restore do in 7.1 / 7.4: what a call
 // of a few MB spends behind and in front of its rows hides behind other wavefronts' rows in one of 32.
 // On 1 GB of 5 KiB tensors, where the lookups hid behind the memory, a restore took 407 us, 396 with the product, and on
-// another machine 433 so and 401 now (kShortXcdGroup), though the weights leave room for two workgroups on a compute unit and
+// another machine 431 so and 395 now (kShortXcdGroup, kCachedRestoreBytes), though the weights leave room for two workgroups on a compute unit and
 // the tables left it for three; a long pack takes half the weights, and has three (block_kernel_lean).
 //
 // A call is one launch where it can be (T.tally set): the sums of a chunk meet in a 64-bit word of the

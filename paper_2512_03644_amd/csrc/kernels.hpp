@@ -16,9 +16,14 @@ constexpr uint32_t kDefaultXcdGroup = 2048;
 // (of 1 MB above kLongerRunsFrom), so that the XCDs sweep one region and not eight.  Default / short, us: pack of 75 / 90 / 100 / 130 /
 // 180 MB 24.9 / 32.6 / 45.4 / 54.1 / 74.3 and 25.1 / 31.2 / 41.8 / 50.9 / 70.7, of 5 KiB tensors 0.15 / 0.3 / 1 GB 61.9 / 113.8 /
 // 356.8 and 59.4 / 110.6 / 348.4; restore of 60 / 110 / 150 / 300 / 600 MB 22.7 / 44.8 / 60.7 / 123.3 / 223 and 22.8 / 42.6 / 56.5 /
-// 116.2 / 213, of 1 / 2 / 4 GB 354 / 667 / 1345 and 342 / 650 / 1334, 11.8 GB 3642 both; of 5 KiB tensors 0.3 / 1 GB 121.6 / 386.8 and
-// 116.5 / 379.2; 24 listed chunks of them 44.3 and 43.5.  A pack on tiles gains or loses as the tensors lie (0.3 / 0.6 GB 117.6 / 222.9
+// 116.2 / 213, of 1 / 2 / 4 GB 354 / 667 / 1345 and 342 / 650 / 1334, 11.8 GB 3642 both; of 5 KiB tensors 0.3 / 1 GB 121.6 / 407.1 and
+// 116.5 / 402.7; 24 listed chunks of them 44.3 and 43.5.  A pack on tiles gains or loses as the tensors lie (0.3 / 0.6 GB 117.6 / 222.9
 // and 115.2 / 213.2, of large tensors in one allocation 112.2 / 207.8 and 120.9 / 215.0; 15 GB 4862 and 4928), a verify nothing.
+// First passes over new states (medians of 9 to 20) gain as well or lose nothing, the code with long runs alone / with short ones:
+// restore of 110 / 300 MB, 1 / 3 GB 68.7 / 151.4 / 391.6 / 1078 and 63.7 / 142.6 / 376.8 / 1069, of 5 KiB tensors,
+// 0.15 / 0.3 GB 86.9 / 148.3 and 80.6 / 136.6, pack of 130 MB 76.7 and 75.1, of 5 KiB tensors, 0.3 GB 189.2 and 178.0; by run length alone,
+// 8 / 16 / 32 / 64 / 128 / 512 / 2048, restore of 5 KiB tensors, 1 GB 439 / 434 / 440 / 435 / 441 / 437 / 439, 28 listed chunks of 4 MiB
+// 137 / 134 / 128 / 128 / 132 / 136 / 136 (these differ by 8 between states).
 constexpr uint32_t kShortXcdGroup = 8;
 constexpr uint64_t kShortRunsFrom = 80ull << 20, kLongerRunsFrom = 384ull << 20, kShortRunsTo = 4096ull << 20;
 

@@ -149,14 +149,15 @@ constexpr uint64_t kCrowdedShare = 16;  // blocks if a tile in so many holds mor
 // buffers in turn, plain against non-temporal loads: pack of 8 / 32 / 64 / 128 MB 11.8 / 17.4 / 27.8 / 60.1
 // against 12.1 / 20.9 / 35.7 / 58.5 us, restore 12.2 / 18.8 / 29.9 / 61.0 against 13.6 / 20.5 / 35.5 / 59.3.
 constexpr uint64_t kWarmBytes = 96ull << 20;
-// Above 1 GiB a restore in blocks, which is then one of small tensors, goes through the caches both ways: the L2 puts the lines
+// Above, a restore in blocks, which is then one of small tensors, goes through the caches both ways: the L2 puts the lines
 // together that two tensors, or two rows of one that lies off the lines, share.  Below, the first pass over a received buffer,
-// often the only one, pays more for it than the next ones gain.  Both non-temporal / both plain, first pass over a new state and
-// repeated ones, us, tensors of 5 KiB, 0.45 / 0.6 / 0.8 / 1 GB 196 / 252 / 337 / 429 and 176 / 235 / 313 / 401 against
-// 218 / 274 / 356 / 437 and 178 / 236 / 311 / 397, 1.2 / 1.4 / 2 / 4 GB 500 / 582 / 823 / 1643 and 470 / 549 / 777 / 1540 against
-// 500 / 577 / 806 / 1605 and 469 / 544 / 768 / 1510, of 2 KB, 1 / 2 GB 447 / 883 and 437 / 870 against 456 / 882 and 443 / 877, of
-// 1 KB, 0.6 GB 310 and 276 against 312 and 280.
-constexpr uint64_t kCachedRestoreBytes = 1024ull << 20;
+// often the only one, loses more by it than a repeated one gains.  Both non-temporal / both plain, medians of first passes over new
+// states and of repeated ones, us, tensors of 5 KiB, 0.45 / 0.6 / 0.8 / 0.9 GB 196 / 252 / 333 / 373 and 176 / 235 / 312 / 350 against
+// 218 / 274 / 349 / 389 and 178 / 236 / 310 / 348 (the first passes with long runs and non-temporal 214 / 268 / 347 / 389), 0.95 / 1 / 1.1 GB
+// 397 / 423 / 462 and 370 / 400 / 422 against 403 / 430 / 460 and 366 / 395 / 423, 1.4 / 2 / 4 GB 582 / 823 / 1643 and 549 / 777 / 1540 against
+// 577 / 806 / 1605 and 544 / 768 / 1510, of 2 KB, 1 / 2 GB 447 / 883 and 437 / 870 against 456 / 882 and 443 / 877, of 1 KB, 0.6 GB 310
+// and 276 against 312 and 280.
+constexpr uint64_t kCachedRestoreBytes = 896ull << 20;
 constexpr uint64_t kListBytes = 256ull << 20;  // listed chunks of one launch go in blocks up to here
 constexpr uint64_t kVerifyTileBytes = 1ull << 16;
 

@@ -540,7 +540,7 @@ static void order_by_size()
     }
 }
 
-// The caches that a pass in blocks goes through: warm up to 96 MiB; a restore of small tensors through them again above 1 GiB.
+// The caches that a pass in blocks goes through: warm up to 96 MiB; a restore of small tensors through them again above 896 MiB.
 static void caches_by_size()
 {
     const uint32_t around = 3, mid = FF_PLAN_TILE_LOG2(13);
@@ -548,10 +548,10 @@ static void caches_by_size()
         {1, 96ull << 20, 0, 0, kHintWarm(kRestore)},
         {1, 97ull << 20, 0, 0, around},
         {100000, 4096, 6, 0, around},                       // 390 MiB, in blocks
-        {262144, 4096, 6, 0, around},                       // 1 GiB
-        {262145, 4096, 6, 0, 0},
-        {262145, 4096, 6, mid, around},                     // blocks that are asked for
-        {262145, 4096, 6, FF_PLAN_CACHE_HINT(1), 1},
+        {229376, 4096, 6, 0, around},                       // 896 MiB
+        {229377, 4096, 6, 0, 0},
+        {229377, 4096, 6, mid, around},                     // blocks that are asked for
+        {229377, 4096, 6, FF_PLAN_CACHE_HINT(1), 1},
         {1, 1100ull << 20, 0, 0, around},                   // tiles
     };
     for (const auto& c : cases) {

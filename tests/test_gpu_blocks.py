@@ -452,8 +452,8 @@ def test_flags_written_over_the_checksums(nbytes):
     assert torch.equal(t.view(torch.int16), want.view(torch.int16))
 
 
-# a restore of small tensors takes longer runs of the XCDs' order above 384 MiB, and goes through the caches above 1 GiB
-@pytest.mark.parametrize("nbytes", [(384 << 20) - 4096, (384 << 20) + 4096, (1 << 30) - 4096, (1 << 30) + 4096])
+# a restore of small tensors takes longer runs of the XCDs' order above 384 MiB, and goes through the caches above 896 MiB
+@pytest.mark.parametrize("nbytes", [(384 << 20) - 4096, (384 << 20) + 4096, (896 << 20) - 4096, (896 << 20) + 4096])
 def test_restore_of_small_tensors_on_both_sides_of_384_mib(nbytes):
     arena = torch.empty(nbytes + (64 << 20), dtype=torch.uint8, device=DEV)
     gen = torch.Generator(device=DEV)
